@@ -237,8 +237,6 @@ __global__ __launch_bounds__(256) void reduce_replicas_kernel(const u32x4* __res
   if (live) __builtin_nontemporal_store(sum_vec(acc, Elem{}), dw + (size_t)e * vec_per_slot + v);
 }
 
-inline bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
-
 // ---- workspace of the training entry points
 struct TrainWorkspace {
   uint16_t* dh;        // [P, ffn]
@@ -252,8 +250,6 @@ struct TrainWorkspace {
   size_t total_bytes;
   int n1;
 };
-
-inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 TrainWorkspace carve_train(void* ws, const lz_shape* s) {
   TrainWorkspace w;
@@ -270,22 +266,23 @@ TrainWorkspace carve_train(void* ws, const lz_shape* s) {
   w.dz = (uint16_t*)take((size_t)P * w.n1 * 2);
   w.virt_w2 = (int32_t*)take(sizeof(int32_t) * (S + 1));
   w.virt_w1 = (int32_t*)take(sizeof(int32_t) * (S + 1));
-  w.tiles_fwd = take(tile_table_bytes(P, S, BM, kGroupM, ceil_div(s->ffn, s->act == LZ_SWIGLU ? BN / 2 : BN), s->d / BN));
-  w.tiles_bwd = take(tile_table_bytes(P, S, BM, kGroupM, ceil_div(s->ffn, BN), s->d / BN));
-  w.tiles_w2 = take(tile_table_bytes((long long)S * s->ffn, S, BM, kGroupM, s->d / BN, 0));
+  w.tiles_fwd = take(tile_table_bytes(P, S, BM, kGroupM, ceil_div(s->ffn, s->act == LZ_SWIGLU ? BN / 2 : BN), ceil_div(s->d, BN)));
+  w.tiles_bwd = take(tile_table_bytes(P, S, BM, kGroupM, ceil_div(s->ffn, BN), ceil_div(s->d, BN)));
+  w.tiles_w2 = take(tile_table_bytes((long long)S * s->ffn, S, BM, kGroupM, ceil_div(s->d, BN), 0));
   w.tiles_w1 = take(tile_table_bytes((long long)S * s->d, S, BM, kGroupM, ceil_div(w.n1, BN), 0));
   w.total_bytes = size_t(p - (char*)ws);
   return w;
 }
 
-// the shapes the MFMA kernel serves: bf16, d a multiple of 256, ffn of 64, a slot's weights within 32-bit offsets
+// The shapes the MFMA kernels serve: bf16 rows of whole 16-byte pieces, virtual row indices within int32.
 inline bool train_shape(const lz_shape* s) {
-  if (!lz::shape_ok(s) || s->dtype != LZ_BF16) return false;
-  if (s->d % BN != 0 || s->ffn % 64 != 0) return false;
-  if ((long long)s->d * s->ffn * 4 >= (1ll << 31)) return false;
+  if (!lz::shape_ok(s) || !mfma_sizes(s)) return false;
   const long long S = (long long)s->N * s->c;
-  return S * s->d * 2 < (1ll << 31) && S * s->ffn * 2 < (1ll << 31);  // virtual row indices are int32
+  return S * s->d * 2 < (1ll << 31) && S * s->ffn * 2 < (1ll << 31);
 }
+// ... of these, sizes that the tiles do not divide also take unaligned tensors, on the FMA kernels (each call
+// by itself: no state passes between the calls through the workspace)
+inline bool whole_tiles(const lz_shape* s) { return s->d % BN == 0 && s->ffn % 64 == 0; }
 
 int32_t check_train(const lz_shape* shape, void* ws, size_t ws_bytes, TrainWorkspace* w) {
   if (!train_shape(shape)) return LZ_ESHAPE;
@@ -379,15 +376,17 @@ int32_t check_train_generic(const lz_shape* shape, void* ws, size_t ws_bytes, Ge
 }  // namespace
 
 extern "C" size_t lz_train_workspace_bytes(const lz_shape* shape) {
-  if (train_shape(shape)) return carve_train(nullptr, shape).total_bytes;
-  if (generic_train_shape(shape)) return carve_train_generic(nullptr, shape).total_bytes;
-  return 0;
+  const size_t generic = generic_train_shape(shape) ? carve_train_generic(nullptr, shape).total_bytes : 0;
+  if (!train_shape(shape)) return generic;
+  const size_t bytes = carve_train(nullptr, shape).total_bytes;
+  return bytes > generic || whole_tiles(shape) ? bytes : generic;
 }
 
 extern "C" int32_t lz_ffn_forward_train(const void* xp, const int32_t* slot_offsets, const void* w1, const void* w2,
                                         const lz_shape* shape, void* z, void* h, void* yp, void* ws,
                                         size_t ws_bytes, void* stream) {
-  if (!train_shape(shape)) {
+  const bool aligned = aligned16(z) && aligned16(h) && aligned16(yp) && aligned16(xp) && aligned16(w1) && aligned16(w2);
+  if (!train_shape(shape) || (!aligned && !whole_tiles(shape))) {
     GenericTrainWorkspace gw;
     const int32_t grc = check_train_generic(shape, ws, ws_bytes, &gw);
     if (grc != LZ_OK) return grc;
@@ -403,14 +402,13 @@ extern "C" int32_t lz_ffn_forward_train(const void* xp, const int32_t* slot_offs
   const long long P = (long long)shape->T * shape->k;
   if (P == 0) return LZ_OK;
   if (!xp || !slot_offsets || !w1 || !w2 || !z || !h || !yp) return LZ_EINVAL;
-  if (!aligned16(z) || !aligned16(h) || !aligned16(yp) || !aligned16(xp) || !aligned16(w1) || !aligned16(w2))
-    return LZ_EINVAL;
+  if (!aligned) return LZ_EINVAL;
   hipStream_t st = (hipStream_t)stream;
   const int S = shape->N * shape->c;
   const bool swiglu = shape->act == LZ_SWIGLU;
   const int n_up = ceil_div(shape->ffn, swiglu ? BN / 2 : BN);
   TileTable t;
-  int32_t r = build_table(slot_offsets, S, P, n_up, shape->d / BN, w.tiles_fwd, st, &t);
+  int32_t r = build_table(slot_offsets, S, P, n_up, ceil_div(shape->d, BN), w.tiles_fwd, st, &t);
   if (r != LZ_OK) return r;
   // z = xp W1 and h = act(z) from one epilogue
   MfmaArgs g{};
@@ -476,7 +474,9 @@ namespace {
 int32_t ffn_backward(const void* dyp, const void* xp, const void* z, const void* h, const int32_t* slot_offsets,
                      const void* w1, const void* w2, const lz_shape* shape, void* dxp, void* dw1, void* dw2,
                      bool accumulate, void* ws, size_t ws_bytes, void* stream) {
-  if (!train_shape(shape)) {
+  const bool aligned = aligned16(dyp) && aligned16(xp) && aligned16(z) && aligned16(h) && aligned16(dxp) &&
+                       aligned16(w1) && aligned16(w2) && aligned16(dw1) && aligned16(dw2);
+  if (!train_shape(shape) || (!aligned && !whole_tiles(shape))) {
     GenericTrainWorkspace gw;
     const int32_t grc = check_train_generic(shape, ws, ws_bytes, &gw);
     if (grc != LZ_OK) return grc;
@@ -507,8 +507,8 @@ int32_t ffn_backward(const void* dyp, const void* xp, const void* z, const void*
   int32_t r = lz::launch_status();
   if (r != LZ_OK) return r;
   TileTable t_rows, t_w2, t_w1;
-  if ((r = build_table(slot_offsets, S, P, ceil_div(ffn, BN), d / BN, w.tiles_bwd, st, &t_rows)) != LZ_OK) return r;
-  if ((r = build_table(w.virt_w2, S, (long long)S * ffn, d / BN, 0, w.tiles_w2, st, &t_w2)) != LZ_OK) return r;
+  if ((r = build_table(slot_offsets, S, P, ceil_div(ffn, BN), ceil_div(d, BN), w.tiles_bwd, st, &t_rows)) != LZ_OK) return r;
+  if ((r = build_table(w.virt_w2, S, (long long)S * ffn, ceil_div(d, BN), 0, w.tiles_w2, st, &t_w2)) != LZ_OK) return r;
   if ((r = build_table(w.virt_w1, S, (long long)S * d, ceil_div(n1, BN), 0, w.tiles_w1, st, &t_w1)) != LZ_OK) return r;
 
   if (P > 0) {

@@ -1,5 +1,5 @@
-// Training entry points for the shapes the MFMA kernels do not serve (fp32 tensors, bf16 shapes the
-// MFMA tiling does not divide): the same chain-rule steps as backward.hip on plain LDS-tiled
+// Training entry points for what the MFMA kernels do not serve (fp32 tensors, bf16 rows that are no whole
+// 16-byte pieces, unaligned tensors): the same chain-rule steps as backward.hip on plain LDS-tiled
 // fp32-FMA kernels with full bounds checks.  fp32 accumulation, every stored tensor rounded once
 // to the tensor type; the fp32 path uses erff / expf so that it meets the fp32 error bar.
 // Device code, not part of the C ABI; included by backward.hip.

@@ -293,7 +293,12 @@ __device__ __forceinline__ int swz_kmajor(int kr) { return ((kr & 3) << 2) | (((
 // One output tile of 64*XF rows x 256 columns n of the weight operand W(n, k) ("weight rows"
 // below, whichever way W lies in memory).  XF = 32-row activation fragments per wave: the 2x2 waves each own (32*XF) x 128 of the tile, so a slot's ragged last tile costs
 // MFMAs and activation loads only for its rows rounded up to 64.
-template <int EPI, int XF, int MODE, bool GATHER>
+//
+// KTAIL: K is not a multiple of 64 and an operand is k-contiguous, so the last K step's 128-byte rows run
+// past the end of K into the next row.  The lanes whose 16-byte chunk lies there fetch from beyond the
+// descriptor instead and get zeros (both operands: a zero against what the other row holds would let an
+// infinity or NaN of a neighbouring row through).  k-major operands end with their descriptor.
+template <int EPI, int XF, int MODE, bool GATHER, bool KTAIL>
 __device__ __forceinline__ void gemm_tile(const MfmaArgs& a, char* smem, int slot, int row0, int row_end, int n0) {
   constexpr bool TA = MODE == MODE_TN || MODE == MODE_TN_WIDE, TB = MODE != MODE_NT;  // k-major left / right operand
   constexpr bool kGated = EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_KEEP;
@@ -426,6 +431,16 @@ __device__ __forceinline__ void gemm_tile(const MfmaArgs& a, char* smem, int slo
     }
   }
 
+  // KTAIL: what the last K step ORs into the offsets of loads with even / odd i (swz of a load's rows
+  // depends on i only through its parity, the same for both operands)
+  [[maybe_unused]] int tail_or[2] = {0, 0};
+  if constexpr (KTAIL) {
+    const int k_left = K - (K - 1) / BK * BK;  // 1..64; multiples of 8, so chunks are whole
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      tail_or[i] = ((lane & 7) ^ swz(i * 8 + (lane >> 3))) * 8 >= k_left ? (int)0x80000000 : 0;
+  }
+
   // ---- fragment read addresses.  A fragment is 16 rows (of the activation tile, or weight rows) x
   // the 32 k of a slice; lane l holds row l%16, the 8 consecutive k of chunk l/16 (the operand
   // layout of v_mfma_f32_16x16x32_bf16).  k-contiguous tile: one ds_read_b128 at row l%16, logical
@@ -519,7 +534,10 @@ __device__ __forceinline__ void gemm_tile(const MfmaArgs& a, char* smem, int slo
       const bool isx = q < kLoadsX;
       const i32x4 words = isx ? wa : wb;
       const uint32_t lds = isx ? ldsX + (wave * kLoadsX + q) * 1024 : ldsW + (wave * kLoadsW + q - kLoadsX) * 1024;
-      const int voff = isx ? voffX[q < kLoadsX ? q : 0] : voffW[q >= kLoadsX ? q - kLoadsX : 0];
+      int voff = isx ? voffX[q < kLoadsX ? q : 0] : voffW[q >= kLoadsX ? q - kLoadsX : 0];
+      if constexpr (KTAIL) {  // kLoadsX is even: a weight load's parity is that of q as well
+        if (isx ? !TA : !TB) voff |= tail_or[q & 1] & ((isx ? a_step : w_step) == k_steps - 1 ? -1 : 0);
+      }
       const int soff = isx ? a_step * stepA : w_step * stepW;
       if (with_mfma != nullptr && q == q0) mfma_then_load16_to_lds(*with_mfma, *mw, *mx, words, lds, voff, soff);
       else load16_to_lds(words, lds, voff, soff);
@@ -796,7 +814,7 @@ __device__ __forceinline__ void gemm_tile(const MfmaArgs& a, char* smem, int slo
 // its own pace.  (The hardware hands the workgroups of an ordinary launch to the XCDs strictly
 // in order of their index: there an XCD whose tiles take longer holds back the workgroups
 // queued behind it for every other XCD, which costs 10-40 % on ragged plans.)
-template <int EPI, int MODE, bool GATHER>
+template <int EPI, int MODE, bool GATHER, bool KTAIL>
 __global__ __launch_bounds__(256, 1) void gemm_mfma_kernel(MfmaArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub, not the gfx950 builtins
   extern __shared__ __attribute__((aligned(1024))) char smem[];
@@ -828,10 +846,10 @@ __global__ __launch_bounds__(256, 1) void gemm_mfma_kernel(MfmaArgs a) {
       const int row_end = a.t.row_end[row_tile];
       const int n0 = nt * BN_OUT;
       const int rows = row_end - row0;  // > 0; more than 256 means a full tile
-      if (rows > 192) gemm_tile<EPI, 4, MODE, GATHER>(a, smem, slot, row0, row_end, n0);
-      else if (rows > 128) gemm_tile<EPI, 3, MODE, GATHER>(a, smem, slot, row0, row_end, n0);
-      else if (rows > 64) gemm_tile<EPI, 2, MODE, GATHER>(a, smem, slot, row0, row_end, n0);
-      else gemm_tile<EPI, 1, MODE, GATHER>(a, smem, slot, row0, row_end, n0);
+      if (rows > 192) gemm_tile<EPI, 4, MODE, GATHER, KTAIL>(a, smem, slot, row0, row_end, n0);
+      else if (rows > 128) gemm_tile<EPI, 3, MODE, GATHER, KTAIL>(a, smem, slot, row0, row_end, n0);
+      else if (rows > 64) gemm_tile<EPI, 2, MODE, GATHER, KTAIL>(a, smem, slot, row0, row_end, n0);
+      else gemm_tile<EPI, 1, MODE, GATHER, KTAIL>(a, smem, slot, row0, row_end, n0);
     }
   }
   // the last workgroup to finish leaves the tickets at zero for the next launch on this table
@@ -847,10 +865,10 @@ __global__ __launch_bounds__(256, 1) void gemm_mfma_kernel(MfmaArgs a) {
 
 constexpr int kMaxDevices = 64;
 
-template <int EPI, int MODE = MODE_NT, bool GATHER = false>
-int32_t launch_mfma(const MfmaArgs& a, hipStream_t st) {
+template <int EPI, int MODE, bool GATHER, bool KTAIL>
+int32_t launch_mfma_kernel(const MfmaArgs& a, hipStream_t st) {
   static_assert(!GATHER || MODE == MODE_NN, "the gather is part of the forward's first GEMM only");
-  void (*kern)(MfmaArgs) = gemm_mfma_kernel<EPI, MODE, GATHER>;
+  void (*kern)(MfmaArgs) = gemm_mfma_kernel<EPI, MODE, GATHER, KTAIL>;
   // per device: the LDS attribute is set and the CU count read on the first launch there (both
   // idempotent, so two threads racing through the set-up do the same thing twice)
   static std::atomic<int> workgroups_of_device[kMaxDevices];
@@ -869,5 +887,24 @@ int32_t launch_mfma(const MfmaArgs& a, hipStream_t st) {
   hipLaunchKernelGGL(kern, dim3(n_workgroups), dim3(256), kLdsBytes, st, a);
   return lz::launch_status();
 }
+
+template <int EPI, int MODE = MODE_NT, bool GATHER = false>
+int32_t launch_mfma(const MfmaArgs& a, hipStream_t st) {
+  if constexpr (MODE == MODE_NT || MODE == MODE_NN) {
+    if (a.K % BK != 0) return launch_mfma_kernel<EPI, MODE, GATHER, true>(a, st);
+  }
+  return launch_mfma_kernel<EPI, MODE, GATHER, false>(a, st);
+}
+
+// bf16 shapes the MFMA kernel takes: rows of whole 16-byte pieces, one slot's weights and one 256-row
+// activation tile within 32-bit byte offsets.
+inline bool mfma_sizes(const lz_shape* s) {
+  if (s->dtype != LZ_BF16 || s->d % 8 != 0 || s->ffn % 8 != 0 || (long long)s->d * s->ffn * 4 >= (1ll << 31)) return false;
+  // KTAIL sets bit 31 of such an offset
+  return (s->d % BK == 0 && s->ffn % BK == 0) || (long long)BM * (s->d > s->ffn ? s->d : s->ffn) * 4 < (1ll << 31);
+}
+
+inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
+inline bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 }  // namespace
