@@ -732,47 +732,48 @@ __device__ __forceinline__ void gemm_tile(const MfmaArgs& a, char* smem, int slo
   auto rounded = [](float v) { return __uint_as_float(pack_bf16x2(v, 0.f) << 16); };  // the bf16 value that is stored
   const int out0 = n0 + wn * kWaveCols;
   if constexpr (EPI == EPI_ACCUM) {
-    // fp32 read-modify-write: one 32 x 32 block at a time through the patch (128-byte rows), so that
-    // every row of the block is one whole line of the fp32 matrix
-    constexpr int kPitchF = 32 * 4 + 16;
+    // fp32 read-modify-write of 32 rows x 128 columns at a time: through the patch into whole 512-byte runs of
+    // the fp32 matrix, whose old values are fetched one pass ahead.  HBM bound where slots are short: an optimizer
+    // step of two micro-batches on 128 slots of 192 rows (d = 2048, ffn = 1408, SwiGLU; 17.7 GB of old and new
+    // sums in the weight gradients) takes 8.4 ms, 12.0 ms with 32 x 32 blocks read only when they are added.
+    constexpr int kPitchF = 128 * 4 + 16;
+    constexpr int kRuns = 16;  // 16-byte pieces per lane and pass, two rows per wave access
     char* const patchf = smem + wave * (32 * kPitchF);
+    const int piece = lane & 31, col = n0 + wn * 128 + piece * 4;  // row lengths are multiples of 8
+    const bool col_ok = col < a.n_out;
+    f32x4* const base = (f32x4*)(a.Cacc + (col_ok ? col : 0));
+    auto row_of = [&](int jj, int t) { return row0 + wm * 32 * XF + jj * 32 + 2 * t + (lane >> 5); };
+    f32x4 old[2][kRuns];
+    auto fetch = [&](int jj) {  // pieces outside the tile fetch its last row or the row's first column: not stored
 #pragma unroll
-    for (int jj = 0; jj < XF; ++jj)
-#pragma unroll
-      for (int ii = 0; ii < 4; ++ii) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          char* const prow = patchf + (16 * h + (lane & 15)) * kPitchF;
-#pragma unroll
-          for (int c = 0; c < 2; ++c) {
-            const f32x4& blk = acc[2 * ii + c][2 * jj + h];
-            const float4 v = {blk[0], blk[1], blk[2], blk[3]};
-            *(float4*)(prow + (16 * c + 4 * quad) * 4) = v;
-          }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const int r = t * 8 + (lane >> 3), piece = lane & 7;
-          const float4 v = *(const float4*)(patchf + r * kPitchF + piece * 16);
-          const int row = row0 + wm * 32 * XF + jj * 32 + r;
-          const int col = n0 + wn * 128 + ii * 32 + piece * 4;  // row lengths are multiples of 8
-          if (row < row_end && col < a.n_out) {
-            float4* const dst = (float4*)(a.Cacc + (size_t)row * a.n_out + col);
-            float4 c = *dst;
-            c.x += v.x;
-            c.y += v.y;
-            c.z += v.z;
-            c.w += v.w;
-            *dst = c;
-          }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      for (int t = 0; t < kRuns; ++t) {
+        const int row = row_of(jj, t);
+        old[jj & 1][t] = __builtin_nontemporal_load(base + (size_t)(row < row_end ? row : row_end - 1) * (a.n_out / 4));
       }
+    };
+    fetch(0);
+#pragma unroll
+    for (int jj = 0; jj < XF; ++jj) {
+      if (jj + 1 < XF) fetch(jj + 1);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        char* const prow = patchf + (16 * h + (lane & 15)) * kPitchF;
+#pragma unroll
+        for (int c = 0; c < NW; ++c) *(f32x4*)(prow + (16 * c + 4 * quad) * 4) = acc[c][2 * jj + h];
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+      for (int t = 0; t < kRuns; ++t) {
+        const f32x4 v = *(const f32x4*)(patchf + (2 * t + (lane >> 5)) * kPitchF + piece * 16);
+        const int row = row_of(jj, t);
+        if (row < row_end && col_ok) __builtin_nontemporal_store(old[jj & 1][t] + v, base + (size_t)row * (a.n_out / 4));
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
     return;
   }
   // Gated weights: the tile's 32-column groups alternate gate and up columns, so of a wave's eight
