@@ -171,9 +171,9 @@ int32_t lz_pack_weights(const void* w, int32_t S, int32_t rows, int32_t cols, in
  * load in 512-byte runs and measured 2-4 % faster than [out, in].
  * Every slot owns its own copy of its expert's weights (replicas are separate buffers).
  * The hidden activation is kept in shape->dtype in the workspace; products accumulate
- * in fp32.  LZ_BF16 uses MFMA kernels when d % 8 == 0 and ffn % 8 == 0 and a generic tiled
- * kernel otherwise; LZ_F32 always uses the generic kernel.  Where d % 256 or ffn % 128 (256 for GELU)
- * is not zero, tensors that are not 16-byte aligned are accepted too and take the generic kernel.
+ * in fp32.  LZ_BF16 uses bf16 matrix instructions when d % 8 == 0 and ffn % 8 == 0; other
+ * bf16 sizes and LZ_F32 use fp32 matrix instructions.  Where d % 256 or ffn % 128 (256 for GELU) is not
+ * zero, bf16 tensors that are not 16-byte aligned are accepted too and take the fp32 kernel.
  * slot_offsets is read on the device only; offsets outside [0,P] are clipped.
  *   xp dev [P,d] (in), yp dev [P,d] (out, 16-byte aligned), ws >= lz_ffn_workspace_bytes(shape). */
 int32_t lz_expert_ffn(const void* xp, const int32_t* slot_offsets,
@@ -235,8 +235,8 @@ int32_t lz_unpermute_combine(const void* yp, const int32_t* pair_to_row,
  * Products are accumulated in fp32 and every stored tensor is rounded once to shape->dtype.
  * bf16 shapes with d % 8 == 0, ffn % 8 == 0, d*ffn*4 < 2^31 and N*c*2*max(d, ffn) < 2^31 run on
  * the MFMA kernels, whatever the size of the activation tensors (tensor pointers 16-byte aligned there;
- * where d % 256 or ffn % 64 is not zero, unaligned ones take the plain kernels);
- * every other valid shape (fp32 tensors, other bf16 sizes) runs on plain tiled fp32-FMA kernels
+ * where d % 256 or ffn % 64 is not zero, unaligned ones take the fp32 kernels);
+ * every other valid shape (fp32 tensors, other bf16 sizes) runs on fp32 matrix-core kernels
  * that use erff / expf (the fp32 configuration meets its 1e-5 bar), as long as T*k/64 + N*c is
  * at most 65535.  All tensor pointers are device memory; `ws` is 256-byte aligned device memory of
  * lz_train_workspace_bytes(shape) bytes that serves one call at a time. */

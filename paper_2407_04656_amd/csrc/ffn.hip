@@ -10,114 +10,15 @@
 //
 // bf16 path: the MFMA kernel of gemm_mfma.h.
 //
-// Generic path (fp32 tensors, bf16 rows that are no whole 16-byte pieces): a plain
-// 64x64x16 LDS-tiled kernel with fp32 FMA accumulation and full bounds checks.
-#include "gemm_mfma.h"
+// fp32 tensors, and bf16 rows that are no whole 16-byte pieces: the fp32 matrix-core kernel of gemm_f32.h.
+#include "gemm_f32.h"
 
 namespace {
 
-__device__ __forceinline__ float gelu_exact(float v) {
-  return 0.5f * v * (1.0f + erff(v * 0.70710678118654752440f));
-}
-__device__ __forceinline__ float silu(float v) { return v / (1.0f + expf(-v)); }
-
-// ------------------------------------------------------------------------------------------
-// generic tiled kernel
-// ------------------------------------------------------------------------------------------
-template <typename Elem>
-__device__ __forceinline__ float load_elem(const Elem* p);
-template <>
-__device__ __forceinline__ float load_elem<float>(const float* p) { return *p; }
-template <>
-__device__ __forceinline__ float load_elem<uint16_t>(const uint16_t* p) { return lz::bf16_to_f32(*p); }
-template <typename Elem>
-__device__ __forceinline__ void store_elem(Elem* p, float v);
-template <>
-__device__ __forceinline__ void store_elem<float>(float* p, float v) { *p = v; }
-template <>
-__device__ __forceinline__ void store_elem<uint16_t>(uint16_t* p, float v) { *p = lz::f32_to_bf16(v); }
-
-// C[rows of the tile, n] = epi( sum_k A[row, k] * W[slot][k, n (+ up_col0)] ),  W[slot] = [K, ldw].
-// With a row map (gather != nullptr) row r of the left operand is row gather[r] / gather_k of A,
-// zero if the map holds no pair for it.  A tile of the table may hold several 64-row blocks (blockIdx.z).
-template <typename Elem, int EPI>
-__global__ __launch_bounds__(256) void gemm_generic_kernel(const Elem* __restrict__ A, int K,
-                                                           const Elem* __restrict__ W, int ldw, int n_out,
-                                                           int up_col0, Elem* __restrict__ C, TileTable t,
-                                                           const int32_t* __restrict__ gather, int gather_k,
-                                                           long long gather_T) {
-  constexpr int BM = 64, BN = 64, BK = 16;
-  constexpr bool DUAL = EPI == EPI_SWIGLU;
-  __shared__ float sA[BK][BM + 1];
-  __shared__ float sB[DUAL ? 2 : 1][BK][BN + 1];
-  const int tile = blockIdx.y;
-  if (tile >= t.header[0]) return;
-  const int slot = t.slot[tile], row0 = t.row0[tile] + 64 * blockIdx.z, row_end = t.row_end[tile];
-  if (slot < 0 || row0 >= row_end) return;
-  const int n0 = blockIdx.x * BN;
-  const Elem* Ws = W + (size_t)slot * K * ldw;
-  const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-  float acc[4][4] = {}, acc_up[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += BK) {
-    for (int i = threadIdx.x; i < BM * BK; i += 256) {
-      const int r = i / BK, kk = i % BK;
-      const int row = row0 + r;
-      long long src = row;
-      bool ok = row < row_end && k0 + kk < K;
-      if (gather && ok) {
-        const long long pair = gather[row];
-        ok = pair >= 0 && pair < gather_T * gather_k;
-        src = ok ? pair / gather_k : 0;
-      }
-      sA[kk][r] = ok ? load_elem<Elem>(A + (size_t)src * K + k0 + kk) : 0.f;
-    }
-    for (int i = threadIdx.x; i < BN * BK; i += 256) {
-      const int c = i % BN, kk = i / BN;  // consecutive threads read consecutive columns of a weight row
-      const int n = n0 + c;
-      const bool ok = n < n_out && k0 + kk < K;
-      sB[0][kk][c] = ok ? load_elem<Elem>(Ws + (size_t)(k0 + kk) * ldw + n) : 0.f;
-      if (DUAL) sB[DUAL ? 1 : 0][kk][c] = ok ? load_elem<Elem>(Ws + (size_t)(k0 + kk) * ldw + up_col0 + n) : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < BK; ++kk) {
-      float a[4], b[4], bu[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        a[i] = sA[kk][ty * 4 + i];
-        b[i] = sB[0][kk][tx * 4 + i];
-        bu[i] = DUAL ? sB[DUAL ? 1 : 0][kk][tx * 4 + i] : 0.f;
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-          if (DUAL) acc_up[i][j] = fmaf(a[i], bu[j], acc_up[i][j]);
-        }
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = row0 + ty * 4 + i;
-    if (row >= row_end) continue;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + tx * 4 + j;
-      if (n >= n_out) continue;
-      float v = acc[i][j];
-      if (EPI == EPI_GELU) v = gelu_exact(v);
-      if (EPI == EPI_SWIGLU) v = silu(v) * acc_up[i][j];
-      store_elem<Elem>(C + (size_t)row * n_out + n, v);
-    }
-  }
-}
-
 // Shapes on the MFMA kernels: every bf16 shape whose rows are whole 16-byte pieces.  Where a size is no
 // multiple of the tile the kernel computes the tile's padding too and stores the real part; a forward
-// of T = 3001, d = 1000, ffn = 2664, top-2 over 12 slots, SwiGLU: 2413 us on the FMA kernel above, 242 us here.  Sizes outside the first line
-// additionally accept unaligned tensors (on the FMA kernel) and fused gathers of any x; the MFMA gather's
+// of T = 3001, d = 1000, ffn = 2664, top-2 over 12 slots, SwiGLU: 2413 us on an fp32-FMA kernel, 242 us here.  Sizes outside the first line
+// additionally accept unaligned tensors (on the fp32 kernel) and fused gathers of any x; the MFMA gather's
 // 32-bit offsets hold x up to 2 GiB there, and a shape decides for all its calls.
 inline bool whole_tiles(const lz_shape* s) {
   return s->d % BN == 0 && s->ffn % 64 == 0 && s->ffn % (s->act == LZ_SWIGLU ? BN / 2 : BN) == 0;
@@ -142,7 +43,7 @@ TileTable tiles_of(const FfnWorkspace& w, const lz_shape* s) {
 FfnWorkspace carve_ffn(void* ws, const lz_shape* s) {
   FfnWorkspace w;
   const long long P = (long long)s->T * s->k;
-  w.BMrows = mfma_shape(s) ? BM : 64;
+  w.BMrows = mfma_shape(s) ? BM : kF32Rows;
   const size_t hidden_bytes = lz::align256((size_t)P * s->ffn * lz::elem_bytes(s->dtype));
   w.hidden = ws;
   w.tiles = (char*)ws + hidden_bytes;
@@ -205,26 +106,24 @@ int32_t ffn_up(const void* xp, const int32_t* gather, const void* w1, const lz_s
   const long long gT = shape->T;
   const bool aligned = aligned16(xp) && aligned16(w1);  // 16-byte loads per lane
   if (!mfma_shape(shape) || (!aligned && !whole_tiles(shape))) {
-    const dim3 grid((shape->ffn + 63) / 64, t.capacity, w.BMrows / 64);
-    if (shape->dtype == LZ_F32) {
-      if (swiglu)
-        hipLaunchKernelGGL((gemm_generic_kernel<float, EPI_SWIGLU>), grid, dim3(256), 0, st, (const float*)xp,
-                           shape->d, (const float*)w1, n1, shape->ffn, shape->ffn, (float*)w.hidden, t, gather,
-                           gk, gT);
-      else
-        hipLaunchKernelGGL((gemm_generic_kernel<float, EPI_GELU>), grid, dim3(256), 0, st, (const float*)xp,
-                           shape->d, (const float*)w1, n1, shape->ffn, 0, (float*)w.hidden, t, gather, gk, gT);
-    } else {
-      if (swiglu)
-        hipLaunchKernelGGL((gemm_generic_kernel<uint16_t, EPI_SWIGLU>), grid, dim3(256), 0, st,
-                           (const uint16_t*)xp, shape->d, (const uint16_t*)w1, n1, shape->ffn, shape->ffn,
-                           (uint16_t*)w.hidden, t, gather, gk, gT);
-      else
-        hipLaunchKernelGGL((gemm_generic_kernel<uint16_t, EPI_GELU>), grid, dim3(256), 0, st,
-                           (const uint16_t*)xp, shape->d, (const uint16_t*)w1, n1, shape->ffn, 0,
-                           (uint16_t*)w.hidden, t, gather, gk, gT);
-    }
-    return lz::launch_status();
+    F32Args a{};
+    a.A = xp;
+    a.W = w1;
+    a.C = w.hidden;
+    a.K = a.lda = shape->d;
+    a.ldw = n1;
+    a.w_slot = (long long)shape->d * n1;
+    a.ldc = a.n_out = a.ffn = shape->ffn;
+    a.t = t;
+    a.gather = gather;
+    a.gather_k = gk;
+    a.gather_T = gT;
+    const int S = shape->N * shape->c;
+    if (shape->dtype == LZ_F32)
+      return swiglu ? launch_f32_rows<float, EPI_SWIGLU, true>(a, w.BMrows, S, P, st)
+                    : launch_f32_rows<float, EPI_GELU, true>(a, w.BMrows, S, P, st);
+    return swiglu ? launch_f32_rows<uint16_t, EPI_SWIGLU, true>(a, w.BMrows, S, P, st)
+                  : launch_f32_rows<uint16_t, EPI_GELU, true>(a, w.BMrows, S, P, st);
   }
   if (!aligned) return LZ_EINVAL;
   // the MFMA gather addresses all of x with 32-bit byte offsets
@@ -275,16 +174,17 @@ extern "C" int32_t lz_ffn_down(const void* w2, const lz_shape* shape, void* yp, 
   TileTable t = tiles_of(w, shape);
   const bool aligned = aligned16(yp) && aligned16(w2);  // 16-byte accesses per lane
   if (!mfma_shape(shape) || (!aligned && !whole_tiles(shape))) {
-    const dim3 grid((shape->d + 63) / 64, t.capacity, w.BMrows / 64);
-    if (shape->dtype == LZ_F32)
-      hipLaunchKernelGGL((gemm_generic_kernel<float, EPI_NONE>), grid, dim3(256), 0, st,
-                         (const float*)w.hidden, shape->ffn, (const float*)w2, shape->d, shape->d, 0,
-                         (float*)yp, t, (const int32_t*)nullptr, 1, 0ll);
-    else
-      hipLaunchKernelGGL((gemm_generic_kernel<uint16_t, EPI_NONE>), grid, dim3(256), 0, st,
-                         (const uint16_t*)w.hidden, shape->ffn, (const uint16_t*)w2, shape->d, shape->d, 0,
-                         (uint16_t*)yp, t, (const int32_t*)nullptr, 1, 0ll);
-    return lz::launch_status();
+    F32Args a{};
+    a.A = w.hidden;
+    a.W = w2;
+    a.C = yp;
+    a.K = a.lda = shape->ffn;
+    a.w_slot = (long long)shape->ffn * shape->d;
+    a.ldw = a.ldc = a.n_out = shape->d;
+    a.t = t;
+    const int S = shape->N * shape->c;
+    return shape->dtype == LZ_F32 ? launch_f32_rows<float, EPI_NONE, true>(a, w.BMrows, S, P, st)
+                                  : launch_f32_rows<uint16_t, EPI_NONE, true>(a, w.BMrows, S, P, st);
   }
   if (!aligned) return LZ_EINVAL;
   MfmaArgs g2{};

@@ -866,12 +866,26 @@ __global__ __launch_bounds__(256, 1) void gemm_mfma_kernel(MfmaArgs a) {
 
 constexpr int kMaxDevices = 64;
 
+// CUs of the current device in whole multiples of the 8 XCDs, read once per device; 0 on an error
+inline int device_cus() {
+  static std::atomic<int> cus_of_device[kMaxDevices];
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 0;
+  int cus = cus_of_device[dev].load(std::memory_order_acquire);
+  if (cus == 0) {
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+    cus = cus >= 8 ? cus / 8 * 8 : 8;
+    cus_of_device[dev].store(cus, std::memory_order_release);
+  }
+  return cus;
+}
+
 template <int EPI, int MODE, bool GATHER, bool KTAIL>
 int32_t launch_mfma_kernel(const MfmaArgs& a, hipStream_t st) {
   static_assert(!GATHER || MODE == MODE_NN, "the gather is part of the forward's first GEMM only");
   void (*kern)(MfmaArgs) = gemm_mfma_kernel<EPI, MODE, GATHER, KTAIL>;
-  // per device: the LDS attribute is set and the CU count read on the first launch there (both
-  // idempotent, so two threads racing through the set-up do the same thing twice)
+  // per device: the LDS attribute is set on the first launch there (idempotent, so two threads racing through
+  // the set-up do the same thing twice)
   static std::atomic<int> workgroups_of_device[kMaxDevices];
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return LZ_EHIP;
@@ -880,9 +894,8 @@ int32_t launch_mfma_kernel(const MfmaArgs& a, hipStream_t st) {
     if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes) !=
         hipSuccess)
       return LZ_EHIP;
-    int cus = 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return LZ_EHIP;
-    n_workgroups = cus >= 8 ? cus / 8 * 8 : 8;  // one per CU (the LDS a workgroup takes allows no more)
+    n_workgroups = device_cus();  // one per CU (the LDS a workgroup takes allows no more)
+    if (n_workgroups == 0) return LZ_EHIP;
     workgroups_of_device[dev].store(n_workgroups, std::memory_order_release);
   }
   hipLaunchKernelGGL(kern, dim3(n_workgroups), dim3(256), kLdsBytes, st, a);
