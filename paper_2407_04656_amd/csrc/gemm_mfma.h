@@ -30,7 +30,10 @@ namespace {
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
-constexpr int kTileHeader = 64;  // ints before the tile arrays; [0] = number of row tiles
+// ints before the tile arrays; [0] = number of row tiles, then the lengths of the unit lists (kUnitCount), then,
+// a 128-byte line each, the queue counters (kTicket, kDone)
+constexpr int kLine = 32;
+constexpr int kTileHeader = 64 + 2 * (8 + 8 + 1) * kLine;
 constexpr int kGroupM = 4;       // row tiles of a work unit (same slot)
 constexpr int kGroupN = 8;       // column tiles of a work unit
 
@@ -50,6 +53,9 @@ struct TileTable {
 };
 
 constexpr int kUnitCount = 16;  // header[kUnitCount + 16*g + x] = length of XCD x's unit list for GEMM g
+// Counters of GEMM g: header[kTicket + (17*g + x) * kLine] = tickets drawn from XCD x's queue, x < 8;
+// x = 8..15: workgroups of XCD x - 8 that have finished; x = 16: XCDs that have finished
+constexpr int kTicket = 64;
 
 // Row tiles are listed slot after slot; with group > 1 every slot's list is padded (slot = -1)
 // to a multiple of `group`, so that a group of consecutive row tiles never spans two slots.
@@ -112,6 +118,7 @@ __global__ __launch_bounds__(256) void build_tiles_kernel(const int32_t* __restr
                                                           int S, long long P, int BM, int group,
                                                           int n_tiles_up, int n_tiles_down, TileTable t) {
   __shared__ int s_first[lz::kMaxN * lz::kMaxC + 1];
+  for (int i = threadIdx.x; i < 2 * 17; i += blockDim.x) t.header[kTicket + i * kLine] = 0;
   // padded tile count of every slot (parallel: the offsets come from global memory), then one
   // thread's running sum over LDS
   for (int s = threadIdx.x; s < S; s += blockDim.x) {
@@ -131,7 +138,6 @@ __global__ __launch_bounds__(256) void build_tiles_kernel(const int32_t* __restr
     }
     s_first[S] = running;
     t.header[0] = running;
-    for (int i = 40; i < 64; ++i) t.header[i] = 0;  // tile-queue tickets of the GEMM kernels
   }
   __syncthreads();
   for (int s = threadIdx.x; s < S; s += blockDim.x) {
@@ -804,13 +810,15 @@ __device__ __forceinline__ void gemm_tile(const MfmaArgs& a, char* smem, int slo
   }
 }
 
-[[maybe_unused]] constexpr int kTicket = 40;  // header[kTicket + 8*g + x]: next entry of XCD x's tile queue for GEMM g
-[[maybe_unused]] constexpr int kDone = 56;    // header[kDone + g]: workgroups of GEMM g's launch that have finished
-
-// Persistent kernel: one workgroup per CU.  Every XCD has a queue of tiles (its unit list, 32
-// tile slots per unit: kGroupM row tiles of one slot x kGroupN column tiles); a workgroup takes
-// the next slot of its own XCD's queue with an atomic ticket, and once that queue is empty
-// helps with the other XCDs' queues.  The 32 tiles an XCD works on at a time therefore share
+// Persistent kernel: one workgroup per CU.  Every XCD has a queue of tiles (its unit list, up to 32
+// tile slots per unit: kGroupM row tiles of one slot x at most kGroupN column tiles); a workgroup
+// starts with the entry of its index in its own XCD's queue, draws the next ones with an atomic ticket,
+// and once that queue is empty helps with the other XCDs' queues, of which it looks at the counters
+// first.  Atomics from all CUs on one line take their turns: with all counters in one line and a ticket
+// drawn past the end of every queue by every workgroup, the draws alone held the second GEMM at 80 us
+// and more however small it was.  A forward of 64 tokens over 16 slots (d = 1024, ffn = 4096): 206 -> 151 us, a
+// training step of 40960 tokens, top-1 over 60 slots (d = 768, ffn = 3072): 1983 -> 1805 us, with the units'
+// columns cut evenly (d = 768: units of 3 columns where 5 of 8 entries used to be padding).  The 32 tiles an XCD works on at a time therefore share
 // their activation and weight panels through that XCD's L2, and each XCD drains its queue at
 // its own pace.  (The hardware hands the workgroups of an ordinary launch to the XCDs strictly
 // in order of their index: there an XCD whose tiles take longer holds back the workgroups
@@ -820,47 +828,73 @@ __global__ __launch_bounds__(256, 1) void gemm_mfma_kernel(MfmaArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub, not the gfx950 builtins
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   constexpr int BN_OUT = (EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_KEEP) ? BN / 2 : BN;
-  constexpr int kUnitTiles = kGroupM * kGroupN;
   const int xcd = blockIdx.x % 8;  // workgroups are dealt round-robin to the 8 XCDs
+  const int per_xcd = gridDim.x / 8;
   const int n_col_groups = (a.n_tiles + kGroupN - 1) / kGroupN;
-  int* const ticket = a.t.header + kTicket + 8 * a.which;
+  const int group_n = (a.n_tiles + n_col_groups - 1) / n_col_groups;  // equal column groups, few entries past the last tile
+  const int unit_tiles = kGroupM * group_n;
+  int* const counter = a.t.header + kTicket + 17 * kLine * a.which;
   const int32_t* const count = a.t.header + kUnitCount + 16 * a.which;
-  for (int hop = 0; hop < 8; ++hop) {
-    const int q = (xcd + hop) % 8;
-    const int n_slots = count[q] * kUnitTiles;
-    const int32_t* const list = a.t.units[a.which] + (size_t)q * a.t.unit_cap[a.which];
+  // thread 0's next entry of queue q, -1 when no queue has one left
+  int q = xcd, home_entry = blockIdx.x / 8;
+  auto draw = [&]() {
+    if (home_entry >= 0) {
+      const int t = home_entry;
+      home_entry = -1;
+      if (t < count[q] * unit_tiles) return t;
+    }
     for (;;) {
-      __syncthreads();  // the previous tile's fragment reads are done: LDS may be reused
-      if (threadIdx.x == 0) *(volatile int*)smem = atomicAdd(ticket + q, 1);
-      __syncthreads();
-      const int t = __builtin_amdgcn_readfirstlane(*(volatile int*)smem);
-      __syncthreads();
-      if (t >= n_slots) break;  // every workgroup draws one ticket past the end of every queue, no more
-      const int unit = list[t / kUnitTiles];
-      const int within = t % kUnitTiles;
-      const int nt = (unit % n_col_groups) * kGroupN + within / kGroupM;
-      if (nt >= a.n_tiles) continue;
-      const int row_tile = (unit / n_col_groups) * kGroupM + within % kGroupM;
-      const int slot = a.t.slot[row_tile];
-      if (slot < 0) continue;
-      const int row0 = a.t.row0[row_tile];
-      const int row_end = a.t.row_end[row_tile];
-      const int n0 = nt * BN_OUT;
-      const int rows = row_end - row0;  // > 0; more than 256 means a full tile
-      if (rows > 192) gemm_tile<EPI, 4, MODE, GATHER, KTAIL>(a, smem, slot, row0, row_end, n0);
-      else if (rows > 128) gemm_tile<EPI, 3, MODE, GATHER, KTAIL>(a, smem, slot, row0, row_end, n0);
-      else if (rows > 64) gemm_tile<EPI, 2, MODE, GATHER, KTAIL>(a, smem, slot, row0, row_end, n0);
-      else gemm_tile<EPI, 1, MODE, GATHER, KTAIL>(a, smem, slot, row0, row_end, n0);
+      const int t = per_xcd + atomicAdd(counter + q * kLine, 1);
+      if (t < count[q] * unit_tiles) return t;
+      // the first queue from this XCD's on with an entry left (counters only grow: one that reads as empty is)
+      int drawn[8], left = -1;
+#pragma unroll
+      for (int h = 0; h < 8; ++h) drawn[h] = __hip_atomic_load(counter + h * kLine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+      for (int h = 0; h < 8; ++h)
+        if (per_xcd + drawn[h] < count[h] * unit_tiles && (left < 0 || ((h - xcd) & 7) < ((left - xcd) & 7))) left = h;
+      if (left < 0) return -1;
+      q = left;
     }
-  }
-  // the last workgroup to finish leaves the tickets at zero for the next launch on this table
-  if (threadIdx.x == 0) {
-    int* const done = a.t.header + kDone + a.which;
-    if (atomicAdd(done, 1) == (int)gridDim.x - 1) {
-      for (int q = 0; q < 8; ++q) ticket[q] = 0;
-      *done = 0;
+  };
+  struct TileRows {
+    int slot, row0, row_end, n0;
+  };
+  for (;;) {
+    __syncthreads();  // the previous tile's fragment reads are done: LDS may be reused
+    if (threadIdx.x == 0) {
+      TileRows tile{-1, 0, 0, 0};
+      for (int t = draw(); t >= 0; t = draw()) {
+        const int unit = a.t.units[a.which][(size_t)q * a.t.unit_cap[a.which] + t / unit_tiles];
+        const int within = t % unit_tiles;
+        const int nt = (unit % n_col_groups) * group_n + within / kGroupM;
+        const int row_tile = (unit / n_col_groups) * kGroupM + within % kGroupM;
+        tile = TileRows{a.t.slot[row_tile], a.t.row0[row_tile], a.t.row_end[row_tile], nt * BN_OUT};
+        if (nt < a.n_tiles && tile.slot >= 0) break;  // else an entry that only pads a unit
+        tile.slot = -1;
+      }
+      volatile int* const to = (volatile int*)smem;
+      to[0] = tile.slot;
+      to[1] = tile.row0;
+      to[2] = tile.row_end;
+      to[3] = tile.n0;
     }
+    __syncthreads();
+    const int slot = __builtin_amdgcn_readfirstlane(((volatile int*)smem)[0]);
+    const int row0 = __builtin_amdgcn_readfirstlane(((volatile int*)smem)[1]);
+    const int row_end = __builtin_amdgcn_readfirstlane(((volatile int*)smem)[2]);
+    const int n0 = __builtin_amdgcn_readfirstlane(((volatile int*)smem)[3]);
+    __syncthreads();
+    if (slot < 0) break;
+    const int rows = row_end - row0;  // > 0; more than 256 means a full tile
+    if (rows > 192) gemm_tile<EPI, 4, MODE, GATHER, KTAIL>(a, smem, slot, row0, row_end, n0);
+    else if (rows > 128) gemm_tile<EPI, 3, MODE, GATHER, KTAIL>(a, smem, slot, row0, row_end, n0);
+    else if (rows > 64) gemm_tile<EPI, 2, MODE, GATHER, KTAIL>(a, smem, slot, row0, row_end, n0);
+    else gemm_tile<EPI, 1, MODE, GATHER, KTAIL>(a, smem, slot, row0, row_end, n0);
   }
+  // the last workgroup to finish leaves the counters at zero for the next launch on this table
+  if (threadIdx.x == 0 && atomicAdd(counter + (8 + xcd) * kLine, 1) == per_xcd - 1 && atomicAdd(counter + 16 * kLine, 1) == 7)
+    for (int i = 0; i < 17; ++i) counter[i * kLine] = 0;
 #endif
 }
 
