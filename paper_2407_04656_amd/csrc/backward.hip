@@ -20,7 +20,7 @@
 // run over S x (rows of the weight matrix) virtual rows; each tile takes its contraction range
 // from slot_offsets.
 #include "backward_generic.h"
-#include "gemm_mfma.h"
+#include "gemm_narrow.h"
 
 namespace {
 
@@ -174,15 +174,6 @@ __global__ __launch_bounds__(256) void act_backward_kernel(const u32x4* __restri
   }
 }
 
-// slot offsets of the S x rows_per_slot virtual rows of the two weight-gradient outputs
-__global__ void virtual_rows_kernel(int S, int rows_w2, int rows_w1, int32_t* __restrict__ virt_w2,
-                                    int32_t* __restrict__ virt_w1) {
-  for (int s = threadIdx.x; s <= S; s += blockDim.x) {
-    virt_w2[s] = s * rows_w2;
-    virt_w1[s] = s * rows_w1;
-  }
-}
-
 // dW[e] = sum over slots s with slot_expert[s] == e of dW_slot[s], ascending s, fp32 sum, one rounding.
 // HBM bound: (S + E) x elems read and written once.  A thread owns one 16-byte vector of an expert's
 // gradient and has it loaded from kReduceAhead of the expert's slots before the first is added; the
@@ -241,12 +232,12 @@ __global__ __launch_bounds__(256) void reduce_replicas_kernel(const u32x4* __res
 struct TrainWorkspace {
   uint16_t* dh;        // [P, ffn]
   uint16_t* dz;        // [P, n1]
-  int32_t* virt_w2;    // [S+1]
-  int32_t* virt_w1;    // [S+1]
   void* tiles_fwd;     // rows of the batch: lists for the forward's two GEMMs (ffn / 128 or 256, d / 256 column tiles)
   void* tiles_bwd;     // rows of the batch: lists for ffn / 256 and d / 256 column tiles
   void* tiles_w2;      // S * ffn virtual rows, d / 256 column tiles
   void* tiles_w1;      // S * d virtual rows, n1 / 256 column tiles
+  void* tiles_narrow;  // rows of the batch, tiles of the GEMMs on narrow tiles
+  bool narrow_up, narrow_ffn, narrow_d;  // z, h; dH; yp and dxp on narrow tiles
   size_t total_bytes;
   int n1;
 };
@@ -264,12 +255,14 @@ TrainWorkspace carve_train(void* ws, const lz_shape* s) {
   };
   w.dh = (uint16_t*)take((size_t)P * s->ffn * 2);
   w.dz = (uint16_t*)take((size_t)P * w.n1 * 2);
-  w.virt_w2 = (int32_t*)take(sizeof(int32_t) * (S + 1));
-  w.virt_w1 = (int32_t*)take(sizeof(int32_t) * (S + 1));
   w.tiles_fwd = take(tile_table_bytes(P, S, BM, kGroupM, ceil_div(s->ffn, s->act == LZ_SWIGLU ? BN / 2 : BN), ceil_div(s->d, BN)));
   w.tiles_bwd = take(tile_table_bytes(P, S, BM, kGroupM, ceil_div(s->ffn, BN), ceil_div(s->d, BN)));
   w.tiles_w2 = take(tile_table_bytes((long long)S * s->ffn, S, BM, kGroupM, ceil_div(s->d, BN), 0));
   w.tiles_w1 = take(tile_table_bytes((long long)S * s->d, S, BM, kGroupM, ceil_div(w.n1, BN), 0));
+  w.narrow_ffn = use_narrow(P, S, s->ffn);
+  w.narrow_up = w.narrow_ffn && s->act == LZ_GELU;
+  w.narrow_d = use_narrow(P, S, s->d);
+  w.tiles_narrow = take(w.narrow_ffn || w.narrow_d ? tile_table_bytes(P, S, kNarrow, 1, 0, 0) : 0);
   w.total_bytes = size_t(p - (char*)ws);
   return w;
 }
@@ -291,16 +284,24 @@ int32_t check_train(const lz_shape* shape, void* ws, size_t ws_bytes, TrainWorks
   return LZ_OK;
 }
 
-int32_t build_table(const int32_t* offsets, int S, long long rows, int n_a, int n_b, void* mem, hipStream_t st,
-                    TileTable* out) {
-  *out = carve_tiles(mem, rows, S, BM, kGroupM, n_a, n_b);
-  hipLaunchKernelGGL(build_tiles_kernel, dim3(1), dim3(256), 0, st, offsets, S, rows, BM, kGroupM, n_a, n_b, *out);
+TileTable narrow_tiles(const TrainWorkspace& w, int S, long long P) {
+  return carve_tiles(w.tiles_narrow, P, S, kNarrow, 1, 0, 0);
+}
+
+// appends the table of the narrow GEMMs to n specs
+int add_narrow(TileSpecs* specs, int n, const TrainWorkspace& w, int S, long long P) {
+  specs->spec[n] = {kNarrow, 1, 0, 0, 0, P, narrow_tiles(w, S, P)};
+  return n + 1;
+}
+
+int32_t build_tables(const int32_t* offsets, int S, const TileSpecs& specs, int n, hipStream_t st) {
+  hipLaunchKernelGGL(build_tiles_kernel, dim3(n), dim3(256), 0, st, offsets, S, specs);
   return lz::launch_status();
 }
 
 // C[rows, n_out] = A[rows, K] W[slot][n_out, K]^T over the batch's ragged row ranges
 int32_t gemm_nt(const uint16_t* A, const uint16_t* W, uint16_t* C, long long P, int K, int n_out, int which,
-                  const TileTable& t, hipStream_t st) {
+                const TileTable& t, bool narrow, const TrainWorkspace& w, int S, hipStream_t st) {
   MfmaArgs g{};
   g.A = A;
   g.W = W;
@@ -312,12 +313,13 @@ int32_t gemm_nt(const uint16_t* A, const uint16_t* W, uint16_t* C, long long P, 
   g.n_tiles = ceil_div(n_out, BN);
   g.which = which;
   g.t = t;
+  if (narrow) return launch_narrow<EPI_NONE, MODE_NT>(g, narrow_tiles(w, S, P), st);
   return launch_mfma<EPI_NONE>(g, st);
 }
 
 // C[rows, n_out] = A[rows, K] W[slot][K, n_out] over the batch's ragged row ranges
 int32_t gemm_nn(const uint16_t* A, const uint16_t* W, uint16_t* C, long long P, int K, int n_out, int which,
-                   const TileTable& t, hipStream_t st) {
+                const TileTable& t, bool narrow, const TrainWorkspace& w, int S, hipStream_t st) {
   MfmaArgs g{};
   g.A = A;
   g.W = W;
@@ -330,6 +332,7 @@ int32_t gemm_nn(const uint16_t* A, const uint16_t* W, uint16_t* C, long long P, 
   g.which = which;
   g.t = t;
   g.ldw = n_out;
+  if (narrow) return launch_narrow<EPI_NONE, MODE_NN>(g, narrow_tiles(w, S, P), st);
   return launch_mfma<EPI_NONE, MODE_NN>(g, st);
 }
 
@@ -407,8 +410,10 @@ extern "C" int32_t lz_ffn_forward_train(const void* xp, const int32_t* slot_offs
   const int S = shape->N * shape->c;
   const bool swiglu = shape->act == LZ_SWIGLU;
   const int n_up = ceil_div(shape->ffn, swiglu ? BN / 2 : BN);
-  TileTable t;
-  int32_t r = build_table(slot_offsets, S, P, n_up, ceil_div(shape->d, BN), w.tiles_fwd, st, &t);
+  const TileTable t = carve_tiles(w.tiles_fwd, P, S, BM, kGroupM, n_up, ceil_div(shape->d, BN));
+  TileSpecs specs{};
+  specs.spec[0] = {BM, kGroupM, n_up, ceil_div(shape->d, BN), 0, P, t};
+  int32_t r = build_tables(slot_offsets, S, specs, w.narrow_up || w.narrow_d ? add_narrow(&specs, 1, w, S, P) : 1, st);
   if (r != LZ_OK) return r;
   // z = xp W1 and h = act(z) from one epilogue
   MfmaArgs g{};
@@ -426,9 +431,11 @@ extern "C" int32_t lz_ffn_forward_train(const void* xp, const int32_t* slot_offs
   g.which = 0;
   g.t = t;
   g.ldw = w.n1;
-  r = swiglu ? launch_mfma<EPI_SWIGLU_KEEP, MODE_NN>(g, st) : launch_mfma<EPI_GELU_KEEP, MODE_NN>(g, st);
+  if (w.narrow_up) r = launch_narrow<EPI_GELU_KEEP, MODE_NN>(g, narrow_tiles(w, S, P), st);
+  else r = swiglu ? launch_mfma<EPI_SWIGLU_KEEP, MODE_NN>(g, st) : launch_mfma<EPI_GELU_KEEP, MODE_NN>(g, st);
   if (r != LZ_OK) return r;
-  return gemm_nn((const uint16_t*)h, (const uint16_t*)w2, (uint16_t*)yp, P, shape->ffn, shape->d, 1, t, st);
+  return gemm_nn((const uint16_t*)h, (const uint16_t*)w2, (uint16_t*)yp, P, shape->ffn, shape->d, 1, t,
+                 w.narrow_d, w, S, st);
 }
 
 extern "C" int32_t lz_combine_backward(const void* dy, const void* yp, const int32_t* pair_to_row,
@@ -503,17 +510,21 @@ int32_t ffn_backward(const void* dyp, const void* xp, const void* z, const void*
   const int d = shape->d, ffn = shape->ffn, n1 = w.n1;
   const bool swiglu = shape->act == LZ_SWIGLU;
 
-  hipLaunchKernelGGL(virtual_rows_kernel, dim3(1), dim3(256), 0, st, S, ffn, d, w.virt_w2, w.virt_w1);
-  int32_t r = lz::launch_status();
+  const int n_ffn = ceil_div(ffn, BN), n_d = ceil_div(d, BN), n_n1 = ceil_div(n1, BN);
+  const long long rows_w2 = (long long)S * ffn, rows_w1 = (long long)S * d;
+  const TileTable t_rows = carve_tiles(w.tiles_bwd, P, S, BM, kGroupM, n_ffn, n_d);
+  const TileTable t_w2 = carve_tiles(w.tiles_w2, rows_w2, S, BM, kGroupM, n_d, 0);
+  const TileTable t_w1 = carve_tiles(w.tiles_w1, rows_w1, S, BM, kGroupM, n_n1, 0);
+  TileSpecs specs{};
+  specs.spec[0] = {BM, kGroupM, n_ffn, n_d, 0, P, t_rows};
+  specs.spec[1] = {BM, kGroupM, n_d, 0, ffn, rows_w2, t_w2};
+  specs.spec[2] = {BM, kGroupM, n_n1, 0, d, rows_w1, t_w1};
+  int32_t r = build_tables(slot_offsets, S, specs, w.narrow_ffn || w.narrow_d ? add_narrow(&specs, 3, w, S, P) : 3, st);
   if (r != LZ_OK) return r;
-  TileTable t_rows, t_w2, t_w1;
-  if ((r = build_table(slot_offsets, S, P, ceil_div(ffn, BN), ceil_div(d, BN), w.tiles_bwd, st, &t_rows)) != LZ_OK) return r;
-  if ((r = build_table(w.virt_w2, S, (long long)S * ffn, ceil_div(d, BN), 0, w.tiles_w2, st, &t_w2)) != LZ_OK) return r;
-  if ((r = build_table(w.virt_w1, S, (long long)S * d, ceil_div(n1, BN), 0, w.tiles_w1, st, &t_w1)) != LZ_OK) return r;
 
   if (P > 0) {
     // dH = dyp W2^T    (W2 [ffn, d]: contraction along its rows)
-    if ((r = gemm_nt((const uint16_t*)dyp, (const uint16_t*)w2, w.dh, P, d, ffn, 0, t_rows, st)) != LZ_OK) return r;
+    if ((r = gemm_nt((const uint16_t*)dyp, (const uint16_t*)w2, w.dh, P, d, ffn, 0, t_rows, w.narrow_ffn, w, S, st)) != LZ_OK) return r;
     // dZ = dH * act'(Z)
     const int ffn_vec = ffn / 8;
     const unsigned blocks = (unsigned)((P * ffn_vec + 255) / 256);
@@ -525,7 +536,7 @@ int32_t ffn_backward(const void* dyp, const void* xp, const void* z, const void*
                          (const u32x4*)z, P, ffn_vec, (u32x4*)w.dz);
     if ((r = lz::launch_status()) != LZ_OK) return r;
     // dxp = dZ W1^T    (W1 [d, n1])
-    if ((r = gemm_nt(w.dz, (const uint16_t*)w1, (uint16_t*)dxp, P, n1, d, 1, t_rows, st)) != LZ_OK) return r;
+    if ((r = gemm_nt(w.dz, (const uint16_t*)w1, (uint16_t*)dxp, P, n1, d, 1, t_rows, w.narrow_d, w, S, st)) != LZ_OK) return r;
   }
   // dW2[s] = H_s^T dyp_s  [ffn, d],   dW1[s] = xp_s^T dZ_s  [d, n1]
   if ((r = gemm_wgrad((const uint16_t*)h, (const uint16_t*)dyp, accumulate ? nullptr : (uint16_t*)dw2,

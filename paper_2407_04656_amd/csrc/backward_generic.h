@@ -75,9 +75,10 @@ inline GenericTrainWorkspace carve_train_generic(void* ws, const lz_shape* s) {
 }
 
 inline TileTable generic_tiles(const int32_t* slot_offsets, int S, long long P, const GenericTrainWorkspace& w, hipStream_t st) {
-  const TileTable t = carve_tiles(w.tiles, P, S, kF32Rows, 1, 0, 0);
-  hipLaunchKernelGGL(build_tiles_kernel, dim3(1), dim3(256), 0, st, slot_offsets, S, P, kF32Rows, 1, 0, 0, t);
-  return t;
+  TileSpecs specs{};
+  specs.spec[0] = {kF32Rows, 1, 0, 0, 0, P, carve_tiles(w.tiles, P, S, kF32Rows, 1, 0, 0)};
+  hipLaunchKernelGGL(build_tiles_kernel, dim3(1), dim3(256), 0, st, slot_offsets, S, specs);
+  return specs.spec[0].t;
 }
 
 template <typename Elem>

@@ -12,6 +12,7 @@
 //
 // fp32 tensors, and bf16 rows that are no whole 16-byte pieces: the fp32 matrix-core kernel of gemm_f32.h.
 #include "gemm_f32.h"
+#include "gemm_narrow.h"
 
 namespace {
 
@@ -34,10 +35,16 @@ struct FfnWorkspace {
   int BMrows;
   int group;
   int n_up, n_down;  // column tiles of the two MFMA GEMMs (0 on the generic path)
+  bool narrow_up, narrow_down;  // GEMMs on narrow tiles, which have a table of their own
+  void* tiles_narrow;
 };
 
 TileTable tiles_of(const FfnWorkspace& w, const lz_shape* s) {
   return carve_tiles(w.tiles, (long long)s->T * s->k, s->N * s->c, w.BMrows, w.group, w.n_up, w.n_down);
+}
+
+TileTable narrow_tiles_of(const FfnWorkspace& w, const lz_shape* s) {
+  return carve_tiles(w.tiles_narrow, (long long)s->T * s->k, s->N * s->c, kNarrow, 1, 0, 0);
 }
 
 FfnWorkspace carve_ffn(void* ws, const lz_shape* s) {
@@ -51,6 +58,10 @@ FfnWorkspace carve_ffn(void* ws, const lz_shape* s) {
   w.n_up = mfma_shape(s) ? ceil_div(s->ffn, s->act == LZ_SWIGLU ? BN / 2 : BN) : 0;
   w.n_down = mfma_shape(s) ? ceil_div(s->d, BN) : 0;
   w.total_bytes = hidden_bytes + tile_table_bytes(P, s->N * s->c, w.BMrows, w.group, w.n_up, w.n_down);
+  w.narrow_up = mfma_shape(s) && s->act == LZ_GELU && use_narrow(P, s->N * s->c, s->ffn);
+  w.narrow_down = mfma_shape(s) && use_narrow(P, s->N * s->c, s->d);
+  w.tiles_narrow = (char*)ws + w.total_bytes;
+  if (w.narrow_up || w.narrow_down) w.total_bytes += tile_table_bytes(P, s->N * s->c, kNarrow, 1, 0, 0);
   return w;
 }
 
@@ -81,9 +92,11 @@ extern "C" int32_t lz_ffn_tiles(const int32_t* slot_offsets, const lz_shape* sha
   if (P == 0) return LZ_OK;
   if (!slot_offsets) return LZ_EINVAL;
   const int S = shape->N * shape->c;
-  TileTable t = tiles_of(w, shape);
-  hipLaunchKernelGGL(build_tiles_kernel, dim3(1), dim3(256), 0, (hipStream_t)stream, slot_offsets, S, P,
-                     w.BMrows, w.group, w.n_up, w.n_down, t);
+  TileSpecs specs{};
+  int n = 0;
+  specs.spec[n++] = {w.BMrows, w.group, w.n_up, w.n_down, 0, P, tiles_of(w, shape)};
+  if (w.narrow_up || w.narrow_down) specs.spec[n++] = {kNarrow, 1, 0, 0, 0, P, narrow_tiles_of(w, shape)};
+  hipLaunchKernelGGL(build_tiles_kernel, dim3(n), dim3(256), 0, (hipStream_t)stream, slot_offsets, S, specs);
   return lz::launch_status();
 }
 
@@ -144,6 +157,9 @@ int32_t ffn_up(const void* xp, const int32_t* gather, const void* w1, const lz_s
   g1.gather = gather;
   g1.gather_k = gk;
   g1.gather_T = gT;
+  if (w.narrow_up)
+    return gather ? launch_narrow<EPI_GELU, MODE_NN, true>(g1, narrow_tiles_of(w, shape), st)
+                  : launch_narrow<EPI_GELU, MODE_NN>(g1, narrow_tiles_of(w, shape), st);
   if (gather)
     return swiglu ? launch_mfma<EPI_SWIGLU, MODE_NN, true>(g1, st) : launch_mfma<EPI_GELU, MODE_NN, true>(g1, st);
   return swiglu ? launch_mfma<EPI_SWIGLU, MODE_NN>(g1, st) : launch_mfma<EPI_GELU, MODE_NN>(g1, st);
@@ -200,6 +216,7 @@ extern "C" int32_t lz_ffn_down(const void* w2, const lz_shape* shape, void* yp, 
   g2.which = 1;
   g2.t = t;
   g2.ldw = shape->d;
+  if (w.narrow_down) return launch_narrow<EPI_NONE, MODE_NN>(g2, narrow_tiles_of(w, shape), st);
   return launch_mfma<EPI_NONE, MODE_NN>(g2, st);
 }
 

@@ -114,35 +114,68 @@ __device__ __forceinline__ void clip_slot(const int32_t* slot_offsets, int s, lo
 // kernel evens out by itself.  (Dealing by estimated cost, least-loaded queue first, was
 // within 2 % of this and costs a serial pass over the units; dealing the full row groups
 // first and the ragged ones last measured 1-5 % slower.)
-__global__ __launch_bounds__(256) void build_tiles_kernel(const int32_t* __restrict__ slot_offsets,
-                                                          int S, long long P, int BM, int group,
-                                                          int n_tiles_up, int n_tiles_down, TileTable t) {
+struct TileSpec {
+  int BM, group;                 // rows of a tile, tiles of a group
+  int n_tiles_up, n_tiles_down;  // column tiles of the two GEMMs that draw units from the table (0: none does)
+  int virtual_rows;              // > 0: every slot has this many rows (weight gradients), slot_offsets is not read
+  long long P;
+  TileTable t;
+};
+struct TileSpecs {
+  TileSpec spec[4];
+};
+
+// One workgroup per table.
+__global__ __launch_bounds__(256) void build_tiles_kernel(const int32_t* __restrict__ slot_offsets, int S,
+                                                          TileSpecs specs) {
   __shared__ int s_first[lz::kMaxN * lz::kMaxC + 1];
-  for (int i = threadIdx.x; i < 2 * 17; i += blockDim.x) t.header[kTicket + i * kLine] = 0;
-  // padded tile count of every slot (parallel: the offsets come from global memory), then one
-  // thread's running sum over LDS
-  for (int s = threadIdx.x; s < S; s += blockDim.x) {
-    long long a, b;
-    clip_slot(slot_offsets, s, P, &a, &b);
-    const int tiles = int((b - a + BM - 1) / BM);
-    s_first[s + 1] = (tiles + group - 1) / group * group;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int running = 0;
-    for (int s = 0; s < S; ++s) {
-      int padded = s_first[s + 1];
-      if (running + padded > t.capacity) padded = t.capacity - running;  // cannot happen for clipped offsets
-      s_first[s] = running;
-      running += padded;
+  __shared__ int s_wave[4];
+  const TileSpec& spec = specs.spec[blockIdx.x];
+  const TileTable t = spec.t;
+  const int BM = spec.BM, group = spec.group, n_tiles_up = spec.n_tiles_up, n_tiles_down = spec.n_tiles_down;
+  const int tid = threadIdx.x, lane = tid % lz::kWave, wave = tid / lz::kWave;
+  auto slot_rows = [&](int s, long long* a, long long* b) {
+    if (spec.virtual_rows > 0) {
+      *a = (long long)s * spec.virtual_rows;
+      *b = *a + spec.virtual_rows;
+    } else {
+      clip_slot(slot_offsets, s, spec.P, a, b);
     }
-    s_first[S] = running;
-    t.header[0] = running;
-  }
-  __syncthreads();
-  for (int s = threadIdx.x; s < S; s += blockDim.x) {
+  };
+  // padded tile count of every slot and its exclusive sum: each thread owns a run of consecutive slots
+  const int per = (S + 255) / 256, first = tid * per;
+  int mine = 0;
+  for (int s = first; s < first + per && s < S; ++s) {
     long long a, b;
-    clip_slot(slot_offsets, s, P, &a, &b);
+    slot_rows(s, &a, &b);
+    const int tiles = int((b - a + BM - 1) / BM);
+    s_first[s] = mine;
+    mine += (tiles + group - 1) / group * group;
+  }
+  int incl = mine;
+#pragma unroll
+  for (int off = 1; off < lz::kWave; off <<= 1) {
+    const int n = __shfl_up(incl, off);
+    if (lane >= off) incl += n;
+  }
+  if (lane == lz::kWave - 1) s_wave[wave] = incl;
+  __syncthreads();
+  int base = incl - mine;
+  for (int w = 0; w < wave; ++w) base += s_wave[w];
+  for (int s = first; s < first + per && s < S; ++s) {
+    const int f = s_first[s] + base;
+    s_first[s] = f < t.capacity ? f : t.capacity;  // always below for clipped offsets
+  }
+  if (tid == 255) {
+    const int all = base + mine < t.capacity ? base + mine : t.capacity;
+    s_first[S] = all;
+    t.header[0] = all;
+  }
+  if (tid < 2 * 17) t.header[kTicket + tid * kLine] = 0;
+  __syncthreads();
+  for (int s = tid; s < S; s += 256) {
+    long long a, b;
+    slot_rows(s, &a, &b);
     for (int i = s_first[s]; i < s_first[s + 1]; ++i) {
       const long long r0 = a + (long long)(i - s_first[s]) * BM;
       t.slot[i] = r0 < b ? s : -1;  // -1: padding entry, no rows
@@ -818,7 +851,8 @@ __device__ __forceinline__ void gemm_tile(const MfmaArgs& a, char* smem, int slo
 // drawn past the end of every queue by every workgroup, the draws alone held the second GEMM at 80 us
 // and more however small it was.  A forward of 64 tokens over 16 slots (d = 1024, ffn = 4096): 206 -> 151 us, a
 // training step of 40960 tokens, top-1 over 60 slots (d = 768, ffn = 3072): 1983 -> 1805 us, with the units'
-// columns cut evenly (d = 768: units of 3 columns where 5 of 8 entries used to be padding).  The 32 tiles an XCD works on at a time therefore share
+// columns cut evenly (d = 768: units of 3 columns where 5 of 8 entries used to be padding).
+// The 32 tiles an XCD works on at a time share
 // their activation and weight panels through that XCD's L2, and each XCD drains its queue at
 // its own pace.  (The hardware hands the workgroups of an ordinary launch to the XCDs strictly
 // in order of their index: there an XCD whose tiles take longer holds back the workgroups
