@@ -61,6 +61,17 @@ class Shape:
     def c_struct(self):
         return _Shape(self.T, self.d, self.ffn, self.E, self.k, self.N, self.c, self.dtype, self.act)
 
+    def _arg(self):
+        """c_struct() by reference, built once: a Shape does not change."""
+        ref = self.__dict__.get("_ref")
+        if ref is None:
+            ref = C.byref(self.c_struct())
+            object.__setattr__(self, "_ref", ref)
+        return ref
+
+    def __reduce__(self):
+        return (Shape, (self.T, self.d, self.ffn, self.E, self.k, self.N, self.c, self.dtype, self.act))
+
     @staticmethod
     def from_config(cfg):
         return Shape(cfg.T, cfg.d, cfg.ffn, cfg.E, cfg.k, cfg.N, cfg.c,
@@ -135,6 +146,18 @@ def _load():
 
 
 lib = _load()
+# The current stream's handle as torch.cuda.current_stream().cuda_stream gives it, without the Stream object that
+# call builds (the larger part of a small call's host time).
+try:
+    from torch._C import _cuda_getCurrentRawStream as _raw_stream
+    from torch.cuda import current_device as _current_device
+except ImportError:  # no torch, or one without that entry
+    def _current_device():
+        return None
+
+    def _raw_stream(_):
+        import torch
+        return torch.cuda.current_stream().cuda_stream
 def lz_strerror(code: int) -> str:
     return lib.lz_strerror(int(code)).decode()
 
@@ -160,16 +183,15 @@ def _ptr(t):
 
 
 def _stream():
-    import torch
-    return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_current_device())
 
 
 def lz_plan_workspace_bytes(shape: Shape) -> int:
-    return int(lib.lz_plan_workspace_bytes(C.byref(shape.c_struct())))
+    return int(lib.lz_plan_workspace_bytes(shape._arg()))
 
 
 def lz_ffn_workspace_bytes(shape: Shape) -> int:
-    return int(lib.lz_ffn_workspace_bytes(C.byref(shape.c_struct())))
+    return int(lib.lz_ffn_workspace_bytes(shape._arg()))
 
 
 # ------------------------------------------------------------------ device hot path
@@ -180,7 +202,7 @@ def lz_route(logits, T, E, k, topk_ids, topk_gates, stream=None):
 
 def lz_plan_dispatch(topk_ids, shape, rank_tok_off, slot_expert, slot_counts, slot_offsets, pair_to_row,
                      row_to_pair, Tej_opt, D_opt, status_opt, ws, ws_bytes, stream=None):
-    _check(lib.lz_plan_dispatch(_ptr(topk_ids), C.byref(shape.c_struct()), _ptr(rank_tok_off),
+    _check(lib.lz_plan_dispatch(_ptr(topk_ids), shape._arg(), _ptr(rank_tok_off),
                                 _ptr(slot_expert), _ptr(slot_counts), _ptr(slot_offsets),
                                 _ptr(pair_to_row), _ptr(row_to_pair), _ptr(Tej_opt), _ptr(D_opt),
                                 _ptr(status_opt), _ptr(ws), ws_bytes,
@@ -189,7 +211,7 @@ def lz_plan_dispatch(topk_ids, shape, rank_tok_off, slot_expert, slot_counts, sl
 
 def lz_plan_dispatch_noalloc(topk_ids, shape, rank_tok_off, slot_expert, slot_counts, slot_offsets, pair_to_row,
                              row_to_pair, Tej_opt, D_opt, status_opt, stream=None):
-    _check(lib.lz_plan_dispatch_noalloc(_ptr(topk_ids), C.byref(shape.c_struct()), _ptr(rank_tok_off),
+    _check(lib.lz_plan_dispatch_noalloc(_ptr(topk_ids), shape._arg(), _ptr(rank_tok_off),
                                         _ptr(slot_expert), _ptr(slot_counts), _ptr(slot_offsets),
                                         _ptr(pair_to_row), _ptr(row_to_pair), _ptr(Tej_opt), _ptr(D_opt),
                                         _ptr(status_opt), _stream() if stream is None else stream),
@@ -197,12 +219,12 @@ def lz_plan_dispatch_noalloc(topk_ids, shape, rank_tok_off, slot_expert, slot_co
 
 
 def lz_permute(x, row_to_pair, shape, xp, stream=None):
-    _check(lib.lz_permute(_ptr(x), _ptr(row_to_pair), C.byref(shape.c_struct()), _ptr(xp),
+    _check(lib.lz_permute(_ptr(x), _ptr(row_to_pair), shape._arg(), _ptr(xp),
                           _stream() if stream is None else stream), "lz_permute")
 
 
 def lz_permute_scatter(x, pair_to_row, shape, xp, stream=None):
-    _check(lib.lz_permute_scatter(_ptr(x), _ptr(pair_to_row), C.byref(shape.c_struct()), _ptr(xp),
+    _check(lib.lz_permute_scatter(_ptr(x), _ptr(pair_to_row), shape._arg(), _ptr(xp),
                                   _stream() if stream is None else stream), "lz_permute_scatter")
 
 
@@ -212,81 +234,81 @@ def lz_pack_weights(w, S, rows, cols, dtype, packed, stream=None):
 
 
 def lz_expert_ffn(xp, slot_offsets, w1, w2, shape, yp, ws, ws_bytes, stream=None):
-    _check(lib.lz_expert_ffn(_ptr(xp), _ptr(slot_offsets), _ptr(w1), _ptr(w2), C.byref(shape.c_struct()),
+    _check(lib.lz_expert_ffn(_ptr(xp), _ptr(slot_offsets), _ptr(w1), _ptr(w2), shape._arg(),
                              _ptr(yp), _ptr(ws), ws_bytes,
                              _stream() if stream is None else stream), "lz_expert_ffn")
 
 
 def lz_ffn_tiles(slot_offsets, shape, ws, ws_bytes, stream=None):
-    _check(lib.lz_ffn_tiles(_ptr(slot_offsets), C.byref(shape.c_struct()), _ptr(ws), ws_bytes,
+    _check(lib.lz_ffn_tiles(_ptr(slot_offsets), shape._arg(), _ptr(ws), ws_bytes,
                             _stream() if stream is None else stream), "lz_ffn_tiles")
 
 
 def lz_ffn_up(xp, w1, shape, ws, ws_bytes, stream=None):
-    _check(lib.lz_ffn_up(_ptr(xp), _ptr(w1), C.byref(shape.c_struct()), _ptr(ws), ws_bytes,
+    _check(lib.lz_ffn_up(_ptr(xp), _ptr(w1), shape._arg(), _ptr(ws), ws_bytes,
                          _stream() if stream is None else stream), "lz_ffn_up")
 
 
 def lz_ffn_up_gather(x, row_to_pair, w1, shape, ws, ws_bytes, stream=None):
-    _check(lib.lz_ffn_up_gather(_ptr(x), _ptr(row_to_pair), _ptr(w1), C.byref(shape.c_struct()), _ptr(ws), ws_bytes,
+    _check(lib.lz_ffn_up_gather(_ptr(x), _ptr(row_to_pair), _ptr(w1), shape._arg(), _ptr(ws), ws_bytes,
                                 _stream() if stream is None else stream), "lz_ffn_up_gather")
 
 
 def lz_expert_ffn_gather(x, row_to_pair, slot_offsets, w1, w2, shape, yp, ws, ws_bytes, stream=None):
     _check(lib.lz_expert_ffn_gather(_ptr(x), _ptr(row_to_pair), _ptr(slot_offsets), _ptr(w1), _ptr(w2),
-                                    C.byref(shape.c_struct()), _ptr(yp), _ptr(ws), ws_bytes,
+                                    shape._arg(), _ptr(yp), _ptr(ws), ws_bytes,
                                     _stream() if stream is None else stream), "lz_expert_ffn_gather")
 
 
 def lz_ffn_down(w2, shape, yp, ws, ws_bytes, stream=None):
-    _check(lib.lz_ffn_down(_ptr(w2), C.byref(shape.c_struct()), _ptr(yp), _ptr(ws), ws_bytes,
+    _check(lib.lz_ffn_down(_ptr(w2), shape._arg(), _ptr(yp), _ptr(ws), ws_bytes,
                            _stream() if stream is None else stream), "lz_ffn_down")
 
 
 def lz_unpermute_combine(yp, pair_to_row, topk_gates, shape, y, stream=None):
     _check(lib.lz_unpermute_combine(_ptr(yp), _ptr(pair_to_row), _ptr(topk_gates),
-                                    C.byref(shape.c_struct()), _ptr(y),
+                                    shape._arg(), _ptr(y),
                                     _stream() if stream is None else stream), "lz_unpermute_combine")
 
 
 # ------------------------------------------------------------------ training
 def lz_train_workspace_bytes(shape: Shape) -> int:
-    return int(lib.lz_train_workspace_bytes(C.byref(shape.c_struct())))
+    return int(lib.lz_train_workspace_bytes(shape._arg()))
 
 
 def lz_ffn_forward_train(xp, slot_offsets, w1, w2, shape, z, h, yp, ws, ws_bytes, stream=None):
-    _check(lib.lz_ffn_forward_train(_ptr(xp), _ptr(slot_offsets), _ptr(w1), _ptr(w2), C.byref(shape.c_struct()),
+    _check(lib.lz_ffn_forward_train(_ptr(xp), _ptr(slot_offsets), _ptr(w1), _ptr(w2), shape._arg(),
                                     _ptr(z), _ptr(h), _ptr(yp), _ptr(ws), ws_bytes,
                                     _stream() if stream is None else stream), "lz_ffn_forward_train")
 
 
 def lz_combine_backward(dy, yp, pair_to_row, topk_gates, shape, dyp, dgates, stream=None):
     _check(lib.lz_combine_backward(_ptr(dy), _ptr(yp), _ptr(pair_to_row), _ptr(topk_gates),
-                                   C.byref(shape.c_struct()), _ptr(dyp), _ptr(dgates),
+                                   shape._arg(), _ptr(dyp), _ptr(dgates),
                                    _stream() if stream is None else stream), "lz_combine_backward")
 
 
 def lz_ffn_backward(dyp, xp, z, h, slot_offsets, w1, w2, shape, dxp, dw1, dw2, ws, ws_bytes, stream=None):
     _check(lib.lz_ffn_backward(_ptr(dyp), _ptr(xp), _ptr(z), _ptr(h), _ptr(slot_offsets), _ptr(w1), _ptr(w2),
-                               C.byref(shape.c_struct()), _ptr(dxp), _ptr(dw1), _ptr(dw2), _ptr(ws), ws_bytes,
+                               shape._arg(), _ptr(dxp), _ptr(dw1), _ptr(dw2), _ptr(ws), ws_bytes,
                                _stream() if stream is None else stream), "lz_ffn_backward")
 
 
 def lz_ffn_backward_accumulate(dyp, xp, z, h, slot_offsets, w1, w2, shape, dxp, dw1_acc, dw2_acc, ws, ws_bytes,
                                stream=None):
     _check(lib.lz_ffn_backward_accumulate(_ptr(dyp), _ptr(xp), _ptr(z), _ptr(h), _ptr(slot_offsets), _ptr(w1),
-                                          _ptr(w2), C.byref(shape.c_struct()), _ptr(dxp), _ptr(dw1_acc),
+                                          _ptr(w2), shape._arg(), _ptr(dxp), _ptr(dw1_acc),
                                           _ptr(dw2_acc), _ptr(ws), ws_bytes,
                                           _stream() if stream is None else stream), "lz_ffn_backward_accumulate")
 
 
 def lz_permute_backward(dxp, pair_to_row, shape, dx, stream=None):
-    _check(lib.lz_permute_backward(_ptr(dxp), _ptr(pair_to_row), C.byref(shape.c_struct()), _ptr(dx),
+    _check(lib.lz_permute_backward(_ptr(dxp), _ptr(pair_to_row), shape._arg(), _ptr(dx),
                                    _stream() if stream is None else stream), "lz_permute_backward")
 
 
 def lz_route_backward(dgates, topk_gates, topk_ids, shape, dlogits, stream=None):
-    _check(lib.lz_route_backward(_ptr(dgates), _ptr(topk_gates), _ptr(topk_ids), C.byref(shape.c_struct()),
+    _check(lib.lz_route_backward(_ptr(dgates), _ptr(topk_gates), _ptr(topk_ids), shape._arg(),
                                  _ptr(dlogits), _stream() if stream is None else stream), "lz_route_backward")
 
 
@@ -373,7 +395,7 @@ def lz_apply_transfers(transfers, w1_old, w2_old, S_old, w1_new, w2_new, S_new, 
     for i, (d, s, e, r) in enumerate(transfers):
         arr[i] = _Transfer(d, s, e, r)
     _check(lib.lz_apply_transfers(C.addressof(arr), len(transfers), _ptr(w1_old), _ptr(w2_old), S_old,
-                                  _ptr(w1_new), _ptr(w2_new), S_new, C.byref(shape.c_struct()),
+                                  _ptr(w1_new), _ptr(w2_new), S_new, shape._arg(),
                                   _stream() if stream is None else stream), "lz_apply_transfers")
 
 
