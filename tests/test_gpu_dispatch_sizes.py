@@ -35,7 +35,10 @@ def test_route_sizes(E):
 
 
 @pytest.mark.parametrize("T,E,k,N,c", [(1, 1, 1, 1, 1), (129, 3, 2, 2, 2), (1000, 17, 5, 3, 6), (2000, 256, 8, 64, 5),
-                                       (4097, 130, 3, 33, 4), (640, 8, 1, 5, 64), (3000, 64, 6, 17, 4)])
+                                       (4097, 130, 3, 33, 4), (640, 8, 1, 5, 64), (3000, 64, 6, 17, 4),
+                                       # one workgroup for all, at and past its bounds: pairs, triples, slots, experts
+                                       (4096, 8, 1, 16, 8), (4097, 8, 1, 16, 8), (512, 2, 2, 32, 16), (100, 2, 2, 33, 15),
+                                       (50, 32, 8, 8, 64), (40, 33, 3, 4, 9), (1, 32, 1, 1, 40)])
 def test_dispatch_sizes(T, E, k, N, c):
     rng = np.random.default_rng(T + E)
     logits = (rng.standard_normal((T, E)) - 1.1 * np.log(1.0 + rng.permutation(E))).astype(np.float32)
