@@ -235,10 +235,10 @@ int32_t lz_unpermute_combine(const void* yp, const int32_t* pair_to_row,
  * Products are accumulated in fp32 and every stored tensor is rounded once to shape->dtype.
  * bf16 shapes with d % 8 == 0, ffn % 8 == 0, d*ffn*4 < 2^31 and N*c*2*max(d, ffn) < 2^31 run on
  * the MFMA kernels, whatever the size of the activation tensors (tensor pointers 16-byte aligned there;
- * where d % 256 or ffn % 64 is not zero, unaligned ones take the fp32 kernels);
- * every other valid shape (fp32 tensors, other bf16 sizes) runs on fp32 matrix-core kernels
- * that use erff / expf (the fp32 configuration meets its 1e-5 bar), as long as T*k/64 + N*c is
- * at most 65535.  All tensor pointers are device memory; `ws` is 256-byte aligned device memory of
+ * where d % 256 or ffn % 64 is not zero, unaligned ones take the fp32 kernels and T*k/64 + N*c is at
+ * most 65535); every other valid shape (fp32 tensors, other bf16 sizes) runs on fp32 matrix-core
+ * kernels that use erff / expf (the fp32 configuration meets its 1e-5 bar), as long as T*k/64 + N*c
+ * is at most 65535.  All tensor pointers are device memory; `ws` is 256-byte aligned device memory of
  * lz_train_workspace_bytes(shape) bytes that serves one call at a time. */
 size_t lz_train_workspace_bytes(const lz_shape* shape);
 

@@ -267,15 +267,21 @@ TrainWorkspace carve_train(void* ws, const lz_shape* s) {
   return w;
 }
 
-// The shapes the MFMA kernels serve: bf16 rows of whole 16-byte pieces, virtual row indices within int32.
+// the fp32 kernels' envelope: every valid shape of at most 65535 64-row tiles
+inline bool generic_train_shape(const lz_shape* s) {
+  if (!lz::shape_ok(s)) return false;
+  return tile_capacity((long long)s->T * s->k, s->N * s->c, 64, 1) <= 65535;
+}
+
+// The shapes the MFMA kernels serve: bf16 rows of whole 16-byte pieces, virtual row indices within int32.  Sizes
+// that the tiles do not divide stay inside the envelope above: they also take unaligned tensors, on the fp32
+// kernels (each call by itself: no state passes between the calls through the workspace).
+inline bool whole_tiles(const lz_shape* s) { return s->d % BN == 0 && s->ffn % 64 == 0; }
 inline bool train_shape(const lz_shape* s) {
   if (!lz::shape_ok(s) || !mfma_sizes(s)) return false;
   const long long S = (long long)s->N * s->c;
-  return S * s->d * 2 < (1ll << 31) && S * s->ffn * 2 < (1ll << 31);
+  return S * s->d * 2 < (1ll << 31) && S * s->ffn * 2 < (1ll << 31) && (whole_tiles(s) || generic_train_shape(s));
 }
-// ... of these, sizes that the tiles do not divide also take unaligned tensors, on the FMA kernels (each call
-// by itself: no state passes between the calls through the workspace)
-inline bool whole_tiles(const lz_shape* s) { return s->d % BN == 0 && s->ffn % 64 == 0; }
 
 int32_t check_train(const lz_shape* shape, void* ws, size_t ws_bytes, TrainWorkspace* w) {
   if (!train_shape(shape)) return LZ_ESHAPE;
@@ -361,12 +367,6 @@ int32_t gemm_wgrad(const uint16_t* A, const uint16_t* W, uint16_t* C, float* Cac
   const bool wide = ((unsigned long long)P + 4 * BK) * (unsigned)ld_max * 2ull > 0xFFFFFFFFull;
   if (wide) return Cacc ? launch_mfma<EPI_ACCUM, MODE_TN_WIDE>(g, st) : launch_mfma<EPI_NONE, MODE_TN_WIDE>(g, st);
   return Cacc ? launch_mfma<EPI_ACCUM, MODE_TN>(g, st) : launch_mfma<EPI_NONE, MODE_TN>(g, st);
-}
-
-// the generic path takes every valid shape whose 64-row tile count fits a grid dimension
-inline bool generic_train_shape(const lz_shape* s) {
-  if (!lz::shape_ok(s)) return false;
-  return tile_capacity((long long)s->T * s->k, s->N * s->c, 64, 1) <= 65535;
 }
 
 int32_t check_train_generic(const lz_shape* shape, void* ws, size_t ws_bytes, GenericTrainWorkspace* w) {
