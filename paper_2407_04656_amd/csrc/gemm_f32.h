@@ -441,7 +441,8 @@ int32_t launch_f32(F32Args a, long long rows32, long long max_rows32, hipStream_
   const long long resident = (long long)cus * (nw == 1 ? 4 : 3);  // what the LDS of a CU holds
   const dim3 grid((unsigned)(max_rows32 * a.n_tiles < resident ? max_rows32 * a.n_tiles : resident));
   const long long stage_bytes = 128ll * 4 * (a.lda > a.ldw ? a.lda : a.ldw);  // at most 128 rows of either operand
-  const bool vec = stage_bytes < (1ll << 31) && (!a.gather || a.gather_T * a.lda * 4 < (1ll << 31)) && a.K % 4 == 0 && a.lda % 4 == 0 && a.ldw % 4 == 0 && a.ldc % 4 == 0 && a.ldz % 4 == 0 &&
+  const bool vec = stage_bytes < (1ll << 31) && (!a.gather || a.gather_T * a.lda * 4 < (1ll << 31)) &&
+                   a.K % 4 == 0 && a.lda % 4 == 0 && a.ldw % 4 == 0 && a.ldc % 4 == 0 && a.ldz % 4 == 0 &&
                    a.n_out % 4 == 0 && a.ffn % 4 == 0 && a.m_rows % 4 == 0 && a.w_slot % 4 == 0 && aligned16(a.A) &&
                    aligned16(a.W) && aligned16(a.C) && aligned16(a.Z) && aligned16(a.Cacc);
   if (nw == 4) launch_f32_waves<Elem, EPI, WGRAD, WKM, 4>(a, grid, vec, st);

@@ -645,7 +645,8 @@ int32_t enqueue_plan(const int32_t* topk_ids, const lz_shape* shape, const int32
   if (P > 0)
     hipLaunchKernelGGL(count_kernel, dim3(blocks), dim3(256), 0, st, topk_ids, rank_tok_off, shape->T,
                        shape->E, shape->N, shape->k, t, row_to_pair);
-  hipLaunchKernelGGL(schedule_expert_kernel, dim3(shape->E), dim3(lz::kWave * (shape->N < 4 ? 4 : shape->N < 16 ? shape->N : 16)), 0, st, rank_tok_off,
+  const int expert_waves = shape->N < 4 ? 4 : shape->N < 16 ? shape->N : 16;  // one per source rank
+  hipLaunchKernelGGL(schedule_expert_kernel, dim3(shape->E), dim3(lz::kWave * expert_waves), 0, st, rank_tok_off,
                      slot_expert, shape->T, shape->E, shape->N, shape->c, shape->k, t, Tej_opt, D_opt);
   hipLaunchKernelGGL(schedule_slots_kernel, dim3(1), dim3(kSchedThreads), 0, st, rank_tok_off, slot_expert,
                      shape->T, shape->E, shape->N, shape->c, shape->k, t, slot_counts, slot_offsets,
