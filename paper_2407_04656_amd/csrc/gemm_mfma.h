@@ -142,32 +142,33 @@ __global__ __launch_bounds__(256) void build_tiles_kernel(const int32_t* __restr
       clip_slot(slot_offsets, s, spec.P, a, b);
     }
   };
-  // padded tile count of every slot and its exclusive sum: each thread owns a run of consecutive slots
+  // padded tile count of every slot and its exclusive sum: each thread owns a run of consecutive slots.  The sums
+  // end at the table's capacity, which the slots of ascending offsets stay within: offsets that fall again make
+  // slots overlap, any number of tiles in all.
+  auto add = [&](int x, int y) { return x + y < t.capacity ? x + y : t.capacity; };  // both at most capacity < 2^26
   const int per = (S + 255) / 256, first = tid * per;
   int mine = 0;
   for (int s = first; s < first + per && s < S; ++s) {
     long long a, b;
     slot_rows(s, &a, &b);
-    const int tiles = int((b - a + BM - 1) / BM);
+    const int tiles = int((b - a + BM - 1) / BM), padded = (tiles + group - 1) / group * group;
     s_first[s] = mine;
-    mine += (tiles + group - 1) / group * group;
+    mine = add(mine, padded < t.capacity ? padded : t.capacity);
   }
   int incl = mine;
 #pragma unroll
   for (int off = 1; off < lz::kWave; off <<= 1) {
     const int n = __shfl_up(incl, off);
-    if (lane >= off) incl += n;
+    if (lane >= off) incl = add(incl, n);
   }
   if (lane == lz::kWave - 1) s_wave[wave] = incl;
+  const int before = __shfl_up(incl, 1);
   __syncthreads();
-  int base = incl - mine;
-  for (int w = 0; w < wave; ++w) base += s_wave[w];
-  for (int s = first; s < first + per && s < S; ++s) {
-    const int f = s_first[s] + base;
-    s_first[s] = f < t.capacity ? f : t.capacity;  // always below for clipped offsets
-  }
+  int base = lane == 0 ? 0 : before;
+  for (int w = 0; w < wave; ++w) base = add(base, s_wave[w]);
+  for (int s = first; s < first + per && s < S; ++s) s_first[s] = add(s_first[s], base);
   if (tid == 255) {
-    const int all = base + mine < t.capacity ? base + mine : t.capacity;
+    const int all = add(base, mine);
     s_first[S] = all;
     t.header[0] = all;
   }
