@@ -980,9 +980,11 @@ int32_t launch_mfma(const MfmaArgs& a, hipStream_t st) {
 }
 
 // bf16 shapes the MFMA kernel takes: rows of whole 16-byte pieces, one slot's weights and one 256-row
-// activation tile within 32-bit byte offsets.
+// activation tile (rows of d, ffn or, dZ, n1 elements) within 32-bit byte offsets.
 inline bool mfma_sizes(const lz_shape* s) {
   if (s->dtype != LZ_BF16 || s->d % 8 != 0 || s->ffn % 8 != 0 || (long long)s->d * s->ffn * 4 >= (1ll << 31)) return false;
+  const long long n1 = (long long)s->ffn * (s->act == LZ_SWIGLU ? 2 : 1);
+  if ((long long)BM * 2 * (s->d > n1 ? s->d : n1) >= (1ll << 32)) return false;
   // KTAIL sets bit 31 of such an offset
   return (s->d % BK == 0 && s->ffn % BK == 0) || (long long)BM * (s->d > s->ffn ? s->d : s->ffn) * 4 < (1ll << 31);
 }
