@@ -139,7 +139,9 @@ extern "C" int32_t lz_apply_transfers(const lz_transfer* xfers, int32_t n, const
   // copies in the order of the list.
   const void* const ptrs[4] = {w1_old, w2_old, w1_new, w2_new};
   const size_t sizes[4] = {w1_bytes * S_old, w2_bytes * S_old, w1_bytes * S_new, w2_bytes * S_new};
-  bool plain = w1_bytes % 16 == 0 && w2_bytes % 16 == 0 && w1_bytes / 16 <= (1ull << 38) && w2_bytes / 16 <= (1ull << 38);
+  // (a grid holds fewer than 2^32 threads in x, one for kCopyAhead pieces each)
+  constexpr size_t kMostVecs = ((1ull << 32) - 256) * kCopyAhead;
+  bool plain = w1_bytes % 16 == 0 && w2_bytes % 16 == 0 && w1_bytes / 16 <= kMostVecs && w2_bytes / 16 <= kMostVecs;
   for (int p = 0; p < 4; ++p) {
     plain = plain && (uintptr_t)ptrs[p] % 16 == 0;
     for (int q = 2; q < 4; ++q) plain = plain && (p >= q || !overlap(ptrs[p], sizes[p], ptrs[q], sizes[q]));

@@ -13,3 +13,15 @@ for ffn in ((1 << 22) - 64, 1 << 22):
 """)
     assert out[0] == [0, 4]    # dH, dxp and both weight gradients: 96 wide tiles in the least of them
     assert out[1] == [0, 0]
+
+
+def test_transfers_of_slots_too_large_for_a_grid_are_copies(tmp_path):
+    """A grid holds fewer than 2^32 threads in x; four 16-byte pieces are a thread's."""
+    out = recorded(tmp_path, """
+out = []
+for d, ffn in ((1 << 18, (1 << 18) - 1), (1 << 18, 1 << 18)):     # 2^34 - 2^16 and 2^34 pieces of a slot's w1
+    s = lz.Shape(1, d, ffn, 1, 1, 1, 1, lz.LZ_F32, lz.LZ_GELU)
+    rc = code(lz.lz_apply_transfers, [(0, 0, 0, 0)], At(1 << 52), At(2 << 52), 1, At(3 << 52), At(4 << 52), 1, s)
+    out.append((rc, [c.split()[0] for c in calls()]))
+""")
+    assert out == [[0, ["launch"]], [0, ["copy", "copy"]]]
