@@ -49,6 +49,19 @@ inline bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes
   return (uintptr_t)a < (uintptr_t)b + b_bytes && (uintptr_t)b < (uintptr_t)a + a_bytes;
 }
 
+// Whether all of `ptrs` is memory of the stream's own GPU: only that can a kernel read and write without peer access
+// or a mapping; a device-to-device copy finds its way between any two places.
+bool on_device_of(hipStream_t st, const void* const* ptrs, int n) {
+  hipDevice_t dev = 0;
+  if (hipStreamGetDevice(st, &dev) != hipSuccess) return (void)hipGetLastError(), false;
+  for (int i = 0; i < n; ++i) {
+    hipPointerAttribute_t at{};
+    if (hipPointerGetAttributes(&at, ptrs[i]) != hipSuccess) return (void)hipGetLastError(), false;
+    if (at.type != hipMemoryTypeDevice || at.device != dev) return false;
+  }
+  return true;
+}
+
 int32_t copy_slots(std::vector<lz_transfer>& order, CopyMatrix a, CopyMatrix b, hipStream_t st) {
   const int n = (int)order.size();
   std::stable_sort(order.begin(), order.end(), [](const lz_transfer& x, const lz_transfer& y) { return x.src_slot < y.src_slot; });
@@ -135,8 +148,8 @@ extern "C" int32_t lz_apply_transfers(const lz_transfer* xfers, int32_t n, const
         xfers[i].src_slot >= S_old)
       return LZ_EINVAL;
   hipStream_t st = (hipStream_t)stream;
-  // One kernel for slots of whole, aligned 16-byte pieces that nothing else in the list reads or writes; else
-  // copies in the order of the list.
+  // One kernel for slots of whole, aligned 16-byte pieces that nothing else in the list reads or writes, on one GPU;
+  // else copies in the order of the list.
   const void* const ptrs[4] = {w1_old, w2_old, w1_new, w2_new};
   const size_t sizes[4] = {w1_bytes * S_old, w2_bytes * S_old, w1_bytes * S_new, w2_bytes * S_new};
   // (a grid holds fewer than 2^32 threads in x, one for kCopyAhead pieces each)
@@ -146,6 +159,7 @@ extern "C" int32_t lz_apply_transfers(const lz_transfer* xfers, int32_t n, const
     plain = plain && (uintptr_t)ptrs[p] % 16 == 0;
     for (int q = 2; q < 4; ++q) plain = plain && (p >= q || !overlap(ptrs[p], sizes[p], ptrs[q], sizes[q]));
   }
+  plain = plain && on_device_of(st, ptrs, 4);
   std::vector<lz_transfer> order;
   if (plain) try {
       std::vector<bool> written((size_t)S_new, false);

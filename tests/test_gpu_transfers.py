@@ -52,3 +52,23 @@ def test_transfers_inside_one_buffer_follow_the_list():
     for t, s in xfers:
         w1[t], w2[t] = w1[s], w2[s]
     assert np.array_equal(to_host(a), w1) and np.array_equal(to_host(b), w2)
+
+
+def test_transfers_under_capture():
+    """The one-kernel form is taken, captured and replayed like the other calls of a pass."""
+    shape = lz.Shape(1, 64, 64, 1, 1, 1, 1, lz.LZ_BF16, lz.LZ_GELU)
+    w1, w2 = (torch.randn((3, 64, 64), device=DEV).bfloat16() for _ in range(2))
+    n1, n2 = (torch.zeros((4, 64, 64), dtype=torch.bfloat16, device=DEV) for _ in range(2))
+    xfers = [(0, 2, 0, 0), (3, 2, 0, 0), (1, 0, 0, 0)]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        lz.lz_apply_transfers(xfers, w1, w2, 3, n1, n2, 4, shape)
+    for replay in range(3):
+        w1.add_(replay)
+        n1.zero_(), n2.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        for old, new in ((w1, n1), (w2, n2)):
+            for t, s, _, _ in xfers:
+                assert torch.equal(new[t], old[s])
+            assert not new[2].any()

@@ -25,3 +25,29 @@ for d, ffn in ((1 << 18, (1 << 18) - 1), (1 << 18, 1 << 18)):     # 2^34 - 2^16 
     out.append((rc, [c.split()[0] for c in calls()]))
 """)
     assert out == [[0, ["launch"]], [0, ["copy", "copy"]]]
+
+
+def test_transfers_between_places_are_copies(tmp_path):
+    """The kernel serves buffers of the stream's own GPU; a buffer of another one, or memory the runtime does not know
+    as a GPU's, is left to the runtime's copies, one per matrix and transfer, in the order of the list."""
+    out = recorded(tmp_path, """
+s = lz.Shape(64, 64, 64, 4, 2, 2, 2, lz.LZ_BF16, lz.LZ_GELU)
+size = 64 * 64 * 2
+def run(addresses, stream=0):
+    rc = code(lz.lz_apply_transfers, [(0, 1, 0, 0), (2, 0, 0, 0)], At(addresses[0]), At(addresses[1]), 4,
+              At(addresses[2]), At(addresses[3]), 4, s, stream=stream)
+    return rc, calls()
+here = [1 << 20, 2 << 20, 3 << 20, 4 << 20]
+out = [run(here), run([a + (1 << 40) for a in here], stream=1), run(here, stream=1)]
+for i in range(4):
+    for bit in (40, 44):
+        out.append(run([a + (1 << bit) * (j == i) for j, a in enumerate(here)]))
+w = [here[0], here[1], here[2], here[3] + (1 << 40)]
+out = [[rc, [c.split()[0] for c in cs]] for rc, cs in out] + [[[w[2 + m] + d * size, w[m] + q * size, size] for d, q in ((0, 1), (2, 0)) for m in range(2)],
+       [[int(v) for v in c.split()[1:]] for c in run(w)[1]]]
+""")
+    for one_device in out[:2]:
+        assert one_device == [0, ["launch"]]
+    for across in out[2:-2]:
+        assert across == [0, ["copy"] * 4]
+    assert out[-1] == out[-2]
