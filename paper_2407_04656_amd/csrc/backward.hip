@@ -262,7 +262,7 @@ TrainWorkspace carve_train(void* ws, const lz_shape* s) {
   w.narrow_ffn = use_narrow(P, S, s->ffn);
   w.narrow_up = w.narrow_ffn && s->act == LZ_GELU;
   w.narrow_d = use_narrow(P, S, s->d);
-  w.tiles_narrow = take(w.narrow_ffn || w.narrow_d ? tile_table_bytes(P, S, kNarrow, 1, 0, 0) : 0);
+  w.tiles_narrow = take(tile_table_bytes(P, S, kNarrow, 1, 0, 0));  // also where this P does not use it, as in the forward
   w.total_bytes = size_t(p - (char*)ws);
   return w;
 }

@@ -30,13 +30,13 @@ inline bool mfma_shape(const lz_shape* s) {
 
 struct FfnWorkspace {
   void* hidden;
-  void* tiles;
+  void* tiles;         // of the route the shape takes: BMrows-row tiles
+  void* tiles_narrow;  // of the GEMMs on narrow tiles
   size_t total_bytes;
   int BMrows;
   int group;
-  int n_up, n_down;  // column tiles of the two MFMA GEMMs (0 on the generic path)
-  bool narrow_up, narrow_down;  // GEMMs on narrow tiles, which have a table of their own
-  void* tiles_narrow;
+  int n_up, n_down;  // column tiles of the two MFMA GEMMs (0 on the fp32 kernel)
+  bool narrow_up, narrow_down;  // GEMMs on narrow tiles
 };
 
 TileTable tiles_of(const FfnWorkspace& w, const lz_shape* s) {
@@ -47,21 +47,38 @@ TileTable narrow_tiles_of(const FfnWorkspace& w, const lz_shape* s) {
   return carve_tiles(w.tiles_narrow, (long long)s->T * s->k, s->N * s->c, kNarrow, 1, 0, 0);
 }
 
+// Every table that some number of tokens of the same layer uses has its room, so that a workspace made for the
+// largest batch serves the smaller ones.
 FfnWorkspace carve_ffn(void* ws, const lz_shape* s) {
-  FfnWorkspace w;
+  FfnWorkspace w{};
   const long long P = (long long)s->T * s->k;
-  w.BMrows = mfma_shape(s) ? BM : kF32Rows;
-  const size_t hidden_bytes = lz::align256((size_t)P * s->ffn * lz::elem_bytes(s->dtype));
-  w.hidden = ws;
-  w.tiles = (char*)ws + hidden_bytes;
-  w.group = mfma_shape(s) ? kGroupM : 1;
-  w.n_up = mfma_shape(s) ? ceil_div(s->ffn, s->act == LZ_SWIGLU ? BN / 2 : BN) : 0;
-  w.n_down = mfma_shape(s) ? ceil_div(s->d, BN) : 0;
-  w.total_bytes = hidden_bytes + tile_table_bytes(P, s->N * s->c, w.BMrows, w.group, w.n_up, w.n_down);
-  w.narrow_up = mfma_shape(s) && s->act == LZ_GELU && use_narrow(P, s->N * s->c, s->ffn);
-  w.narrow_down = mfma_shape(s) && use_narrow(P, s->N * s->c, s->d);
-  w.tiles_narrow = (char*)ws + w.total_bytes;
-  if (w.narrow_up || w.narrow_down) w.total_bytes += tile_table_bytes(P, s->N * s->c, kNarrow, 1, 0, 0);
+  const int S = s->N * s->c;
+  const int n_up = ceil_div(s->ffn, s->act == LZ_SWIGLU ? BN / 2 : BN), n_down = ceil_div(s->d, BN);
+  char* p = (char*)ws;
+  auto take = [&](size_t bytes) {
+    char* r = p;
+    p += lz::align256(bytes);
+    return r;
+  };
+  w.hidden = take((size_t)P * s->ffn * lz::elem_bytes(s->dtype));
+  if (mfma_sizes(s)) {
+    w.tiles = take(tile_table_bytes(P, S, BM, kGroupM, n_up, n_down));
+    w.tiles_narrow = take(tile_table_bytes(P, S, kNarrow, 1, 0, 0));
+  }
+  void* const tiles_f32 = mfma_sizes(s) && whole_tiles(s) ? nullptr : take(tile_table_bytes(P, S, kF32Rows, 1, 0, 0));
+  if (mfma_shape(s)) {
+    w.BMrows = BM;
+    w.group = kGroupM;
+    w.n_up = n_up;
+    w.n_down = n_down;
+    w.narrow_up = s->act == LZ_GELU && use_narrow(P, S, s->ffn);
+    w.narrow_down = use_narrow(P, S, s->d);
+  } else {
+    w.tiles = tiles_f32;
+    w.BMrows = kF32Rows;
+    w.group = 1;
+  }
+  w.total_bytes = size_t(p - (char*)ws);
   return w;
 }
 

@@ -1,4 +1,8 @@
 """Which kernels a call launches, on a host without a GPU: the rules that choose by size, alignment and place."""
+import pytest
+
+import paper_2407_04656_amd as lz
+
 from hip_record import recorded
 
 
@@ -51,3 +55,25 @@ out = [[rc, [c.split()[0] for c in cs]] for rc, cs in out] + [[[w[2 + m] + d * s
     for across in out[2:-2]:
         assert across == [0, ["copy"] * 4]
     assert out[-1] == out[-2]
+
+
+@pytest.mark.parametrize("d,ffn,k,N,c", [
+    (512, 512, 1, 32, 40), (256, 128, 1, 64, 64), (4096, 14336, 2, 8, 2), (1000, 2664, 2, 6, 2), (72, 200, 1, 64, 64),
+    (20000, 20000, 1, 64, 64),     # 2 GiB of x at 53687 tokens, where the fp32 kernel takes over
+    (71, 205, 2, 4, 4),
+])
+@pytest.mark.parametrize("act", [lz.LZ_GELU, lz.LZ_SWIGLU])
+@pytest.mark.parametrize("dtype", [lz.LZ_F32, lz.LZ_BF16])
+def test_a_workspace_of_the_largest_batch_serves_the_smaller_ones(dtype, act, d, ffn, k, N, c):
+    def sizes(T):
+        s = lz.Shape(T, d, ffn, N * c if N * c < 256 else 256, k, N, c, dtype, act)
+        return lz.lz_plan_workspace_bytes(s), lz.lz_ffn_workspace_bytes(s), lz.lz_train_workspace_bytes(s)
+
+    edge = 2 ** 31 // (2 * d)
+    tokens = sorted({*range(1, 800), *(int(800 * 1.07 ** i) for i in range(110)), *range(edge - 3, edge + 4)})
+    last = (0, 0, 0)
+    for T in tokens:
+        now = sizes(T)
+        # training refuses batches past its limit of row tiles: 0 bytes, no workspace to share
+        assert all(n >= l or (n == 0 and i == 2) for i, (n, l) in enumerate(zip(now, last))), (T, now, last)
+        last = now
