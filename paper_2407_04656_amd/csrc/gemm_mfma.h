@@ -174,14 +174,29 @@ __global__ __launch_bounds__(256) void build_tiles_kernel(const int32_t* __restr
   }
   if (tid < 2 * 17) t.header[kTicket + tid * kLine] = 0;
   __syncthreads();
-  for (int s = tid; s < S; s += 256) {
-    long long a, b;
-    slot_rows(s, &a, &b);
-    for (int i = s_first[s]; i < s_first[s + 1]; ++i) {
-      const long long r0 = a + (long long)(i - s_first[s]) * BM;
-      t.slot[i] = r0 < b ? s : -1;  // -1: padding entry, no rows
-      t.row0[i] = int(r0 < b ? r0 : b);
-      t.row_end[i] = int(b);
+  // A thread writes the entries of its slot, 45 ns each.  Where a wave holds a few long slots (few slots share a large
+  // batch) it writes what is past kOwn of those together, slot after slot: 130 ns a slot and 64 entries a step.
+  // 32-row tiles of 10^6 rows in 1, 4, 32, 128 slots: 1390, 867, 136, 64 us by the threads alone, 28, 29, 31, 31 us so.
+  constexpr int kOwn = 64;
+  auto entry = [&](int i, int s, int first_i, long long a, long long b) {
+    const long long r0 = a + (long long)(i - first_i) * BM;
+    t.slot[i] = r0 < b ? s : -1;  // -1: padding entry, no rows
+    t.row0[i] = int(r0 < b ? r0 : b);
+    t.row_end[i] = int(b);
+  };
+  for (int s0 = wave * lz::kWave; s0 < S; s0 += 256) {  // the same trips in every lane
+    const int s = s0 + lane, from = s < S ? s_first[s] : 0, to = s < S ? s_first[s + 1] : 0;
+    long long a = 0, b = 0;
+    if (s < S) slot_rows(s, &a, &b);
+    unsigned long long many = __ballot(to - from > kOwn);
+    if (!__any(to - from > kOwn + 4 * __popcll(many))) many = 0;
+    const int own_end = many && to - from > kOwn ? from + kOwn : to;
+    for (int i = from; i < own_end; ++i) entry(i, s, from, a, b);
+    for (; many; many &= many - 1) {
+      const int l = __ffsll((long long)many) - 1;
+      const int f = __shfl(from, l), end = __shfl(to, l);
+      const long long sa = __shfl(a, l), sb = __shfl(b, l);
+      for (int i = f + kOwn + lane; i < end; i += lz::kWave) entry(i, s0 + l, f, sa, sb);
     }
   }
   // deal the units, in (row group, column group) order, to the XCD queues in rows of eight,

@@ -27,3 +27,28 @@ def test_offsets_that_fall_again_stay_inside_the_table(log_P):
     torch.cuda.synchronize()
     assert bool((ws[n:] == 0x5A).all())
     assert float((yp - torch.nn.functional.gelu(x)).abs().max()) <= 1e-6   # |gelu| <= 2: a few fp32 roundings
+
+
+@pytest.mark.parametrize("dtype,d", [(lz.LZ_F32, 1), (lz.LZ_BF16, 8), (lz.LZ_BF16, 9)])
+@pytest.mark.parametrize("counts", [
+    [40000],                                            # one slot, a long list of tiles
+    [0, 4 * 32, 4 * 32 + 1, 5 * 64, 1, 5 * 256 + 7, 20011, 0],
+    [33] * 70 + [3000] + [0] * 60 + [161] * 69,         # long and short lists in each wave of the table's kernel
+])
+def test_slots_of_few_and_of_many_tiles(dtype, d, counts):
+    P, S = sum(counts), len(counts)
+    shape = lz.Shape(P, d, d, 1, 1, S // 50 + 1, -(-S // (S // 50 + 1)), dtype, lz.LZ_GELU)
+    counts = counts + [0] * (shape.S - S)
+    tdt = torch.float32 if dtype == lz.LZ_F32 else torch.bfloat16
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(S)
+    x, w1, w2 = (torch.randn(n, generator=gen, device=DEV).to(tdt) for n in ((P, d), (shape.S, d, d), (shape.S, d, d)))
+    off = to_dev(np.concatenate([[0], np.cumsum(counts)]).astype(np.int32))
+    n = lz.lz_ffn_workspace_bytes(shape)
+    ws, yp = torch.empty(n, dtype=torch.uint8, device=DEV), torch.full((P, d), 7.0, dtype=tdt, device=DEV)
+    lz.lz_expert_ffn(x, off, w1, w2, shape, yp, ws, n)
+    slot = torch.from_numpy(np.repeat(np.arange(shape.S), counts)).to(DEV)
+    h = torch.nn.functional.gelu((x.double()[:, :, None] * w1.double()[slot]).sum(1))
+    ref = (h[:, :, None] * w2.double()[slot]).sum(1)
+    # the layer's bars: 1e-5 in fp32, 2e-2 of the largest value in bf16
+    assert float((yp.double() - ref).abs().max()) <= (1e-5 if dtype == lz.LZ_F32 else 2e-2) * float(ref.abs().max())
