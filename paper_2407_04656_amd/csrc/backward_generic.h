@@ -98,8 +98,8 @@ int32_t generic_forward_train(const void* xp, const int32_t* slot_offsets, const
   a.ldw = a.ldz = n1;
   a.w_slot = (long long)d * n1;
   a.ldc = a.n_out = a.ffn = ffn;
-  const int32_t r = s->act == LZ_SWIGLU ? launch_f32_rows<Elem, EPI_SWIGLU_KEEP, true>(a, kF32Rows, S, P, st)
-                                        : launch_f32_rows<Elem, EPI_GELU_KEEP, true>(a, kF32Rows, S, P, st);
+  const int32_t r = s->act == LZ_SWIGLU ? launch_f32_rows<Elem, EPI_SWIGLU_KEEP, true>(a, S, P, st)
+                                        : launch_f32_rows<Elem, EPI_GELU_KEEP, true>(a, S, P, st);
   if (r != LZ_OK) return r;
   // yp = h W2   (W2[s] = [ffn, d])
   F32Args b{};
@@ -110,7 +110,7 @@ int32_t generic_forward_train(const void* xp, const int32_t* slot_offsets, const
   b.K = b.lda = ffn;
   b.w_slot = (long long)ffn * d;
   b.ldw = b.ldc = b.n_out = d;
-  return launch_f32_rows<Elem, EPI_NONE, true>(b, kF32Rows, S, P, st);
+  return launch_f32_rows<Elem, EPI_NONE, true>(b, S, P, st);
 }
 
 template <typename Elem>
@@ -133,8 +133,8 @@ int32_t generic_ffn_backward(const void* dyp, const void* xp, const void* z, con
     a.w_slot = (long long)ffn * d;
     a.ldc = a.ldz = n1;
     a.n_out = a.ffn = ffn;
-    r = s->act == LZ_SWIGLU ? launch_f32_rows<Elem, EPI_DSWIGLU, false>(a, kF32Rows, S, P, st)
-                            : launch_f32_rows<Elem, EPI_DGELU, false>(a, kF32Rows, S, P, st);
+    r = s->act == LZ_SWIGLU ? launch_f32_rows<Elem, EPI_DSWIGLU, false>(a, S, P, st)
+                            : launch_f32_rows<Elem, EPI_DGELU, false>(a, S, P, st);
     if (r != LZ_OK) return r;
     // dxp = dZ W1^T: W1[s] [d, n1] along its rows
     F32Args b{};
@@ -145,7 +145,7 @@ int32_t generic_ffn_backward(const void* dyp, const void* xp, const void* z, con
     b.K = b.lda = b.ldw = n1;
     b.w_slot = (long long)d * n1;
     b.ldc = b.n_out = d;
-    if ((r = launch_f32_rows<Elem, EPI_NONE, false>(b, kF32Rows, S, P, st)) != LZ_OK) return r;
+    if ((r = launch_f32_rows<Elem, EPI_NONE, false>(b, S, P, st)) != LZ_OK) return r;
   }
   // dW2[s] = H_s^T dyp_s  [ffn, d],   dW1[s] = xp_s^T dZ_s  [d, n1]
   r = launch_f32_wgrad<Elem>(h, ffn, dyp, d, slot_offsets, S, P, accumulate ? nullptr : dw2, accumulate ? (float*)dw2 : nullptr, st);

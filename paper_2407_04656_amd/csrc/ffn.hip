@@ -30,21 +30,24 @@ inline bool mfma_shape(const lz_shape* s) {
 
 struct FfnWorkspace {
   void* hidden;
-  void* tiles;         // of the route the shape takes: BMrows-row tiles
+  void* tiles;         // of the wide bf16 GEMMs
   void* tiles_narrow;  // of the GEMMs on narrow tiles
+  void* tiles_f32;     // of the fp32 kernel
   size_t total_bytes;
-  int BMrows;
-  int group;
-  int n_up, n_down;  // column tiles of the two MFMA GEMMs (0 on the fp32 kernel)
+  int n_up, n_down;    // column tiles of the two wide GEMMs
   bool narrow_up, narrow_down;  // GEMMs on narrow tiles
 };
 
 TileTable tiles_of(const FfnWorkspace& w, const lz_shape* s) {
-  return carve_tiles(w.tiles, (long long)s->T * s->k, s->N * s->c, w.BMrows, w.group, w.n_up, w.n_down);
+  return carve_tiles(w.tiles, (long long)s->T * s->k, s->N * s->c, BM, kGroupM, w.n_up, w.n_down);
 }
 
 TileTable narrow_tiles_of(const FfnWorkspace& w, const lz_shape* s) {
   return carve_tiles(w.tiles_narrow, (long long)s->T * s->k, s->N * s->c, kNarrow, 1, 0, 0);
+}
+
+TileTable f32_tiles_of(const FfnWorkspace& w, const lz_shape* s) {
+  return carve_tiles(w.tiles_f32, (long long)s->T * s->k, s->N * s->c, kF32Rows, 1, 0, 0);
 }
 
 // Every table that some number of tokens of the same layer uses has its room, so that a workspace made for the
@@ -53,7 +56,8 @@ FfnWorkspace carve_ffn(void* ws, const lz_shape* s) {
   FfnWorkspace w{};
   const long long P = (long long)s->T * s->k;
   const int S = s->N * s->c;
-  const int n_up = ceil_div(s->ffn, s->act == LZ_SWIGLU ? BN / 2 : BN), n_down = ceil_div(s->d, BN);
+  w.n_up = ceil_div(s->ffn, s->act == LZ_SWIGLU ? BN / 2 : BN);
+  w.n_down = ceil_div(s->d, BN);
   char* p = (char*)ws;
   auto take = [&](size_t bytes) {
     char* r = p;
@@ -62,22 +66,12 @@ FfnWorkspace carve_ffn(void* ws, const lz_shape* s) {
   };
   w.hidden = take((size_t)P * s->ffn * lz::elem_bytes(s->dtype));
   if (mfma_sizes(s)) {
-    w.tiles = take(tile_table_bytes(P, S, BM, kGroupM, n_up, n_down));
+    w.tiles = take(tile_table_bytes(P, S, BM, kGroupM, w.n_up, w.n_down));
     w.tiles_narrow = take(tile_table_bytes(P, S, kNarrow, 1, 0, 0));
   }
-  void* const tiles_f32 = mfma_sizes(s) && whole_tiles(s) ? nullptr : take(tile_table_bytes(P, S, kF32Rows, 1, 0, 0));
-  if (mfma_shape(s)) {
-    w.BMrows = BM;
-    w.group = kGroupM;
-    w.n_up = n_up;
-    w.n_down = n_down;
-    w.narrow_up = s->act == LZ_GELU && use_narrow(P, S, s->ffn);
-    w.narrow_down = use_narrow(P, S, s->d);
-  } else {
-    w.tiles = tiles_f32;
-    w.BMrows = kF32Rows;
-    w.group = 1;
-  }
+  if (!mfma_sizes(s) || !whole_tiles(s)) w.tiles_f32 = take(tile_table_bytes(P, S, kF32Rows, 1, 0, 0));
+  w.narrow_up = mfma_shape(s) && s->act == LZ_GELU && use_narrow(P, S, s->ffn);
+  w.narrow_down = mfma_shape(s) && use_narrow(P, S, s->d);
   w.total_bytes = size_t(p - (char*)ws);
   return w;
 }
@@ -111,8 +105,10 @@ extern "C" int32_t lz_ffn_tiles(const int32_t* slot_offsets, const lz_shape* sha
   const int S = shape->N * shape->c;
   TileSpecs specs{};
   int n = 0;
-  specs.spec[n++] = {w.BMrows, w.group, w.n_up, w.n_down, 0, P, tiles_of(w, shape)};
+  if (mfma_shape(shape)) specs.spec[n++] = {BM, kGroupM, w.n_up, w.n_down, 0, P, tiles_of(w, shape)};
   if (w.narrow_up || w.narrow_down) specs.spec[n++] = {kNarrow, 1, 0, 0, 0, P, narrow_tiles_of(w, shape)};
+  // the calls that follow may bring unaligned tensors where that is allowed
+  if (!mfma_shape(shape) || !whole_tiles(shape)) specs.spec[n++] = {kF32Rows, 1, 0, 0, 0, P, f32_tiles_of(w, shape)};
   hipLaunchKernelGGL(build_tiles_kernel, dim3(n), dim3(256), 0, (hipStream_t)stream, slot_offsets, S, specs);
   return lz::launch_status();
 }
@@ -129,7 +125,6 @@ int32_t ffn_up(const void* xp, const int32_t* gather, const void* w1, const lz_s
   if (P == 0) return LZ_OK;
   if (!xp || !w1) return LZ_EINVAL;
   hipStream_t st = (hipStream_t)stream;
-  TileTable t = tiles_of(w, shape);
   const bool swiglu = shape->act == LZ_SWIGLU;
   const int n1 = shape->ffn * (swiglu ? 2 : 1);
   const int gk = shape->k;
@@ -144,16 +139,16 @@ int32_t ffn_up(const void* xp, const int32_t* gather, const void* w1, const lz_s
     a.ldw = n1;
     a.w_slot = (long long)shape->d * n1;
     a.ldc = a.n_out = a.ffn = shape->ffn;
-    a.t = t;
+    a.t = f32_tiles_of(w, shape);
     a.gather = gather;
     a.gather_k = gk;
     a.gather_T = gT;
     const int S = shape->N * shape->c;
     if (shape->dtype == LZ_F32)
-      return swiglu ? launch_f32_rows<float, EPI_SWIGLU, true>(a, w.BMrows, S, P, st)
-                    : launch_f32_rows<float, EPI_GELU, true>(a, w.BMrows, S, P, st);
-    return swiglu ? launch_f32_rows<uint16_t, EPI_SWIGLU, true>(a, w.BMrows, S, P, st)
-                  : launch_f32_rows<uint16_t, EPI_GELU, true>(a, w.BMrows, S, P, st);
+      return swiglu ? launch_f32_rows<float, EPI_SWIGLU, true>(a, S, P, st)
+                    : launch_f32_rows<float, EPI_GELU, true>(a, S, P, st);
+    return swiglu ? launch_f32_rows<uint16_t, EPI_SWIGLU, true>(a, S, P, st)
+                  : launch_f32_rows<uint16_t, EPI_GELU, true>(a, S, P, st);
   }
   if (!aligned) return LZ_EINVAL;
   // the MFMA gather addresses all of x with 32-bit byte offsets
@@ -169,7 +164,7 @@ int32_t ffn_up(const void* xp, const int32_t* gather, const void* w1, const lz_s
   g1.up_row0 = swiglu ? shape->ffn : 0;
   g1.n_tiles = w.n_up;
   g1.which = 0;
-  g1.t = t;
+  g1.t = tiles_of(w, shape);
   g1.ldw = n1;
   g1.gather = gather;
   g1.gather_k = gk;
@@ -204,7 +199,6 @@ extern "C" int32_t lz_ffn_down(const void* w2, const lz_shape* shape, void* yp, 
   if (P == 0) return LZ_OK;
   if (!w2 || !yp) return LZ_EINVAL;
   hipStream_t st = (hipStream_t)stream;
-  TileTable t = tiles_of(w, shape);
   const bool aligned = aligned16(yp) && aligned16(w2);  // 16-byte accesses per lane
   if (!mfma_shape(shape) || (!aligned && !whole_tiles(shape))) {
     F32Args a{};
@@ -214,10 +208,10 @@ extern "C" int32_t lz_ffn_down(const void* w2, const lz_shape* shape, void* yp, 
     a.K = a.lda = shape->ffn;
     a.w_slot = (long long)shape->ffn * shape->d;
     a.ldw = a.ldc = a.n_out = shape->d;
-    a.t = t;
+    a.t = f32_tiles_of(w, shape);
     const int S = shape->N * shape->c;
-    return shape->dtype == LZ_F32 ? launch_f32_rows<float, EPI_NONE, true>(a, w.BMrows, S, P, st)
-                                  : launch_f32_rows<uint16_t, EPI_NONE, true>(a, w.BMrows, S, P, st);
+    return shape->dtype == LZ_F32 ? launch_f32_rows<float, EPI_NONE, true>(a, S, P, st)
+                                  : launch_f32_rows<uint16_t, EPI_NONE, true>(a, S, P, st);
   }
   if (!aligned) return LZ_EINVAL;
   MfmaArgs g2{};
@@ -231,7 +225,7 @@ extern "C" int32_t lz_ffn_down(const void* w2, const lz_shape* shape, void* yp, 
   g2.up_row0 = 0;
   g2.n_tiles = w.n_down;
   g2.which = 1;
-  g2.t = t;
+  g2.t = tiles_of(w, shape);
   g2.ldw = shape->d;
   if (w.narrow_down) return launch_narrow<EPI_NONE, MODE_NN>(g2, narrow_tiles_of(w, shape), st);
   return launch_mfma<EPI_NONE, MODE_NN>(g2, st);

@@ -37,7 +37,6 @@ struct F32Args {
   long long w_slot;     // elements between the weights of two slots
   int n_out;            // result columns
   int n_tiles;          // column tiles
-  int parts;            // TM-row parts of an entry of the tile table
   int slots, m_tiles;   // weight gradients: row tiles of a slot's result
   int ffn;              // gated epilogues: columns between the gate and the up half
   TileTable t;
@@ -127,7 +126,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(F32Args a) {
   static_assert(2 * (kSizeA + kSizeW) >= KSPLIT * 32 * (TN + 4), "the K split's partial sums reuse the stages");
 
   constexpr int kOutCols = kGated ? TN / 2 : TN;
-  const int n_row_tiles = WGRAD ? a.slots * a.m_tiles : a.t.header[0] * a.parts;
+  const int n_row_tiles = WGRAD ? a.slots * a.m_tiles : a.t.header[0];
   const long long n_all = (long long)n_row_tiles * a.n_tiles;
   for (long long tile = blockIdx.x; tile < n_all; tile += gridDim.x) {
     const int row_tile = int(tile / a.n_tiles), n0 = int(tile % a.n_tiles) * kOutCols;
@@ -146,11 +145,10 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(F32Args a) {
       W += (size_t)lo * a.ldw;
       if (EPI == EPI_ACCUM && K == 0) continue;
     } else {
-      const int entry = row_tile / a.parts;
-      slot = __builtin_amdgcn_readfirstlane(a.t.slot[entry]);  // the same in every lane: buffer bases are scalar
-      row0 = __builtin_amdgcn_readfirstlane(a.t.row0[entry]) + TM * (row_tile % a.parts);
-      row_end = __builtin_amdgcn_readfirstlane(a.t.row_end[entry]);
-      if (slot < 0 || row0 >= row_end) continue;
+      slot = __builtin_amdgcn_readfirstlane(a.t.slot[row_tile]);  // the same in every lane: buffer bases are scalar
+      row0 = __builtin_amdgcn_readfirstlane(a.t.row0[row_tile]);
+      row_end = __builtin_amdgcn_readfirstlane(a.t.row_end[row_tile]);
+      if (slot < 0) continue;
       W += (size_t)slot * a.w_slot;
     }
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -450,13 +448,11 @@ int32_t launch_f32(F32Args a, long long rows32, long long max_rows32, hipStream_
   return lz::launch_status();
 }
 
-// One GEMM over the batch's row tiles (`table_rows` rows per entry of a.t: kF32Rows, or 256 where the table was
-// built for the bf16 MFMA kernel); S and P size the launch only.
+// One GEMM over the batch's row tiles (a.t: kF32Rows rows an entry); S and P size the launch only.
 template <typename Elem, int EPI, bool WKM>
-int32_t launch_f32_rows(F32Args a, int table_rows, int S, long long P, hipStream_t st) {
-  a.parts = table_rows / kF32Rows;
+int32_t launch_f32_rows(F32Args a, int S, long long P, hipStream_t st) {
   const long long used = P < S ? P : S;  // slots that can have rows, half a tile more each
-  return launch_f32<Elem, EPI, false, WKM>(a, P / kF32Rows + (used + 1) / 2, (long long)a.t.capacity * a.parts, st);
+  return launch_f32<Elem, EPI, false, WKM>(a, P / kF32Rows + (used + 1) / 2, a.t.capacity, st);
 }
 
 // The weight gradients of all slots: C[s] [m_rows, n_out] = A[rows of s]^T W[rows of s], or added to Cacc.

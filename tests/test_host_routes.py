@@ -77,3 +77,24 @@ def test_a_workspace_of_the_largest_batch_serves_the_smaller_ones(dtype, act, d,
         # training refuses batches past its limit of row tiles: 0 bytes, no workspace to share
         assert all(n >= l or (n == 0 and i == 2) for i, (n, l) in enumerate(zip(now, last))), (T, now, last)
         last = now
+
+
+def test_unaligned_forwards_have_a_table_of_the_fp32_kernels_tiles(tmp_path):
+    """Sizes that no tile divides take unaligned tensors on the fp32 kernel.  On the padded 256-row table of the bf16
+    GEMMs that kernel spends most of its steps on entries without rows (128 slots, 3000 tokens: 4 to 7 times the time),
+    so lz_ffn_tiles builds one of 32-row tiles beside it; whole tiles refuse such tensors and need none."""
+    out = recorded(tmp_path, """
+A, U, out = At(1 << 20), At((1 << 20) + 2), []
+for c, T, d, ffn in ((8, 3000, 1000, 2664), (1, 64, 1000, 2664), (8, 3000, 1024, 2560), (8, 3000, 1001, 2664)):
+    s = lz.Shape(T, d, ffn, 8, 2, 16, c, lz.LZ_BF16, lz.LZ_SWIGLU)
+    n = lz.lz_ffn_workspace_bytes(s)
+    rc = [code(lz.lz_expert_ffn, x, A, A, A, s, A, At(1 << 30), n) for x in (A, U)]
+    c = [x.split() for x in calls()]
+    tables = [int(x[2]) for x in c if "build_tiles" in x[1]]
+    gemms = ["f32" if "gemm_f32" in x[1] else "bf16" for x in c if "gemm" in x[1]]
+    out.append([rc, tables, gemms])
+""")
+    assert out[0] == [[0, 0], [2, 2], ["bf16", "bf16", "f32", "bf16"]]    # wide and 32-row tables
+    assert out[1] == [[0, 0], [3, 3], ["bf16", "bf16", "f32", "bf16"]]    # and the narrow tiles'
+    assert out[2] == [[0, -1], [1, 1], ["bf16", "bf16"]]
+    assert out[3] == [[0, 0], [1, 1], ["f32"] * 4]
