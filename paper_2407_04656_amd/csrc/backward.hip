@@ -182,7 +182,11 @@ __global__ __launch_bounds__(256) void act_backward_kernel(const u32x4* __restri
 // experts, 4.4 GB in and 2.2 GB out: 11.4 ms with one 4-byte element per thread and the slot loop,
 // 1.24 ms now (5.3 TB/s).  Four vectors of one slot in flight per thread instead are level there, but
 // leave a long tail where one expert holds half the slots (60 slots of 8 experts, 0.6 GB: +40 %).
-constexpr int kReduceAhead = 4;
+// fp32 sums of a few experts whose gradients are short are too few threads for that: they load kReduceAheadFew slots
+// ahead, where 64 slots hold that many of one expert.  512 slots of 1 expert of 65536, 2048 of 2 experts of 4096:
+// 140, 192 us by elements with caching loads, 234, 237 us with four ahead, 59, 90 us so.  With more experts the longer
+// chain of tests costs up to 70 %; bf16 is within 5 % either way.
+constexpr int kReduceAhead = 4, kReduceAheadFew = 16, kReduceFewExperts = 4, kReduceFewBlocks = 1024;
 
 __device__ __forceinline__ void add_vec(float* acc, const u32x4& v, float) {
 #pragma unroll
@@ -199,7 +203,7 @@ __device__ __forceinline__ u32x4 sum_vec(const float* acc, float) {
 }
 __device__ __forceinline__ u32x4 sum_vec(const float* acc, uint16_t) { return pack8(acc); }
 
-template <typename Elem>
+template <typename Elem, int AHEAD>
 __global__ __launch_bounds__(256) void reduce_replicas_kernel(const u32x4* __restrict__ dw_slot,
                                                               const int32_t* __restrict__ slot_expert, int S,
                                                               long long vec_per_slot, u32x4* __restrict__ dw) {
@@ -210,10 +214,10 @@ __global__ __launch_bounds__(256) void reduce_replicas_kernel(const u32x4* __res
   for (int s0 = 0; s0 < S; s0 += lz::kWave) {
     unsigned long long mine = __ballot(s0 + lane < S && slot_expert[s0 + lane < S ? s0 + lane : 0] == e);
     while (mine) {
-      u32x4 in[kReduceAhead];
+      u32x4 in[AHEAD];
       int n = 0;
 #pragma unroll
-      for (int u = 0; u < kReduceAhead; ++u)
+      for (int u = 0; u < AHEAD; ++u)
         if (mine) {
           const int s = s0 + __ffsll((long long)mine) - 1;
           mine &= mine - 1;
@@ -221,7 +225,7 @@ __global__ __launch_bounds__(256) void reduce_replicas_kernel(const u32x4* __res
           n = u + 1;
         }
 #pragma unroll
-      for (int u = 0; u < kReduceAhead; ++u)
+      for (int u = 0; u < AHEAD; ++u)
         if (u < n && live) add_vec(acc, in[u], Elem{});
     }
   }
@@ -572,8 +576,11 @@ int32_t reduce_vectors(const void* dw_slot, const int32_t* slot_expert, int32_t 
   const long long vec = elems_per_slot / (16 / (int)sizeof(Elem));
   const long long blocks = (vec + 255) / 256;
   if (blocks > 0x7FFFFFFFll) return LZ_ESHAPE;
-  hipLaunchKernelGGL(reduce_replicas_kernel<Elem>, dim3((unsigned)blocks, (unsigned)E), dim3(256), 0,
-                     (hipStream_t)stream, (const u32x4*)dw_slot, slot_expert, S, vec, (u32x4*)dw);
+  void (*kern)(const u32x4*, const int32_t*, int, long long, u32x4*) = reduce_replicas_kernel<Elem, kReduceAhead>;
+  if constexpr (sizeof(Elem) == 4)
+    if (E <= kReduceFewExperts && blocks * E < kReduceFewBlocks) kern = reduce_replicas_kernel<Elem, kReduceAheadFew>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)blocks, (unsigned)E), dim3(256), 0, (hipStream_t)stream,
+                     (const u32x4*)dw_slot, slot_expert, S, vec, (u32x4*)dw);
   return lz::launch_status();
 }
 

@@ -98,3 +98,16 @@ for c, T, d, ffn in ((8, 3000, 1000, 2664), (1, 64, 1000, 2664), (8, 3000, 1024,
     assert out[1] == [[0, 0], [3, 3], ["bf16", "bf16", "f32", "bf16"]]    # and the narrow tiles'
     assert out[2] == [[0, -1], [1, 1], ["bf16", "bf16"]]
     assert out[3] == [[0, 0], [1, 1], ["f32"] * 4]
+
+
+def test_replica_sums_of_few_short_experts_load_further_ahead(tmp_path):
+    """fp32, at most 4 experts in under 1024 workgroups: 16 slots' loads in flight, 4 otherwise."""
+    out = recorded(tmp_path, """
+A, out = At(1 << 20), []
+for S, E, n, dtype in ((512, 1, 65536, lz.LZ_F32), (2048, 4, 1 << 18, lz.LZ_F32), (2048, 4, 255 * 1024, lz.LZ_F32), (512, 5, 65536, lz.LZ_F32),
+                       (512, 1, 65536, lz.LZ_BF16), (512, 1, 65534, lz.LZ_F32)):
+    rc = code(lz.lz_reduce_replica_grads_dtype, A, A, S, E, n, dtype, A)
+    (c,) = calls()
+    out.append([rc, "generic" if "generic" in c else c[c.index("kernelI"):][7:12]])
+""")
+    assert out == [[0, "fLi16"], [0, "fLi4E"], [0, "fLi16"], [0, "fLi4E"], [0, "tLi4E"], [0, "generic"]]
