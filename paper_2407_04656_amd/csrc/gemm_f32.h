@@ -308,7 +308,15 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(F32Args a) {
         put(next, (s + 1) * TK);  // this LDS stage was last read before the previous barrier
         __syncthreads();
       };
-      if (stages > 0) {
+      // Rows of one stage: no fetches past the end (8 columns to 8, 200000 rows, 128 slots: 104 -> 71 us a forward).
+      // Leaving them out of the loop below by a test costs the longer rows up to 8 %, weight gradients half.
+      if (!WGRAD && stages == 1) {
+        fetch(S0{}, 0);
+        put(S0{}, 0);
+        __syncthreads();
+        compute(0);
+        __syncthreads();
+      } else if (stages > 0) {
         fetch(S0{}, 0);
         fetch(S1{}, TK);
         put(S0{}, 0);
