@@ -231,11 +231,15 @@ int32_t launch_narrow(MfmaArgs a, const TileTable& t, hipStream_t st) {
 }
 
 // Whether a GEMM over the batch's rows runs on narrow tiles: where it has fewer than 96 wide ones (half a tile
-// more per slot that can have rows).  In the sweep the figures above are from, all 15 launches under 93 gained,
-// by 4 % (64 tiles, 940 MB of weights) to half; of those from 100 to 150 five of seven lost, up to 40 %.
+// more per slot that can have rows).  In the sweep the figures above are from, all 15 launches under 93 gained, by
+// 4 % (64 tiles, 940 MB of weights) to half; of the eight from 100 to 150 six lost, 11 to 51 %, and the two of
+// 40 slots with rows of 512 gained (30 -> 19, 22 -> 18 us), as did two of 196 and 294 tiles with 3 rows a slot (58 ->
+// 53, 66 -> 55): the tile count alone does not tell these apart.  And where one narrow tile holds all columns,
+// three quarters and more of a wide one are padding: 40000 rows of 8 columns to 8 over 32 slots 40 -> 19 us a
+// forward, 64 to 64 40 -> 19 (a grid has fewer than 2^32 threads: a workgroup per 64 rows of P up to 2^28).
 inline bool use_narrow(long long P, int S, int n_out) {
   const long long used = P < S ? P : S;
-  return (P / BM + (used + 1) / 2) * ceil_div(n_out, BN) < 96;
+  return (n_out <= kNarrow && P <= (1ll << 28)) || (P / BM + (used + 1) / 2) * ceil_div(n_out, BN) < 96;
 }
 
 }  // namespace

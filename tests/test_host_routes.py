@@ -13,9 +13,9 @@ A, out = At(1 << 20), []
 for ffn in ((1 << 22) - 64, 1 << 22):
     s = lz.Shape(192, 64, ffn, 192, 1, 48, 4, lz.LZ_BF16, lz.LZ_SWIGLU)
     rc = code(lz.lz_ffn_backward, A, A, A, A, A, A, A, s, A, A, A, A, lz.lz_train_workspace_bytes(s))
-    out.append((rc, sum("gemm_mfma" in c for c in calls())))
+    out.append((rc, sum("gemm_mfma" in c or "gemm_narrow" in c for c in calls())))
 """)
-    assert out[0] == [0, 4]    # dH, dxp and both weight gradients: 96 wide tiles in the least of them
+    assert out[0] == [0, 4]    # dH, dxp and both weight gradients
     assert out[1] == [0, 0]
 
 
@@ -111,3 +111,17 @@ for S, E, n, dtype in ((512, 1, 65536, lz.LZ_F32), (2048, 4, 1 << 18, lz.LZ_F32)
     out.append([rc, "generic" if "generic" in c else c[c.index("kernelI"):][7:12]])
 """)
     assert out == [[0, "fLi16"], [0, "fLi4E"], [0, "fLi16"], [0, "fLi4E"], [0, "tLi4E"], [0, "generic"]]
+
+
+def test_results_of_one_narrow_tile_of_columns_run_on_narrow_tiles(tmp_path):
+    """Where all columns fit 64 a 256-wide tile is mostly padding; gated first GEMMs have no narrow form."""
+    out = recorded(tmp_path, """
+A, out = At(1 << 20), []
+for T, d, ffn, act in ((40000, 8, 64, lz.LZ_GELU), (40000, 8, 64, lz.LZ_SWIGLU), (40000, 64, 72, lz.LZ_GELU), (40000, 72, 64, lz.LZ_GELU),
+                       (1 << 25, 8, 64, lz.LZ_GELU), ((1 << 25) + 1, 8, 64, lz.LZ_GELU)):
+    s = lz.Shape(T, d, ffn, 32, 8 if T > 40000 else 1, 4, 8, lz.LZ_BF16, act)
+    rc = code(lz.lz_expert_ffn, A, A, A, A, s, A, At(1 << 30), lz.lz_ffn_workspace_bytes(s))
+    out.append([rc] + ["narrow" if "narrow" in c else "wide" for c in calls() if "gemm" in c])
+""")
+    n, w = "narrow", "wide"
+    assert out == [[0, n, n], [0, w, n], [0, w, n], [0, n, w], [0, n, n], [0, w, w]]
