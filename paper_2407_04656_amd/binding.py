@@ -69,8 +69,8 @@ class Shape:
             object.__setattr__(self, "_ref", ref)
         return ref
 
-    def __reduce__(self):
-        return (Shape, (self.T, self.d, self.ffn, self.E, self.k, self.N, self.c, self.dtype, self.act))
+    def __getstate__(self):
+        return {n: v for n, v in self.__dict__.items() if n != "_ref"}  # an address is of this process
 
     @staticmethod
     def from_config(cfg):

@@ -1,4 +1,7 @@
 """Host planning functions of the C ABI against the oracle (bit-exact), no GPU needed."""
+import copy
+import dataclasses
+import pickle
 import re
 import os
 
@@ -135,6 +138,21 @@ def test_device_calls_validate_arguments_without_a_gpu():
     with pytest.raises(lz.LzError) as ei:
         lz.lz_permute(None, None, bad, None, stream=0)
     assert ei.value.code == -2
+
+
+@dataclasses.dataclass(frozen=True)
+class _NamedShape(lz.Shape):
+    name: str
+
+
+def test_a_shape_that_was_passed_to_a_call_pickles_and_copies_whole():
+    plain = lz.Shape(T=16, d=8, ffn=8, E=4, k=2, N=2, c=2, dtype=lz.LZ_F32, act=lz.LZ_GELU)
+    for shape in (plain, _NamedShape(*dataclasses.astuple(plain), name="a layer")):
+        n = lz.lz_plan_workspace_bytes(shape)
+        for other in (pickle.loads(pickle.dumps(shape)), copy.copy(shape), copy.deepcopy(shape)):
+            assert type(other) is type(shape) and other == shape
+            assert lz.lz_plan_workspace_bytes(other) == n
+            assert dataclasses.replace(other, T=17).T == 17
 
 
 def test_training_calls_validate_arguments_without_a_gpu():
