@@ -139,7 +139,8 @@ def test_ffn_backward_against_the_oracle_rounded_where_the_device_rounds(act):
                                        ("swiglu", 512, 384)])
 def test_ffn_forward_train_and_backward_ragged(act, d, ffn):
     cfg = scaled(CONFIGS["c1_tiny"], act=act, dtype="bf16", T=700, k=2, d=d, ffn=ffn, N=4, c=2)
-    # several row tiles, a tile boundary + 1, an empty slot, one-row slots, ragged tails: the weight
+    # several row tiles, a tile boundary + 1, an empty slot, one-row slots, ragged tails (the row GEMMs on
+    # 64 x 64 tiles but for the gated first; on 256 x 256: test_gpu_wide_tiles.py): the weight
     # gradients contract over 257, 0, 1, 512, 300, 255, 74 and 1 rows (whole and partial K steps)
     _ffn_backward_case(cfg, [257, 0, 1, 512, 300, 255, 74, 1], 3)
 
@@ -299,7 +300,9 @@ def test_odd_number_of_k_steps_with_short_tail_tiles_is_reproducible():
     wait for every wave's loads before the first patch is written.  ffn = 320 gives the data
     gradient dxp = dZ W1^T five K steps, the slot sizes give the weight gradients 1, 3 and 5 K
     steps, and the <= 64-row tail tiles run the narrowest tile variant.  Every repetition must
-    give the same bits, and those bits must match the oracle."""
+    give the same bits, and those bits must match the oracle.  (The row GEMMs of so few rows take the
+    64 x 64 tiles, whose trailing loads and patches share LDS in the same way; the weight gradients
+    here and the row GEMMs of test_gpu_wide_tiles.py, nine K steps, are on the 256-row ones.)"""
     cfg = scaled(CONFIGS["c1_tiny"], act="gelu", dtype="bf16", T=361, k=2, d=256, ffn=320, N=3, c=2)
     counts = [60, 300, 33, 1, 64, 264]
     S, P = 6, cfg.T * cfg.k
@@ -556,13 +559,13 @@ def _layer_backward_generic(cfg, tol):
 
 def test_layer_backward_fp32_config_1():
     """Config 1 (fp32, GELU, fixed replica counts, spread placement) in full through the training
-    entry points: the plain tiled fp32 kernels meet the fp32 error bar of the forward."""
+    entry points: the fp32 kernels meet the fp32 error bar of the forward."""
     _layer_backward_generic(CONFIGS["c1_tiny"], 1e-5)
 
 
 @pytest.mark.parametrize("act,dtype,tol", [("swiglu", "f32", 1e-5), ("gelu", "bf16", 2e-2), ("swiglu", "bf16", 2e-2)])
 def test_layer_backward_generic_shapes(act, dtype, tol):
-    """Sizes the MFMA tiling does not divide (d = 72, ffn = 200, top-3, ragged ranks), both dtypes."""
+    """Sizes no tile divides (d = 72, ffn = 200, top-3, ragged ranks): the fp32 kernels and, in bf16, partial tiles."""
     cfg = scaled(CONFIGS["c1_tiny"], act=act, dtype=dtype, T=333, d=72, ffn=200, E=8, k=3, N=3, c=4,
                  replica_counts=(2, 2, 2, 2, 1, 1, 1, 1))
     _layer_backward_generic(cfg, tol)

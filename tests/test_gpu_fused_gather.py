@@ -58,7 +58,8 @@ def _case(cfg, counts, seed):
 @pytest.mark.parametrize("act,d,ffn", [("gelu", 256, 256), ("swiglu", 256, 128), ("swiglu", 512, 384)])
 def test_fused_gather_mfma_ragged(act, d, ffn):
     cfg = scaled(CONFIGS["c1_tiny"], act=act, dtype="bf16", T=700, k=2, d=d, ffn=ffn, N=4, c=2)
-    # several row tiles, a tile boundary + 1, an empty slot, one-row slots, every 64-row tail class
+    # several row tiles, a tile boundary + 1, an empty slot, one-row slots, every 64-row tail class; GELU and the
+    # second GEMM on 64 x 64 tiles at these sizes (256 x 256: test_gpu_wide_tiles.py)
     assert _case(cfg, [257, 0, 1, 512, 300, 255, 74, 1], 3) <= 2e-2
     assert _case(cfg, [130, 190, 65, 128, 64, 193, 400, 230], 4) <= 2e-2
 

@@ -68,7 +68,7 @@ def test_a_row_of_nan_stays_in_its_row(fused):
 
 
 def test_unaligned_tensors_of_odd_sizes():
-    """Odd sizes take tensors at any element offset (the FMA kernels, on the same tile table)."""
+    """Odd sizes take tensors at any element offset (the fp32 kernel, with a tile table of its own)."""
     T, d, ffn = 333, 264, 200
     shape = lz.Shape(T, d, ffn, 2, 1, 1, 2, lz.LZ_BF16, lz.LZ_GELU)
     rng = np.random.default_rng(6)

@@ -106,12 +106,13 @@ def test_plan_dispatch_random_plans(T, E, k, N, c):
                 assert np.array_equal(got[key], ref[key]), key
 
 
-def test_plan_dispatch_is_deterministic_and_flags_bad_input():
+@pytest.mark.parametrize("T", [3000, 500])    # the four kernels, and all in one workgroup (at most 4096 pairs)
+def test_plan_dispatch_is_deterministic_and_flags_bad_input(T):
     rng = np.random.default_rng(5)
-    T, E, k, N, c = 3000, 16, 2, 4, 4
+    E, k, N, c = 16, 2, 4, 4
     shape = lz.Shape(T, 64, 64, E, k, N, c, lz.LZ_BF16, lz.LZ_GELU)
     ids, _ = om.route(rng.standard_normal((T, E)).astype(np.float32), k)
-    off = np.array([0, 750, 1500, 2250, 3000])
+    off = np.array([0, 750, 1500, 2250, 3000]) * T // 3000
     plan = _random_plan(rng, E, N, c)
     a = _plan_gpu(ids, shape, off, plan)
     b = _plan_gpu(ids, shape, off, plan)
@@ -132,10 +133,22 @@ def test_plan_dispatch_is_deterministic_and_flags_bad_input():
     ids_bad = ids.copy()
     ids_bad[5, 1] = E + 3
     ids_bad[9, 0] = -2
-    got = _plan_gpu(ids_bad, shape, np.array([0, 900, 800, 5000, 3000]), plan)
+    got = _plan_gpu(ids_bad, shape, np.array([0, 900, 800, 5000, 3000]) * T // 3000, plan)
     assert got["status"][0] & 2 and got["status"][0] & 4
     assert got["pair_to_row"][5 * k + 1] == -1 and got["pair_to_row"][9 * k] == -1
     assert got["pair_to_row"].max() < T * k
+    # slots that hold no expert: flagged, empty, and the rest of the plan works as if they were not there
+    plan3 = plan.copy()
+    spare = [s for s in range(N * c) if np.sum(plan == plan[s]) > 1][:1] or [0]
+    for bad in (-1, E, 1 << 30):
+        plan3[spare[0]] = bad
+        got = _plan_gpu(ids, shape, off, plan3)
+        assert got["status"][0] & 2 and got["slot_counts"][spare[0]] == 0
+        lost = ids.reshape(-1) == plan[spare[0]] if plan[spare[0]] not in plan3 else np.zeros(T * k, dtype=bool)
+        assert np.all((got["pair_to_row"] == -1) == lost)
+        assert got["slot_offsets"][-1] == T * k - lost.sum() and bool(got["status"][0] & 1) == bool(lost.any())
+        placed = got["row_to_pair"][:got["slot_offsets"][-1]]
+        assert np.array_equal(np.sort(placed), np.nonzero(~lost)[0])
 
 
 def test_plan_dispatch_empty_batch():
@@ -223,9 +236,10 @@ def test_expert_ffn_bf16_generic_odd_shape(act):
                                        ("gelu", 512, 512)])
 def test_expert_ffn_bf16_mfma_ragged(act, d, ffn):
     cfg = scaled(CONFIGS["c1_tiny"], act=act, dtype="bf16", T=700, k=2, d=d, ffn=ffn, N=4, c=2)
+    # on 256 x 256 tiles the gated first GEMM, on 64 x 64 ones the rest (all of it on 256 x 256: test_gpu_wide_tiles.py)
     # several row tiles, a tile boundary +1, an empty slot, a one-row slot, ragged tails
     assert _ffn_case(cfg, [257, 0, 1, 512, 300, 255, 74, 1], 3) <= 2e-2
-    # tails in every 64-row class (the kernel has one code path per class) and their edges
+    # tails in every 64-row class (the 256-row tiles have one code path per class) and their edges
     assert _ffn_case(cfg, [130, 190, 65, 128, 64, 193, 400, 230], 4) <= 2e-2
 
 

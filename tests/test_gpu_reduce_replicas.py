@@ -14,10 +14,11 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("S,E,n", [(1, 1, 8), (64, 5, 4088), (65, 3, 4096), (130, 67, 8200), (7, 4, 4099)])
+@pytest.mark.parametrize("S,E,n", [(1, 1, 8), (64, 5, 4088), (65, 3, 4096), (130, 67, 8200), (7, 4, 4099),
+                                   (5, 2, 1020), (5, 2, 1028), (5, 2, 2040), (5, 2, 2056), (200, 3, 1032)])
 def test_replica_sums(dtype, S, E, n):
-    """Slots in more than one group of 64, an expert without a slot, vector counts around a block's 1024, and
-    a size that is no whole number of 16-byte vectors.  An fp32 sum of r terms is off by at most (r - 1) 2^-24
+    """Slots in more than one group of 64, an expert without a slot, vector counts around a block's 256, more and
+    fewer of an expert's slots than are loaded ahead, and sizes that are no whole number of 16-byte vectors.  An fp32 sum of r terms is off by at most (r - 1) 2^-24
     of the sum of their absolute values; a bf16 result by half a bf16 step (2^-9) more."""
     rng = np.random.default_rng(S + n)
     plan = rng.integers(0, max(1, E - 1), size=S).astype(np.int32)   # the last expert has no slot (E > 1)

@@ -165,7 +165,7 @@ def test_training_calls_validate_arguments_without_a_gpu():
     n = lz.lz_train_workspace_bytes(ok)
     # at least the two gradient intermediates dH [P, ffn] and dZ [P, 2 ffn]
     assert n >= ok.P * ok.ffn * 2 + ok.P * 2 * ok.ffn * 2
-    # served by the plain tiled kernels: fp32, sizes the MFMA tiling does not divide
+    # fp32, sizes the bf16 tiles do not divide, bf16 rows that are no whole 16-byte pieces
     for generic in (shape(dtype=lz.LZ_F32), shape(d=264), shape(ffn=100)):
         assert lz.lz_train_workspace_bytes(generic) > 0
         with pytest.raises(lz.LzError) as ei:                        # no workspace
@@ -174,7 +174,7 @@ def test_training_calls_validate_arguments_without_a_gpu():
     # activation tensors beyond 32-bit byte offsets are served too (the workspace is what it is)
     assert lz.lz_train_workspace_bytes(shape(T=1 << 20, k=8, d=4096, ffn=14336)) > (1 << 36)
     # invalid, or beyond both paths (one slot's weights past 32-bit offsets on the MFMA path and too
-    # many 64-row tiles for the plain one)
+    # many 64-row tiles for the fp32 kernels)
     for bad in (shape(k=9), shape(T=1 << 23, k=2, d=264, ffn=128)):
         assert lz.lz_train_workspace_bytes(bad) == 0
         with pytest.raises(lz.LzError) as ei:

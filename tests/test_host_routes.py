@@ -125,3 +125,38 @@ for T, d, ffn, act in ((40000, 8, 64, lz.LZ_GELU), (40000, 8, 64, lz.LZ_SWIGLU),
 """)
     n, w = "narrow", "wide"
     assert out == [[0, n, n], [0, w, n], [0, w, n], [0, n, w], [0, n, n], [0, w, w]]
+
+
+def test_the_ragged_wide_tests_run_on_wide_tiles(tmp_path):
+    import test_gpu_wide_tiles as wide
+
+    out = recorded(tmp_path, f"""
+A, out = At(1 << 20), []
+for d, ffn in {wide.SIZES}:
+    for act in (lz.LZ_GELU, lz.LZ_SWIGLU):
+        s = lz.Shape({sum(wide.COUNTS)}, d, ffn, 64, 1, 1, 64, lz.LZ_BF16, act)
+        n = max(lz.lz_ffn_workspace_bytes(s), lz.lz_train_workspace_bytes(s))
+        rc = [code(lz.lz_expert_ffn, A, A, A, A, s, A, At(1 << 30), n), code(lz.lz_expert_ffn_gather, A, A, A, A, A, s, A, At(1 << 30), n),
+              code(lz.lz_ffn_forward_train, A, A, A, A, s, A, A, A, A, n), code(lz.lz_ffn_backward, A, A, A, A, A, A, A, s, A, A, A, A, n)]
+        out.append([rc, sum("gemm_mfma" in c for c in calls())])
+        out.append([rc, sum("gemm" in c and "gemm_mfma" not in c for c in calls())])
+""")
+    assert out[0::2] == [[[0] * 4, 10]] * 4 and out[1::2] == [[[0] * 4, 0]] * 4
+
+
+def test_the_large_fp32_weight_gradient_tests_run_on_four_waves(tmp_path):
+    import test_gpu_f32_sizes as f32
+
+    out = recorded(tmp_path, f"""
+A, out = At(1 << 20), []
+for d, ffn, slots in {[(d, f, s) for d, f, s in f32.WIDE_GRADIENTS]}:
+    s = lz.Shape(1500, d, ffn, 8, 2, 1, slots, lz.LZ_F32, lz.LZ_GELU)
+    n = lz.lz_train_workspace_bytes(s)
+    rc = [code(f, A, A, A, A, A, A, A, s, A, A, A, A, n) for f in (lz.lz_ffn_backward, lz.lz_ffn_backward_accumulate)]
+    names = [c[c.index("kernelIfLi") + 10:] for c in calls() if "gemm_f32" in c]
+    out.append([rc, [n[:18] for n in names if n[1:6] == "ELb1E"]])   # WGRAD: both operands k-major
+""")
+    for (d, ffn, _), (rc, names) in zip(f32.WIDE_GRADIENTS, out):
+        vec = "1" if d % 4 == 0 and ffn % 4 == 0 else "0"
+        assert rc == [0, 0]
+        assert names == [f"{epi}ELb1ELb1ELi4ELb{vec}E" for epi in (0, 0, 5, 5)]
