@@ -174,8 +174,9 @@ __global__ __launch_bounds__(256) void build_tiles_kernel(const int32_t* __restr
   }
   if (tid < 2 * 17) t.header[kTicket + tid * kLine] = 0;
   __syncthreads();
-  // A thread writes the entries of its slot, 45 ns each.  Where a wave holds a few long slots (few slots share a large
-  // batch) it writes what is past kOwn of those together, slot after slot: 130 ns a slot and 64 entries a step.
+  // Few entries: a thread each, its slot found by bisection.  More: a thread writes the entries of its slot, 45 ns
+  // each, and where a wave holds a few long slots (few slots share a large batch) it writes what is past kOwn of
+  // those together, slot after slot: 130 ns a slot and 64 entries a step.
   // 32-row tiles of 10^6 rows in 1, 4, 32, 128 slots: 1390, 867, 136, 64 us by the threads alone, 28, 29, 31, 31 us so.
   constexpr int kOwn = 64;
   auto entry = [&](int i, int s, int first_i, long long a, long long b) {
@@ -184,7 +185,19 @@ __global__ __launch_bounds__(256) void build_tiles_kernel(const int32_t* __restr
     t.row0[i] = int(r0 < b ? r0 : b);
     t.row_end[i] = int(b);
   };
-  for (int s0 = wave * lz::kWave; s0 < S; s0 += 256) {  // the same trips in every lane
+  const bool few = s_first[S] <= 1024;
+  for (int i = tid; few && i < s_first[S]; i += 256) {
+    int s = 0;
+    for (int hi = S - 1; s < hi;) {  // the last slot that starts at or before i
+      const int mid = (s + hi + 1) >> 1;
+      if (s_first[mid] <= i) s = mid;
+      else hi = mid - 1;
+    }
+    long long a, b;
+    slot_rows(s, &a, &b);
+    entry(i, s, s_first[s], a, b);
+  }
+  for (int s0 = wave * lz::kWave; !few && s0 < S; s0 += 256) {  // the same trips in every lane
     const int s = s0 + lane, from = s < S ? s_first[s] : 0, to = s < S ? s_first[s + 1] : 0;
     long long a = 0, b = 0;
     if (s < S) slot_rows(s, &a, &b);
