@@ -24,7 +24,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA
-PEAK_F32_TFLOPS = 157.3     # MI355X fp32 vector
+PEAK_F32_TFLOPS = 157.3     # MI355X fp32, vector and matrix instructions alike
 PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 
 # HBM-side bytes per launch of the dominant kernel, from the rocprofv3 FETCH_SIZE / WRITE_SIZE passes
@@ -635,7 +635,7 @@ def main():
                     "frac": tf_up / PEAK_BF16_TFLOPS, "traffic": MEASURED_TRAFFIC_BYTES.get(cfg.name),
                     "flops_per_launch": m["flops_up"], "avg_ms": per["ffn_up"]}
     else:
-        roofline = {"bound": "alu", "kernel": "gemm_generic_kernel (fp32 FMA)", "achieved": tf_up,
+        roofline = {"bound": "mfma", "kernel": "gemm_f32_kernel (first grouped GEMM, fp32 matrix instructions)", "achieved": tf_up,
                     "peak": PEAK_F32_TFLOPS, "unit": "TFLOP/s", "frac": tf_up / PEAK_F32_TFLOPS, "traffic": None,
                     "flops_per_launch": m["flops_up"], "avg_ms": per["ffn_up"]}
 

@@ -72,7 +72,8 @@ const char* lz_strerror(int32_t code);
 int32_t lz_version(void);
 
 /* Bytes of device workspace (256-byte aligned) lz_plan_dispatch / lz_expert_ffn need
- * for this shape; 0 if the shape is invalid. */
+ * for this shape; 0 if the shape is invalid.  The sizes do not fall as T grows: a workspace made for
+ * the largest batch of a layer serves its smaller ones (training: those lz_train_workspace_bytes is not 0 for). */
 size_t lz_plan_workspace_bytes(const lz_shape* shape);
 size_t lz_ffn_workspace_bytes(const lz_shape* shape);
 
@@ -162,8 +163,8 @@ int32_t lz_pack_weights(const void* w, int32_t S, int32_t rows, int32_t cols, in
  * processes the tokens dispatched to it).  Rows [slot_offsets[s], slot_offsets[s+1]) use
  * the weights of slot s:
  *   LZ_GELU    yp = gelu(xp W1) W2              gelu = 0.5 v (1 + erf(v/sqrt 2)), the erf form (not tanh);
- *                                                fp32 path: erff; bf16 MFMA path: erf to < 1e-6 absolute
- *   LZ_SWIGLU  yp = (silu(xp Wg) * (xp Wu)) W2
+ *                                                fp32 instructions: erff; bf16 ones: erf to < 1e-6 absolute
+ *   LZ_SWIGLU  yp = (silu(xp Wg) * (xp Wu)) W2    fp32 instructions: expf; bf16 ones: hardware exp2 and reciprocal
  *   w1  dev [S, d, n1]   n1 = ffn (GELU) or 2*ffn (SwiGLU: columns [0,ffn) = Wg, [ffn,2ffn) = Wu)
  *   w2  dev [S, ffn, d]
  * The weights are stored input-major (row = input feature, column = output feature, the
@@ -362,7 +363,9 @@ int32_t lz_replan(const int32_t* old_slot_expert, int32_t N_old, int32_t c_old,
 
 /* Carry out a transfer list on the device: for each entry copy the source slot's w1 and
  * w2 blocks from the old weight buffers into the destination slot of the new ones
- * (device-to-device copies on `stream`; stands in for the batched send/recv of Sec. 5).
+ * (on `stream`; stands in for the batched send/recv of Sec. 5).  Slots of whole 16-byte pieces
+ * in buffers that do not overlap, all on the stream's GPU, no destination twice: one kernel;
+ * else device-to-device copies in the order of the list.
  *   xfers host [n]; w1_old/w2_old dev [S_old,...]; w1_new/w2_new dev [S_new,...]. */
 int32_t lz_apply_transfers(const lz_transfer* xfers, int32_t n,
                            const void* w1_old, const void* w2_old, int32_t S_old,

@@ -280,11 +280,11 @@ inline bool generic_train_shape(const lz_shape* s) {
 // The shapes the MFMA kernels serve: bf16 rows of whole 16-byte pieces, virtual row indices within int32.  Sizes
 // that the tiles do not divide stay inside the envelope above: they also take unaligned tensors, on the fp32
 // kernels (each call by itself: no state passes between the calls through the workspace).
-inline bool whole_tiles(const lz_shape* s) { return s->d % BN == 0 && s->ffn % 64 == 0; }
+inline bool train_whole_tiles(const lz_shape* s) { return s->d % BN == 0 && s->ffn % 64 == 0; }
 inline bool train_shape(const lz_shape* s) {
   if (!lz::shape_ok(s) || !mfma_sizes(s)) return false;
   const long long S = (long long)s->N * s->c;
-  return S * s->d * 2 < (1ll << 31) && S * s->ffn * 2 < (1ll << 31) && (whole_tiles(s) || generic_train_shape(s));
+  return S * s->d * 2 < (1ll << 31) && S * s->ffn * 2 < (1ll << 31) && (train_whole_tiles(s) || generic_train_shape(s));
 }
 
 int32_t check_train(const lz_shape* shape, void* ws, size_t ws_bytes, TrainWorkspace* w) {
@@ -386,14 +386,14 @@ extern "C" size_t lz_train_workspace_bytes(const lz_shape* shape) {
   const size_t generic = generic_train_shape(shape) ? carve_train_generic(nullptr, shape).total_bytes : 0;
   if (!train_shape(shape)) return generic;
   const size_t bytes = carve_train(nullptr, shape).total_bytes;
-  return bytes > generic || whole_tiles(shape) ? bytes : generic;
+  return bytes > generic || train_whole_tiles(shape) ? bytes : generic;
 }
 
 extern "C" int32_t lz_ffn_forward_train(const void* xp, const int32_t* slot_offsets, const void* w1, const void* w2,
                                         const lz_shape* shape, void* z, void* h, void* yp, void* ws,
                                         size_t ws_bytes, void* stream) {
   const bool aligned = aligned16(z) && aligned16(h) && aligned16(yp) && aligned16(xp) && aligned16(w1) && aligned16(w2);
-  if (!train_shape(shape) || (!aligned && !whole_tiles(shape))) {
+  if (!train_shape(shape) || (!aligned && !train_whole_tiles(shape))) {
     GenericTrainWorkspace gw;
     const int32_t grc = check_train_generic(shape, ws, ws_bytes, &gw);
     if (grc != LZ_OK) return grc;
@@ -487,7 +487,7 @@ int32_t ffn_backward(const void* dyp, const void* xp, const void* z, const void*
                      bool accumulate, void* ws, size_t ws_bytes, void* stream) {
   const bool aligned = aligned16(dyp) && aligned16(xp) && aligned16(z) && aligned16(h) && aligned16(dxp) &&
                        aligned16(w1) && aligned16(w2) && aligned16(dw1) && aligned16(dw2);
-  if (!train_shape(shape) || (!aligned && !whole_tiles(shape))) {
+  if (!train_shape(shape) || (!aligned && !train_whole_tiles(shape))) {
     GenericTrainWorkspace gw;
     const int32_t grc = check_train_generic(shape, ws, ws_bytes, &gw);
     if (grc != LZ_OK) return grc;

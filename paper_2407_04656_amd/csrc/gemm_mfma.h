@@ -31,7 +31,7 @@ typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
 // ints before the tile arrays; [0] = number of row tiles, then the lengths of the unit lists (kUnitCount), then,
-// a 128-byte line each, the queue counters (kTicket, kDone)
+// a 128-byte line each, the queue counters (kTicket)
 constexpr int kLine = 32;
 constexpr int kTileHeader = 64 + 2 * (8 + 8 + 1) * kLine;
 constexpr int kGroupM = 4;       // row tiles of a work unit (same slot)
@@ -218,7 +218,7 @@ __global__ __launch_bounds__(256) void build_tiles_kernel(const int32_t* __restr
   for (int which = 0; which < 2; ++which) {
     const int nt = which == 0 ? n_tiles_up : n_tiles_down;
     const int ncg = (nt + kGroupN - 1) / kGroupN;
-    const int n_units = n_groups * ncg;  // 0 on the generic path
+    const int n_units = n_groups * ncg;  // 0 on the fp32 kernel
     const int cap = t.unit_cap[which];
     for (int u = threadIdx.x; u < n_units; u += blockDim.x) {
       const int row = u / 8, i = u % 8;
