@@ -236,10 +236,11 @@ __global__ __launch_bounds__(256) void reduce_replicas_kernel(const u32x4* __res
 struct TrainWorkspace {
   uint16_t* dh;        // [P, ffn]
   uint16_t* dz;        // [P, n1]
-  void* tiles_fwd;     // rows of the batch: lists for the forward's two GEMMs (ffn / 128 or 256, d / 256 column tiles)
-  void* tiles_bwd;     // rows of the batch: lists for ffn / 256 and d / 256 column tiles
-  void* tiles_w2;      // S * ffn virtual rows, d / 256 column tiles
-  void* tiles_w1;      // S * d virtual rows, n1 / 256 column tiles
+  void* units_up;      // rows of the batch, ffn / 128 (gated) or 256 column tiles
+  void* units_ffn;     // rows of the batch, ffn / 256 column tiles
+  void* units_d;       // rows of the batch, d / 256 column tiles
+  void* units_w2;      // S * ffn virtual rows, d / 256 column tiles
+  void* units_w1;      // S * d virtual rows, n1 / 256 column tiles
   void* tiles_narrow;  // rows of the batch, tiles of the GEMMs on narrow tiles
   bool narrow_up, narrow_ffn, narrow_d;  // z, h; dH; yp and dxp on narrow tiles
   size_t total_bytes;
@@ -259,14 +260,15 @@ TrainWorkspace carve_train(void* ws, const lz_shape* s) {
   };
   w.dh = (uint16_t*)take((size_t)P * s->ffn * 2);
   w.dz = (uint16_t*)take((size_t)P * w.n1 * 2);
-  w.tiles_fwd = take(tile_table_bytes(P, S, BM, kGroupM, ceil_div(s->ffn, s->act == LZ_SWIGLU ? BN / 2 : BN), ceil_div(s->d, BN)));
-  w.tiles_bwd = take(tile_table_bytes(P, S, BM, kGroupM, ceil_div(s->ffn, BN), ceil_div(s->d, BN)));
-  w.tiles_w2 = take(tile_table_bytes((long long)S * s->ffn, S, BM, kGroupM, ceil_div(s->d, BN), 0));
-  w.tiles_w1 = take(tile_table_bytes((long long)S * s->d, S, BM, kGroupM, ceil_div(w.n1, BN), 0));
+  w.units_up = take(unit_table_bytes(P, S, BM, ceil_div(s->ffn, s->act == LZ_SWIGLU ? BN / 2 : BN)));
+  w.units_ffn = take(unit_table_bytes(P, S, BM, ceil_div(s->ffn, BN)));
+  w.units_d = take(unit_table_bytes(P, S, BM, ceil_div(s->d, BN)));
+  w.units_w2 = take(unit_table_bytes((long long)S * s->ffn, S, BM, ceil_div(s->d, BN)));
+  w.units_w1 = take(unit_table_bytes((long long)S * s->d, S, BM, ceil_div(w.n1, BN)));
   w.narrow_ffn = use_narrow(P, S, s->ffn);
   w.narrow_up = w.narrow_ffn && s->act == LZ_GELU;
   w.narrow_d = use_narrow(P, S, s->d);
-  w.tiles_narrow = take(tile_table_bytes(P, S, kNarrow, 1, 0, 0));  // also where this P does not use it, as in the forward
+  w.tiles_narrow = take(tile_table_bytes(P, S, kNarrow));  // also where this P does not use it, as in the forward
   w.total_bytes = size_t(p - (char*)ws);
   return w;
 }
@@ -274,7 +276,7 @@ TrainWorkspace carve_train(void* ws, const lz_shape* s) {
 // the fp32 kernels' envelope: every valid shape of at most 65535 64-row tiles
 inline bool generic_train_shape(const lz_shape* s) {
   if (!lz::shape_ok(s)) return false;
-  return tile_capacity((long long)s->T * s->k, s->N * s->c, 64, 1) <= 65535;
+  return tile_capacity((long long)s->T * s->k, s->N * s->c, 64) <= 65535;
 }
 
 // The shapes the MFMA kernels serve: bf16 rows of whole 16-byte pieces, virtual row indices within int32.  Sizes
@@ -294,24 +296,11 @@ int32_t check_train(const lz_shape* shape, void* ws, size_t ws_bytes, TrainWorks
   return LZ_OK;
 }
 
-TileTable narrow_tiles(const TrainWorkspace& w, int S, long long P) {
-  return carve_tiles(w.tiles_narrow, P, S, kNarrow, 1, 0, 0);
-}
-
-// appends the table of the narrow GEMMs to n specs
-int add_narrow(TileSpecs* specs, int n, const TrainWorkspace& w, int S, long long P) {
-  specs->spec[n] = {kNarrow, 1, 0, 0, 0, P, narrow_tiles(w, S, P)};
-  return n + 1;
-}
-
-int32_t build_tables(const int32_t* offsets, int S, const TileSpecs& specs, int n, hipStream_t st) {
-  hipLaunchKernelGGL(build_tiles_kernel, dim3(n), dim3(256), 0, st, offsets, S, specs);
-  return lz::launch_status();
-}
+TileTable narrow_tiles(const TrainWorkspace& w, int S, long long P) { return carve_tiles(w.tiles_narrow, P, S, kNarrow); }
 
 // C[rows, n_out] = A[rows, K] W[slot][n_out, K]^T over the batch's ragged row ranges
-int32_t gemm_nt(const uint16_t* A, const uint16_t* W, uint16_t* C, long long P, int K, int n_out, int which,
-                const TileTable& t, bool narrow, const TrainWorkspace& w, int S, hipStream_t st) {
+int32_t gemm_nt(const uint16_t* A, const uint16_t* W, uint16_t* C, long long P, int K, int n_out,
+                const UnitTable& u, bool narrow, const TrainWorkspace& w, int S, hipStream_t st) {
   MfmaArgs g{};
   g.A = A;
   g.W = W;
@@ -321,15 +310,14 @@ int32_t gemm_nt(const uint16_t* A, const uint16_t* W, uint16_t* C, long long P, 
   g.w_rows = n_out;
   g.n_out = n_out;
   g.n_tiles = ceil_div(n_out, BN);
-  g.which = which;
-  g.t = t;
+  g.u = u;
   if (narrow) return launch_narrow<EPI_NONE, MODE_NT>(g, narrow_tiles(w, S, P), st);
   return launch_mfma<EPI_NONE>(g, st);
 }
 
 // C[rows, n_out] = A[rows, K] W[slot][K, n_out] over the batch's ragged row ranges
-int32_t gemm_nn(const uint16_t* A, const uint16_t* W, uint16_t* C, long long P, int K, int n_out, int which,
-                const TileTable& t, bool narrow, const TrainWorkspace& w, int S, hipStream_t st) {
+int32_t gemm_nn(const uint16_t* A, const uint16_t* W, uint16_t* C, long long P, int K, int n_out,
+                const UnitTable& u, bool narrow, const TrainWorkspace& w, int S, hipStream_t st) {
   MfmaArgs g{};
   g.A = A;
   g.W = W;
@@ -339,8 +327,7 @@ int32_t gemm_nn(const uint16_t* A, const uint16_t* W, uint16_t* C, long long P, 
   g.w_rows = n_out;
   g.n_out = n_out;
   g.n_tiles = ceil_div(n_out, BN);
-  g.which = which;
-  g.t = t;
+  g.u = u;
   g.ldw = n_out;
   if (narrow) return launch_narrow<EPI_NONE, MODE_NN>(g, narrow_tiles(w, S, P), st);
   return launch_mfma<EPI_NONE, MODE_NN>(g, st);
@@ -349,7 +336,7 @@ int32_t gemm_nn(const uint16_t* A, const uint16_t* W, uint16_t* C, long long P, 
 // dW[s] [rows_per_slot, n_out] = A[rows of s, :rows_per_slot]^T W[rows of s, :n_out], stored as bf16 in C,
 // or, if Cacc is given, added to that fp32 matrix instead
 int32_t gemm_wgrad(const uint16_t* A, const uint16_t* W, uint16_t* C, float* Cacc, int S, long long P,
-                   int rows_per_slot, int n_out, const int32_t* slot_offsets, const TileTable& t, hipStream_t st) {
+                   int rows_per_slot, int n_out, const UnitTable& u, hipStream_t st) {
   MfmaArgs g{};
   g.A = A;
   g.W = W;
@@ -359,12 +346,9 @@ int32_t gemm_wgrad(const uint16_t* A, const uint16_t* W, uint16_t* C, float* Cac
   g.w_rows = n_out;
   g.n_out = n_out;
   g.n_tiles = ceil_div(n_out, BN);
-  g.which = 0;
-  g.t = t;
+  g.u = u;
   g.lda = rows_per_slot;
   g.ldw = n_out;
-  g.slot_offsets = slot_offsets;
-  g.k_rows = P;
   g.rows_per_slot = rows_per_slot;
   // 32-bit byte offsets do if no operand reaches 4 GiB, the K steps past a slot's end included
   const int ld_max = rows_per_slot > n_out ? rows_per_slot : n_out;
@@ -414,10 +398,13 @@ extern "C" int32_t lz_ffn_forward_train(const void* xp, const int32_t* slot_offs
   const int S = shape->N * shape->c;
   const bool swiglu = shape->act == LZ_SWIGLU;
   const int n_up = ceil_div(shape->ffn, swiglu ? BN / 2 : BN);
-  const TileTable t = carve_tiles(w.tiles_fwd, P, S, BM, kGroupM, n_up, ceil_div(shape->d, BN));
+  const UnitTable u_up = carve_units(w.units_up, P, S, BM, n_up);
+  const UnitTable u_d = carve_units(w.units_d, P, S, BM, ceil_div(shape->d, BN));
   TileSpecs specs{};
-  specs.spec[0] = {BM, kGroupM, n_up, ceil_div(shape->d, BN), 0, P, t};
-  int32_t r = build_tables(slot_offsets, S, specs, w.narrow_up || w.narrow_d ? add_narrow(&specs, 1, w, S, P) : 1, st);
+  if (!w.narrow_up) add_units(specs, BM, n_up, 0, P, u_up);
+  if (!w.narrow_d) add_units(specs, BM, ceil_div(shape->d, BN), 0, P, u_d);
+  if (w.narrow_up || w.narrow_d) add_rows(specs, kNarrow, P, narrow_tiles(w, S, P));
+  int32_t r = launch_build_tiles(slot_offsets, S, specs, st);
   if (r != LZ_OK) return r;
   // z = xp W1 and h = act(z) from one epilogue
   MfmaArgs g{};
@@ -432,13 +419,12 @@ extern "C" int32_t lz_ffn_forward_train(const void* xp, const int32_t* slot_offs
   g.n_out = shape->ffn;
   g.up_row0 = swiglu ? shape->ffn : 0;
   g.n_tiles = n_up;
-  g.which = 0;
-  g.t = t;
+  g.u = u_up;
   g.ldw = w.n1;
   if (w.narrow_up) r = launch_narrow<EPI_GELU_KEEP, MODE_NN>(g, narrow_tiles(w, S, P), st);
   else r = swiglu ? launch_mfma<EPI_SWIGLU_KEEP, MODE_NN>(g, st) : launch_mfma<EPI_GELU_KEEP, MODE_NN>(g, st);
   if (r != LZ_OK) return r;
-  return gemm_nn((const uint16_t*)h, (const uint16_t*)w2, (uint16_t*)yp, P, shape->ffn, shape->d, 1, t,
+  return gemm_nn((const uint16_t*)h, (const uint16_t*)w2, (uint16_t*)yp, P, shape->ffn, shape->d, u_d,
                  w.narrow_d, w, S, st);
 }
 
@@ -516,19 +502,20 @@ int32_t ffn_backward(const void* dyp, const void* xp, const void* z, const void*
 
   const int n_ffn = ceil_div(ffn, BN), n_d = ceil_div(d, BN), n_n1 = ceil_div(n1, BN);
   const long long rows_w2 = (long long)S * ffn, rows_w1 = (long long)S * d;
-  const TileTable t_rows = carve_tiles(w.tiles_bwd, P, S, BM, kGroupM, n_ffn, n_d);
-  const TileTable t_w2 = carve_tiles(w.tiles_w2, rows_w2, S, BM, kGroupM, n_d, 0);
-  const TileTable t_w1 = carve_tiles(w.tiles_w1, rows_w1, S, BM, kGroupM, n_n1, 0);
+  const UnitTable u_ffn = carve_units(w.units_ffn, P, S, BM, n_ffn), u_d = carve_units(w.units_d, P, S, BM, n_d);
+  const UnitTable u_w2 = carve_units(w.units_w2, rows_w2, S, BM, n_d), u_w1 = carve_units(w.units_w1, rows_w1, S, BM, n_n1);
   TileSpecs specs{};
-  specs.spec[0] = {BM, kGroupM, n_ffn, n_d, 0, P, t_rows};
-  specs.spec[1] = {BM, kGroupM, n_d, 0, ffn, rows_w2, t_w2};
-  specs.spec[2] = {BM, kGroupM, n_n1, 0, d, rows_w1, t_w1};
-  int32_t r = build_tables(slot_offsets, S, specs, w.narrow_ffn || w.narrow_d ? add_narrow(&specs, 3, w, S, P) : 3, st);
+  if (!w.narrow_ffn) add_units(specs, BM, n_ffn, 0, P, u_ffn);
+  if (!w.narrow_d) add_units(specs, BM, n_d, 0, P, u_d);
+  add_units(specs, BM, n_d, ffn, P, u_w2);
+  add_units(specs, BM, n_n1, d, P, u_w1);
+  if (w.narrow_ffn || w.narrow_d) add_rows(specs, kNarrow, P, narrow_tiles(w, S, P));
+  int32_t r = launch_build_tiles(slot_offsets, S, specs, st);
   if (r != LZ_OK) return r;
 
   if (P > 0) {
     // dH = dyp W2^T    (W2 [ffn, d]: contraction along its rows)
-    if ((r = gemm_nt((const uint16_t*)dyp, (const uint16_t*)w2, w.dh, P, d, ffn, 0, t_rows, w.narrow_ffn, w, S, st)) != LZ_OK) return r;
+    if ((r = gemm_nt((const uint16_t*)dyp, (const uint16_t*)w2, w.dh, P, d, ffn, u_ffn, w.narrow_ffn, w, S, st)) != LZ_OK) return r;
     // dZ = dH * act'(Z)
     const int ffn_vec = ffn / 8;
     const unsigned blocks = (unsigned)((P * ffn_vec + 255) / 256);
@@ -540,14 +527,14 @@ int32_t ffn_backward(const void* dyp, const void* xp, const void* z, const void*
                          (const u32x4*)z, P, ffn_vec, (u32x4*)w.dz);
     if ((r = lz::launch_status()) != LZ_OK) return r;
     // dxp = dZ W1^T    (W1 [d, n1])
-    if ((r = gemm_nt(w.dz, (const uint16_t*)w1, (uint16_t*)dxp, P, n1, d, 1, t_rows, w.narrow_d, w, S, st)) != LZ_OK) return r;
+    if ((r = gemm_nt(w.dz, (const uint16_t*)w1, (uint16_t*)dxp, P, n1, d, u_d, w.narrow_d, w, S, st)) != LZ_OK) return r;
   }
   // dW2[s] = H_s^T dyp_s  [ffn, d],   dW1[s] = xp_s^T dZ_s  [d, n1]
   if ((r = gemm_wgrad((const uint16_t*)h, (const uint16_t*)dyp, accumulate ? nullptr : (uint16_t*)dw2,
-                      accumulate ? (float*)dw2 : nullptr, S, P, ffn, d, slot_offsets, t_w2, st)) != LZ_OK)
+                      accumulate ? (float*)dw2 : nullptr, S, P, ffn, d, u_w2, st)) != LZ_OK)
     return r;
   return gemm_wgrad((const uint16_t*)xp, w.dz, accumulate ? nullptr : (uint16_t*)dw1,
-                    accumulate ? (float*)dw1 : nullptr, S, P, d, n1, slot_offsets, t_w1, st);
+                    accumulate ? (float*)dw1 : nullptr, S, P, d, n1, u_w1, st);
 }
 
 }  // namespace

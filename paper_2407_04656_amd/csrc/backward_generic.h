@@ -69,16 +69,17 @@ inline GenericTrainWorkspace carve_train_generic(void* ws, const lz_shape* s) {
     return r;
   };
   w.dz = take((size_t)P * w.n1 * lz::elem_bytes(s->dtype));
-  w.tiles = take(tile_table_bytes(P, s->N * s->c, kF32Rows, 1, 0, 0));
+  w.tiles = take(tile_table_bytes(P, s->N * s->c, kF32Rows));
   w.total_bytes = size_t(p - (char*)ws);
   return w;
 }
 
 inline TileTable generic_tiles(const int32_t* slot_offsets, int S, long long P, const GenericTrainWorkspace& w, hipStream_t st) {
   TileSpecs specs{};
-  specs.spec[0] = {kF32Rows, 1, 0, 0, 0, P, carve_tiles(w.tiles, P, S, kF32Rows, 1, 0, 0)};
-  hipLaunchKernelGGL(build_tiles_kernel, dim3(1), dim3(256), 0, st, slot_offsets, S, specs);
-  return specs.spec[0].t;
+  const TileTable t = carve_tiles(w.tiles, P, S, kF32Rows);
+  add_rows(specs, kF32Rows, P, t);
+  launch_build_tiles(slot_offsets, S, specs, st);
+  return t;
 }
 
 template <typename Elem>

@@ -4,9 +4,9 @@
 //   GEMM-1   hidden[P, ffn] = act(xp[P, d] * W1[slot])        act = GELU | SwiGLU, fused;  W1[slot] = [d, n1]
 //   GEMM-2   yp[P, d]       = hidden[P, ffn] * W2[slot]                                        W2[slot] = [ffn, d]
 //
-// Group sizes are data dependent and only known on the device, so a one-workgroup kernel
-// first turns slot_offsets into a table of row tiles (slot, first row, end row) and, for the
-// MFMA path, into one queue of work units per XCD.
+// Group sizes are data dependent and only known on the device, so a small kernel
+// first turns slot_offsets into a table of row tiles (slot, first row, end row) or, for the
+// wide MFMA kernel, into one list of work units per XCD.
 //
 // bf16 path: the MFMA kernel of gemm_mfma.h.
 //
@@ -32,7 +32,8 @@ inline bool mfma_shape(const lz_shape* s) {
 
 struct FfnWorkspace {
   void* hidden;
-  void* tiles;         // of the wide bf16 GEMMs
+  void* units_up;      // of the wide bf16 GEMMs
+  void* units_down;
   void* tiles_narrow;  // of the GEMMs on narrow tiles
   void* tiles_f32;     // of the fp32 kernel
   size_t total_bytes;
@@ -40,16 +41,20 @@ struct FfnWorkspace {
   bool narrow_up, narrow_down;  // GEMMs on narrow tiles
 };
 
-TileTable tiles_of(const FfnWorkspace& w, const lz_shape* s) {
-  return carve_tiles(w.tiles, (long long)s->T * s->k, s->N * s->c, BM, kGroupM, w.n_up, w.n_down);
+UnitTable units_up_of(const FfnWorkspace& w, const lz_shape* s) {
+  return carve_units(w.units_up, (long long)s->T * s->k, s->N * s->c, BM, w.n_up);
+}
+
+UnitTable units_down_of(const FfnWorkspace& w, const lz_shape* s) {
+  return carve_units(w.units_down, (long long)s->T * s->k, s->N * s->c, BM, w.n_down);
 }
 
 TileTable narrow_tiles_of(const FfnWorkspace& w, const lz_shape* s) {
-  return carve_tiles(w.tiles_narrow, (long long)s->T * s->k, s->N * s->c, kNarrow, 1, 0, 0);
+  return carve_tiles(w.tiles_narrow, (long long)s->T * s->k, s->N * s->c, kNarrow);
 }
 
 TileTable f32_tiles_of(const FfnWorkspace& w, const lz_shape* s) {
-  return carve_tiles(w.tiles_f32, (long long)s->T * s->k, s->N * s->c, kF32Rows, 1, 0, 0);
+  return carve_tiles(w.tiles_f32, (long long)s->T * s->k, s->N * s->c, kF32Rows);
 }
 
 // Every table that some number of tokens of the same layer uses has its room, so that a workspace made for the
@@ -68,10 +73,11 @@ FfnWorkspace carve_ffn(void* ws, const lz_shape* s) {
   };
   w.hidden = take((size_t)P * s->ffn * lz::elem_bytes(s->dtype));
   if (mfma_sizes(s)) {
-    w.tiles = take(tile_table_bytes(P, S, BM, kGroupM, w.n_up, w.n_down));
-    w.tiles_narrow = take(tile_table_bytes(P, S, kNarrow, 1, 0, 0));
+    w.units_up = take(unit_table_bytes(P, S, BM, w.n_up));
+    w.units_down = take(unit_table_bytes(P, S, BM, w.n_down));
+    w.tiles_narrow = take(tile_table_bytes(P, S, kNarrow));
   }
-  if (!mfma_sizes(s) || !whole_tiles(s)) w.tiles_f32 = take(tile_table_bytes(P, S, kF32Rows, 1, 0, 0));
+  if (!mfma_sizes(s) || !whole_tiles(s)) w.tiles_f32 = take(tile_table_bytes(P, S, kF32Rows));
   w.narrow_up = mfma_shape(s) && s->act == LZ_GELU && use_narrow(P, S, s->ffn);
   w.narrow_down = mfma_shape(s) && use_narrow(P, S, s->d);
   w.total_bytes = size_t(p - (char*)ws);
@@ -106,13 +112,14 @@ extern "C" int32_t lz_ffn_tiles(const int32_t* slot_offsets, const lz_shape* sha
   if (!slot_offsets) return LZ_EINVAL;
   const int S = shape->N * shape->c;
   TileSpecs specs{};
-  int n = 0;
-  if (mfma_shape(shape)) specs.spec[n++] = {BM, kGroupM, w.n_up, w.n_down, 0, P, tiles_of(w, shape)};
-  if (w.narrow_up || w.narrow_down) specs.spec[n++] = {kNarrow, 1, 0, 0, 0, P, narrow_tiles_of(w, shape)};
+  if (mfma_shape(shape)) {
+    if (!w.narrow_up) add_units(specs, BM, w.n_up, 0, P, units_up_of(w, shape));
+    if (!w.narrow_down) add_units(specs, BM, w.n_down, 0, P, units_down_of(w, shape));
+  }
+  if (w.narrow_up || w.narrow_down) add_rows(specs, kNarrow, P, narrow_tiles_of(w, shape));
   // the calls that follow may bring unaligned tensors where that is allowed
-  if (!mfma_shape(shape) || !whole_tiles(shape)) specs.spec[n++] = {kF32Rows, 1, 0, 0, 0, P, f32_tiles_of(w, shape)};
-  hipLaunchKernelGGL(build_tiles_kernel, dim3(n), dim3(256), 0, (hipStream_t)stream, slot_offsets, S, specs);
-  return lz::launch_status();
+  if (!mfma_shape(shape) || !whole_tiles(shape)) add_rows(specs, kF32Rows, P, f32_tiles_of(w, shape));
+  return launch_build_tiles(slot_offsets, S, specs, (hipStream_t)stream);
 }
 
 namespace {
@@ -165,8 +172,7 @@ int32_t ffn_up(const void* xp, const int32_t* gather, const void* w1, const lz_s
   g1.n_out = shape->ffn;
   g1.up_row0 = swiglu ? shape->ffn : 0;
   g1.n_tiles = w.n_up;
-  g1.which = 0;
-  g1.t = tiles_of(w, shape);
+  g1.u = units_up_of(w, shape);
   g1.ldw = n1;
   g1.gather = gather;
   g1.gather_k = gk;
@@ -226,8 +232,7 @@ extern "C" int32_t lz_ffn_down(const void* w2, const lz_shape* shape, void* yp, 
   g2.n_out = shape->d;
   g2.up_row0 = 0;
   g2.n_tiles = w.n_down;
-  g2.which = 1;
-  g2.t = tiles_of(w, shape);
+  g2.u = units_down_of(w, shape);
   g2.ldw = shape->d;
   if (w.narrow_down) return launch_narrow<EPI_NONE, MODE_NN>(g2, narrow_tiles_of(w, shape), st);
   return launch_mfma<EPI_NONE, MODE_NN>(g2, st);

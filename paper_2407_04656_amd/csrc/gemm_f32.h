@@ -94,7 +94,6 @@ template <typename Elem>
 struct Raw4 {
   Elem e[4];
 };
-typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 
 template <typename Elem, bool VEC>
 __device__ __forceinline__ void store_piece(Elem* p, const f32x4& v, int n) {

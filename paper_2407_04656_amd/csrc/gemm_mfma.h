@@ -29,11 +29,10 @@ namespace {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 
-// ints before the tile arrays; [0] = number of row tiles, then the lengths of the unit lists (kUnitCount), then,
-// a 128-byte line each, the queue counters (kTicket)
-constexpr int kLine = 32;
-constexpr int kTileHeader = 64 + 2 * (8 + 8 + 1) * kLine;
+constexpr int kLine = 32;        // ints of a 128-byte line
 constexpr int kGroupM = 4;       // row tiles of a work unit (same slot)
 constexpr int kGroupN = 8;       // column tiles of a work unit
 
@@ -42,56 +41,57 @@ constexpr int kGroupN = 8;       // column tiles of a work unit
 // micro-batches) instead of being stored as bf16.
 enum { EPI_NONE = 0, EPI_GELU = 1, EPI_SWIGLU = 2, EPI_GELU_KEEP = 3, EPI_SWIGLU_KEEP = 4, EPI_ACCUM = 5 };
 
+// Row tiles of a grouped GEMM, slot after slot: what the narrow and the fp32 kernels index by workgroup.
 struct TileTable {
-  int32_t* header;
+  int32_t* header;  // [0] = number of row tiles
   int32_t* slot;
   int32_t* row0;
   int32_t* row_end;
-  int32_t* units[2];  // per GEMM (0 = up, 1 = down): 8 lists of unit_cap[g] work units, one list per XCD
-  int unit_cap[2];
   int capacity;
 };
+constexpr int kTileHeader = 64;
 
-constexpr int kUnitCount = 16;  // header[kUnitCount + 16*g + x] = length of XCD x's unit list for GEMM g
-// Counters of GEMM g: header[kTicket + (17*g + x) * kLine] = tickets drawn from XCD x's queue, x < 8;
-// x = 8..15: workgroups of XCD x - 8 that have finished; x = 16: XCDs that have finished
-constexpr int kTicket = 64;
+inline int tile_capacity(long long P, int S, int BM) { return int((P + BM - 1) / BM + S); }
 
-// Row tiles are listed slot after slot; with group > 1 every slot's list is padded (slot = -1)
-// to a multiple of `group`, so that a group of consecutive row tiles never spans two slots.
-inline int tile_capacity(long long P, int S, int BM, int group) {
-  const long long n = (P + BM - 1) / BM + (long long)S * group;
-  return int((n + group - 1) / group * group);
+inline size_t tile_table_bytes(long long P, int S, int BM) {
+  return lz::align256(sizeof(int32_t) * (kTileHeader + 3 * (size_t)tile_capacity(P, S, BM)));
 }
 
-// Room in one XCD's list of work units (a unit = one row group x kGroupN column tiles): twice
-// an eighth of the worst-case number of units, so that lists of equal cost but unequal length
-// normally fit as they are.
-inline int unit_capacity(int capacity, int group, int n_tiles) {
-  if (n_tiles <= 0) return 0;
-  const long long units = (long long)(capacity / group) * ((n_tiles + kGroupN - 1) / kGroupN);
-  return int((units + 7) / 8 * 2);
-}
-
-inline size_t tile_table_bytes(long long P, int S, int BM, int group, int n_up, int n_down) {
-  const int cap = tile_capacity(P, S, BM, group);
-  const size_t ints = kTileHeader + 3 * (size_t)cap +
-                      8 * ((size_t)unit_capacity(cap, group, n_up) + unit_capacity(cap, group, n_down));
-  return lz::align256(sizeof(int32_t) * ints);
-}
-
-inline TileTable carve_tiles(void* base, long long P, int S, int BM, int group, int n_up, int n_down) {
+inline TileTable carve_tiles(void* base, long long P, int S, int BM) {
   TileTable t;
-  t.capacity = tile_capacity(P, S, BM, group);
+  t.capacity = tile_capacity(P, S, BM);
   t.header = (int32_t*)base;
   t.slot = t.header + kTileHeader;
   t.row0 = t.slot + t.capacity;
   t.row_end = t.row0 + t.capacity;
-  t.unit_cap[0] = unit_capacity(t.capacity, group, n_up);
-  t.unit_cap[1] = unit_capacity(t.capacity, group, n_down);
-  t.units[0] = t.row_end + t.capacity;
-  t.units[1] = t.units[0] + 8 * (size_t)t.unit_cap[0];
   return t;
+}
+
+// Work of one launch of the persistent GEMM: a list of units per XCD.  A unit is up to kGroupM row tiles of one slot x up
+// to kGroupN column tiles; its tiles have consecutive tickets, so that a ticket leads to its tile by one look at the
+// list, and none is padding.
+struct UnitTable {
+  int32_t* header;   // [x] = tickets of XCD x's list, [8 + x] = its units, then, a line each, the counters below
+  int32_t* records;  // 8 lists of `cap` records
+  int cap, groups;   // room: records of a list, groups of row tiles in all
+};
+// A record: first ticket, slot, first row, end of the slot's rows, row tiles | column tiles << 8, first column tile, and
+// for the weight gradients the rows [k0, k1) that the slot contracts over.
+constexpr int kRecord = 8;
+// Counters: header[kTicket + x * kLine] = tickets drawn from XCD x's list, x < 8;  x = 8..15: workgroups of XCD
+// x - 8 that have finished;  x = 16: XCDs that have finished
+constexpr int kTicket = 64;
+constexpr int kUnitHeader = kTicket + 17 * kLine;
+
+inline int unit_groups(long long P, int S, int BM) { return int(P / (BM * kGroupM) + S); }
+inline int unit_capacity(long long P, int S, int BM, int n_tiles) {
+  return int(((long long)unit_groups(P, S, BM) * ((n_tiles + kGroupN - 1) / kGroupN) + 7) / 8);
+}
+inline size_t unit_table_bytes(long long P, int S, int BM, int n_tiles) {
+  return lz::align256(sizeof(int32_t) * (kUnitHeader + 8 * kRecord * (size_t)unit_capacity(P, S, BM, n_tiles)));
+}
+inline UnitTable carve_units(void* base, long long P, int S, int BM, int n_tiles) {
+  return UnitTable{(int32_t*)base, (int32_t*)base + kUnitHeader, unit_capacity(P, S, BM, n_tiles), unit_groups(P, S, BM)};
 }
 
 __device__ __forceinline__ void clip_slot(const int32_t* slot_offsets, int s, long long P, long long* a,
@@ -103,11 +103,10 @@ __device__ __forceinline__ void clip_slot(const int32_t* slot_offsets, int s, lo
   *b = hi;
 }
 
-// slot_offsets -> row tiles.  Offsets are clipped to [0, P] and made non-decreasing.
+// slot_offsets -> row tiles or units.  Offsets are clipped to [0, P] and made non-decreasing.
 //
-// For the MFMA GEMMs (n_tiles_up/down > 0) the kernel also deals each GEMM's work units (one
-// row group x kGroupN column tiles) to the 8 XCDs' queues: in (row group, column group) order,
-// eight at a time, alternate eights in opposite directions.  The XCDs thus work on neighbouring
+// Units are dealt to the 8 XCDs' lists in (row group, column group) order, eight at a time, alternate eights in
+// opposite directions.  The XCDs thus work on neighbouring
 // column groups of the same row group at the same time and share its activation panel in the
 // memory-side cache, and a regular pattern of large and small units (a narrow last column
 // group, say) does not pile the large ones on the same XCDs; what imbalance is left the GEMM
@@ -115,15 +114,81 @@ __device__ __forceinline__ void clip_slot(const int32_t* slot_offsets, int s, lo
 // within 2 % of this and costs a serial pass over the units; dealing the full row groups
 // first and the ragged ones last measured 1-5 % slower.)
 struct TileSpec {
-  int BM, group;                 // rows of a tile, tiles of a group
-  int n_tiles_up, n_tiles_down;  // column tiles of the two GEMMs that draw units from the table (0: none does)
-  int virtual_rows;              // > 0: every slot has this many rows (weight gradients), slot_offsets is not read
-  long long P;
-  TileTable t;
+  int BM;            // rows of a tile
+  int n_tiles;       // column tiles; 0: row tiles for `rows`, else units for `units`
+  int virtual_rows;  // > 0: every slot has this many rows (weight gradients)
+  long long P;       // rows of the batch
+  TileTable rows;
+  UnitTable units;
 };
 struct TileSpecs {
-  TileSpec spec[4];
+  TileSpec spec[5];
+  int n;
 };
+inline void add_rows(TileSpecs& specs, int BM, long long P, const TileTable& t) {
+  specs.spec[specs.n++] = TileSpec{BM, 0, 0, P, t, UnitTable{}};
+}
+inline void add_units(TileSpecs& specs, int BM, int n_tiles, int virtual_rows, long long P, const UnitTable& u) {
+  specs.spec[specs.n++] = TileSpec{BM, n_tiles, virtual_rows, P, TileTable{}, u};
+}
+
+// The unit lists: 32 threads a list, each a run of consecutive records; s_first: first group of every slot.
+__device__ __forceinline__ void deal_units(const int32_t* slot_offsets, int S, const TileSpec& spec, const int* s_first) {
+  const int ncg = (spec.n_tiles + kGroupN - 1) / kGroupN;
+  const int n_units = s_first[S] * ncg;
+  const int x = threadIdx.x >> 5, seg = threadIdx.x & 31;
+  const int full = n_units / 8, count = full + (((full & 1) ? 7 - x : x) < n_units % 8 ? 1 : 0);
+  const int per = (count + 31) / 32, r0 = seg * per < count ? seg * per : count, r1 = r0 + per < count ? r0 + per : count;
+  auto unit_of = [&](int r) { return r * 8 + ((r & 1) ? 7 - x : x); };
+  auto first_col = [&](int c) { return int((long long)c * spec.n_tiles / ncg); };  // equal column groups
+  int s_start = 0;
+  if (r0 < r1) {  // the last slot that starts at or before the first unit's group
+    const int g = unit_of(r0) / ncg;
+    for (int hi = S - 1; s_start < hi;) {
+      const int mid = (s_start + hi + 1) >> 1;
+      if (s_first[mid] <= g) s_start = mid;
+      else hi = mid - 1;
+    }
+  }
+  int32_t* const list = spec.units.records + (size_t)x * spec.units.cap * kRecord;
+  auto walk = [&](int ticket, bool write) {
+    int s = s_start, loaded = -1;
+    long long a = 0, b = 0, k0 = 0, k1 = 0;
+    for (int r = r0; r < r1; ++r) {
+      const int u = unit_of(r), g = u / ncg, c = u - g * ncg;
+      while (s_first[s + 1] <= g) ++s;
+      if (s != loaded) {
+        loaded = s;
+        clip_slot(slot_offsets, s, spec.P, &k0, &k1);
+        a = spec.virtual_rows > 0 ? (long long)s * spec.virtual_rows : k0;
+        b = spec.virtual_rows > 0 ? a + spec.virtual_rows : k1;
+      }
+      const long long row0 = a + (long long)(g - s_first[s]) * (kGroupM * spec.BM);
+      const long long left = (b - row0 + spec.BM - 1) / spec.BM;
+      const int nr = left < kGroupM ? int(left) : kGroupM, c0 = first_col(c), nc = first_col(c + 1) - c0;
+      if (write) {
+        i32x4* const to = (i32x4*)(list + (size_t)r * kRecord);
+        to[0] = i32x4{ticket, s, int(row0), int(b)};
+        to[1] = i32x4{nr | nc << 8, c0, int(k0), int(k1)};
+      }
+      ticket += nr * nc;
+    }
+    return ticket;
+  };
+  const int mine = walk(0, false);
+  int incl = mine;
+#pragma unroll
+  for (int off = 1; off < 32; off <<= 1) {
+    const int n = __shfl_up(incl, off, 32);
+    if (seg >= off) incl += n;
+  }
+  walk(incl - mine, true);
+  if (seg == 31) {
+    spec.units.header[x] = incl;
+    spec.units.header[8 + x] = count;
+  }
+  if (threadIdx.x < 17) spec.units.header[kTicket + threadIdx.x * kLine] = 0;
+}
 
 // One workgroup per table.
 __global__ __launch_bounds__(256) void build_tiles_kernel(const int32_t* __restrict__ slot_offsets, int S,
@@ -131,8 +196,10 @@ __global__ __launch_bounds__(256) void build_tiles_kernel(const int32_t* __restr
   __shared__ int s_first[lz::kMaxN * lz::kMaxC + 1];
   __shared__ int s_wave[4];
   const TileSpec& spec = specs.spec[blockIdx.x];
-  const TileTable t = spec.t;
-  const int BM = spec.BM, group = spec.group, n_tiles_up = spec.n_tiles_up, n_tiles_down = spec.n_tiles_down;
+  const TileTable t = spec.rows;
+  const bool units = spec.n_tiles > 0;
+  const int BM = spec.BM, group_rows = units ? BM * kGroupM : BM;
+  const int capacity = units ? spec.units.groups : t.capacity;
   const int tid = threadIdx.x, lane = tid % lz::kWave, wave = tid / lz::kWave;
   auto slot_rows = [&](int s, long long* a, long long* b) {
     if (spec.virtual_rows > 0) {
@@ -142,18 +209,18 @@ __global__ __launch_bounds__(256) void build_tiles_kernel(const int32_t* __restr
       clip_slot(slot_offsets, s, spec.P, a, b);
     }
   };
-  // padded tile count of every slot and its exclusive sum: each thread owns a run of consecutive slots.  The sums
+  // tile or group count of every slot and its exclusive sum: each thread owns a run of consecutive slots.  The sums
   // end at the table's capacity, which the slots of ascending offsets stay within: offsets that fall again make
   // slots overlap, any number of tiles in all.
-  auto add = [&](int x, int y) { return x + y < t.capacity ? x + y : t.capacity; };  // both at most capacity < 2^26
+  auto add = [&](int x, int y) { return x + y < capacity ? x + y : capacity; };  // both at most capacity < 2^26
   const int per = (S + 255) / 256, first = tid * per;
   int mine = 0;
   for (int s = first; s < first + per && s < S; ++s) {
     long long a, b;
     slot_rows(s, &a, &b);
-    const int tiles = int((b - a + BM - 1) / BM), padded = (tiles + group - 1) / group * group;
+    const int tiles = int((b - a + group_rows - 1) / group_rows);
     s_first[s] = mine;
-    mine = add(mine, padded < t.capacity ? padded : t.capacity);
+    mine = add(mine, tiles < capacity ? tiles : capacity);
   }
   int incl = mine;
 #pragma unroll
@@ -167,13 +234,13 @@ __global__ __launch_bounds__(256) void build_tiles_kernel(const int32_t* __restr
   int base = lane == 0 ? 0 : before;
   for (int w = 0; w < wave; ++w) base = add(base, s_wave[w]);
   for (int s = first; s < first + per && s < S; ++s) s_first[s] = add(s_first[s], base);
-  if (tid == 255) {
-    const int all = add(base, mine);
-    s_first[S] = all;
-    t.header[0] = all;
-  }
-  if (tid < 2 * 17) t.header[kTicket + tid * kLine] = 0;
+  if (tid == 255) s_first[S] = add(base, mine);
   __syncthreads();
+  if (units) {
+    deal_units(slot_offsets, S, spec, s_first);
+    return;
+  }
+  if (tid == 0) t.header[0] = s_first[S];
   // Few entries: a thread each, its slot found by bisection.  More: a thread writes the entries of its slot, 45 ns
   // each, and where a wave holds a few long slots (few slots share a large batch) it writes what is past kOwn of
   // those together, slot after slot: 130 ns a slot and 64 entries a step.
@@ -181,7 +248,7 @@ __global__ __launch_bounds__(256) void build_tiles_kernel(const int32_t* __restr
   constexpr int kOwn = 64;
   auto entry = [&](int i, int s, int first_i, long long a, long long b) {
     const long long r0 = a + (long long)(i - first_i) * BM;
-    t.slot[i] = r0 < b ? s : -1;  // -1: padding entry, no rows
+    t.slot[i] = s;
     t.row0[i] = int(r0 < b ? r0 : b);
     t.row_end[i] = int(b);
   };
@@ -212,25 +279,11 @@ __global__ __launch_bounds__(256) void build_tiles_kernel(const int32_t* __restr
       for (int i = f + kOwn + lane; i < end; i += lz::kWave) entry(i, s0 + l, f, sa, sb);
     }
   }
-  // deal the units, in (row group, column group) order, to the XCD queues in rows of eight,
-  // alternate rows in opposite directions
-  const int n_groups = s_first[S] / group;
-  for (int which = 0; which < 2; ++which) {
-    const int nt = which == 0 ? n_tiles_up : n_tiles_down;
-    const int ncg = (nt + kGroupN - 1) / kGroupN;
-    const int n_units = n_groups * ncg;  // 0 on the fp32 kernel
-    const int cap = t.unit_cap[which];
-    for (int u = threadIdx.x; u < n_units; u += blockDim.x) {
-      const int row = u / 8, i = u % 8;
-      const int x = (row & 1) ? 7 - i : i;
-      if (row < cap) t.units[which][(size_t)x * cap + row] = u;  // n_units <= 4 * cap: always true
-    }
-    if (threadIdx.x < 8) {
-      const int rows = n_units / 8, rest = n_units % 8;
-      const int i = (rows & 1) ? 7 - (int)threadIdx.x : (int)threadIdx.x;  // position of this XCD in the last row
-      t.header[kUnitCount + 16 * which + threadIdx.x] = rows + (i < rest ? 1 : 0);
-    }
-  }
+}
+
+inline int32_t launch_build_tiles(const int32_t* slot_offsets, int S, const TileSpecs& specs, hipStream_t st) {
+  hipLaunchKernelGGL(build_tiles_kernel, dim3(specs.n), dim3(256), 0, st, slot_offsets, S, specs);
+  return lz::launch_status();
 }
 
 // ------------------------------------------------------------------------------------------
@@ -257,16 +310,14 @@ struct MfmaArgs {
   int n_out;            // output columns
   int up_row0;          // SwiGLU: offset of the up projection inside a slot's W (rows, or columns if k-major)
   int n_tiles;          // column tiles per row tile
-  int which;            // which of the tile table's two unit lists and ticket sets this launch draws from
-  TileTable t;
-  // MODE_TN (weight gradients): slot s contracts over the rows [slot_offsets[s], slot_offsets[s+1])
+  TileTable t;          // narrow kernel
+  UnitTable u;          // wide kernel
+  // MODE_TN (weight gradients): slot s contracts over its rows of the batch (in its units' records)
   // of both operands and owns rows_per_slot rows of C (row index = s * rows_per_slot + m, m =
   // column of A).
   uint16_t* Z;          // *_KEEP epilogues: pre-activations [P, z_cols] (SwiGLU: gate columns, then up columns)
   int z_cols;
   int lda, ldw;         // row strides (elements) of the k-major operands
-  const int32_t* slot_offsets;
-  long long k_rows;
   int rows_per_slot;
   // GATHER (forward only): A is x [gather_T, K] and row r of the permuted buffer is row
   // gather[r] / gather_k of it (gather = row_to_pair of the dispatcher)
@@ -274,6 +325,10 @@ struct MfmaArgs {
   int gather_k;
   long long gather_T;
 };
+
+// stores of an epilogue's last pass (EPI_ACCUM: not the same in every wave)
+template <int EPI>
+constexpr int kLastStores = EPI == EPI_ACCUM ? 0 : EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_KEEP ? 4 : 8;
 
 // Operand layouts of the contraction C[m, n] = sum_k A(m, k) W(n, k):
 //   MODE_NT  A [m, k], W [n, k]: both contiguous along k (the data gradients)
@@ -289,7 +344,6 @@ struct MfmaArgs {
 // do not change.
 enum { MODE_NT = 0, MODE_NN = 1, MODE_TN = 2, MODE_TN_WIDE = 3 };
 typedef short i16x4 __attribute__((ext_vector_type(4)));
-typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 // The four words of a raw buffer descriptor (base, stride 0, bytes, data format word).
 __device__ __forceinline__ i32x4 rsrc_words(const void* base, uint32_t bytes) {
@@ -358,156 +412,329 @@ __device__ __forceinline__ int swz(int row) { return (row >> 1) & 7; }
 // eight 32-byte runs fall into eight different bank groups.
 __device__ __forceinline__ int swz_kmajor(int kr) { return ((kr & 3) << 2) | (((kr >> 3) & 1) << 1); }
 
-// One output tile of 64*XF rows x 256 columns n of the weight operand W(n, k) ("weight rows"
-// below, whichever way W lies in memory).  XF = 32-row activation fragments per wave: the 2x2 waves each own (32*XF) x 128 of the tile, so a slot's ragged last tile costs
-// MFMAs and activation loads only for its rows rounded up to 64.
+// A tile: rows [row0, row_end) of a slot (row_end: the slot's end, at most 256 rows are the tile's), output columns from
+// n0; weight gradients: the rows [k0, k1) of the batch that the slot contracts over.  slot < 0: none.
+struct Tile {
+  int slot, row0, row_end, n0, k0, k1;
+};
+
+// Where a tile's operands lie, and their direct-to-LDS loads.
 //
 // KTAIL: K is not a multiple of 64 and an operand is k-contiguous, so the last K step's 128-byte rows run
 // past the end of K into the next row.  The lanes whose 16-byte chunk lies there fetch from beyond the
 // descriptor instead and get zeros (both operands: a zero against what the other row holds would let an
 // infinity or NaN of a neighbouring row through).  k-major operands end with their descriptor.
+template <int EPI, int MODE, bool GATHER, bool KTAIL>
+struct Operands {
+  static constexpr bool TA = MODE == MODE_TN || MODE == MODE_TN_WIDE, TB = MODE != MODE_NT;  // k-major left / right operand
+  static constexpr bool kGated = EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_KEEP;
+  i32x4 wordsA, wordsW, wordsNull;  // descriptors; Null has no bytes
+  const uint16_t *tileA, *tileW;
+  uint32_t a_extent, w_extent;      // bytes the two descriptors cover
+  int stepA, stepW;                 // bytes one K step advances in each operand
+  // MODE_TN, MODE_TN_WIDE: the contraction ends with the slot's last row, wherever in a K step that
+  // is, so the descriptors are rebuilt for every K step (base advanced by whole steps, extent =
+  // what is left of the slot); in 64-bit arithmetic where a slot's rows may cover more than 4 GiB
+  unsigned long long a_bytes, w_bytes, stepA64, stepW64;
+  int k_steps;
+  uint32_t lds;                     // LDS address of the stages, this wave's place in a 4-KiB row of loads added
+  int voffX[8], voffW[8];           // byte offsets of the loads of one stage
+  int tail_or;                      // KTAIL: what the last K step ORs into them
+  int no_row;                       // GATHER: bit i: load i's row lies past the tile's end
+
+  // ---- buffer descriptors: out-of-range loads return zero instead of faulting.  The activation
+  // descriptor covers just this tile's rows, so 32-bit offsets do however large P is.
+  //
+  // ---- per-lane global offsets of the direct-to-LDS loads of one stage.
+  // Load i of a wave fills the LDS bytes [u*1024, u*1024+1024), u = 4 i + wave: 8 whole rows, lane l
+  // landing at row 8u + l/8, 16-byte chunk l%8.  That LDS chunk must hold logical chunk
+  // (l%8) ^ swz(row), so the lane fetches that one (the swizzle is applied on the global side
+  // because a direct-to-LDS load fixes the LDS side to lane order).  The first 2 XF loads of the four
+  // waves hold the first 64 XF rows.
+  //
+  // k-major operand: load i fills two k-rows of 512 B, lane l landing at k-row 2u + l/32, 16-byte
+  // piece l%32, which must hold logical piece (l%32) ^ swz_kmajor(k-row).
+  __device__ __forceinline__ void set(const MfmaArgs& a, char* smem, const Tile& t) {
+    if (t.slot < 0) {  // no tile: its loads have no bytes
+      k_steps = 0;
+      a_bytes = w_bytes = 0;
+      return;
+    }
+    // The empty asm keeps the per-lane address arithmetic below inside the tile: hoisted out of
+    // the caller's tile loop it would be carried in registers through the whole kernel and spill.
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem + wave * 1024;
+    const int n_rows = t.row_end - t.row0 < BM ? t.row_end - t.row0 : BM;
+    int K = a.K;
+    stepA = stepW = BK * 2;
+    if constexpr (TA) {
+      // The descriptors start at the slot's first row and this tile's first column and end with
+      // the slot's last row: the rows of the last, partial K step that belong to the next slot
+      // read as zero.
+      K = t.k1 - t.k0;
+      const int m0 = t.row0 - t.slot * a.rows_per_slot;
+      tileA = a.A + (size_t)t.k0 * a.lda + m0;
+      tileW = a.W + (size_t)t.k0 * a.ldw + t.n0;
+      a_bytes = K > 0 ? ((unsigned long long)K * (unsigned)a.lda - (unsigned)m0) * 2ull : 0ull;
+      w_bytes = K > 0 ? ((unsigned long long)K * (unsigned)a.ldw - (unsigned)t.n0) * 2ull : 0ull;
+      stepA64 = 64ull * (unsigned)a.lda * 2ull;
+      stepW64 = 64ull * (unsigned)a.ldw * 2ull;
+      a_extent = (uint32_t)a_bytes;  // MODE_TN: the host checked that they fit; MODE_TN_WIDE: unused, see words_*()
+      w_extent = (uint32_t)w_bytes;
+      stepA = stepW = 0;
+    } else if constexpr (MODE == MODE_NN) {
+      if constexpr (GATHER) {
+        tileA = a.A;  // the whole of x: a tile's rows lie anywhere in it (the host checked that it fits 32-bit offsets)
+        a_extent = (uint32_t)((unsigned long long)a.gather_T * (unsigned)K * 2ull);
+      } else {
+        tileA = a.A + (size_t)t.row0 * K;
+        a_extent = (uint32_t)n_rows * (uint32_t)K * 2u;
+      }
+      tileW = a.W + (size_t)t.slot * K * a.ldw;
+      w_extent = (uint32_t)K * (uint32_t)a.ldw * 2u;
+      stepW = 64 * a.ldw * 2;
+    } else {
+      tileA = a.A + (size_t)t.row0 * K;
+      a_extent = (uint32_t)n_rows * (uint32_t)K * 2u;
+      tileW = a.W + (size_t)t.slot * a.w_rows * K;
+      w_extent = (uint32_t)((unsigned long long)a.w_rows * K * 2);
+    }
+    k_steps = (K + BK - 1) / BK;
+    wordsA = rsrc_words(tileA, a_extent);
+    wordsW = rsrc_words(tileW, w_extent);
+    wordsNull = rsrc_words(a.A, 0);
+    no_row = 0;
+    auto voff_kmajor = [&](int i, int ld, int col0) {
+      const int kr = (i * 4 + wave) * 2 + (lane >> 5);
+      const int piece = (lane & 31) ^ swz_kmajor(kr);
+      return (int)(((uint32_t)kr * (uint32_t)ld + (uint32_t)col0 + (uint32_t)piece * 8u) * 2u);
+    };
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      if constexpr (TA) {
+        voffX[i] = voff_kmajor(i, a.lda, 0);  // columns past the operand's edge fetch its neighbours: never stored
+      } else {
+        const int r = (i * 4 + wave) * 8 + (lane >> 3);
+        const int chunk = (lane & 7) ^ swz(r);
+        // rows past the tile's end (never stored), and rows without a pair, lie beyond the descriptor: zeros
+        if constexpr (GATHER) {
+          voffX[i] = a.gather[t.row0 + (r < n_rows ? r : n_rows - 1)];  // the pair; the offset once it has arrived
+          if (r >= n_rows) no_row |= 1 << i;
+        } else {
+          voffX[i] = (int)(((uint32_t)r * (uint32_t)K + (uint32_t)chunk * 8u) * 2u);
+        }
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      if constexpr (TB && kGated) {
+        // k-major SwiGLU weights [K, 2 ffn]: 32-column fragments alternate gate and up columns
+        const int kr = (i * 4 + wave) * 2 + (lane >> 5);
+        const int piece = (lane & 31) ^ swz_kmajor(kr);
+        const int f = piece >> 2;
+        const int col = t.n0 + (f >> 1) * 32 + (piece & 3) * 8 + ((f & 1) ? a.up_row0 : 0);
+        voffW[i] = (int)(((uint32_t)kr * (uint32_t)a.ldw + (uint32_t)col) * 2u);
+      } else if constexpr (TB) {
+        voffW[i] = voff_kmajor(i, a.ldw, MODE == MODE_NN ? t.n0 : 0);
+      } else {
+        static_assert(!kGated || TB, "gated weights are k-major");
+        const int r = (i * 4 + wave) * 8 + (lane >> 3);
+        const int chunk = (lane & 7) ^ swz(r);
+        voffW[i] = (int)(((uint32_t)(t.n0 + r) * (uint32_t)K + (uint32_t)chunk * 8u) * 2u);
+      }
+    }
+    if constexpr (KTAIL) {  // the swizzle of a load's rows is the same for all of a wave's loads
+      const int k_left = K - (K - 1) / BK * BK;  // 1..64; multiples of 8, so chunks are whole
+      tail_or = ((lane & 7) ^ swz(wave * 8 + (lane >> 3))) * 8 >= k_left ? (int)0x80000000 : 0;
+    }
+  }
+
+  // The descriptors for K step `step`.  A step past the end of K is "loaded" through a zero-length one: no memory traffic.
+  __device__ __forceinline__ i32x4 words_x(int step) const {
+    const bool real = step < k_steps;
+    if constexpr (MODE == MODE_TN) {
+      // bytes left of the slot: a step that begins inside the slot begins inside both extents (the
+      // tile's first column lies inside the operand's row)
+      const uint32_t off = (uint32_t)step * (uint32_t)stepA64;
+      return rsrc_words((const char*)tileA + off, real ? a_extent - off : 0u);
+    } else if constexpr (MODE == MODE_TN_WIDE) {
+      const unsigned long long off = (unsigned long long)(unsigned)step * stepA64, left = a_bytes > off ? a_bytes - off : 0ull;
+      return rsrc_words((const char*)tileA + off, left > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)left);
+    } else {
+      return real ? wordsA : wordsNull;
+    }
+  }
+  __device__ __forceinline__ i32x4 words_w(int step) const {
+    const bool real = step < k_steps;
+    if constexpr (MODE == MODE_TN) {
+      const uint32_t off = (uint32_t)step * (uint32_t)stepW64;
+      return rsrc_words((const char*)tileW + off, real ? w_extent - off : 0u);
+    } else if constexpr (MODE == MODE_TN_WIDE) {
+      const unsigned long long off = (unsigned long long)(unsigned)step * stepW64, left = w_bytes > off ? w_bytes - off : 0ull;
+      return rsrc_words((const char*)tileW + off, left > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)left);
+    } else {
+      return real ? wordsW : wordsNull;
+    }
+  }
+  // Load i of a wave for K step `step` into an activation / weight stage; with_mfma: an MFMA (accumulator, weight and
+  // activation fragment) to issue together with it
+  __device__ __forceinline__ void load_x(int stage, int step, int i, const i32x4& words, f32x4* with_mfma = nullptr,
+                                         const bf16x8* mw = nullptr, const bf16x8* mx = nullptr) const {
+    int voff = voffX[i];
+    if constexpr (KTAIL && !TA) voff |= tail_or & (step == k_steps - 1 ? -1 : 0);
+    const uint32_t to = lds + a_stage_off(stage) + i * 4096;
+    if (with_mfma != nullptr) mfma_then_load16_to_lds(*with_mfma, *mw, *mx, words, to, voff, step * stepA);
+    else load16_to_lds(words, to, voff, step * stepA);
+  }
+  __device__ __forceinline__ void load_w(int stage, int step, int i, const i32x4& words, f32x4* with_mfma = nullptr,
+                                         const bf16x8* mw = nullptr, const bf16x8* mx = nullptr) const {
+    int voff = voffW[i];
+    if constexpr (KTAIL && !TB) voff |= tail_or & (step == k_steps - 1 ? -1 : 0);
+    const uint32_t to = lds + w_stage_off(stage) + i * 4096;
+    if (with_mfma != nullptr) mfma_then_load16_to_lds(*with_mfma, *mw, *mx, words, to, voff, step * stepW);
+    else load16_to_lds(words, to, voff, step * stepW);
+  }
+  // GATHER: pairs to offsets
+  __device__ __forceinline__ void gather_rows(const MfmaArgs& a) {
+    if constexpr (GATHER) {
+      int tid = threadIdx.x;
+      asm volatile("" : "+v"(tid));
+      const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+      const uint32_t n_pairs = (uint32_t)(a.gather_T * a.gather_k);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int chunk = (lane & 7) ^ swz((i * 4 + wave) * 8 + (lane >> 3));
+        const uint32_t pair = (uint32_t)voffX[i];
+        const bool ok = pair < n_pairs && (no_row >> i & 1) == 0;
+        voffX[i] = ok ? (int)((pair / (uint32_t)a.gather_k * (uint32_t)a.K + (uint32_t)chunk * 8u) * 2u) : (int)a_extent;
+      }
+    }
+  }
+  // Load l of the 32 of the first two K steps.
+  __device__ __forceinline__ void load_first(int l) const {
+    const int step = l / 16, i = l % 8;
+    if (l % 16 < 8) load_w(step, step, i, words_w(step));
+    else load_x(step, step, i, words_x(step));
+  }
+};
+constexpr int kFirstLoads = 32;  // of which the first half belong to step 0
+
+// Draws a workgroup's tiles.  Every XCD has a queue of tickets, its unit list's; a workgroup
+// starts with the ticket of its index in its own XCD's queue, draws the next ones with an atomic,
+// and once that queue is empty helps with the other XCDs' queues, of which it looks at the counters
+// first.  Atomics from all CUs on one line take their turns: with all counters in one line and a ticket
+// drawn past the end of every queue by every workgroup, the draws alone held the second GEMM at 80 us
+// and more however small it was.
+//
+// Wave 0 draws; the ticket goes to the other waves through LDS, and each looks its tile up by itself.
+struct Draws {
+  const UnitTable u;
+  const int per_xcd, xcd;
+  int q, tickets, units;  // the queue it draws from, tickets and units in it
+  int ticket, drawn;      // drawn: what the atomic returned (lane 0 of wave 0)
+  i32x4 rec[2];           // lane l: record `at` + l of queue q
+  int at;
+
+  __device__ __forceinline__ Draws(const UnitTable& table)
+      : u(table), per_xcd(gridDim.x / 8), xcd(blockIdx.x % 8) {  // workgroups are dealt round-robin to the 8 XCDs
+    set_queue(xcd);
+  }
+  static __device__ __forceinline__ bool mine() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x) == 0; }
+  __device__ __forceinline__ int* counter(int x) const { return u.header + kTicket + x * kLine; }
+  __device__ __forceinline__ void set_queue(int x) {
+    q = x;
+    tickets = __builtin_amdgcn_readfirstlane(u.header[x]);
+    units = __builtin_amdgcn_readfirstlane(u.header[8 + x]);
+  }
+  // asks for the next ticket of the queue
+  __device__ __forceinline__ void request() {
+    if (mine()) {
+      drawn = 0;
+      if (threadIdx.x == 0) drawn = atomicAdd(counter(q), 1);
+    }
+  }
+  // the ticket asked for, or one of another queue, -1 when no queue has one left, to `to` in LDS
+  __device__ __forceinline__ void publish(char* to) {
+    if (mine()) publish_ticket(per_xcd + __builtin_amdgcn_readfirstlane(drawn), to);
+  }
+  __device__ __forceinline__ void publish_ticket(int t, char* to) {
+    while (t >= tickets) {
+      // the first queue from this XCD's on with a ticket left (counters only grow: one that reads as empty is)
+      int taken[8], left = -1;
+#pragma unroll
+      for (int h = 0; h < 8; ++h) taken[h] = __hip_atomic_load(counter(h), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+      for (int h = 0; h < 8; ++h)
+        if (per_xcd + taken[h] < u.header[h] && (left < 0 || ((h - xcd) & 7) < ((left - xcd) & 7))) left = h;
+      left = __builtin_amdgcn_readfirstlane(left);
+      if (left < 0) {
+        t = -1;
+        break;
+      }
+      set_queue(left);
+      request();
+      t = per_xcd + __builtin_amdgcn_readfirstlane(drawn);
+    }
+    if (threadIdx.x == 0) *(int2*)to = int2{t, q};
+  }
+  // what was published goes to every wave, which loads the records the ticket may belong to
+  __device__ __forceinline__ void receive(const char* from) {
+    __syncthreads();
+    const int2 v = *(const int2*)from;
+    ticket = __builtin_amdgcn_readfirstlane(v.x);
+    const int from_q = __builtin_amdgcn_readfirstlane(v.y);
+    __syncthreads();  // the place may be written again
+    if (from_q != q) set_queue(from_q);
+    at = ticket < 0 ? 0 : ticket / (kGroupM * kGroupN);  // a unit has at most that many tiles
+    load_records();
+  }
+  __device__ __forceinline__ void load_records() {
+    const int i = at + (int)(threadIdx.x & 63), last = units > 0 ? units - 1 : 0;
+    const i32x4* const from = (const i32x4*)(u.records + ((size_t)q * u.cap + (i < last ? i : last)) * kRecord);
+    rec[0] = from[0];
+    rec[1] = from[1];
+    if (i > last) rec[0].x = 0x7FFFFFFF;
+  }
+  __device__ __forceinline__ Tile tile(int n_out_cols) {
+    if (ticket < 0) return Tile{-1, 0, 0, 0, 0, 0};
+    unsigned long long le;
+    while ((le = __ballot(rec[0].x <= ticket)) == ~0ull) {
+      at += 63;
+      load_records();
+    }
+    const int l = __popcll(le) - 1;  // the unit: the last that starts at or before the ticket
+    auto of = [&](int v) { return __builtin_amdgcn_readlane(v, l); };
+    const int within = ticket - of(rec[0].x), nr = of(rec[1].x) & 255;
+    const int col = within / nr;
+    return Tile{of(rec[0].y), of(rec[0].z) + (within - col * nr) * BM, of(rec[0].w), (of(rec[1].y) + col) * n_out_cols,
+                of(rec[1].z), of(rec[1].w)};
+  }
+};
+
+template <int EPI>
+constexpr int kOutCols = (EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_KEEP) ? BN / 2 : BN;
+
+// One output tile of 64*XF rows x 256 columns n of the weight operand W(n, k) ("weight rows"
+// below, whichever way W lies in memory).  XF = 32-row activation fragments per wave: the 2x2 waves each own (32*XF) x 128 of the tile, so a slot's ragged last tile costs
+// MFMAs and activation loads only for its rows rounded up to 64.
+//
+// ops: the tile's operands, whose first loads are under way.  The next tile is drawn while the last K steps run; its operands
+// go to ops and its first loads out within the epilogue.
 template <int EPI, int XF, int MODE, bool GATHER, bool KTAIL>
-__device__ __forceinline__ void gemm_tile(const MfmaArgs& a, char* smem, int slot, int row0, int row_end, int n0) {
+__device__ __forceinline__ Tile gemm_tile(const MfmaArgs& a, char* smem, const Tile tile, Operands<EPI, MODE, GATHER, KTAIL>& ops,
+                                          Draws& draws) {
   constexpr bool TA = MODE == MODE_TN || MODE == MODE_TN_WIDE, TB = MODE != MODE_NT;  // k-major left / right operand
   constexpr bool kGated = EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_KEEP;
   constexpr int KS = BK / 32;             // 32-wide MFMA slices per stage
   constexpr int kLoadsX = TA ? 8 : 2 * XF;  // 1-KiB wave loads per wave for the left tile (8 rows, or 2 k-rows, each)
   constexpr int kLoadsW = 8;              // ... for the 256-row weight tile
-  // The empty asm keeps the per-lane address arithmetic below inside the tile: hoisted out of
-  // the caller's tile loop it would be carried in registers through the whole kernel and spill.
   int tid = threadIdx.x;
-  asm volatile("" : "+v"(tid));
+  asm volatile("" : "+v"(tid));  // see Operands::set
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
-
-  // ---- buffer descriptors: out-of-range loads return zero instead of faulting.  The activation
-  // descriptor covers just this tile's rows, so 32-bit offsets do however large P is.
-  const int n_rows = row_end - row0 < BM ? row_end - row0 : BM;
-  int K = a.K;
-  const uint16_t* tileA;
-  const uint16_t* tileW;
-  uint32_t a_extent, w_extent;          // bytes the two descriptors cover
-  int stepA = BK * 2, stepW = BK * 2;   // bytes one K step advances in each operand
-  // MODE_TN, MODE_TN_WIDE: the contraction ends with the slot's last row, wherever in a K step that
-  // is, so the descriptors are rebuilt for every K step (base advanced by whole steps, extent =
-  // what is left of the slot); in 64-bit arithmetic where a slot's rows may cover more than 4 GiB
-  [[maybe_unused]] unsigned long long a_bytes = 0, w_bytes = 0, stepA64 = 0, stepW64 = 0;
-  if constexpr (TA) {
-    // The descriptors start at the slot's first row and this tile's first column and end with
-    // the slot's last row: the rows of the last, partial K step that belong to the next slot
-    // read as zero.
-    long long s0, s1;
-    clip_slot(a.slot_offsets, slot, a.k_rows, &s0, &s1);
-    // (the offsets are int32 values read through the vector memory path: tell the compiler that they are
-    // the same in every lane, the descriptors built from them are scalar operands)
-    s0 = __builtin_amdgcn_readfirstlane((int)s0);
-    K = __builtin_amdgcn_readfirstlane(int(s1 - s0));
-    const int m0 = row0 - slot * a.rows_per_slot;
-    tileA = a.A + (size_t)s0 * a.lda + m0;
-    tileW = a.W + (size_t)s0 * a.ldw + n0;
-    a_bytes = K > 0 ? ((unsigned long long)K * (unsigned)a.lda - (unsigned)m0) * 2ull : 0ull;
-    w_bytes = K > 0 ? ((unsigned long long)K * (unsigned)a.ldw - (unsigned)n0) * 2ull : 0ull;
-    stepA64 = 64ull * (unsigned)a.lda * 2ull;
-    stepW64 = 64ull * (unsigned)a.ldw * 2ull;
-    a_extent = (uint32_t)a_bytes;  // MODE_TN: the host checked that they fit; MODE_TN_WIDE: unused, see issue()
-    w_extent = (uint32_t)w_bytes;
-    stepA = 0;
-    stepW = 0;
-  } else if constexpr (MODE == MODE_NN) {
-    if constexpr (GATHER) {
-      tileA = a.A;  // the whole of x: a tile's rows lie anywhere in it (the host checked that it fits 32-bit offsets)
-      a_extent = (uint32_t)((unsigned long long)a.gather_T * (unsigned)K * 2ull);
-    } else {
-      tileA = a.A + (size_t)row0 * K;
-      a_extent = (uint32_t)n_rows * (uint32_t)K * 2u;
-    }
-    tileW = a.W + (size_t)slot * K * a.ldw;
-    w_extent = (uint32_t)K * (uint32_t)a.ldw * 2u;
-    stepW = 64 * a.ldw * 2;
-  } else {
-    tileA = a.A + (size_t)row0 * K;
-    a_extent = (uint32_t)n_rows * (uint32_t)K * 2u;
-    tileW = a.W + (size_t)slot * a.w_rows * K;
-    w_extent = (uint32_t)((unsigned long long)a.w_rows * K * 2);
-  }
-  const i32x4 wordsA = rsrc_words(tileA, a_extent), wordsB = rsrc_words(tileW, w_extent);
-  const i32x4 wordsNull = rsrc_words(a.A, 0);
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
-
-  // ---- per-lane global offsets of the direct-to-LDS loads of one stage.
-  // Load u of an operand tile fills LDS bytes [u*1024, u*1024+1024): 8 whole rows, lane l
-  // landing at row 8u + l/8, 16-byte chunk l%8.  That LDS chunk must hold logical chunk
-  // (l%8) ^ swz(row), so the lane fetches that one (the swizzle is applied on the global side
-  // because a direct-to-LDS load fixes the LDS side to lane order).
-  //
-  // k-major operand: load u fills two k-rows of 512 B, lane l landing at k-row 2u + l/32, 16-byte
-  // piece l%32, which must hold logical piece (l%32) ^ swz_kmajor(k-row).
-  auto voff_kmajor = [&](int i, int ld, int col0) {
-    const int kr = (wave * 8 + i) * 2 + (lane >> 5);
-    const int piece = (lane & 31) ^ swz_kmajor(kr);
-    return (int)(((uint32_t)kr * (uint32_t)ld + (uint32_t)col0 + (uint32_t)piece * 8u) * 2u);
-  };
-  int voffX[kLoadsX], voffW[kLoadsW];
-  // GATHER: the activation rows are looked up through the row map.  The index loads go out first
-  // and are waited for only after the first weight loads have been issued (further down), so
-  // their latency hides behind the weights' way from HBM.
-  [[maybe_unused]] int gidx[kLoadsX];
-  if constexpr (GATHER) {
-    const i32x4 wordsG = rsrc_words(a.gather + row0, (uint32_t)n_rows * 4u);
-#pragma unroll
-    for (int i = 0; i < kLoadsX; ++i) {
-      const int r = (wave * kLoadsX + i) * 8 + (lane >> 3);
-      const int ga = r < n_rows ? r : n_rows - 1;
-      asm volatile("buffer_load_dword %0, %1, %2, 0 offen" : "=v"(gidx[i]) : "v"(ga * 4), "s"(wordsG) : "memory");
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < kLoadsX; ++i) {
-    if constexpr (GATHER) {
-      voffX[i] = 0;  // set once the indices have arrived
-    } else if constexpr (TA) {
-      voffX[i] = voff_kmajor(i, a.lda, 0);  // columns past the operand's edge fetch its neighbours: never stored
-    } else {
-      const int r = (wave * kLoadsX + i) * 8 + (lane >> 3);
-      const int chunk = (lane & 7) ^ swz(r);
-      const int ga = r < n_rows ? r : n_rows - 1;  // rows past the tile's end repeat its last row (never stored)
-      voffX[i] = (int)(((uint32_t)ga * (uint32_t)K + (uint32_t)chunk * 8u) * 2u);
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < kLoadsW; ++i) {
-    if constexpr (TB && kGated) {
-      // k-major SwiGLU weights [K, 2 ffn]: 32-column fragments alternate gate and up columns
-      const int kr = (wave * 8 + i) * 2 + (lane >> 5);
-      const int piece = (lane & 31) ^ swz_kmajor(kr);
-      const int f = piece >> 2;
-      const int col = n0 + (f >> 1) * 32 + (piece & 3) * 8 + ((f & 1) ? a.up_row0 : 0);
-      voffW[i] = (int)(((uint32_t)kr * (uint32_t)a.ldw + (uint32_t)col) * 2u);
-    } else if constexpr (TB) {
-      voffW[i] = voff_kmajor(i, a.ldw, MODE == MODE_NN ? n0 : 0);
-    } else {
-      const int r = (wave * kLoadsW + i) * 8 + (lane >> 3);
-      const int chunk = (lane & 7) ^ swz(r);
-      int gb;
-      if (kGated) {
-        const int f = r >> 5;  // fragment index: even = gate rows, odd = up rows
-        gb = n0 + (f >> 1) * 32 + (r & 31) + ((f & 1) ? a.up_row0 : 0);
-      } else {
-        gb = n0 + r;
-      }
-      voffW[i] = (int)(((uint32_t)gb * (uint32_t)K + (uint32_t)chunk * 8u) * 2u);
-    }
-  }
-
-  // KTAIL: what the last K step ORs into the offsets of loads with even / odd i (swz of a load's rows
-  // depends on i only through its parity, the same for both operands)
-  [[maybe_unused]] int tail_or[2] = {0, 0};
-  if constexpr (KTAIL) {
-    const int k_left = K - (K - 1) / BK * BK;  // 1..64; multiples of 8, so chunks are whole
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-      tail_or[i] = ((lane & 7) ^ swz(i * 8 + (lane >> 3))) * 8 >= k_left ? (int)0x80000000 : 0;
-  }
+  const int row0 = tile.row0, row_end = tile.row_end, n0 = tile.n0;
 
   // ---- fragment read addresses.  A fragment is 16 rows (of the activation tile, or weight rows) x
   // the 32 k of a slice; lane l holds row l%16, the 8 consecutive k of chunk l/16 (the operand
@@ -571,44 +798,18 @@ __device__ __forceinline__ void gemm_tile(const MfmaArgs& a, char* smem, int slo
   // texture unit has accepted it, and the MFMA pipe with it.  The activation loads go out during
   // the unit after barrier kt (they must have landed by the next barrier); the weight loads, which
   // have a whole step longer, are spread over the three units that follow.
-  const int k_steps = (K + BK - 1) / BK;
+  const int k_steps = ops.k_steps;
   constexpr int kLoads = kLoadsW + kLoadsX;
-  // Loads [q0, q1) of a wave's 16 per step: the activation loads (q < kLoadsX) of K step a_step into
+  // Loads [q0, q1) of a wave's per step: the activation loads (q < kLoadsX) of K step a_step into
   // activation stage a_stage, the weight loads of K step w_step into weight stage w_stage.
   // with_mfma: an MFMA (accumulator, weight and activation fragment) to issue together with load q0
   auto issue = [&](int a_stage, int a_step, int w_stage, int w_step, int q0, int q1, f32x4* with_mfma = nullptr,
                    const bf16x8* mw = nullptr, const bf16x8* mx = nullptr) {
-    // a step past the end of K is "loaded" through a zero-length descriptor: no memory traffic
-    const bool real_a = a_step < k_steps, real_w = w_step < k_steps;
-    i32x4 wa = real_a ? wordsA : wordsNull, wb = real_w ? wordsB : wordsNull;
-    if constexpr (MODE == MODE_TN) {
-      const uint32_t offA = (uint32_t)a_step * (uint32_t)stepA64, offW = (uint32_t)w_step * (uint32_t)stepW64;
-      // bytes left of the slot: a step that begins inside the slot begins inside both extents (the
-      // tile's first column lies inside the operand's row)
-      const uint32_t leftA = real_a ? a_extent - offA : 0u, leftW = real_w ? w_extent - offW : 0u;
-      wa = rsrc_words((const char*)tileA + offA, leftA);
-      wb = rsrc_words((const char*)tileW + offW, leftW);
-    } else if constexpr (MODE == MODE_TN_WIDE) {
-      const unsigned long long offA = (unsigned long long)(unsigned)a_step * stepA64;
-      const unsigned long long offW = (unsigned long long)(unsigned)w_step * stepW64;
-      const unsigned long long leftA = a_bytes > offA ? a_bytes - offA : 0ull;
-      const unsigned long long leftW = w_bytes > offW ? w_bytes - offW : 0ull;
-      wa = rsrc_words((const char*)tileA + offA, leftA > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)leftA);
-      wb = rsrc_words((const char*)tileW + offW, leftW > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)leftW);
-    }
-    const uint32_t ldsX = lds0 + a_stage_off(a_stage), ldsW = lds0 + w_stage_off(w_stage);
 #pragma unroll
     for (int q = q0; q < q1; ++q) {
-      const bool isx = q < kLoadsX;
-      const i32x4 words = isx ? wa : wb;
-      const uint32_t lds = isx ? ldsX + (wave * kLoadsX + q) * 1024 : ldsW + (wave * kLoadsW + q - kLoadsX) * 1024;
-      int voff = isx ? voffX[q < kLoadsX ? q : 0] : voffW[q >= kLoadsX ? q - kLoadsX : 0];
-      if constexpr (KTAIL) {  // kLoadsX is even: a weight load's parity is that of q as well
-        if (isx ? !TA : !TB) voff |= tail_or[q & 1] & ((isx ? a_step : w_step) == k_steps - 1 ? -1 : 0);
-      }
-      const int soff = isx ? a_step * stepA : w_step * stepW;
-      if (with_mfma != nullptr && q == q0) mfma_then_load16_to_lds(*with_mfma, *mw, *mx, words, lds, voff, soff);
-      else load16_to_lds(words, lds, voff, soff);
+      f32x4* const mfma = q == q0 ? with_mfma : nullptr;
+      if (q < kLoadsX) ops.load_x(a_stage, a_step, q, ops.words_x(a_step), mfma, mw, mx);
+      else ops.load_w(w_stage, w_step, q - kLoadsX, ops.words_w(w_step), mfma, mw, mx);
     }
   };
   // A stage is consumed as four units: 32-wide slice s (0, 1) x half hw (0, 1) of the wave's weight
@@ -674,31 +875,12 @@ __device__ __forceinline__ void gemm_tile(const MfmaArgs& a, char* smem, int slo
   constexpr int kHalf = NA / 2;
 
   constexpr int D = kWStages;
-  if constexpr (GATHER) {
-    issue(0, 0, 0, 0, kLoadsX, kLoads);                  // the weight tile of step 0 does not need the row map
-    __builtin_amdgcn_s_waitcnt(0x0F70 | kLoadsW);        // vmcnt: the index loads (issued before those) are back
-    const uint32_t gk = (uint32_t)a.gather_k, n_pairs = (uint32_t)(a.gather_T * a.gather_k);
-#pragma unroll
-    for (int i = 0; i < kLoadsX; ++i) {
-      asm volatile("" : "+v"(gidx[i]));                  // nothing below may move above the wait
-      const int r = (wave * kLoadsX + i) * 8 + (lane >> 3);
-      const int chunk = (lane & 7) ^ swz(r);
-      const uint32_t pair = (uint32_t)gidx[i];
-      // a row without a pair (never inside a slot) reads past the descriptor's end: zeros
-      voffX[i] = pair < n_pairs ? (int)((pair / gk * (uint32_t)K + (uint32_t)chunk * 8u) * 2u) : (int)a_extent;
-    }
-    issue(0, 0, 0, 0, 0, kLoadsX);
-  } else {
-    issue(0, 0, 0, 0, 0, kLoads);
-  }
-  // in flight when the loop starts: the weights of step 1 and what the unit after a barrier issues
-  // (the activations of step 1); the units of step 0 issue the weight loads of step 2
-  constexpr int kAhead = kLoadsW + kAfterBarrier;
-  issue(1, 1, 1, 1, kLoadsX, kLoads);
-  issue(1, 1, 2, 2, 0, kAfterBarrier);
-  // s_waitcnt with only vmcnt set (bits [3:0] and [15:14]): the later steps' loads may still be in flight
+  // In flight when the tile starts: the first two steps' loads and behind them at least the stores of the previous
+  // epilogue's last pass (the first tile's caller has waited for all).  The units of step 0 issue the weight loads of
+  // step 2.  s_waitcnt with only vmcnt set (bits [3:0] and [15:14]).
+  constexpr int kAhead = kFirstLoads / 2 + kLastStores<EPI>;
   __builtin_amdgcn_s_waitcnt(0x0F70 | (kAhead & 15) | ((kAhead >> 4) << 14));
-  __syncthreads();
+  __syncthreads();  // ... everyone's are; and everyone has read its last patch
 #pragma unroll
   for (int r = 0; r < 4 + NA; ++r) read_r(r, 0, 0, 0, 0, 0, 0, 0, 0, NA, true);  // unit (0, 0) of stage 0
 
@@ -719,8 +901,13 @@ __device__ __forceinline__ void gemm_tile(const MfmaArgs& a, char* smem, int slo
     unit(1, 0, 1, wst, 1, 0, 0, as, 1, 1, kHalf, NA, false, as_next, kt + 1, wst_prev, kt - 1 + D, kL1, kL2);
     // unit (1, 0) runs; weight fragments of (1, 1): the last reads of this stage
     unit(0, 1, 0, wst, 1, 1, 1, as, 1, 1, 0, 0, false, as_next, kt + 1, wst_prev, kt - 1 + D, kL2, kLoads);
-    // this wave's loads of the next step are in LDS ...
-    __builtin_amdgcn_s_waitcnt(0x0F70 | kLoadsW);
+    // this wave's loads of the next step are in LDS (step 0: behind them lie the previous epilogue's last stores) ...
+    if (as == 0 && wst == 0 && kt == 0) {
+      constexpr int kNewer = kLoadsW + kLastStores<EPI>;
+      __builtin_amdgcn_s_waitcnt(0x0F70 | (kNewer & 15) | ((kNewer >> 4) << 14));
+    } else {
+      __builtin_amdgcn_s_waitcnt(0x0F70 | kLoadsW);
+    }
     __syncthreads();  // ... everyone's are; nobody reads these stages any more
     // unit (1, 1) runs; all of unit (0, 0) of the next step
     unit(1, 1, 1, wst_next, 0, 0, 0, as_next, 0, 0, 0, NA, true, as, kt + 2, wst, kt + D, 0, kAfterBarrier);
@@ -730,7 +917,7 @@ __device__ __forceinline__ void gemm_tile(const MfmaArgs& a, char* smem, int slo
     using I1 = std::integral_constant<int, 1>;
     using I2 = std::integral_constant<int, 2>;
     int kt = 0;
-    for (; kt + 5 < k_steps; kt += 6) {
+    for (; kt + 6 < k_steps; kt += 6) {  // one to six steps are left behind it
       k_step(kt, I0{}, I0{});
       k_step(kt + 1, I1{}, I1{});
       k_step(kt + 2, I0{}, I2{});
@@ -738,60 +925,106 @@ __device__ __forceinline__ void gemm_tile(const MfmaArgs& a, char* smem, int slo
       k_step(kt + 4, I0{}, I1{});
       k_step(kt + 5, I1{}, I2{});
     }
+    draws.request();  // of the next tile: the answer is there when the last steps are done
     if (kt < k_steps) k_step(kt, I0{}, I0{});
     if (kt + 1 < k_steps) k_step(kt + 1, I1{}, I1{});
     if (kt + 2 < k_steps) k_step(kt + 2, I0{}, I2{});
     if (kt + 3 < k_steps) k_step(kt + 3, I1{}, I0{});
     if (kt + 4 < k_steps) k_step(kt + 4, I0{}, I1{});
+    if (kt + 5 < k_steps) k_step(kt + 5, I1{}, I2{});
   }
   // the compiler does not know that the assembly above is MFMAs: keep their results away from the
   // VALU reads of the epilogue for the wait states such reads need (at most 18)
   asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
   // The trailing loads (steps past the end of K, zero-length descriptor) still write zeros into
-  // their stages, and each wave only waits for its own: one of those stages is activation stage 0,
-  // where the epilogue patches of the other waves lie.  Drain this wave's, then wait
+  // their stages, and each wave only waits for its own: the epilogue patches and the next tile's first stages
+  // lie there.  Drain this wave's, then wait
   // until every wave has drained its own, before anybody writes a patch.
+  char* const patch0 = smem + w_stage_off(2);
   __builtin_amdgcn_s_waitcnt(0x0F70);
-  __syncthreads();
+  draws.publish(patch0);  // into what only this wave's loads write
+  draws.receive(patch0);
 
   // ---- epilogue.  acc[i][j] is the 16x16 block (weight fragment i) x (activation fragment j);
   // lane l holds activation row j*16 + l%16 and the 4 consecutive weight rows i*16 + 4*(l/16) + 0..3
   // -> 4 consecutive output columns.  Stored straight from there, a wave store would touch 16
   // rows with 8 bytes each; such partial-line writes cost the second GEMM 10 % (timed with the
-  // stores removed).  So 32 rows at a time go through a per-wave LDS patch (the stages are dead by
-  // now; LDS serves a wave's accesses in order) and leave as 16 bytes per lane, whole 128-byte
+  // stores removed).  So 32 rows at a time go through a per-wave LDS patch and leave as 16 bytes per lane, whole 128-byte
   // lines at a time.
+  //
+  // The four patches fill weight stage 2, 8 KiB each; the other stages take the next tile's first loads meanwhile.  A
+  // patch row is 2 kWaveCols bytes, its 16-byte pieces XORed with the row: 16 rows at one column, or a row at 16
+  // columns, fall into different banks.
   constexpr int kWaveCols = kGated ? 64 : 128;             // output columns of this wave
-  constexpr int kPitch = kWaveCols * 2 + 16;               // patch row in bytes: 16-byte aligned, rows 4 banks apart
+  constexpr int kPitch = kWaveCols * 2;
   constexpr int kLanesPerRow = kWaveCols / 8;              // 16-byte pieces of a patch row
   constexpr int kRowsPerStore = 64 / kLanesPerRow;
-  char* const patch = smem + wave * (32 * kPitch);
+  char* const patch = patch0 + wave * 8192;
   const int quad = lane >> 4;
+  // Before pass kTurn of kPasses the next tile is looked up, and its first loads go out one by one within the writes to the
+  // patch of the last two passes (a burst of 32 holds the wave for 2600 to 4700 cycles, until the texture unit has taken it).
+  constexpr int kPerRows = EPI == EPI_SWIGLU_KEEP ? 3 : EPI == EPI_GELU_KEEP ? 2 : 1;  // passes over the same 32 rows
+  constexpr int kPasses = EPI == EPI_ACCUM ? 2 * XF : XF * kPerRows;
+  constexpr int kFeedPasses = kPasses < 2 ? 1 : 2, kFeed0 = kPasses - kFeedPasses;
+  constexpr int kTurn = kFeed0 - (GATHER && kFeed0 > 0 ? 1 : 0);
+  Tile next;
+  auto begin_pass = [&](int p) {
+    if (p == kTurn) {
+      next = draws.tile(kOutCols<EPI>);
+      ops.set(a, smem, next);
+    }
+    if (p == kFeed0) ops.gather_rows(a);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // after cell c of n of pass p's writes
+  auto feed = [&](int p, int c, int n) {
+    if (p < kFeed0) return;
+    constexpr int kEach = kFirstLoads / kFeedPasses;
+    const int l0 = (p - kFeed0) * kEach;
+#pragma unroll
+    for (int l = l0 + kEach * c / n; l < l0 + kEach * (c + 1) / n; ++l) ops.load_first(l);
+  };
+  // the accumulators of activation fragment j stay in their registers up to here (left alone, the compiler moves all 256
+  // into VGPRs when the K loop ends, and spills)
+  auto hold = [&](int j) {
+#pragma unroll
+    for (int i = 0; i < NW; ++i) asm volatile("" : "+a"(acc[i][j]));
+  };
+  const uint32_t n_rows = row_end - row0 < BM ? row_end - row0 : BM;
   // One pass of the 32 activation rows [32 jj, 32 jj + 32) through the patch: value(c, h, v) is the
   // number for patch row 16 h + l%16, patch column 16 c + 4 quad + v; the patch then leaves for
-  // dst[row, col0 + ...], columns from col_end on are not stored.
-  auto pass = [&](int jj, auto value, uint16_t* dst, int ld, int col0, int col_end) {
+  // dst[row, col0 + ...], columns from col_end on are not stored (nor rows past the tile's end: their offsets lie
+  // beyond the descriptor, so that a pass has the same number of stores everywhere).
+  auto pass = [&](int p, auto value, uint16_t* dst, int ld, int col0, int col_end) {
+    const int jj = p / kPerRows;
+    begin_pass(p);
+    hold(2 * jj);
+    hold(2 * jj + 1);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      char* const prow = patch + (16 * h + (lane & 15)) * kPitch;
+      const int r = 16 * h + (lane & 15);
 #pragma unroll
       for (int c = 0; c < kWaveCols / 16; ++c) {
         uint2 pk;
         pk.x = pack_bf16x2(value(c, h, 0), value(c, h, 1));
         pk.y = pack_bf16x2(value(c, h, 2), value(c, h, 3));
-        *(uint2*)(prow + (c * 16 + 4 * quad) * 2) = pk;
+        *(uint2*)(patch + r * kPitch + ((((2 * c) | (quad >> 1)) ^ (r & (kLanesPerRow - 1))) << 4) + (quad & 1) * 8) = pk;
+        feed(p, h * (kWaveCols / 16) + c, kWaveCols / 8);
       }
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // keep the patch writes before the reads below
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const auto buf = __builtin_amdgcn_make_buffer_rsrc((void*)(dst + (size_t)row0 * ld), 0, (int)(n_rows * (uint32_t)ld * 2u), 0x00020000);
+    const int lane_row = lane / kLanesPerRow, piece = lane % kLanesPerRow;
+    const int col = col0 + piece * 8;  // row lengths are multiples of 8
+    const uint32_t off = ((uint32_t)(wm * 32 * XF + lane_row) * (uint32_t)ld + (uint32_t)col) * 2u;
 #pragma unroll
     for (int t = 0; t < 32 / kRowsPerStore; ++t) {
-      const int r = t * kRowsPerStore + lane / kLanesPerRow, piece = lane % kLanesPerRow;
-      const uint4 v = *(const uint4*)(patch + r * kPitch + piece * 16);
-      const int row = row0 + wm * 32 * XF + jj * 32 + r;
-      const int col = col0 + piece * 8;  // row lengths are multiples of 8
-      if (row < row_end && col < col_end) *(uint4*)(dst + (size_t)row * ld + col) = v;
+      const int r = t * kRowsPerStore + lane_row;
+      const u32x4_t v = *(const u32x4_t*)(patch + r * kPitch + ((piece ^ (r & (kLanesPerRow - 1))) << 4));
+      const uint32_t at = off + (uint32_t)(jj * 32 + t * kRowsPerStore) * (uint32_t)ld * 2u;
+      __builtin_amdgcn_raw_buffer_store_b128(v, buf, (int)(col < col_end ? at : 0xFFFFFFF0u), 0, 0);
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // ... and the reads before the next pass's writes
     __builtin_amdgcn_wave_barrier();
@@ -800,49 +1033,50 @@ __device__ __forceinline__ void gemm_tile(const MfmaArgs& a, char* smem, int slo
   auto rounded = [](float v) { return __uint_as_float(pack_bf16x2(v, 0.f) << 16); };  // the bf16 value that is stored
   const int out0 = n0 + wn * kWaveCols;
   if constexpr (EPI == EPI_ACCUM) {
-    // fp32 read-modify-write of 32 rows x 128 columns at a time: through the patch into whole 512-byte runs of
-    // the fp32 matrix, whose old values are fetched one pass ahead.  HBM bound where slots are short: an optimizer
+    // fp32 read-modify-write of 16 rows x 128 columns at a time: through the patch into whole 512-byte runs of
+    // the fp32 matrix, whose old values are fetched two passes ahead.  HBM bound where slots are short: an optimizer
     // step of two micro-batches on 128 slots of 192 rows (d = 2048, ffn = 1408, SwiGLU; 17.7 GB of old and new
     // sums in the weight gradients) takes 8.4 ms, 12.0 ms with 32 x 32 blocks read only when they are added.
-    constexpr int kPitchF = 128 * 4 + 16;
-    constexpr int kRuns = 16;  // 16-byte pieces per lane and pass, two rows per wave access
-    char* const patchf = smem + wave * (32 * kPitchF);
+    constexpr int kRuns = 8;  // 16-byte pieces per lane and pass, two rows per wave access
     const int piece = lane & 31, col = n0 + wn * 128 + piece * 4;  // row lengths are multiples of 8
     const bool col_ok = col < a.n_out;
     f32x4* const base = (f32x4*)(a.Cacc + (col_ok ? col : 0));
-    auto row_of = [&](int jj, int t) { return row0 + wm * 32 * XF + jj * 32 + 2 * t + (lane >> 5); };
-    f32x4 old[2][kRuns];
-    auto fetch = [&](int jj) {  // pieces outside the tile fetch its last row or the row's first column: not stored
+    auto row_of = [&](int j, int t) { return row0 + wm * 32 * XF + j * 16 + 2 * t + (lane >> 5); };
+    f32x4 old[3][kRuns];
+    auto fetch = [&](int j) {  // pieces outside the tile fetch its last row or the row's first column: not stored
 #pragma unroll
       for (int t = 0; t < kRuns; ++t) {
-        const int row = row_of(jj, t);
-        old[jj & 1][t] = __builtin_nontemporal_load(base + (size_t)(row < row_end ? row : row_end - 1) * (a.n_out / 4));
+        const int row = row_of(j, t);
+        old[j % 3][t] = __builtin_nontemporal_load(base + (size_t)(row < row_end ? row : row_end - 1) * (a.n_out / 4));
       }
     };
     fetch(0);
+    fetch(1);
 #pragma unroll
-    for (int jj = 0; jj < XF; ++jj) {
-      if (jj + 1 < XF) fetch(jj + 1);
+    for (int j = 0; j < NA; ++j) {
+      begin_pass(j);
+      if (j + 2 < NA) fetch(j + 2);
+      hold(j);
+      const int r = lane & 15;
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        char* const prow = patchf + (16 * h + (lane & 15)) * kPitchF;
-#pragma unroll
-        for (int c = 0; c < NW; ++c) *(f32x4*)(prow + (16 * c + 4 * quad) * 4) = acc[c][2 * jj + h];
+      for (int c = 0; c < NW; ++c) {
+        *(f32x4*)(patch + r * 512 + (((4 * c + quad) ^ r) << 4)) = acc[c][j];
+        feed(j, c, NW);
       }
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
       for (int t = 0; t < kRuns; ++t) {
-        const f32x4 v = *(const f32x4*)(patchf + (2 * t + (lane >> 5)) * kPitchF + piece * 16);
-        const int row = row_of(jj, t);
-        if (row < row_end && col_ok) __builtin_nontemporal_store(old[jj & 1][t] + v, base + (size_t)row * (a.n_out / 4));
+        const int pr = 2 * t + (lane >> 5), row = row_of(j, t);
+        const f32x4 v = *(const f32x4*)(patch + pr * 512 + ((piece ^ pr) << 4));
+        if (row < row_end && col_ok) __builtin_nontemporal_store(old[j % 3][t] + v, base + (size_t)row * (a.n_out / 4));
       }
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
-    return;
+    return next;
   }
   // Gated weights: the tile's 32-column groups alternate gate and up columns, so of a wave's eight
   // 16-wide weight fragments 0, 1, 4, 5 are gate columns and i + 2 holds the up columns of the same
@@ -854,33 +1088,30 @@ __device__ __forceinline__ void gemm_tile(const MfmaArgs& a, char* smem, int slo
       pass(jj, [&](int c, int h, int v) { return silu_fast(acc[gate_frag(c)][2 * jj + h][v]) * acc[gate_frag(c) + 2][2 * jj + h][v]; },
            a.C, a.n_out, out0, a.n_out);
     } else if constexpr (EPI == EPI_SWIGLU_KEEP) {
-      pass(jj, [&](int c, int h, int v) { return acc[gate_frag(c)][2 * jj + h][v]; }, a.Z, a.z_cols, out0, a.n_out);
-      pass(jj, [&](int c, int h, int v) { return acc[gate_frag(c) + 2][2 * jj + h][v]; }, a.Z, a.z_cols, a.up_row0 + out0,
+      pass(3 * jj, [&](int c, int h, int v) { return acc[gate_frag(c)][2 * jj + h][v]; }, a.Z, a.z_cols, out0, a.n_out);
+      pass(3 * jj + 1, [&](int c, int h, int v) { return acc[gate_frag(c) + 2][2 * jj + h][v]; }, a.Z, a.z_cols, a.up_row0 + out0,
            a.up_row0 + a.n_out);
-      pass(jj, [&](int c, int h, int v) {
+      pass(3 * jj + 2, [&](int c, int h, int v) {
              return silu_fast(rounded(acc[gate_frag(c)][2 * jj + h][v])) * rounded(acc[gate_frag(c) + 2][2 * jj + h][v]);
            },
            a.C, a.n_out, out0, a.n_out);
     } else if constexpr (EPI == EPI_GELU_KEEP) {
-      pass(jj, [&](int c, int h, int v) { return acc[c][2 * jj + h][v]; }, a.Z, a.z_cols, out0, a.n_out);
-      pass(jj, [&](int c, int h, int v) { return gelu_fast(rounded(acc[c][2 * jj + h][v])); }, a.C, a.n_out, out0, a.n_out);
+      pass(2 * jj, [&](int c, int h, int v) { return acc[c][2 * jj + h][v]; }, a.Z, a.z_cols, out0, a.n_out);
+      pass(2 * jj + 1, [&](int c, int h, int v) { return gelu_fast(rounded(acc[c][2 * jj + h][v])); }, a.C, a.n_out, out0, a.n_out);
     } else if constexpr (EPI == EPI_GELU) {
       pass(jj, [&](int c, int h, int v) { return gelu_fast(acc[c][2 * jj + h][v]); }, a.C, a.n_out, out0, a.n_out);
     } else {
       pass(jj, [&](int c, int h, int v) { return acc[c][2 * jj + h][v]; }, a.C, a.n_out, out0, a.n_out);
     }
   }
+  return next;
 }
 
-// Persistent kernel: one workgroup per CU.  Every XCD has a queue of tiles (its unit list, up to 32
-// tile slots per unit: kGroupM row tiles of one slot x at most kGroupN column tiles); a workgroup
-// starts with the entry of its index in its own XCD's queue, draws the next ones with an atomic ticket,
-// and once that queue is empty helps with the other XCDs' queues, of which it looks at the counters
-// first.  Atomics from all CUs on one line take their turns: with all counters in one line and a ticket
-// drawn past the end of every queue by every workgroup, the draws alone held the second GEMM at 80 us
-// and more however small it was.  A forward of 64 tokens over 16 slots (d = 1024, ffn = 4096): 206 -> 151 us, a
-// training step of 40960 tokens, top-1 over 60 slots (d = 768, ffn = 3072): 1983 -> 1805 us, with the units'
-// columns cut evenly (d = 768: units of 3 columns where 5 of 8 entries used to be padding).
+// Persistent kernel: one workgroup per CU, whose matrix cores rest between two K loops.  What lies there is the draw of the
+// next tile, its first loads and the epilogue: 4000, 5500 and 7000 cycles one after the other (weight gradients of 60
+// slots of 680 rows, 768 x 3072, against 30500 of K loop), 13500 in all with the draw under the last K steps and
+// the loads within the epilogue.  That training step (40960 tokens, top-1) 1795 -> 1737 us, the headline layer's (8192
+// tokens, 4096 x 14336) 16350 -> 16090; both the texture unit's and the stores' paths are busy for half of the rest.
 // The 32 tiles an XCD works on at a time share
 // their activation and weight panels through that XCD's L2, and each XCD drains its queue at
 // its own pace.  (The hardware hands the workgroups of an ordinary launch to the XCDs strictly
@@ -890,74 +1121,29 @@ template <int EPI, int MODE, bool GATHER, bool KTAIL>
 __global__ __launch_bounds__(256, 1) void gemm_mfma_kernel(MfmaArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub, not the gfx950 builtins
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  constexpr int BN_OUT = (EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_KEEP) ? BN / 2 : BN;
-  const int xcd = blockIdx.x % 8;  // workgroups are dealt round-robin to the 8 XCDs
-  const int per_xcd = gridDim.x / 8;
-  const int n_col_groups = (a.n_tiles + kGroupN - 1) / kGroupN;
-  const int group_n = (a.n_tiles + n_col_groups - 1) / n_col_groups;  // equal column groups, few entries past the last tile
-  const int unit_tiles = kGroupM * group_n;
-  int* const counter = a.t.header + kTicket + 17 * kLine * a.which;
-  const int32_t* const count = a.t.header + kUnitCount + 16 * a.which;
-  // thread 0's next entry of queue q, -1 when no queue has one left
-  int q = xcd, home_entry = blockIdx.x / 8;
-  auto draw = [&]() {
-    if (home_entry >= 0) {
-      const int t = home_entry;
-      home_entry = -1;
-      if (t < count[q] * unit_tiles) return t;
-    }
-    for (;;) {
-      const int t = per_xcd + atomicAdd(counter + q * kLine, 1);
-      if (t < count[q] * unit_tiles) return t;
-      // the first queue from this XCD's on with an entry left (counters only grow: one that reads as empty is)
-      int drawn[8], left = -1;
+  Draws draws(a.u);
+  if (Draws::mine()) draws.publish_ticket(blockIdx.x / 8, smem);
+  draws.receive(smem);
+  Tile tile = draws.tile(kOutCols<EPI>);
+  Operands<EPI, MODE, GATHER, KTAIL> ops;
+  ops.set(a, smem, tile);
+  ops.gather_rows(a);
+  if (tile.slot >= 0) {
 #pragma unroll
-      for (int h = 0; h < 8; ++h) drawn[h] = __hip_atomic_load(counter + h * kLine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-      for (int h = 0; h < 8; ++h)
-        if (per_xcd + drawn[h] < count[h] * unit_tiles && (left < 0 || ((h - xcd) & 7) < ((left - xcd) & 7))) left = h;
-      if (left < 0) return -1;
-      q = left;
-    }
-  };
-  struct TileRows {
-    int slot, row0, row_end, n0;
-  };
-  for (;;) {
-    __syncthreads();  // the previous tile's fragment reads are done: LDS may be reused
-    if (threadIdx.x == 0) {
-      TileRows tile{-1, 0, 0, 0};
-      for (int t = draw(); t >= 0; t = draw()) {
-        const int unit = a.t.units[a.which][(size_t)q * a.t.unit_cap[a.which] + t / unit_tiles];
-        const int within = t % unit_tiles;
-        const int nt = (unit % n_col_groups) * group_n + within / kGroupM;
-        const int row_tile = (unit / n_col_groups) * kGroupM + within % kGroupM;
-        tile = TileRows{a.t.slot[row_tile], a.t.row0[row_tile], a.t.row_end[row_tile], nt * BN_OUT};
-        if (nt < a.n_tiles && tile.slot >= 0) break;  // else an entry that only pads a unit
-        tile.slot = -1;
-      }
-      volatile int* const to = (volatile int*)smem;
-      to[0] = tile.slot;
-      to[1] = tile.row0;
-      to[2] = tile.row_end;
-      to[3] = tile.n0;
-    }
-    __syncthreads();
-    const int slot = __builtin_amdgcn_readfirstlane(((volatile int*)smem)[0]);
-    const int row0 = __builtin_amdgcn_readfirstlane(((volatile int*)smem)[1]);
-    const int row_end = __builtin_amdgcn_readfirstlane(((volatile int*)smem)[2]);
-    const int n0 = __builtin_amdgcn_readfirstlane(((volatile int*)smem)[3]);
-    __syncthreads();
-    if (slot < 0) break;
-    const int rows = row_end - row0;  // > 0; more than 256 means a full tile
-    if (rows > 192) gemm_tile<EPI, 4, MODE, GATHER, KTAIL>(a, smem, slot, row0, row_end, n0);
-    else if (rows > 128) gemm_tile<EPI, 3, MODE, GATHER, KTAIL>(a, smem, slot, row0, row_end, n0);
-    else if (rows > 64) gemm_tile<EPI, 2, MODE, GATHER, KTAIL>(a, smem, slot, row0, row_end, n0);
-    else gemm_tile<EPI, 1, MODE, GATHER, KTAIL>(a, smem, slot, row0, row_end, n0);
+    for (int l = 0; l < kFirstLoads; ++l) ops.load_first(l);
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // no stores are behind them
   }
+  while (tile.slot >= 0) {
+    const int rows = tile.row_end - tile.row0;  // > 0; more than 256 means a full tile
+    if (rows > 192) tile = gemm_tile<EPI, 4, MODE, GATHER, KTAIL>(a, smem, tile, ops, draws);
+    else if (rows > 128) tile = gemm_tile<EPI, 3, MODE, GATHER, KTAIL>(a, smem, tile, ops, draws);
+    else if (rows > 64) tile = gemm_tile<EPI, 2, MODE, GATHER, KTAIL>(a, smem, tile, ops, draws);
+    else tile = gemm_tile<EPI, 1, MODE, GATHER, KTAIL>(a, smem, tile, ops, draws);
+  }
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // the loads of no tile are done with LDS
   // the last workgroup to finish leaves the counters at zero for the next launch on this table
-  if (threadIdx.x == 0 && atomicAdd(counter + (8 + xcd) * kLine, 1) == per_xcd - 1 && atomicAdd(counter + 16 * kLine, 1) == 7)
-    for (int i = 0; i < 17; ++i) counter[i * kLine] = 0;
+  if (threadIdx.x == 0 && atomicAdd(draws.counter(8 + draws.xcd), 1) == draws.per_xcd - 1 && atomicAdd(draws.counter(16), 1) == 7)
+    for (int i = 0; i < 17; ++i) *draws.counter(i) = 0;
 #endif
 }
 

@@ -52,3 +52,31 @@ def test_slots_of_few_and_of_many_tiles(dtype, d, counts):
     ref = (h[:, :, None] * w2.double()[slot]).sum(1)
     # the layer's bars: 1e-5 in fp32, 2e-2 of the largest value in bf16
     assert float((yp.double() - ref).abs().max()) <= (1e-5 if dtype == lz.LZ_F32 else 2e-2) * float(ref.abs().max())
+
+
+@pytest.mark.parametrize("counts", [
+    [(7 * i) % 41 for i in range(700)],                 # 350 units a list, of few tickets each
+    [0, 1029, 0, 0, 2048, 1, 255, 257, 0, 767],         # groups of 1 to 4 row tiles, some of one row
+    [1] + [0] * 62 + [3],                               # fewer tiles than workgroups: most find every list empty
+])
+def test_units_of_the_persistent_kernel(counts):
+    """Tickets of ragged units: every tile is drawn once, and leads to its own rows and columns."""
+    d, ffn, S = 264, 2600, len(counts)                  # 2 and 11 column tiles (one and two column groups)
+    P, c = sum(counts), next(c for c in range(64, 0, -1) if S % c == 0)
+    shape = lz.Shape(P, d, ffn, 1, 1, S // c, c, lz.LZ_BF16, lz.LZ_SWIGLU)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(S)
+    x, w1, w2 = (torch.randn(n, generator=gen, device=DEV).mul_(s).bfloat16()
+                 for n, s in (((P, d), 1), ((S, d, 2 * ffn), 0.1), ((S, ffn, d), 0.1)))
+    off = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    n = lz.lz_ffn_workspace_bytes(shape)
+    ws = torch.empty(n, dtype=torch.uint8, device=DEV)
+    out = [torch.full((P, d), 7.0, dtype=torch.bfloat16, device=DEV) for _ in range(2)]
+    for yp in out:                                      # the second call draws from lists of its own
+        lz.lz_expert_ffn(x, to_dev(off), w1, w2, shape, yp, ws, n)
+    assert torch.equal(out[0], out[1])
+    for s in np.flatnonzero(counts):
+        a, b = off[s], off[s + 1]
+        z = x[a:b].double() @ w1[s].double()
+        ref = (torch.nn.functional.silu(z[:, :ffn]) * z[:, ffn:]) @ w2[s].double()
+        assert float((out[0][a:b].double() - ref).abs().max()) <= 2e-2 * float(ref.abs().max())  # bf16 h and y
