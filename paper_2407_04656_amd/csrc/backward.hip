@@ -260,11 +260,11 @@ TrainWorkspace carve_train(void* ws, const lz_shape* s) {
   };
   w.dh = (uint16_t*)take((size_t)P * s->ffn * 2);
   w.dz = (uint16_t*)take((size_t)P * w.n1 * 2);
-  w.units_up = take(unit_table_bytes(P, S, BM, ceil_div(s->ffn, s->act == LZ_SWIGLU ? BN / 2 : BN)));
-  w.units_ffn = take(unit_table_bytes(P, S, BM, ceil_div(s->ffn, BN)));
-  w.units_d = take(unit_table_bytes(P, S, BM, ceil_div(s->d, BN)));
-  w.units_w2 = take(unit_table_bytes((long long)S * s->ffn, S, BM, ceil_div(s->d, BN)));
-  w.units_w1 = take(unit_table_bytes((long long)S * s->d, S, BM, ceil_div(w.n1, BN)));
+  w.units_up = take(unit_table_bytes(P, S, ceil_div(s->ffn, s->act == LZ_SWIGLU ? BN / 2 : BN)));
+  w.units_ffn = take(unit_table_bytes(P, S, ceil_div(s->ffn, BN)));
+  w.units_d = take(unit_table_bytes(P, S, ceil_div(s->d, BN)));
+  w.units_w2 = take(unit_table_bytes((long long)S * s->ffn, S, ceil_div(s->d, BN)));
+  w.units_w1 = take(unit_table_bytes((long long)S * s->d, S, ceil_div(w.n1, BN)));
   w.narrow_ffn = use_narrow(P, S, s->ffn);
   w.narrow_up = w.narrow_ffn && s->act == LZ_GELU;
   w.narrow_d = use_narrow(P, S, s->d);
@@ -398,11 +398,11 @@ extern "C" int32_t lz_ffn_forward_train(const void* xp, const int32_t* slot_offs
   const int S = shape->N * shape->c;
   const bool swiglu = shape->act == LZ_SWIGLU;
   const int n_up = ceil_div(shape->ffn, swiglu ? BN / 2 : BN);
-  const UnitTable u_up = carve_units(w.units_up, P, S, BM, n_up);
-  const UnitTable u_d = carve_units(w.units_d, P, S, BM, ceil_div(shape->d, BN));
+  const UnitTable u_up = carve_units(w.units_up, P, S, n_up);
+  const UnitTable u_d = carve_units(w.units_d, P, S, ceil_div(shape->d, BN));
   TileSpecs specs{};
-  if (!w.narrow_up) add_units(specs, BM, n_up, 0, P, u_up);
-  if (!w.narrow_d) add_units(specs, BM, ceil_div(shape->d, BN), 0, P, u_d);
+  if (!w.narrow_up) add_units(specs, n_up, 0, P, u_up);
+  if (!w.narrow_d) add_units(specs, ceil_div(shape->d, BN), 0, P, u_d);
   if (w.narrow_up || w.narrow_d) add_rows(specs, kNarrow, P, narrow_tiles(w, S, P));
   int32_t r = launch_build_tiles(slot_offsets, S, specs, st);
   if (r != LZ_OK) return r;
@@ -502,13 +502,13 @@ int32_t ffn_backward(const void* dyp, const void* xp, const void* z, const void*
 
   const int n_ffn = ceil_div(ffn, BN), n_d = ceil_div(d, BN), n_n1 = ceil_div(n1, BN);
   const long long rows_w2 = (long long)S * ffn, rows_w1 = (long long)S * d;
-  const UnitTable u_ffn = carve_units(w.units_ffn, P, S, BM, n_ffn), u_d = carve_units(w.units_d, P, S, BM, n_d);
-  const UnitTable u_w2 = carve_units(w.units_w2, rows_w2, S, BM, n_d), u_w1 = carve_units(w.units_w1, rows_w1, S, BM, n_n1);
+  const UnitTable u_ffn = carve_units(w.units_ffn, P, S, n_ffn), u_d = carve_units(w.units_d, P, S, n_d);
+  const UnitTable u_w2 = carve_units(w.units_w2, rows_w2, S, n_d), u_w1 = carve_units(w.units_w1, rows_w1, S, n_n1);
   TileSpecs specs{};
-  if (!w.narrow_ffn) add_units(specs, BM, n_ffn, 0, P, u_ffn);
-  if (!w.narrow_d) add_units(specs, BM, n_d, 0, P, u_d);
-  add_units(specs, BM, n_d, ffn, P, u_w2);
-  add_units(specs, BM, n_n1, d, P, u_w1);
+  if (!w.narrow_ffn) add_units(specs, n_ffn, 0, P, u_ffn);
+  if (!w.narrow_d) add_units(specs, n_d, 0, P, u_d);
+  add_units(specs, n_d, ffn, P, u_w2);
+  add_units(specs, n_n1, d, P, u_w1);
   if (w.narrow_ffn || w.narrow_d) add_rows(specs, kNarrow, P, narrow_tiles(w, S, P));
   int32_t r = launch_build_tiles(slot_offsets, S, specs, st);
   if (r != LZ_OK) return r;

@@ -42,11 +42,11 @@ struct FfnWorkspace {
 };
 
 UnitTable units_up_of(const FfnWorkspace& w, const lz_shape* s) {
-  return carve_units(w.units_up, (long long)s->T * s->k, s->N * s->c, BM, w.n_up);
+  return carve_units(w.units_up, (long long)s->T * s->k, s->N * s->c, w.n_up);
 }
 
 UnitTable units_down_of(const FfnWorkspace& w, const lz_shape* s) {
-  return carve_units(w.units_down, (long long)s->T * s->k, s->N * s->c, BM, w.n_down);
+  return carve_units(w.units_down, (long long)s->T * s->k, s->N * s->c, w.n_down);
 }
 
 TileTable narrow_tiles_of(const FfnWorkspace& w, const lz_shape* s) {
@@ -73,8 +73,8 @@ FfnWorkspace carve_ffn(void* ws, const lz_shape* s) {
   };
   w.hidden = take((size_t)P * s->ffn * lz::elem_bytes(s->dtype));
   if (mfma_sizes(s)) {
-    w.units_up = take(unit_table_bytes(P, S, BM, w.n_up));
-    w.units_down = take(unit_table_bytes(P, S, BM, w.n_down));
+    w.units_up = take(unit_table_bytes(P, S, w.n_up));
+    w.units_down = take(unit_table_bytes(P, S, w.n_down));
     w.tiles_narrow = take(tile_table_bytes(P, S, kNarrow));
   }
   if (!mfma_sizes(s) || !whole_tiles(s)) w.tiles_f32 = take(tile_table_bytes(P, S, kF32Rows));
@@ -113,8 +113,8 @@ extern "C" int32_t lz_ffn_tiles(const int32_t* slot_offsets, const lz_shape* sha
   const int S = shape->N * shape->c;
   TileSpecs specs{};
   if (mfma_shape(shape)) {
-    if (!w.narrow_up) add_units(specs, BM, w.n_up, 0, P, units_up_of(w, shape));
-    if (!w.narrow_down) add_units(specs, BM, w.n_down, 0, P, units_down_of(w, shape));
+    if (!w.narrow_up) add_units(specs, w.n_up, 0, P, units_up_of(w, shape));
+    if (!w.narrow_down) add_units(specs, w.n_down, 0, P, units_down_of(w, shape));
   }
   if (w.narrow_up || w.narrow_down) add_rows(specs, kNarrow, P, narrow_tiles_of(w, shape));
   // the calls that follow may bring unaligned tensors where that is allowed

@@ -71,7 +71,7 @@ inline TileTable carve_tiles(void* base, long long P, int S, int BM) {
 // to kGroupN column tiles; its tiles have consecutive tickets, so that a ticket leads to its tile by one look at the
 // list, and none is padding.
 struct UnitTable {
-  int32_t* header;   // [x] = tickets of XCD x's list, [8 + x] = its units, then, a line each, the counters below
+  int32_t* header;   // [x] = tickets of XCD x's list, [8 + x] = its units, [kTileRows], then, a line each, the counters below
   int32_t* records;  // 8 lists of `cap` records
   int cap, groups;   // room: records of a list, groups of row tiles in all
 };
@@ -80,18 +80,21 @@ struct UnitTable {
 constexpr int kRecord = 8;
 // Counters: header[kTicket + x * kLine] = tickets drawn from XCD x's list, x < 8;  x = 8..15: workgroups of XCD
 // x - 8 that have finished;  x = 16: XCDs that have finished
+constexpr int kTileRows = 16;  // rows of a tile
 constexpr int kTicket = 64;
 constexpr int kUnitHeader = kTicket + 17 * kLine;
 
-inline int unit_groups(long long P, int S, int BM) { return int(P / (BM * kGroupM) + S); }
-inline int unit_capacity(long long P, int S, int BM, int n_tiles) {
-  return int(((long long)unit_groups(P, S, BM) * ((n_tiles + kGroupN - 1) / kGroupN) + 7) / 8);
+// Room for tiles of the fewest rows that build_tiles_kernel chooses.
+constexpr int kLeastTileRows = 64;
+inline int unit_groups(long long P, int S) { return int(P / (kLeastTileRows * kGroupM) + S); }
+inline int unit_capacity(long long P, int S, int n_tiles) {
+  return int(((long long)unit_groups(P, S) * ((n_tiles + kGroupN - 1) / kGroupN) + 7) / 8);
 }
-inline size_t unit_table_bytes(long long P, int S, int BM, int n_tiles) {
-  return lz::align256(sizeof(int32_t) * (kUnitHeader + 8 * kRecord * (size_t)unit_capacity(P, S, BM, n_tiles)));
+inline size_t unit_table_bytes(long long P, int S, int n_tiles) {
+  return lz::align256(sizeof(int32_t) * (kUnitHeader + 8 * kRecord * (size_t)unit_capacity(P, S, n_tiles)));
 }
-inline UnitTable carve_units(void* base, long long P, int S, int BM, int n_tiles) {
-  return UnitTable{(int32_t*)base, (int32_t*)base + kUnitHeader, unit_capacity(P, S, BM, n_tiles), unit_groups(P, S, BM)};
+inline UnitTable carve_units(void* base, long long P, int S, int n_tiles) {
+  return UnitTable{(int32_t*)base, (int32_t*)base + kUnitHeader, unit_capacity(P, S, n_tiles), unit_groups(P, S)};
 }
 
 __device__ __forceinline__ void clip_slot(const int32_t* slot_offsets, int s, long long P, long long* a,
@@ -114,7 +117,7 @@ __device__ __forceinline__ void clip_slot(const int32_t* slot_offsets, int s, lo
 // within 2 % of this and costs a serial pass over the units; dealing the full row groups
 // first and the ragged ones last measured 1-5 % slower.)
 struct TileSpec {
-  int BM;            // rows of a tile
+  int rows_per_tile; // of row tiles; units choose theirs
   int n_tiles;       // column tiles; 0: row tiles for `rows`, else units for `units`
   int virtual_rows;  // > 0: every slot has this many rows (weight gradients)
   long long P;       // rows of the batch
@@ -125,24 +128,33 @@ struct TileSpecs {
   TileSpec spec[5];
   int n;
 };
-inline void add_rows(TileSpecs& specs, int BM, long long P, const TileTable& t) {
-  specs.spec[specs.n++] = TileSpec{BM, 0, 0, P, t, UnitTable{}};
+inline void add_rows(TileSpecs& specs, int rows, long long P, const TileTable& t) {
+  specs.spec[specs.n++] = TileSpec{rows, 0, 0, P, t, UnitTable{}};
 }
-inline void add_units(TileSpecs& specs, int BM, int n_tiles, int virtual_rows, long long P, const UnitTable& u) {
-  specs.spec[specs.n++] = TileSpec{BM, n_tiles, virtual_rows, P, TileTable{}, u};
+inline void add_units(TileSpecs& specs, int n_tiles, int virtual_rows, long long P, const UnitTable& u) {
+  specs.spec[specs.n++] = TileSpec{0, n_tiles, virtual_rows, P, TileTable{}, u};
 }
 
-// The unit lists: 32 threads a list, each a run of consecutive records; s_first: first group of every slot.
-__device__ __forceinline__ void deal_units(const int32_t* slot_offsets, int S, const TileSpec& spec, const int* s_first) {
+// The batch's rows of every slot, clipped, in LDS.
+struct SlotRows {
+  int first[lz::kMaxN * lz::kMaxC], end[lz::kMaxN * lz::kMaxC];
+};
+
+constexpr int kTileThreads = 512, kTileWaves = kTileThreads / lz::kWave;  // a wave per unit list
+
+// The unit lists: a wave each, every lane a run of consecutive records; s_first: first group of every slot.
+__device__ __forceinline__ void deal_units(const SlotRows& slots, int S, const TileSpec& spec, int rows_per_tile,
+                                           const int* s_first) {
   const int ncg = (spec.n_tiles + kGroupN - 1) / kGroupN;
   const int n_units = s_first[S] * ncg;
-  const int x = threadIdx.x >> 5, seg = threadIdx.x & 31;
+  const int x = threadIdx.x / lz::kWave, seg = threadIdx.x % lz::kWave;
+  static_assert(kTileWaves == 8, "one list per XCD");
   const int full = n_units / 8, count = full + (((full & 1) ? 7 - x : x) < n_units % 8 ? 1 : 0);
-  const int per = (count + 31) / 32, r0 = seg * per < count ? seg * per : count, r1 = r0 + per < count ? r0 + per : count;
+  const int per = (count + lz::kWave - 1) / lz::kWave, r0 = seg * per < count ? seg * per : count, r1 = r0 + per < count ? r0 + per : count;
   auto unit_of = [&](int r) { return r * 8 + ((r & 1) ? 7 - x : x); };
-  auto first_col = [&](int c) { return int((long long)c * spec.n_tiles / ncg); };  // equal column groups
+  const int cols = spec.n_tiles / ncg, more = spec.n_tiles % ncg;  // column groups of `cols`, the first `more` of one more
   int s_start = 0;
-  if (r0 < r1) {  // the last slot that starts at or before the first unit's group
+  if (r0 < r1 && S > 1) {  // the last slot that starts at or before the first unit's group
     const int g = unit_of(r0) / ncg;
     for (int hi = S - 1; s_start < hi;) {
       const int mid = (s_start + hi + 1) >> 1;
@@ -152,24 +164,22 @@ __device__ __forceinline__ void deal_units(const int32_t* slot_offsets, int S, c
   }
   int32_t* const list = spec.units.records + (size_t)x * spec.units.cap * kRecord;
   auto walk = [&](int ticket, bool write) {
-    int s = s_start, loaded = -1;
-    long long a = 0, b = 0, k0 = 0, k1 = 0;
+    int s = s_start;
     for (int r = r0; r < r1; ++r) {
       const int u = unit_of(r), g = u / ncg, c = u - g * ncg;
       while (s_first[s + 1] <= g) ++s;
-      if (s != loaded) {
-        loaded = s;
-        clip_slot(slot_offsets, s, spec.P, &k0, &k1);
-        a = spec.virtual_rows > 0 ? (long long)s * spec.virtual_rows : k0;
-        b = spec.virtual_rows > 0 ? a + spec.virtual_rows : k1;
-      }
-      const long long row0 = a + (long long)(g - s_first[s]) * (kGroupM * spec.BM);
-      const long long left = (b - row0 + spec.BM - 1) / spec.BM;
-      const int nr = left < kGroupM ? int(left) : kGroupM, c0 = first_col(c), nc = first_col(c + 1) - c0;
+      const int k0 = slots.first[s], k1 = slots.end[s];
+      const int a = spec.virtual_rows > 0 ? s * spec.virtual_rows : k0;
+      const int b = spec.virtual_rows > 0 ? a + spec.virtual_rows : k1;
+      const int row0 = a + (g - s_first[s]) * (kGroupM * rows_per_tile);
+      int nr = 1;  // of at most kGroupM row tiles
+#pragma unroll
+      for (int i = 1; i < kGroupM; ++i) nr += b - row0 > i * rows_per_tile ? 1 : 0;
+      const int nc = cols + (c < more ? 1 : 0);
       if (write) {
         i32x4* const to = (i32x4*)(list + (size_t)r * kRecord);
-        to[0] = i32x4{ticket, s, int(row0), int(b)};
-        to[1] = i32x4{nr | nc << 8, c0, int(k0), int(k1)};
+        to[0] = i32x4{ticket, s, row0, b};
+        to[1] = i32x4{nr | nc << 8, c * cols + (c < more ? c : more), k0, k1};
       }
       ticket += nr * nc;
     }
@@ -178,47 +188,87 @@ __device__ __forceinline__ void deal_units(const int32_t* slot_offsets, int S, c
   const int mine = walk(0, false);
   int incl = mine;
 #pragma unroll
-  for (int off = 1; off < 32; off <<= 1) {
-    const int n = __shfl_up(incl, off, 32);
+  for (int off = 1; off < lz::kWave; off <<= 1) {
+    const int n = __shfl_up(incl, off);
     if (seg >= off) incl += n;
   }
   walk(incl - mine, true);
-  if (seg == 31) {
+  if (seg == lz::kWave - 1) {
     spec.units.header[x] = incl;
     spec.units.header[8 + x] = count;
   }
+  if (threadIdx.x == 0) spec.units.header[kTileRows] = rows_per_tile;
   if (threadIdx.x < 17) spec.units.header[kTicket + threadIdx.x * kLine] = 0;
 }
 
+// Rows of the wide kernel's tiles, 256, 192, 128 or 64: those with which the launch ends first.  A launch of N tiles takes
+// ceil(N / workgroups) rounds, and a tile of fewer rows costs more than its share (it streams the same columns of W):
+// 100, 82, 65, 50 measured on K loops of 22 to 224 steps.  Where rounds are many 256 rows are the cheapest; with
+// 2.2 rounds of them (the down projection of 40960 tokens over 60 slots, 3072 x 768) 192 rows make 2.9 shorter ones:
+// that training step 1743 -> 1706 us, a forward of 3001 tokens (12 slots, 1000 x 2664, SwiGLU) 197 -> 186.
+// A row's result does not depend on the tile it is in.
+__device__ constexpr int kTileCost[5] = {0, 50, 65, 82, 100};  // by rows in 64s
+template <typename RowsOf>
+__device__ __forceinline__ int choose_tile_rows(int S, const TileSpec& spec, int workgroups, unsigned* s_sum, RowsOf rows_of) {
+  constexpr float kManyRounds = 16.f;
+  const float n_tiles = (float)spec.n_tiles, one_round = (float)workgroups;
+  if ((spec.virtual_rows > 0 ? (float)S * (float)spec.virtual_rows : (float)spec.P) / 256.f * n_tiles > kManyRounds * one_round) return 256;
+  // wave w sums over the slots: tiles (w < 4) or cost of tiles of 64 (w % 4 + 1) rows
+  const int lane = threadIdx.x % lz::kWave, wave = threadIdx.x / lz::kWave, h = 64 * (wave % 4 + 1);
+  static_assert(kTileWaves == 8, "a wave per sum");
+  unsigned sum = 0;
+  for (int s = lane; s < S; s += lz::kWave) {
+    const int rows = rows_of(s), full = rows / h, tail = (rows - full * h + 63) / 64;
+    sum += wave < 4 ? full + (tail > 0 ? 1 : 0) : full * kTileCost[wave % 4 + 1] + kTileCost[tail];
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+  if (lane == 0) s_sum[wave] = sum;
+  __syncthreads();
+  int best = 256;
+  float best_time = 0.f;
+#pragma unroll
+  for (int c = 3; c >= 0; --c) {
+    const float n = (float)s_sum[c], rounds = ceilf(n * n_tiles / one_round);
+    const float time = n > 0.f ? rounds * (float)s_sum[4 + c] / n : 0.f;
+    if (c == 3 || time < 0.95f * best_time) {
+      best = 64 * (c + 1);
+      best_time = time;
+    }
+  }
+  return best;
+}
+
 // One workgroup per table.
-__global__ __launch_bounds__(256) void build_tiles_kernel(const int32_t* __restrict__ slot_offsets, int S,
-                                                          TileSpecs specs) {
+__global__ __launch_bounds__(kTileThreads) void build_tiles_kernel(const int32_t* __restrict__ slot_offsets, int S,
+                                                          TileSpecs specs, int workgroups) {
+  __shared__ SlotRows slots;
   __shared__ int s_first[lz::kMaxN * lz::kMaxC + 1];
-  __shared__ int s_wave[4];
+  __shared__ int s_wave[kTileWaves];
+  __shared__ unsigned s_sum[kTileWaves];
   const TileSpec& spec = specs.spec[blockIdx.x];
   const TileTable t = spec.rows;
   const bool units = spec.n_tiles > 0;
-  const int BM = spec.BM, group_rows = units ? BM * kGroupM : BM;
   const int capacity = units ? spec.units.groups : t.capacity;
   const int tid = threadIdx.x, lane = tid % lz::kWave, wave = tid / lz::kWave;
-  auto slot_rows = [&](int s, long long* a, long long* b) {
-    if (spec.virtual_rows > 0) {
-      *a = (long long)s * spec.virtual_rows;
-      *b = *a + spec.virtual_rows;
-    } else {
-      clip_slot(slot_offsets, s, spec.P, a, b);
-    }
-  };
+  for (int s = tid; s < S; s += kTileThreads) {
+    long long a, b;
+    clip_slot(slot_offsets, s, spec.P, &a, &b);
+    slots.first[s] = int(a);
+    slots.end[s] = int(b);
+  }
+  __syncthreads();
+  auto rows_of = [&](int s) { return spec.virtual_rows > 0 ? spec.virtual_rows : slots.end[s] - slots.first[s]; };
+  const int rows = units ? choose_tile_rows(S, spec, workgroups, s_sum, rows_of) : spec.rows_per_tile;
+  const unsigned group_rows = units ? rows * kGroupM : rows;
   // tile or group count of every slot and its exclusive sum: each thread owns a run of consecutive slots.  The sums
   // end at the table's capacity, which the slots of ascending offsets stay within: offsets that fall again make
   // slots overlap, any number of tiles in all.
   auto add = [&](int x, int y) { return x + y < capacity ? x + y : capacity; };  // both at most capacity < 2^26
-  const int per = (S + 255) / 256, first = tid * per;
+  const int per = (S + kTileThreads - 1) / kTileThreads, first = tid * per;
   int mine = 0;
   for (int s = first; s < first + per && s < S; ++s) {
-    long long a, b;
-    slot_rows(s, &a, &b);
-    const int tiles = int((b - a + group_rows - 1) / group_rows);
+    const int tiles = int(((unsigned)rows_of(s) + group_rows - 1) / group_rows);
     s_first[s] = mine;
     mine = add(mine, tiles < capacity ? tiles : capacity);
   }
@@ -234,10 +284,10 @@ __global__ __launch_bounds__(256) void build_tiles_kernel(const int32_t* __restr
   int base = lane == 0 ? 0 : before;
   for (int w = 0; w < wave; ++w) base = add(base, s_wave[w]);
   for (int s = first; s < first + per && s < S; ++s) s_first[s] = add(s_first[s], base);
-  if (tid == 255) s_first[S] = add(base, mine);
+  if (tid == kTileThreads - 1) s_first[S] = add(base, mine);
   __syncthreads();
   if (units) {
-    deal_units(slot_offsets, S, spec, s_first);
+    deal_units(slots, S, spec, rows, s_first);
     return;
   }
   if (tid == 0) t.header[0] = s_first[S];
@@ -246,44 +296,33 @@ __global__ __launch_bounds__(256) void build_tiles_kernel(const int32_t* __restr
   // those together, slot after slot: 130 ns a slot and 64 entries a step.
   // 32-row tiles of 10^6 rows in 1, 4, 32, 128 slots: 1390, 867, 136, 64 us by the threads alone, 28, 29, 31, 31 us so.
   constexpr int kOwn = 64;
-  auto entry = [&](int i, int s, int first_i, long long a, long long b) {
-    const long long r0 = a + (long long)(i - first_i) * BM;
+  auto entry = [&](int i, int s, int first_i) {
     t.slot[i] = s;
-    t.row0[i] = int(r0 < b ? r0 : b);
-    t.row_end[i] = int(b);
+    t.row0[i] = slots.first[s] + (i - first_i) * rows;
+    t.row_end[i] = slots.end[s];
   };
   const bool few = s_first[S] <= 1024;
-  for (int i = tid; few && i < s_first[S]; i += 256) {
+  for (int i = tid; few && i < s_first[S]; i += kTileThreads) {
     int s = 0;
     for (int hi = S - 1; s < hi;) {  // the last slot that starts at or before i
       const int mid = (s + hi + 1) >> 1;
       if (s_first[mid] <= i) s = mid;
       else hi = mid - 1;
     }
-    long long a, b;
-    slot_rows(s, &a, &b);
-    entry(i, s, s_first[s], a, b);
+    entry(i, s, s_first[s]);
   }
-  for (int s0 = wave * lz::kWave; !few && s0 < S; s0 += 256) {  // the same trips in every lane
+  for (int s0 = wave * lz::kWave; !few && s0 < S; s0 += kTileThreads) {  // the same trips in every lane
     const int s = s0 + lane, from = s < S ? s_first[s] : 0, to = s < S ? s_first[s + 1] : 0;
-    long long a = 0, b = 0;
-    if (s < S) slot_rows(s, &a, &b);
     unsigned long long many = __ballot(to - from > kOwn);
     if (!__any(to - from > kOwn + 4 * __popcll(many))) many = 0;
     const int own_end = many && to - from > kOwn ? from + kOwn : to;
-    for (int i = from; i < own_end; ++i) entry(i, s, from, a, b);
+    for (int i = from; i < own_end; ++i) entry(i, s, from);
     for (; many; many &= many - 1) {
       const int l = __ffsll((long long)many) - 1;
       const int f = __shfl(from, l), end = __shfl(to, l);
-      const long long sa = __shfl(a, l), sb = __shfl(b, l);
-      for (int i = f + kOwn + lane; i < end; i += lz::kWave) entry(i, s0 + l, f, sa, sb);
+      for (int i = f + kOwn + lane; i < end; i += lz::kWave) entry(i, s0 + l, f);
     }
   }
-}
-
-inline int32_t launch_build_tiles(const int32_t* slot_offsets, int S, const TileSpecs& specs, hipStream_t st) {
-  hipLaunchKernelGGL(build_tiles_kernel, dim3(specs.n), dim3(256), 0, st, slot_offsets, S, specs);
-  return lz::launch_status();
 }
 
 // ------------------------------------------------------------------------------------------
@@ -412,8 +451,7 @@ __device__ __forceinline__ int swz(int row) { return (row >> 1) & 7; }
 // eight 32-byte runs fall into eight different bank groups.
 __device__ __forceinline__ int swz_kmajor(int kr) { return ((kr & 3) << 2) | (((kr >> 3) & 1) << 1); }
 
-// A tile: rows [row0, row_end) of a slot (row_end: the slot's end, at most 256 rows are the tile's), output columns from
-// n0; weight gradients: the rows [k0, k1) of the batch that the slot contracts over.  slot < 0: none.
+// A tile: rows [row0, row_end) of a slot, at most 256, output columns from n0; weight gradients: the rows [k0, k1) of the batch that the slot contracts over.  slot < 0: none.
 struct Tile {
   int slot, row0, row_end, n0, k0, k1;
 };
@@ -466,7 +504,7 @@ struct Operands {
     asm volatile("" : "+v"(tid));
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem + wave * 1024;
-    const int n_rows = t.row_end - t.row0 < BM ? t.row_end - t.row0 : BM;
+    const int n_rows = t.row_end - t.row0;
     int K = a.K;
     stepA = stepW = BK * 2;
     if constexpr (TA) {
@@ -631,14 +669,15 @@ constexpr int kFirstLoads = 32;  // of which the first half belong to step 0
 // Wave 0 draws; the ticket goes to the other waves through LDS, and each looks its tile up by itself.
 struct Draws {
   const UnitTable u;
-  const int per_xcd, xcd;
+  const int per_xcd, xcd, tile_rows;
   int q, tickets, units;  // the queue it draws from, tickets and units in it
   int ticket, drawn;      // drawn: what the atomic returned (lane 0 of wave 0)
   i32x4 rec[2];           // lane l: record `at` + l of queue q
   int at;
 
   __device__ __forceinline__ Draws(const UnitTable& table)
-      : u(table), per_xcd(gridDim.x / 8), xcd(blockIdx.x % 8) {  // workgroups are dealt round-robin to the 8 XCDs
+      : u(table), per_xcd(gridDim.x / 8), xcd(blockIdx.x % 8),  // workgroups are dealt round-robin to the 8 XCDs
+        tile_rows(__builtin_amdgcn_readfirstlane(table.header[kTileRows])) {
     set_queue(xcd);
   }
   static __device__ __forceinline__ bool mine() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x) == 0; }
@@ -708,7 +747,8 @@ struct Draws {
     auto of = [&](int v) { return __builtin_amdgcn_readlane(v, l); };
     const int within = ticket - of(rec[0].x), nr = of(rec[1].x) & 255;
     const int col = within / nr;
-    return Tile{of(rec[0].y), of(rec[0].z) + (within - col * nr) * BM, of(rec[0].w), (of(rec[1].y) + col) * n_out_cols,
+    const int row0 = of(rec[0].z) + (within - col * nr) * tile_rows, end = of(rec[0].w);
+    return Tile{of(rec[0].y), row0, end - row0 < tile_rows ? end : row0 + tile_rows, (of(rec[1].y) + col) * n_out_cols,
                 of(rec[1].z), of(rec[1].w)};
   }
 };
@@ -990,7 +1030,7 @@ __device__ __forceinline__ Tile gemm_tile(const MfmaArgs& a, char* smem, const T
 #pragma unroll
     for (int i = 0; i < NW; ++i) asm volatile("" : "+a"(acc[i][j]));
   };
-  const uint32_t n_rows = row_end - row0 < BM ? row_end - row0 : BM;
+  const uint32_t n_rows = row_end - row0;
   // One pass of the 32 activation rows [32 jj, 32 jj + 32) through the patch: value(c, h, v) is the
   // number for patch row 16 h + l%16, patch column 16 c + 4 quad + v; the patch then leaves for
   // dst[row, col0 + ...], columns from col_end on are not stored (nor rows past the tile's end: their offsets lie
@@ -1134,7 +1174,7 @@ __global__ __launch_bounds__(256, 1) void gemm_mfma_kernel(MfmaArgs a) {
     __builtin_amdgcn_s_waitcnt(0x0F70);  // no stores are behind them
   }
   while (tile.slot >= 0) {
-    const int rows = tile.row_end - tile.row0;  // > 0; more than 256 means a full tile
+    const int rows = tile.row_end - tile.row0;  // 1..256
     if (rows > 192) tile = gemm_tile<EPI, 4, MODE, GATHER, KTAIL>(a, smem, tile, ops, draws);
     else if (rows > 128) tile = gemm_tile<EPI, 3, MODE, GATHER, KTAIL>(a, smem, tile, ops, draws);
     else if (rows > 64) tile = gemm_tile<EPI, 2, MODE, GATHER, KTAIL>(a, smem, tile, ops, draws);
@@ -1161,6 +1201,13 @@ inline int device_cus() {
     cus_of_device[dev].store(cus, std::memory_order_release);
   }
   return cus;
+}
+
+inline int32_t launch_build_tiles(const int32_t* slot_offsets, int S, const TileSpecs& specs, hipStream_t st) {
+  const int workgroups = device_cus();  // of the wide kernel, below
+  if (workgroups == 0) return LZ_EHIP;
+  hipLaunchKernelGGL(build_tiles_kernel, dim3(specs.n), dim3(kTileThreads), 0, st, slot_offsets, S, specs, workgroups);
+  return lz::launch_status();
 }
 
 template <int EPI, int MODE, bool GATHER, bool KTAIL>

@@ -58,6 +58,9 @@ def test_slots_of_few_and_of_many_tiles(dtype, d, counts):
     [(7 * i) % 41 for i in range(700)],                 # 350 units a list, of few tickets each
     [0, 1029, 0, 0, 2048, 1, 255, 257, 0, 767],         # groups of 1 to 4 row tiles, some of one row
     [1] + [0] * 62 + [3],                               # fewer tiles than workgroups: most find every list empty
+    [683] * 60,                                         # tiles of 192 rows in the second GEMM (on 256 CUs)
+    [300, 301] * 15,                                    # of 128
+    [130] * 3,                                          # of 64
 ])
 def test_units_of_the_persistent_kernel(counts):
     """Tickets of ragged units: every tile is drawn once, and leads to its own rows and columns."""
