@@ -140,14 +140,14 @@ struct SlotRows {
   int first[lz::kMaxN * lz::kMaxC], end[lz::kMaxN * lz::kMaxC];
 };
 
-constexpr int kTileThreads = 512, kTileWaves = kTileThreads / lz::kWave;  // a wave per unit list
+constexpr int kTileThreads = 512, kTileWaves = kTileThreads / lz::kWave;  // of a table: a wave per unit list
 
 // The unit lists: a wave each, every lane a run of consecutive records; s_first: first group of every slot.
 __device__ __forceinline__ void deal_units(const SlotRows& slots, int S, const TileSpec& spec, int rows_per_tile,
-                                           const int* s_first) {
+                                           const int* s_first, int tid) {
   const int ncg = (spec.n_tiles + kGroupN - 1) / kGroupN;
   const int n_units = s_first[S] * ncg;
-  const int x = threadIdx.x / lz::kWave, seg = threadIdx.x % lz::kWave;
+  const int x = tid / lz::kWave, seg = tid % lz::kWave;
   static_assert(kTileWaves == 8, "one list per XCD");
   const int full = n_units / 8, count = full + (((full & 1) ? 7 - x : x) < n_units % 8 ? 1 : 0);
   const int per = (count + lz::kWave - 1) / lz::kWave, r0 = seg * per < count ? seg * per : count, r1 = r0 + per < count ? r0 + per : count;
@@ -197,8 +197,8 @@ __device__ __forceinline__ void deal_units(const SlotRows& slots, int S, const T
     spec.units.header[x] = incl;
     spec.units.header[8 + x] = count;
   }
-  if (threadIdx.x == 0) spec.units.header[kTileRows] = rows_per_tile;
-  if (threadIdx.x < 17) spec.units.header[kTicket + threadIdx.x * kLine] = 0;
+  if (tid == 0) spec.units.header[kTileRows] = rows_per_tile;
+  if (tid < 17) spec.units.header[kTicket + tid * kLine] = 0;
 }
 
 // Rows of the wide kernel's tiles, 256, 192, 128 or 64: those with which the launch ends first.  A launch of N tiles takes
@@ -208,13 +208,10 @@ __device__ __forceinline__ void deal_units(const SlotRows& slots, int S, const T
 // that training step 1743 -> 1706 us, a forward of 3001 tokens (12 slots, 1000 x 2664, SwiGLU) 197 -> 186.
 // A row's result does not depend on the tile it is in.
 __device__ constexpr int kTileCost[5] = {0, 50, 65, 82, 100};  // by rows in 64s
+// Of a table's 512 threads each wave leaves one sum in s_sum: tiles (wave w < 4) or cost of tiles of 64 (w % 4 + 1) rows.
 template <typename RowsOf>
-__device__ __forceinline__ int choose_tile_rows(int S, const TileSpec& spec, int workgroups, unsigned* s_sum, RowsOf rows_of) {
-  constexpr float kManyRounds = 16.f;
-  const float n_tiles = (float)spec.n_tiles, one_round = (float)workgroups;
-  if ((spec.virtual_rows > 0 ? (float)S * (float)spec.virtual_rows : (float)spec.P) / 256.f * n_tiles > kManyRounds * one_round) return 256;
-  // wave w sums over the slots: tiles (w < 4) or cost of tiles of 64 (w % 4 + 1) rows
-  const int lane = threadIdx.x % lz::kWave, wave = threadIdx.x / lz::kWave, h = 64 * (wave % 4 + 1);
+__device__ __forceinline__ void sum_tile_costs(int S, int tid, unsigned* s_sum, RowsOf rows_of) {
+  const int lane = tid % lz::kWave, wave = tid / lz::kWave, h = 64 * (wave % 4 + 1);
   static_assert(kTileWaves == 8, "a wave per sum");
   unsigned sum = 0;
   for (int s = lane; s < S; s += lz::kWave) {
@@ -224,7 +221,13 @@ __device__ __forceinline__ int choose_tile_rows(int S, const TileSpec& spec, int
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
   if (lane == 0) s_sum[wave] = sum;
-  __syncthreads();
+}
+__device__ __forceinline__ bool many_rounds(int S, const TileSpec& spec, int workgroups) {
+  const float rows = spec.virtual_rows > 0 ? (float)S * (float)spec.virtual_rows : (float)spec.P;
+  return rows / 256.f * (float)spec.n_tiles > 16.f * (float)workgroups;
+}
+__device__ __forceinline__ int choose_tile_rows(const TileSpec& spec, int workgroups, const unsigned* s_sum) {
+  const float n_tiles = (float)spec.n_tiles, one_round = (float)workgroups;
   int best = 256;
   float best_time = 0.f;
 #pragma unroll
@@ -239,27 +242,37 @@ __device__ __forceinline__ int choose_tile_rows(int S, const TileSpec& spec, int
   return best;
 }
 
-// One workgroup per table.
-__global__ __launch_bounds__(kTileThreads) void build_tiles_kernel(const int32_t* __restrict__ slot_offsets, int S,
-                                                          TileSpecs specs, int workgroups) {
+// Tables of units first, two a workgroup (side by side, 512 threads each), then those of row tiles, one a workgroup.
+__global__ __launch_bounds__(2 * kTileThreads) void build_tiles_kernel(const int32_t* __restrict__ slot_offsets, int S,
+                                                          TileSpecs specs, int n_units, int workgroups) {
   __shared__ SlotRows slots;
-  __shared__ int s_first[lz::kMaxN * lz::kMaxC + 1];
-  __shared__ int s_wave[kTileWaves];
-  __shared__ unsigned s_sum[kTileWaves];
-  const TileSpec& spec = specs.spec[blockIdx.x];
+  __shared__ int s_firsts[2][lz::kMaxN * lz::kMaxC + 1];
+  __shared__ int s_waves[2][kTileWaves];
+  __shared__ unsigned s_sums[2][kTileWaves];
+  const int half = threadIdx.x / kTileThreads, tid = threadIdx.x % kTileThreads;
+  const int unit_groups = (n_units + 1) / 2, b = blockIdx.x;
+  const int table = b < unit_groups ? 2 * b + half : b - unit_groups + n_units;
+  // a half without a table of its own follows the other's steps up to the barriers and writes nothing
+  const bool idle = b < unit_groups ? table >= n_units : half > 0;
+  const TileSpec& spec = specs.spec[idle ? (b < unit_groups ? 2 * b : table) : table];
+  int* const s_first = s_firsts[half];
+  int* const s_wave = s_waves[half];
   const TileTable t = spec.rows;
   const bool units = spec.n_tiles > 0;
   const int capacity = units ? spec.units.groups : t.capacity;
-  const int tid = threadIdx.x, lane = tid % lz::kWave, wave = tid / lz::kWave;
-  for (int s = tid; s < S; s += kTileThreads) {
+  const int lane = tid % lz::kWave, wave = tid / lz::kWave;
+  for (int s = threadIdx.x; s < S; s += blockDim.x) {
     long long a, b;
-    clip_slot(slot_offsets, s, spec.P, &a, &b);
+    clip_slot(slot_offsets, s, spec.P, &a, &b);  // the tables of a launch have one P
     slots.first[s] = int(a);
     slots.end[s] = int(b);
   }
   __syncthreads();
   auto rows_of = [&](int s) { return spec.virtual_rows > 0 ? spec.virtual_rows : slots.end[s] - slots.first[s]; };
-  const int rows = units ? choose_tile_rows(S, spec, workgroups, s_sum, rows_of) : spec.rows_per_tile;
+  const bool choose = units && !many_rounds(S, spec, workgroups);
+  if (choose) sum_tile_costs(S, tid, s_sums[half], rows_of);
+  __syncthreads();
+  const int rows = !units ? spec.rows_per_tile : choose ? choose_tile_rows(spec, workgroups, s_sums[half]) : 256;
   const unsigned group_rows = units ? rows * kGroupM : rows;
   // tile or group count of every slot and its exclusive sum: each thread owns a run of consecutive slots.  The sums
   // end at the table's capacity, which the slots of ascending offsets stay within: offsets that fall again make
@@ -286,8 +299,9 @@ __global__ __launch_bounds__(kTileThreads) void build_tiles_kernel(const int32_t
   for (int s = first; s < first + per && s < S; ++s) s_first[s] = add(s_first[s], base);
   if (tid == kTileThreads - 1) s_first[S] = add(base, mine);
   __syncthreads();
+  if (idle) return;
   if (units) {
-    deal_units(slots, S, spec, rows, s_first);
+    deal_units(slots, S, spec, rows, s_first, tid);
     return;
   }
   if (tid == 0) t.header[0] = s_first[S];
@@ -1206,7 +1220,10 @@ inline int device_cus() {
 inline int32_t launch_build_tiles(const int32_t* slot_offsets, int S, const TileSpecs& specs, hipStream_t st) {
   const int workgroups = device_cus();  // of the wide kernel, below
   if (workgroups == 0) return LZ_EHIP;
-  hipLaunchKernelGGL(build_tiles_kernel, dim3(specs.n), dim3(kTileThreads), 0, st, slot_offsets, S, specs, workgroups);
+  int n_units = 0;
+  while (n_units < specs.n && specs.spec[n_units].n_tiles > 0) ++n_units;
+  hipLaunchKernelGGL(build_tiles_kernel, dim3((n_units + 1) / 2 + specs.n - n_units), dim3(n_units > 1 ? 2 * kTileThreads : kTileThreads),
+                     0, st, slot_offsets, S, specs, n_units, workgroups);
   return lz::launch_status();
 }
 
