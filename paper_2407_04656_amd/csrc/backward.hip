@@ -507,8 +507,8 @@ int32_t ffn_backward(const void* dyp, const void* xp, const void* z, const void*
   TileSpecs specs{};
   if (!w.narrow_ffn) add_units(specs, n_ffn, 0, P, u_ffn);
   if (!w.narrow_d) add_units(specs, n_d, 0, P, u_d);
-  add_units(specs, n_d, ffn, P, u_w2);
-  add_units(specs, n_n1, d, P, u_w1);
+  add_units(specs, n_d, ffn, P, u_w2, accumulate);
+  add_units(specs, n_n1, d, P, u_w1, accumulate);
   if (w.narrow_ffn || w.narrow_d) add_rows(specs, kNarrow, P, narrow_tiles(w, S, P));
   int32_t r = launch_build_tiles(slot_offsets, S, specs, st);
   if (r != LZ_OK) return r;

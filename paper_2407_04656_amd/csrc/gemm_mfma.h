@@ -120,6 +120,7 @@ struct TileSpec {
   int rows_per_tile; // of row tiles; units choose theirs
   int n_tiles;       // column tiles; 0: row tiles for `rows`, else units for `units`
   int virtual_rows;  // > 0: every slot has this many rows (weight gradients)
+  bool skip_empty;   // those of slots without rows of the batch have no units: nothing is added to their sums
   long long P;       // rows of the batch
   TileTable rows;
   UnitTable units;
@@ -129,10 +130,10 @@ struct TileSpecs {
   int n;
 };
 inline void add_rows(TileSpecs& specs, int rows, long long P, const TileTable& t) {
-  specs.spec[specs.n++] = TileSpec{rows, 0, 0, P, t, UnitTable{}};
+  specs.spec[specs.n++] = TileSpec{rows, 0, 0, false, P, t, UnitTable{}};
 }
-inline void add_units(TileSpecs& specs, int n_tiles, int virtual_rows, long long P, const UnitTable& u) {
-  specs.spec[specs.n++] = TileSpec{0, n_tiles, virtual_rows, P, TileTable{}, u};
+inline void add_units(TileSpecs& specs, int n_tiles, int virtual_rows, long long P, const UnitTable& u, bool skip_empty = false) {
+  specs.spec[specs.n++] = TileSpec{0, n_tiles, virtual_rows, skip_empty, P, TileTable{}, u};
 }
 
 // The batch's rows of every slot, clipped, in LDS.
@@ -268,7 +269,12 @@ __global__ __launch_bounds__(2 * kTileThreads) void build_tiles_kernel(const int
     slots.end[s] = int(b);
   }
   __syncthreads();
-  auto rows_of = [&](int s) { return spec.virtual_rows > 0 ? spec.virtual_rows : slots.end[s] - slots.first[s]; };
+  // Without skip_empty the sums of empty slots are read and written back: two micro-batches of 50 rows on 90 slots,
+  // 768 x 1792, 1423 us a step, 927 with it.
+  auto rows_of = [&](int s) {
+    const int own = slots.end[s] - slots.first[s];
+    return spec.virtual_rows > 0 && (own > 0 || !spec.skip_empty) ? spec.virtual_rows : own;
+  };
   const bool choose = units && !many_rounds(S, spec, workgroups);
   if (choose) sum_tile_costs(S, tid, s_sums[half], rows_of);
   __syncthreads();
