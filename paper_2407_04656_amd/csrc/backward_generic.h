@@ -4,7 +4,7 @@
 // to the tensor type; the fp32 path uses erff / expf so that it meets the fp32 error bar.
 // Device code, not part of the C ABI; included by backward.hip.
 #pragma once
-#include "gemm_f32.h"
+#include "gemm_split.h"
 
 namespace {
 
@@ -54,12 +54,13 @@ __global__ __launch_bounds__(256) void reduce_replicas_generic_kernel(const Elem
 struct GenericTrainWorkspace {
   void* dz;     // [P, n1]
   void* tiles;  // kF32Rows-row tiles of the batch
+  void* tiles_split;  // fp32: kSplitRows-row tiles
   size_t total_bytes;
   int n1;
 };
 
 inline GenericTrainWorkspace carve_train_generic(void* ws, const lz_shape* s) {
-  GenericTrainWorkspace w;
+  GenericTrainWorkspace w{};
   const long long P = (long long)s->T * s->k;
   w.n1 = s->ffn * (s->act == LZ_SWIGLU ? 2 : 1);
   char* p = (char*)ws;
@@ -70,16 +71,22 @@ inline GenericTrainWorkspace carve_train_generic(void* ws, const lz_shape* s) {
   };
   w.dz = take((size_t)P * w.n1 * lz::elem_bytes(s->dtype));
   w.tiles = take(tile_table_bytes(P, s->N * s->c, kF32Rows));
+  if (s->dtype == LZ_F32) w.tiles_split = take(tile_table_bytes(P, s->N * s->c, kSplitRows));
   w.total_bytes = size_t(p - (char*)ws);
   return w;
 }
 
-inline TileTable generic_tiles(const int32_t* slot_offsets, int S, long long P, const GenericTrainWorkspace& w, hipStream_t st) {
+// The tables of a GEMM's arguments; `split`: that of the 64-row tiles too.
+inline void generic_tiles(F32Args& a, const int32_t* slot_offsets, int S, long long P, const GenericTrainWorkspace& w,
+                          bool split, hipStream_t st) {
   TileSpecs specs{};
-  const TileTable t = carve_tiles(w.tiles, P, S, kF32Rows);
-  add_rows(specs, kF32Rows, P, t);
+  a.t = carve_tiles(w.tiles, P, S, kF32Rows);
+  add_rows(specs, kF32Rows, P, a.t);
+  if (split) {
+    a.t_split = carve_tiles(w.tiles_split, P, S, kSplitRows);
+    add_rows(specs, kSplitRows, P, a.t_split);
+  }
   launch_build_tiles(slot_offsets, S, specs, st);
-  return t;
 }
 
 template <typename Elem>
@@ -90,7 +97,7 @@ int32_t generic_forward_train(const void* xp, const int32_t* slot_offsets, const
   const int S = s->N * s->c, d = s->d, ffn = s->ffn, n1 = w.n1;
   // z = xp W1 and h = act(z) from one epilogue   (W1[s] = [d, n1])
   F32Args a{};
-  a.t = generic_tiles(slot_offsets, S, P, w, st);
+  generic_tiles(a, slot_offsets, S, P, w, split_forward(s), st);
   a.A = xp;
   a.W = w1;
   a.C = h;
@@ -105,6 +112,7 @@ int32_t generic_forward_train(const void* xp, const int32_t* slot_offsets, const
   // yp = h W2   (W2[s] = [ffn, d])
   F32Args b{};
   b.t = a.t;
+  b.t_split = a.t_split;
   b.A = h;
   b.W = w2;
   b.C = yp;
@@ -125,7 +133,7 @@ int32_t generic_ffn_backward(const void* dyp, const void* xp, const void* z, con
   if (P > 0) {
     // dZ = (dyp W2^T) * act'(Z): W2[s] [ffn, d] along its rows
     F32Args a{};
-    a.t = generic_tiles(slot_offsets, S, P, w, st);
+    generic_tiles(a, slot_offsets, S, P, w, false, st);  // the data gradients stay on the 32-row tiles
     a.A = dyp;
     a.W = w2;
     a.C = w.dz;

@@ -11,7 +11,7 @@
 // bf16 path: the MFMA kernel of gemm_mfma.h.
 //
 // fp32 tensors, and bf16 rows that are no whole 16-byte pieces: the fp32 matrix-core kernel of gemm_f32.h.
-#include "gemm_f32.h"
+#include "gemm_split.h"
 #include "gemm_narrow.h"
 
 namespace {
@@ -36,6 +36,7 @@ struct FfnWorkspace {
   void* units_down;
   void* tiles_narrow;  // of the GEMMs on narrow tiles
   void* tiles_f32;     // of the fp32 kernel
+  void* tiles_split;   // of the split fp32 kernel
   size_t total_bytes;
   int n_up, n_down;    // column tiles of the two wide GEMMs
   bool narrow_up, narrow_down;  // GEMMs on narrow tiles
@@ -55,6 +56,10 @@ TileTable narrow_tiles_of(const FfnWorkspace& w, const lz_shape* s) {
 
 TileTable f32_tiles_of(const FfnWorkspace& w, const lz_shape* s) {
   return carve_tiles(w.tiles_f32, (long long)s->T * s->k, s->N * s->c, kF32Rows);
+}
+
+TileTable split_tiles_of(const FfnWorkspace& w, const lz_shape* s) {
+  return carve_tiles(w.tiles_split, (long long)s->T * s->k, s->N * s->c, kSplitRows);
 }
 
 // Every table that some number of tokens of the same layer uses has its room, so that a workspace made for the
@@ -78,6 +83,7 @@ FfnWorkspace carve_ffn(void* ws, const lz_shape* s) {
     w.tiles_narrow = take(tile_table_bytes(P, S, kNarrow));
   }
   if (!mfma_sizes(s) || !whole_tiles(s)) w.tiles_f32 = take(tile_table_bytes(P, S, kF32Rows));
+  if (s->dtype == LZ_F32) w.tiles_split = take(tile_table_bytes(P, S, kSplitRows));
   w.narrow_up = mfma_shape(s) && s->act == LZ_GELU && use_narrow(P, S, s->ffn);
   w.narrow_down = mfma_shape(s) && use_narrow(P, S, s->d);
   w.total_bytes = size_t(p - (char*)ws);
@@ -119,6 +125,7 @@ extern "C" int32_t lz_ffn_tiles(const int32_t* slot_offsets, const lz_shape* sha
   if (w.narrow_up || w.narrow_down) add_rows(specs, kNarrow, P, narrow_tiles_of(w, shape));
   // the calls that follow may bring unaligned tensors where that is allowed
   if (!mfma_shape(shape) || !whole_tiles(shape)) add_rows(specs, kF32Rows, P, f32_tiles_of(w, shape));
+  if (split_forward(shape)) add_rows(specs, kSplitRows, P, split_tiles_of(w, shape));
   return launch_build_tiles(slot_offsets, S, specs, (hipStream_t)stream);
 }
 
@@ -149,6 +156,7 @@ int32_t ffn_up(const void* xp, const int32_t* gather, const void* w1, const lz_s
     a.w_slot = (long long)shape->d * n1;
     a.ldc = a.n_out = a.ffn = shape->ffn;
     a.t = f32_tiles_of(w, shape);
+    a.t_split = split_tiles_of(w, shape);
     a.gather = gather;
     a.gather_k = gk;
     a.gather_T = gT;
@@ -217,6 +225,7 @@ extern "C" int32_t lz_ffn_down(const void* w2, const lz_shape* shape, void* yp, 
     a.w_slot = (long long)shape->ffn * shape->d;
     a.ldw = a.ldc = a.n_out = shape->d;
     a.t = f32_tiles_of(w, shape);
+    a.t_split = split_tiles_of(w, shape);
     const int S = shape->N * shape->c;
     return shape->dtype == LZ_F32 ? launch_f32_rows<float, EPI_NONE, true>(a, S, P, st)
                                   : launch_f32_rows<uint16_t, EPI_NONE, true>(a, S, P, st);

@@ -1,5 +1,6 @@
 // Grouped GEMM with fp32 products on the gfx950 matrix cores (v_mfma_f32_16x16x4_f32): fp32 tensors, and the
-// bf16 tensors the kernel of gemm_mfma.h cannot load (rows or pointers that are no whole 16-byte pieces).
+// bf16 tensors the kernel of gemm_mfma.h cannot load (rows or pointers that are no whole 16-byte pieces).  Large fp32
+// forwards and weight gradients run on the kernel of gemm_split.h.
 // Device code shared by the forward and the backward, not part of the C ABI.
 //
 //   C[rows of a slot, n] = epi( sum_k A(row, k) * W[slot](n, k) )      rows and W, or a slot's k range, ragged
@@ -39,7 +40,7 @@ struct F32Args {
   int n_tiles;          // column tiles
   int slots, m_tiles;   // weight gradients: row tiles of a slot's result
   int ffn;              // gated epilogues: columns between the gate and the up half
-  TileTable t;
+  TileTable t, t_split;  // of the kernel here; of gemm_split.h
   const int32_t* gather;  // row r of A is row gather[r] / gather_k (forward's first GEMM), or nullptr
   int gather_k;
   long long gather_T;
@@ -104,6 +105,55 @@ __device__ __forceinline__ void store_piece(Elem* p, const f32x4& v, int n) {
     for (int j = 0; j < 4; ++j)
       if (j < n) store_elem<Elem>(p + j, v[j]);
   }
+}
+
+// Epilogue on 4 consecutive columns of one row.  col is the result column; gated: v and u belong to it.
+template <typename Elem, int EPI, bool WGRAD, bool VEC>
+__device__ __forceinline__ void f32_emit(const F32Args& a, int slot, int row, int row_end, int col, const f32x4& v,
+                                         const f32x4& u) {
+  constexpr bool kGated = EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_KEEP;
+  const int n = row < row_end ? a.n_out - col : 0;
+  const size_t grow = WGRAD ? (size_t)slot * a.m_rows + row : (size_t)row;
+  if (n <= 0) return;
+  Elem* const c = (Elem*)a.C + grow * a.ldc + col;
+  if constexpr (EPI == EPI_ACCUM) {
+    float* const s = a.Cacc + grow * a.ldc + col;
+    store_piece<float, VEC>(s, load_piece<float, VEC>(s, a.Cacc, n) + v, n);
+    return;
+  }
+  if constexpr (EPI == EPI_GELU_KEEP || EPI == EPI_SWIGLU_KEEP) {
+    Elem* const z = (Elem*)a.Z + grow * a.ldz + col;
+    store_piece<Elem, VEC>(z, v, n);
+    if constexpr (kGated) store_piece<Elem, VEC>(z + a.ffn, u, n);
+  }
+  f32x4 o = v, o2;
+  if constexpr (EPI == EPI_DGELU || EPI == EPI_DSWIGLU) {
+    const Elem* const z = (const Elem*)a.Z + grow * a.ldz + col;
+    const f32x4 zg = load_piece<Elem, VEC>(z, (const Elem*)a.Z, n);
+    if constexpr (EPI == EPI_DGELU) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) o[j] = v[j] * gelu_grad_exact(zg[j]);
+    } else {
+      const f32x4 zu = load_piece<Elem, VEC>(z + a.ffn, (const Elem*)a.Z, n);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float sg = sigmoid_exact(zg[j]);
+        o[j] = v[j] * zu[j] * (sg * fmaf(zg[j], 1.0f - sg, 1.0f));
+        o2[j] = v[j] * (zg[j] * sg);
+      }
+      store_piece<Elem, VEC>(c + a.ffn, o2, n);
+    }
+  } else if constexpr (EPI == EPI_GELU || EPI == EPI_GELU_KEEP) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) o[j] = gelu_exact(EPI == EPI_GELU ? v[j] : stored<Elem>(v[j]));
+  } else if constexpr (kGated) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float g = EPI == EPI_SWIGLU ? v[j] : stored<Elem>(v[j]), w = EPI == EPI_SWIGLU ? u[j] : stored<Elem>(u[j]);
+      o[j] = g * sigmoid_exact(g) * w;
+    }
+  }
+  store_piece<Elem, VEC>(c, o, n);
 }
 
 // WGRAD: both operands k-major, C = [S, m_rows, n_out]; otherwise the rows of the tile table, W k-major or not
@@ -327,51 +377,8 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(F32Args a) {
       }
     }
 
-    // ---- epilogue on 4 consecutive columns of one row.  col is the result column; gated: g and u belong to it.
-    auto emit = [&](int r, int col, f32x4 v, f32x4 u) {
-      const int row = row0 + r;
-      const int n = row < row_end ? a.n_out - col : 0;
-      const size_t grow = WGRAD ? (size_t)slot * a.m_rows + row : (size_t)row;
-      if (n <= 0) return;
-      Elem* const c = (Elem*)a.C + grow * a.ldc + col;
-      if constexpr (EPI == EPI_ACCUM) {
-        float* const s = a.Cacc + grow * a.ldc + col;
-        store_piece<float, VEC>(s, load_piece<float, VEC>(s, a.Cacc, n) + v, n);
-        return;
-      }
-      if constexpr (EPI == EPI_GELU_KEEP || EPI == EPI_SWIGLU_KEEP) {
-        Elem* const z = (Elem*)a.Z + grow * a.ldz + col;
-        store_piece<Elem, VEC>(z, v, n);
-        if constexpr (kGated) store_piece<Elem, VEC>(z + a.ffn, u, n);
-      }
-      f32x4 o = v, o2;
-      if constexpr (EPI == EPI_DGELU || EPI == EPI_DSWIGLU) {
-        const Elem* const z = (const Elem*)a.Z + grow * a.ldz + col;
-        const f32x4 zg = load_piece<Elem, VEC>(z, (const Elem*)a.Z, n);
-        if constexpr (EPI == EPI_DGELU) {
-#pragma unroll
-          for (int j = 0; j < 4; ++j) o[j] = v[j] * gelu_grad_exact(zg[j]);
-        } else {
-          const f32x4 zu = load_piece<Elem, VEC>(z + a.ffn, (const Elem*)a.Z, n);
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const float sg = sigmoid_exact(zg[j]);
-            o[j] = v[j] * zu[j] * (sg * fmaf(zg[j], 1.0f - sg, 1.0f));
-            o2[j] = v[j] * (zg[j] * sg);
-          }
-          store_piece<Elem, VEC>(c + a.ffn, o2, n);
-        }
-      } else if constexpr (EPI == EPI_GELU || EPI == EPI_GELU_KEEP) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) o[j] = gelu_exact(EPI == EPI_GELU ? v[j] : stored<Elem>(v[j]));
-      } else if constexpr (kGated) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const float g = EPI == EPI_SWIGLU ? v[j] : stored<Elem>(v[j]), w = EPI == EPI_SWIGLU ? u[j] : stored<Elem>(u[j]);
-          o[j] = g * sigmoid_exact(g) * w;
-        }
-      }
-      store_piece<Elem, VEC>(c, o, n);
+    auto emit = [&](int r, int col, const f32x4& v, const f32x4& u) {
+      f32_emit<Elem, EPI, WGRAD, VEC>(a, slot, row0 + r, row_end, col, v, u);
     };
     // lane l of block (n, m) holds row 16 m + l % 16 and the columns 16 n + 4 (l / 16) + 0..3
     const int out_n = n0 + wn * (kGated ? 16 : 32);
@@ -424,6 +431,15 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(F32Args a) {
 // 1 wave 63; 2048 x 512 (1152): 88 and 58; weight gradients of 16384: 58 and 81.  Two were never the best.
 inline int f32_waves(long long tiles32) { return tiles32 >= 4 * 768 ? 4 : 1; }
 
+// 16-byte accesses on fp32 tensors, and a stage's pieces within 31-bit offsets.
+inline bool whole_pieces(const F32Args& a) {
+  const long long stage_bytes = 128ll * 4 * (a.lda > a.ldw ? a.lda : a.ldw);  // at most 128 rows of either operand
+  return stage_bytes < (1ll << 31) && (!a.gather || a.gather_T * a.lda * 4 < (1ll << 31)) &&
+         a.K % 4 == 0 && a.lda % 4 == 0 && a.ldw % 4 == 0 && a.ldc % 4 == 0 && a.ldz % 4 == 0 &&
+         a.n_out % 4 == 0 && a.ffn % 4 == 0 && a.m_rows % 4 == 0 && a.w_slot % 4 == 0 && aligned16(a.A) &&
+         aligned16(a.W) && aligned16(a.C) && aligned16(a.Z) && aligned16(a.Cacc);
+}
+
 template <typename Elem, int EPI, bool WGRAD, bool WKM, int NW>
 void launch_f32_waves(const F32Args& a, dim3 grid, bool vec, hipStream_t st) {
   if constexpr (sizeof(Elem) == 4) {
@@ -445,41 +461,10 @@ int32_t launch_f32(F32Args a, long long rows32, long long max_rows32, hipStream_
   if (cus == 0) return LZ_EHIP;
   const long long resident = (long long)cus * (nw == 1 ? 4 : 3);  // what the LDS of a CU holds
   const dim3 grid((unsigned)(max_rows32 * a.n_tiles < resident ? max_rows32 * a.n_tiles : resident));
-  const long long stage_bytes = 128ll * 4 * (a.lda > a.ldw ? a.lda : a.ldw);  // at most 128 rows of either operand
-  const bool vec = stage_bytes < (1ll << 31) && (!a.gather || a.gather_T * a.lda * 4 < (1ll << 31)) &&
-                   a.K % 4 == 0 && a.lda % 4 == 0 && a.ldw % 4 == 0 && a.ldc % 4 == 0 && a.ldz % 4 == 0 &&
-                   a.n_out % 4 == 0 && a.ffn % 4 == 0 && a.m_rows % 4 == 0 && a.w_slot % 4 == 0 && aligned16(a.A) &&
-                   aligned16(a.W) && aligned16(a.C) && aligned16(a.Z) && aligned16(a.Cacc);
+  const bool vec = whole_pieces(a);
   if (nw == 4) launch_f32_waves<Elem, EPI, WGRAD, WKM, 4>(a, grid, vec, st);
   else launch_f32_waves<Elem, EPI, WGRAD, WKM, 1>(a, grid, vec, st);
   return lz::launch_status();
-}
-
-// One GEMM over the batch's row tiles (a.t: kF32Rows rows an entry); S and P size the launch only.
-template <typename Elem, int EPI, bool WKM>
-int32_t launch_f32_rows(F32Args a, int S, long long P, hipStream_t st) {
-  const long long used = P < S ? P : S;  // slots that can have rows, half a tile more each
-  return launch_f32<Elem, EPI, false, WKM>(a, P / kF32Rows + (used + 1) / 2, a.t.capacity, st);
-}
-
-// The weight gradients of all slots: C[s] [m_rows, n_out] = A[rows of s]^T W[rows of s], or added to Cacc.
-template <typename Elem>
-int32_t launch_f32_wgrad(const void* A, int m_rows, const void* W, int n_out, const int32_t* slot_offsets, int S, long long P,
-                         void* C, float* Cacc, hipStream_t st) {
-  F32Args a{};
-  a.A = A;
-  a.W = W;
-  a.C = C;
-  a.Cacc = Cacc;
-  a.lda = a.m_rows = m_rows;
-  a.ldw = a.ldc = a.n_out = n_out;
-  a.slot_offsets = slot_offsets;
-  a.P = P;
-  a.slots = S;
-  a.m_tiles = ceil_div(m_rows, kF32Rows);
-  const long long tiles = (long long)S * a.m_tiles;
-  return Cacc ? launch_f32<Elem, EPI_ACCUM, true, true>(a, tiles, tiles, st)
-              : launch_f32<Elem, EPI_NONE, true, true>(a, tiles, tiles, st);
 }
 
 }  // namespace

@@ -1,0 +1,370 @@
+// Grouped fp32 GEMM on the bf16 matrix cores of gfx950: every fp32 operand is split into three bf16 numbers whose sum
+// it is exactly, and the six largest of the nine products are summed in fp32.  The forward's GEMMs and the weight
+// gradients of fp32 tensors in whole 16-byte pieces, where use_split() below says so; the others run on the kernel of
+// gemm_f32.h.  Device code shared by the forward and the backward, not part of the C ABI.
+//
+//   C[rows of a slot, n] = epi( sum_k A(row, k) * W[slot](k, n) )      rows, or a slot's k range, ragged
+//
+// Why: v_mfma_f32_16x16x4_f32 does 64 flops a cycle and SIMD, v_mfma_f32_16x16x32_bf16 1024: six of them 2.67 times the
+// fp32 instruction.  The split a = a0 + a1 + a2: a0 the upper 16 bits, a1 the rest rounded to bf16, a2 what is then
+// left (at most 8 bits, exact).  Left out are a1 w2, a2 w1 and a2 w2, together below 2^-22 of a product and 2^-26 on
+// average, of either sign.  The five small products of 32 k are summed from zero and added to the accumulator of
+// a0 w0 once, which is thus rounded twice in 32 k where the fp32 instruction rounds it 8 times or more: relative
+// errors against fp64 1.0e-7 to 3.7e-7 on layers of d = 64 to 1024, ffn = 92 to 4096, where that one had 1.5e-7 to 1.3e-6.
+//
+// Tile: 64 rows x 128 columns, stages of 64 k, four waves: two column ranges of 64 times two halves of each stage's k,
+// added through LDS at the end.  A goes global -> registers (one stage ahead) -> split -> LDS, [row][plane][k] with a
+// pitch of 25 x 16 bytes, so that a fragment's 16 rows (one ds_read_b128 a lane) cover the banks once.  W no other
+// wave needs: it goes from global straight to the fragments, a lane loading 4 adjacent columns at its 8 k and splitting
+// the pairs of k in place; its four fragments are the columns 4 i + j, j = 0..3, and a lane's accumulators of them are
+// adjacent columns again.  Two workgroups share a CU.  What bounds it: the split and the additions (some 400 vector
+// instructions to 96 MFMAs a stage) and the latency of a stage.  Tried: both operands through LDS (up projection of
+// 512 x 2048, 16 slots, 2048 rows 53 us against 49), column ranges of one wave (tiles of 64 x 256, all k: 54, and
+// 114 against 70 where tiles are few) or of four (64 x 64: 63), one run of tiles per XCD (level, gradients 20 % slower),
+// and the data gradients, whose W lies along k (65 us against 58 of the fp32 instruction).
+#pragma once
+#include "gemm_f32.h"
+
+namespace {
+
+constexpr int kSplitRows = 64, kSplitCols = 128;  // of a tile
+
+// Two fp32 -> the three planes' dwords.
+__device__ __forceinline__ void split_pair(float a, float b, uint32_t (&d)[3]) {
+  const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
+  d[0] = __builtin_amdgcn_perm(ub, ua, 0x07060302u);
+  const float ra = a - __uint_as_float(ua & 0xFFFF0000u), rb = b - __uint_as_float(ub & 0xFFFF0000u);
+  d[1] = pack_bf16x2(ra, rb);
+  d[2] = pack_bf16x2(ra - __uint_as_float(d[1] << 16), rb - __uint_as_float(d[1] & 0xFFFF0000u));
+}
+
+template <int EPI, bool WGRAD>
+__global__ __launch_bounds__(256, 2) void gemm_split_kernel(F32Args a) {
+  constexpr int TM = kSplitRows, TN = kSplitCols, TK = 64;
+  constexpr bool kGated = EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_KEEP;
+  constexpr bool AKM = WGRAD;
+  constexpr int kPlane = TK * 2, kPitch = 3 * kPlane + 16;  // bytes
+  constexpr int kPieces = TM * TK / 4 / 256;  // of A, per thread
+  constexpr int kExchange = 4 * 2 * 4 * 64 * 16;  // [wave][row fragment][weight fragment][lane] partial sums
+  __shared__ __attribute__((aligned(16))) char lds[TM * kPitch > kExchange ? TM * kPitch : kExchange];
+  __shared__ int s_range;
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wn = wave & 1, wk = wave >> 1;
+  const int frag = lane & 15, quad = lane >> 4;
+  constexpr int kOutCols = kGated ? TN / 2 : TN;
+
+  const int n_row_tiles = WGRAD ? a.slots * a.m_tiles : a.t.header[0];
+  const long long n_all = (long long)n_row_tiles * a.n_tiles;
+  for (long long tile = blockIdx.x; tile < n_all; tile += gridDim.x) {
+    const int row_tile = int(tile / a.n_tiles), n0 = int(tile % a.n_tiles) * kOutCols;
+    int slot, row0, row_end, K = a.K;
+    const float* A = (const float*)a.A;
+    const float* W = (const float*)a.W;
+    if constexpr (WGRAD) {
+      slot = row_tile / a.m_tiles;
+      row0 = row_tile % a.m_tiles * TM;
+      row_end = a.m_rows;
+      long long lo, hi;
+      clip_slot(a.slot_offsets, slot, a.P, &lo, &hi);
+      lo = __builtin_amdgcn_readfirstlane((int)lo);
+      K = __builtin_amdgcn_readfirstlane((int)(hi)) - (int)lo;
+      A += (size_t)lo * a.lda;
+      W += (size_t)lo * a.ldw;
+      if (EPI == EPI_ACCUM && K == 0) continue;
+    } else {
+      slot = __builtin_amdgcn_readfirstlane(a.t.slot[row_tile]);  // the same in every lane: buffer bases are scalar
+      row0 = __builtin_amdgcn_readfirstlane(a.t.row0[row_tile]);
+      row_end = __builtin_amdgcn_readfirstlane(a.t.row_end[row_tile]);
+      W += (size_t)slot * a.w_slot;
+    }
+    // row of A (its index r within the tile) in memory, or -1
+    auto source_row = [&](int r) -> long long {
+      const int row = row0 + r;
+      if (row >= row_end) return -1;
+      if (a.gather == nullptr) return r;
+      const long long pair = a.gather[row];
+      return pair >= 0 && pair < a.gather_T * a.gather_k ? pair / a.gather_k : -1;
+    };
+
+    // ---- byte offsets of this thread's pieces of a stage from the tile's (uniform) base at k = 0, or one that is
+    // outside every buffer; k of the first element
+    constexpr int kNowhere = (int)0x80000000;
+    const float* const baseA = AKM ? A + row0 : a.gather != nullptr ? A : A + (size_t)row0 * a.lda;
+    const float* const baseW = W + n0;
+    // k-major: 4 columns of kPieces consecutive k; otherwise pieces 256 apart in [row][k / 4]
+    const int a_group = tid % (TM / 4), a_k = AKM ? tid / (TM / 4) * kPieces : tid % (TK / 4) * 4;
+    int pa[AKM ? 1 : kPieces];
+    if constexpr (AKM) {
+      pa[0] = row0 + 4 * a_group < row_end ? (a_k * a.lda + 4 * a_group) * 4 : kNowhere;
+    } else {
+#pragma unroll
+      for (int i = 0; i < kPieces; ++i) {
+        const long long src = source_row((tid + 256 * i) / (TK / 4));
+        pa[i] = src >= 0 ? int(src * a.lda + a_k) * 4 : kNowhere;
+      }
+    }
+    // W goes straight to the fragments: this lane's 8 k of 4 adjacent columns.  Gated: the first 32 weight columns of a
+    // wave are gates, the others the up projection of the same results.
+    const int w_col = kGated ? (wn * 8 + (frag & 1) * 4 + (frag >> 2)) * 4 : (wn * 16 + (frag & 3) * 4 + (frag >> 2)) * 4;
+    const int w_k = wk * 32 + quad * 8;
+    int pw = n0 + w_col < a.n_out ? (w_k * a.ldw + w_col + (kGated && (frag & 2) ? a.ffn : 0)) * 4 : kNowhere;
+    u32x4_t ra[kPieces], rw[8];
+    // A piece that is not there arrives as zeros: its offset is outside the descriptor, which for a k-major operand
+    // ends with row K (the host checked that a stage spans less than 2 GiB).
+    auto buffer = [&](const float* base, bool k_major, int ld, int k0) {
+      const long long left = (long long)(K - k0) * ld * 4;
+      const int bytes = !k_major || left > 0x7FFFFFFF ? 0x7FFFFFFF : left < 0 ? 0 : (int)left;
+      return __builtin_amdgcn_make_buffer_rsrc((void*)(base + (k_major ? (size_t)k0 * ld : (size_t)k0)), 0, bytes, 0x00020000);
+    };
+    auto fetch_a = [&](int k0) {
+      const auto buf = buffer(baseA, AKM, a.lda, k0);
+      if constexpr (AKM) asm("" : "+v"(pa[0]));  // the sums below are made again in each stage, not kept in registers
+#pragma unroll
+      for (int i = 0; i < kPieces; ++i)
+        ra[i] = __builtin_amdgcn_raw_buffer_load_b128(buf, AKM ? pa[0] + i * a.lda * 4 : k0 + a_k < K ? pa[AKM ? 0 : i] : kNowhere, 0, 0);
+    };
+    auto fetch_w = [&](int k0) {
+      const auto buf = buffer(baseW, true, a.ldw, k0);
+      asm("" : "+v"(pw));
+#pragma unroll
+      for (int i = 0; i < 8; ++i) rw[i] = __builtin_amdgcn_raw_buffer_load_b128(buf, pw + i * a.ldw * 4, 0, 0);
+    };
+    float largest_a = 0.f, largest_w = 0.f;  // magnitudes, NaNs aside
+    auto note = [](float& to, const f32x4& v) {  // fmaxf would quiet each operand first
+      asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(to) : "v"(v[0]), "v"(v[1]));
+      asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(to) : "v"(v[2]), "v"(v[3]));
+    };
+    auto put_a = [&]() {
+      f32x4 v[kPieces];
+#pragma unroll
+      for (int i = 0; i < kPieces; ++i) note(largest_a, v[i] = __builtin_bit_cast(f32x4, ra[i]));
+      auto store = [&](char* at, float v0, float v1, float v2, float v3) {
+        uint32_t lo[3], hi[3];
+        split_pair(v0, v1, lo);
+        split_pair(v2, v3, hi);
+#pragma unroll
+        for (int p = 0; p < 3; ++p) *(uint2*)(at + p * kPlane) = uint2{lo[p], hi[p]};
+      };
+      if constexpr (AKM) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int i = 0; i < kPieces; i += 4)
+            store(lds + (j * (TM / 4) + a_group) * kPitch + (a_k + i) * 2, v[i][j], v[i + 1][j], v[i + 2][j], v[i + 3][j]);
+      } else {
+#pragma unroll
+        for (int i = 0; i < kPieces; ++i)
+          store(lds + (tid + 256 * i) / (TK / 4) * kPitch + a_k * 2, v[i][0], v[i][1], v[i][2], v[i][3]);
+      }
+    };
+
+    f32x4 acc[4][4] = {};  // [weight fragment][row fragment]
+    const char* const read_a = lds + frag * kPitch + w_k * 2;
+    const bool second_half = WGRAD || row0 + 32 < row_end;  // rows 32 to 63 are not all padding
+    const int stages = (K + TK - 1) / TK;
+    if (tid == 0) s_range = 0;
+    if (stages > 0) {
+      fetch_a(0);
+      fetch_w(0);
+    } else {
+      __syncthreads();
+    }
+    for (int s = 0; s < stages; ++s) {
+      put_a();
+      __syncthreads();
+      fetch_a((s + 1) * TK);  // past the end: no valid piece
+      u32x4_t w[4][3];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) note(largest_w, __builtin_bit_cast(f32x4, rw[i]));
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+          uint32_t d[3];
+          split_pair(__uint_as_float(rw[2 * h][j]), __uint_as_float(rw[2 * h + 1][j]), d);
+#pragma unroll
+          for (int p = 0; p < 3; ++p) w[j][p][h] = d[p];
+        }
+      fetch_w((s + 1) * TK);
+      auto multiply = [&](int f) {
+        bf16x8 x[3];
+#pragma unroll
+        for (int p = 0; p < 3; ++p) x[p] = *(const bf16x8*)(read_a + f * 16 * kPitch + p * kPlane);
+        f32x4 low[4] = {};
+#pragma unroll
+        for (int term = 0; term < 6; ++term) {
+          constexpr int kTermW[6] = {0, 2, 1, 0, 1, 0}, kTermX[6] = {2, 0, 1, 1, 0, 0};
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            f32x4& to = term == 5 ? acc[j][f] : low[j];
+            to = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[j][kTermW[term]]), x[kTermX[term]], to, 0, 0, 0);
+          }
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[j][f] += low[j];
+      };
+      multiply(0);
+      multiply(1);
+      if (second_half) {
+        multiply(2);
+        multiply(3);
+      }
+      __syncthreads();
+    }
+
+    // row within the tile and first of the 4 result columns of this lane's accumulators [0..3][f][t]
+    auto tile_row = [&](int f) { return AKM ? 4 * frag + f : f * 16 + frag; };
+    auto out_col = [&](int t) { return kGated ? (wn * 8 + (t & 1) * 4 + quad) * 4 : (wn * 16 + t * 4 + quad) * 4; };
+    // Infinities and products past the largest number, of which the split makes NaNs where fp32 does not, and operands
+    // so small that their last parts are no normal numbers: such a tile is summed again in fp32.
+    const int flags = (__any(largest_a >= 0x1p64f || largest_w >= 0x1p64f) ? 1 : 0) | (__any(largest_a >= 0x1p-100f) ? 2 : 0) |
+                      (__any(largest_w >= 0x1p-100f) ? 4 : 0) | (__any(largest_a > 0.f) ? 8 : 0) | (__any(largest_w > 0.f) ? 16 : 0);
+    if (lane == 0) atomicOr(&s_range, flags);
+    __syncthreads();
+    const int range = s_range;
+    bool again = (range & 6) != 6 && (range & 24) == 24;
+    if (range & 1) {
+      float bad = 0.f;
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int f = 0; f < 4; ++f)
+#pragma unroll
+          for (int t = 0; t < 4; ++t) bad += acc[j][f][t] * 0.f;
+      again = again || __any(bad != bad);
+    }
+    if (again) {
+      const float* at_a[4];
+      const float* at_w[4];
+#pragma unroll
+      for (int f = 0; f < 4; ++f) {
+        const int r = tile_row(f);
+        const long long src = AKM ? (row0 + r < row_end ? r : -1) : source_row(r);
+        at_a[f] = src < 0 ? nullptr : AKM ? baseA + src : baseA + src * a.lda;
+      }
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int col = out_col(t);
+        at_w[t] = n0 + col >= a.n_out ? nullptr : baseW + col + (kGated && t >= 2 ? a.ffn : 0);
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int f = 0; f < 4; ++f) acc[j][f] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int k = 0; k < K; ++k) {
+        if (k % TK / 32 != wk) continue;
+        float x[4];
+#pragma unroll
+        for (int f = 0; f < 4; ++f) x[f] = at_a[f] ? at_a[f][AKM ? (size_t)k * a.lda : (size_t)k] : 0.f;
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const float w = at_w[t] ? at_w[t][(size_t)k * a.ldw + j] : 0.f;
+#pragma unroll
+            for (int f = 0; f < 4; ++f) acc[j][f][t] = fmaf(x[f], w, acc[j][f][t]);
+          }
+      }
+    }
+
+    // The two waves of a column range exchange two row fragments each and emit the other two.
+    f32x4* const mine = (f32x4*)lds + wave * 8 * 64 + lane;
+    const f32x4* const theirs = (const f32x4*)lds + (wave ^ 2) * 8 * 64 + lane;
+    auto exchange = [&](auto own_c) {
+      constexpr int own = decltype(own_c)::value, given = 2 - own;  // first fragment of either pair
+#pragma unroll
+      for (int o = 0; o < 2; ++o)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) mine[(o * 4 + j) * 64] = acc[j][given + o];
+      __syncthreads();
+#pragma unroll
+      for (int o = 0; o < 2; ++o) {
+        constexpr int f0 = own;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[j][f0 + o] += theirs[(o * 4 + j) * 64];
+        auto vec = [&](int t) { return f32x4{acc[0][f0 + o][t], acc[1][f0 + o][t], acc[2][f0 + o][t], acc[3][f0 + o][t]}; };
+#pragma unroll
+        for (int t = 0; t < (kGated ? 2 : 4); ++t)
+          f32_emit<float, EPI, WGRAD, true>(a, slot, row0 + tile_row(f0 + o), row_end, n0 + out_col(t), vec(t), vec(kGated ? t + 2 : t));
+      }
+    };
+    if (wk == 0) exchange(std::integral_constant<int, 0>{});
+    else exchange(std::integral_constant<int, 2>{});
+    __syncthreads();  // the partial sums are read: the next tile may fill the stage
+  }
+}
+
+// Which fp32 GEMMs run here: those with two tiles a CU and more, columns and k (gradients: both widths) that fill three
+// quarters of their tiles, and 16 rows a slot on average.  us on the fp32 instruction and here: 4096 tokens, 1024 x 4096,
+// 8 slots, top-2: 644 -> 432, 656 -> 431, gradients 598 -> 390 and 383; 3000 tokens, 512 x 512 gated, top-6, 80 slots:
+// 213 -> 159, 106 -> 86, 114 -> 90, 221 -> 162; 1024 tokens, 512 x 2048, 16 slots: 63 -> 51, 61 -> 46; 256 tokens,
+// 1024 x 4096, 32 rows a slot: 74 -> 62, 120 -> 107.  Outside: 2 rows a slot 75 -> 84, 8 rows a slot 209 -> 231,
+// the down projection of 2048 x 512 at 160 tiles 59 -> 70.
+// rows64: row tiles expected to hold rows;  fill: k, or a gradient's rows
+inline bool use_split(long long P, int S, long long rows64, int cols, int fill) {
+  const long long padded = (long long)ceil_div(cols, kSplitCols) * kSplitCols * ceil_div(fill, 64) * 64;
+  return P >= 16ll * S && rows64 * ceil_div(cols, kSplitCols) >= 2ll * device_cus() && 4ll * cols * fill >= 3 * padded;
+}
+inline bool use_split_rows(long long P, int S, int cols, int K) {
+  const long long used = P < S ? P : S;  // slots that can have rows, half a tile more each
+  return use_split(P, S, P / kSplitRows + (used + 1) / 2, cols, K);
+}
+// Whether a forward of this shape reads the table of 64-row tiles.
+inline bool split_forward(const lz_shape* s) {
+  const long long P = (long long)s->T * s->k;
+  const int S = s->N * s->c;
+  return s->dtype == LZ_F32 && (use_split_rows(P, S, s->ffn * (s->act == LZ_SWIGLU ? 2 : 1), s->d) || use_split_rows(P, S, s->d, s->ffn));
+}
+
+template <int EPI, bool WGRAD>
+int32_t launch_split(F32Args a, int cols, long long max_rows64, hipStream_t st) {
+  const int cus = device_cus();
+  if (cus == 0) return LZ_EHIP;
+  a.n_tiles = ceil_div(cols, kSplitCols);
+  const long long resident = 2ll * cus, tiles = max_rows64 * a.n_tiles;
+  hipLaunchKernelGGL((gemm_split_kernel<EPI, WGRAD>), dim3((unsigned)(tiles < resident ? tiles : resident)), dim3(256), 0, st, a);
+  return lz::launch_status();
+}
+
+// One GEMM over the batch's row tiles (a.t: kF32Rows rows an entry, a.t_split: kSplitRows); S and P size the launch only.
+template <typename Elem, int EPI, bool WKM>
+int32_t launch_f32_rows(F32Args a, int S, long long P, hipStream_t st) {
+  const long long used = P < S ? P : S;  // slots that can have rows, half a tile more each
+  if constexpr (sizeof(Elem) == 4 && WKM) {
+    const int cols = a.n_out * (EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_KEEP ? 2 : 1);
+    if (use_split_rows(P, S, cols, a.K) && whole_pieces(a)) {
+      a.t = a.t_split;
+      return launch_split<EPI, false>(a, cols, a.t.capacity, st);
+    }
+  }
+  return launch_f32<Elem, EPI, false, WKM>(a, P / kF32Rows + (used + 1) / 2, a.t.capacity, st);
+}
+
+// The weight gradients of all slots: C[s] [m_rows, n_out] = A[rows of s]^T W[rows of s], or added to Cacc.
+template <typename Elem>
+int32_t launch_f32_wgrad(const void* A, int m_rows, const void* W, int n_out, const int32_t* slot_offsets, int S, long long P,
+                         void* C, float* Cacc, hipStream_t st) {
+  F32Args a{};
+  a.A = A;
+  a.W = W;
+  a.C = C;
+  a.Cacc = Cacc;
+  a.lda = a.m_rows = m_rows;
+  a.ldw = a.ldc = a.n_out = n_out;
+  a.slot_offsets = slot_offsets;
+  a.P = P;
+  a.slots = S;
+  if constexpr (sizeof(Elem) == 4) {
+    a.m_tiles = ceil_div(m_rows, kSplitRows);
+    const long long tiles = (long long)S * a.m_tiles;
+    if (use_split(P, S, tiles, n_out, m_rows) && whole_pieces(a))
+      return Cacc ? launch_split<EPI_ACCUM, true>(a, n_out, tiles, st) : launch_split<EPI_NONE, true>(a, n_out, tiles, st);
+  }
+  a.m_tiles = ceil_div(m_rows, kF32Rows);
+  const long long tiles = (long long)S * a.m_tiles;
+  return Cacc ? launch_f32<Elem, EPI_ACCUM, true, true>(a, tiles, tiles, st)
+              : launch_f32<Elem, EPI_NONE, true, true>(a, tiles, tiles, st);
+}
+
+}  // namespace
