@@ -77,8 +77,8 @@ inline GenericTrainWorkspace carve_train_generic(void* ws, const lz_shape* s) {
 }
 
 // The tables of a GEMM's arguments; `split`: that of the 64-row tiles too.
-inline void generic_tiles(F32Args& a, const int32_t* slot_offsets, int S, long long P, const GenericTrainWorkspace& w,
-                          bool split, hipStream_t st) {
+inline int32_t generic_tiles(F32Args& a, const int32_t* slot_offsets, int S, long long P, const GenericTrainWorkspace& w,
+                             bool split, hipStream_t st) {
   TileSpecs specs{};
   a.t = carve_tiles(w.tiles, P, S, kF32Rows);
   add_rows(specs, kF32Rows, P, a.t);
@@ -86,7 +86,7 @@ inline void generic_tiles(F32Args& a, const int32_t* slot_offsets, int S, long l
     a.t_split = carve_tiles(w.tiles_split, P, S, kSplitRows);
     add_rows(specs, kSplitRows, P, a.t_split);
   }
-  launch_build_tiles(slot_offsets, S, specs, st);
+  return launch_build_tiles(slot_offsets, S, specs, st);
 }
 
 template <typename Elem>
@@ -97,7 +97,8 @@ int32_t generic_forward_train(const void* xp, const int32_t* slot_offsets, const
   const int S = s->N * s->c, d = s->d, ffn = s->ffn, n1 = w.n1;
   // z = xp W1 and h = act(z) from one epilogue   (W1[s] = [d, n1])
   F32Args a{};
-  generic_tiles(a, slot_offsets, S, P, w, split_forward(s), st);
+  int32_t r = generic_tiles(a, slot_offsets, S, P, w, split_forward(s), st);
+  if (r != LZ_OK) return r;
   a.A = xp;
   a.W = w1;
   a.C = h;
@@ -106,8 +107,8 @@ int32_t generic_forward_train(const void* xp, const int32_t* slot_offsets, const
   a.ldw = a.ldz = n1;
   a.w_slot = (long long)d * n1;
   a.ldc = a.n_out = a.ffn = ffn;
-  const int32_t r = s->act == LZ_SWIGLU ? launch_f32_rows<Elem, EPI_SWIGLU_KEEP, true>(a, S, P, st)
-                                        : launch_f32_rows<Elem, EPI_GELU_KEEP, true>(a, S, P, st);
+  r = s->act == LZ_SWIGLU ? launch_f32_rows<Elem, EPI_SWIGLU_KEEP, true>(a, S, P, st)
+                          : launch_f32_rows<Elem, EPI_GELU_KEEP, true>(a, S, P, st);
   if (r != LZ_OK) return r;
   // yp = h W2   (W2[s] = [ffn, d])
   F32Args b{};
@@ -133,7 +134,8 @@ int32_t generic_ffn_backward(const void* dyp, const void* xp, const void* z, con
   if (P > 0) {
     // dZ = (dyp W2^T) * act'(Z): W2[s] [ffn, d] along its rows
     F32Args a{};
-    generic_tiles(a, slot_offsets, S, P, w, false, st);  // the data gradients stay on the 32-row tiles
+    r = generic_tiles(a, slot_offsets, S, P, w, false, st);  // the data gradients stay on the 32-row tiles
+    if (r != LZ_OK) return r;
     a.A = dyp;
     a.W = w2;
     a.C = w.dz;

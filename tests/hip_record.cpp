@@ -21,6 +21,7 @@ struct PointerAttributes {
 };
 int g_last_error = 0;
 int g_cus = 256;
+int g_launches_until_failure = -1;
 }  // namespace
 
 extern "C" {
@@ -36,6 +37,7 @@ int __hipPopCallConfiguration(Dim3* grid, Dim3* block, size_t* lds, void** strea
   return 0;
 }
 int hipLaunchKernel(const void* fn, Dim3 grid, Dim3 block, void**, size_t, void*) {
+  if (g_launches_until_failure >= 0 && g_launches_until_failure-- == 0) return g_last_error = 1;
   g_calls += "launch " + g_kernels[fn] + " " + std::to_string((uint64_t)grid.x * grid.y * grid.z) + " " +
              std::to_string((uint64_t)grid.x * block.x) + "\n";
   return 0;
@@ -57,6 +59,7 @@ int hipGetLastError() {
   const int e = g_last_error;
   return g_last_error = 0, e;
 }
+void record_fail_launch(int after) { g_launches_until_failure = after; }  // the launch after that many more fails
 const char* record_take() {
   static std::string taken;
   taken.swap(g_calls);

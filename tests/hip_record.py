@@ -13,6 +13,8 @@ stub = ctypes.CDLL(sys.argv[1], ctypes.RTLD_GLOBAL)
 stub.record_take.restype = ctypes.c_char_p
 sys.path.insert(0, sys.argv[2])
 import paper_2407_04656_amd as lz
+def fail_launch(after):
+    stub.record_fail_launch(after)
 def calls():
     return stub.record_take().decode().splitlines()
 class At:
@@ -31,8 +33,8 @@ calls()
 
 
 def recorded(tmp_path, body):
-    """Runs `body`, which has `lz`, `At(address)`, `calls()` (what was asked since the last time) and `code(call, ...)` (its status)
-    and assigns `out`; returns `out`."""
+    """Runs `body`, which has `lz`, `At(address)`, `calls()` (what was asked since the last time), `code(call, ...)` (its status) and
+    `fail_launch(n)` (the launch after n more fails), and assigns `out`; returns `out`."""
     so = os.path.join(str(tmp_path), "hip_record.so")
     if not os.path.exists(so):
         subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-o", so, os.path.join(HERE, "hip_record.cpp")], check=True)

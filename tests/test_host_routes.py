@@ -160,3 +160,27 @@ for d, ffn, slots in {[(d, f, s) for d, f, s in f32.WIDE_GRADIENTS]}:
         vec = "1" if d % 4 == 0 and ffn % 4 == 0 else "0"
         assert rc == [0, 0]
         assert names == [f"{epi}ELb1ELb1ELi4ELb{vec}E" for epi in (0, 0, 5, 5)]
+
+
+@pytest.mark.parametrize("dtype,d,address", [("LZ_F32", 64, 1 << 20), ("LZ_F32", 1408, 1 << 20), ("LZ_BF16", 65, 1 << 20),
+                                             ("LZ_BF16", 64, 1 << 20), ("LZ_BF16", 1408, 1 << 20)])
+def test_a_launch_that_fails_ends_the_call(tmp_path, dtype, d, address):
+    """Whichever launch of a call fails, the tile tables' among them: the call says so and launches nothing behind it, which
+    would read what the failed kernel did not write."""
+    out = recorded(tmp_path, f"""
+A, W = At({address}), At(1 << 30)
+s = lz.Shape(2400, {d}, 1408, 20, 1, 1, 20, lz.{dtype}, lz.LZ_GELU)
+n = max(lz.lz_ffn_workspace_bytes(s), lz.lz_train_workspace_bytes(s))
+def forward(): return code(lz.lz_expert_ffn, A, A, A, A, s, A, W, n)
+def train(): return code(lz.lz_ffn_forward_train, A, A, A, A, s, A, A, A, W, n)
+def backward(): return code(lz.lz_ffn_backward, A, A, A, A, A, A, A, s, A, A, A, W, n)
+def accumulate(): return code(lz.lz_ffn_backward_accumulate, A, A, A, A, A, A, A, s, A, A, A, W, n)
+out = []
+for call in (forward, train, backward, accumulate):
+    ok, launches = call(), len(calls())
+    for i in range(launches):
+        fail_launch(i)
+        out.append([ok, call(), len(calls()) - i])
+""")
+    assert len(out) >= 3 + 3 + 5 + 5
+    assert out == [[0, -6, 0]] * len(out)    # LZ_EHIP
