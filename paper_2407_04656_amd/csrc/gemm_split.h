@@ -49,7 +49,7 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(F32Args a) {
   __shared__ __attribute__((aligned(16))) char lds[TM * kPitch > kExchange ? TM * kPitch : kExchange];
   __shared__ int s_range;
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wn = wave & 1, wk = wave >> 1;
   const int frag = lane & 15, quad = lane >> 4;
   constexpr int kOutCols = kGated ? TN / 2 : TN;
@@ -268,19 +268,21 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(F32Args a) {
       }
     }
 
-    // The two waves of a column range exchange two row fragments each and emit the other two.
+    // The two waves of a column range exchange two row fragments each and emit the other two: 0 and 1 the wave of the
+    // first half of k.  The barrier lies between the branches, one for all waves.
     f32x4* const mine = (f32x4*)lds + wave * 8 * 64 + lane;
     const f32x4* const theirs = (const f32x4*)lds + (wave ^ 2) * 8 * 64 + lane;
-    auto exchange = [&](auto own_c) {
-      constexpr int own = decltype(own_c)::value, given = 2 - own;  // first fragment of either pair
+    auto give = [&](auto f0_c) {
+      constexpr int f0 = decltype(f0_c)::value;
 #pragma unroll
       for (int o = 0; o < 2; ++o)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) mine[(o * 4 + j) * 64] = acc[j][given + o];
-      __syncthreads();
+        for (int j = 0; j < 4; ++j) mine[(o * 4 + j) * 64] = acc[j][f0 + o];
+    };
+    auto finish = [&](auto f0_c) {
+      constexpr int f0 = decltype(f0_c)::value;
 #pragma unroll
       for (int o = 0; o < 2; ++o) {
-        constexpr int f0 = own;
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[j][f0 + o] += theirs[(o * 4 + j) * 64];
         auto vec = [&](int t) { return f32x4{acc[0][f0 + o][t], acc[1][f0 + o][t], acc[2][f0 + o][t], acc[3][f0 + o][t]}; };
@@ -289,8 +291,13 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(F32Args a) {
           f32_emit<float, EPI, WGRAD, true>(a, slot, row0 + tile_row(f0 + o), row_end, n0 + out_col(t), vec(t), vec(kGated ? t + 2 : t));
       }
     };
-    if (wk == 0) exchange(std::integral_constant<int, 0>{});
-    else exchange(std::integral_constant<int, 2>{});
+    using F0 = std::integral_constant<int, 0>;
+    using F2 = std::integral_constant<int, 2>;
+    if (wk == 0) give(F2{});
+    else give(F0{});
+    __syncthreads();
+    if (wk == 0) finish(F0{});
+    else finish(F2{});
     __syncthreads();  // the partial sums are read: the next tile may fill the stage
   }
 }

@@ -1,4 +1,12 @@
-"""Which fp32 GEMMs run on split operands, read from the launches that the library makes (no GPU)."""
+"""Which fp32 GEMMs run on split operands, read from the launches that the library makes, and the barriers of their
+kernel, read from its code (no GPU)."""
+import re
+import subprocess
+
+import pytest
+
+from paper_2407_04656_amd import build
+
 from hip_record import recorded
 
 
@@ -18,3 +26,21 @@ for P, S, d, ffn, w1 in ((2400, 20, 1408, 1408, A), (2400, 20, 1412, 1500, A), (
     # up, down, then dZ, dxp, dW2, dW1 of the backward
     assert out == [[[0, 0], [2, 1], "ssffss"], [[0, 0], [2, 1], "ssffss"], [[0, 0], [2, 1], "sfffff"], [[0, 0], [2, 1], "fsffss"],
                    [[0, 0], [1, 1], "ffffff"], [[0, 0], [1, 1], "ffffff"], [[0, 0], [2, 1], "ffffff"]]
+
+
+@pytest.mark.parametrize("epi,wgrad", [("EPI_SWIGLU_KEEP", "false"), ("EPI_ACCUM", "true")])
+def test_every_barrier_is_one_for_all_waves(tmp_path, epi, wgrad):
+    """A barrier in code that is compiled once for each arm of a branch would be another one for the waves of each arm: the
+    kernel's code has as many as its source."""
+    text = open(f"{build.CSRC}/gemm_split.h").read()
+    kernel = text[text.index("void gemm_split_kernel("):]
+    kernel = kernel[:kernel.index("\n}\n")]
+    src, asm = tmp_path / "one.hip", tmp_path / "one.s"
+    src.write_text(f'#include "gemm_split.h"\nvoid* one() {{ return (void*)gemm_split_kernel<{epi}, {wgrad}>; }}\n')
+    done = subprocess.run(["/opt/rocm/bin/hipcc", *build.FLAGS, "-x", "hip", "--cuda-device-only", "-S", str(src), "-o", str(asm)],
+                          capture_output=True, text=True)
+    assert done.returncode == 0, done.stderr
+    code = asm.read_text()
+    code = code[re.search(r"^\S*gemm_split_kernel\S*:", code, re.M).end():]
+    code = code[:code.index(".Lfunc_end")]
+    assert len(re.findall(r"^\s+s_barrier", code, re.M)) == kernel.count("__syncthreads()")
