@@ -1,16 +1,18 @@
 // Grouped fp32 GEMM on the bf16 matrix cores of gfx950: every fp32 operand is split into three bf16 numbers whose sum
-// it is exactly, and the six largest of the nine products are summed in fp32.  The forward's GEMMs and the weight
+// it is exactly, and all but the smallest of the nine products are summed in fp32.  The forward's GEMMs and the weight
 // gradients of fp32 tensors in whole 16-byte pieces, where use_split() below says so; the others run on the kernel of
 // gemm_f32.h.  Device code shared by the forward and the backward, not part of the C ABI.
 //
 //   C[rows of a slot, n] = epi( sum_k A(row, k) * W[slot](k, n) )      rows, or a slot's k range, ragged
 //
-// Why: v_mfma_f32_16x16x4_f32 does 64 flops a cycle and SIMD, v_mfma_f32_16x16x32_bf16 1024: six of them 2.67 times the
-// fp32 instruction.  The split a = a0 + a1 + a2: a0 the upper 16 bits, a1 the rest rounded to bf16, a2 what is then
-// left (at most 8 bits, exact).  Left out are a1 w2, a2 w1 and a2 w2, together below 2^-22 of a product and 2^-26 on
-// average, of either sign.  The five small products of 32 k are summed from zero and added to the accumulator of
-// a0 w0 once, which is thus rounded twice in 32 k where the fp32 instruction rounds it 8 times or more: relative
-// errors against fp64 1.0e-7 to 3.7e-7 on layers of d = 64 to 1024, ffn = 92 to 4096, where that one had 1.5e-7 to 1.3e-6.
+// Why: v_mfma_f32_16x16x4_f32 does 64 flops a cycle and SIMD, v_mfma_f32_16x16x32_bf16 1024: eight of them twice the
+// fp32 instruction.  The split a = a0 + a1 + a2: a0 the upper 16 bits, a1 the rest rounded to bf16, a2 what is then left
+// (at most 8 bits, exact; G. Henry, P. Tang and A. Heinecke, 2019, arXiv 1904.06376).  Left out is a2 w2, below 2^-30 of
+// a product (with a1 w2 and a2 w1 left out too, six instructions, a product was off by up to 4.4 2^-24, which shows in
+// sums of one).  The seven small products of 32 k are summed from zero and added to the accumulator of a0 w0 once, which
+// is thus rounded twice in 32 k where the fp32 instruction rounds it 8 times or more.  Errors against fp64 in 2^-24 of
+// the products' magnitudes, rms of sums of 1, 4, 32 and 1183 of them: 0.42, 0.29, 0.18 and 0.12, by the fp32
+// instruction 0.42, 0.45, 0.47 and 0.47.
 //
 // Tile: 64 rows x 128 columns, stages of 64 k, four waves: two column ranges of 64 times two halves of each stage's k,
 // added through LDS at the end.  A goes global -> registers (one stage ahead) -> split -> LDS, [row][plane][k] with a
@@ -18,7 +20,7 @@
 // wave needs: it goes from global straight to the fragments, a lane loading 4 adjacent columns at its 8 k and splitting
 // the pairs of k in place; its four fragments are the columns 4 i + j, j = 0..3, and a lane's accumulators of them are
 // adjacent columns again.  Two workgroups share a CU.  What bounds it: the split and the additions (some 400 vector
-// instructions to 96 MFMAs a stage) and the latency of a stage.  Tried: both operands through LDS (up projection of
+// instructions to 128 MFMAs a stage) and the latency of a stage.  Tried: both operands through LDS (up projection of
 // 512 x 2048, 16 slots, 2048 rows 53 us against 49), column ranges of one wave (tiles of 64 x 256, all k: 54, and
 // 114 against 70 where tiles are few) or of four (64 x 64: 63), one run of tiles per XCD (level, gradients 20 % slower),
 // and the data gradients, whose W lies along k (65 us against 58 of the fp32 instruction).
@@ -193,11 +195,11 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(F32Args a) {
         for (int p = 0; p < 3; ++p) x[p] = *(const bf16x8*)(read_a + f * 16 * kPitch + p * kPlane);
         f32x4 low[4] = {};
 #pragma unroll
-        for (int term = 0; term < 6; ++term) {
-          constexpr int kTermW[6] = {0, 2, 1, 0, 1, 0}, kTermX[6] = {2, 0, 1, 1, 0, 0};
+        for (int term = 0; term < 8; ++term) {
+          constexpr int kTermW[8] = {2, 1, 0, 2, 1, 0, 1, 0}, kTermX[8] = {1, 2, 2, 0, 1, 1, 0, 0};
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
-            f32x4& to = term == 5 ? acc[j][f] : low[j];
+            f32x4& to = term == 7 ? acc[j][f] : low[j];
             to = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[j][kTermW[term]]), x[kTermX[term]], to, 0, 0, 0);
           }
         }

@@ -1,0 +1,81 @@
+"""The fp32 GEMMs on split operands where their parts are easily lost: sums of one product.
+20 slots, 2400 rows, two 64 x 128 tiles a CU and more: every forward GEMM and both weight gradients run there
+(test_host_split_route.py holds them to that).
+
+Bounds.  A product is rounded once, by 2^-24, and what is left out of it is below 2^-30: 2^-24 1.02.  A sum of n > 1 has n
+roundings and one more, of the matrix instruction, which adds its products at the scale of the largest: (n + 1) 2^-24 1.02
+of the sum of their magnitudes (found: 2.4 and 2.8 for n = 2 and 3; the fp32 instruction 1.9 and 2.5, of a larger rms)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2407_04656_amd as lz
+
+from gpu_util import DEV
+
+pytestmark = pytest.mark.gpu
+ULP = 2.0 ** -24 * 1.02
+S, P, D, FFN = 20, 2400, 1412, 1500   # neither tiles nor stages divide the widths
+COUNTS = [1, 2, 3, 1, 0, 67, 129, 64] + [2133 // 12] * 12
+COUNTS[-1] += P - sum(COUNTS)
+OFF = np.concatenate([[0], np.cumsum(COUNTS)]).astype(np.int32)
+
+
+def _normal(seed, *shape):
+    return torch.randn(shape, generator=torch.Generator(device=DEV).manual_seed(seed), device=DEV)
+
+
+def _shape(act="gelu", d=D, ffn=FFN):
+    return lz.Shape(P, d, ffn, S, 1, 1, S, lz.LZ_F32, lz.LZ_GELU if act == "gelu" else lz.LZ_SWIGLU)
+
+
+def _up(x, w1, act="gelu"):
+    """z and h of the training forward: the first GEMM's sums and their activations."""
+    n1 = w1.shape[2]
+    ffn, d = n1 if act == "gelu" else n1 // 2, x.shape[1]
+    shape = _shape(act, d, ffn)
+    off = torch.from_numpy(OFF).to(DEV)
+    w2 = torch.zeros((S, ffn, d), device=DEV)
+    z, h, yp = (torch.empty((P, n), device=DEV) for n in (n1, ffn, d))
+    ws = torch.empty(lz.lz_train_workspace_bytes(shape), dtype=torch.uint8, device=DEV)
+    lz.lz_ffn_forward_train(x, off, w1, w2, shape, z, h, yp, ws, ws.numel())
+    return z, h
+
+
+def _gradients(x, h, dyp, accumulate):
+    """dW1 [S, D, D] and dW2 [S, D, D] where dZ is dyp: W2 the identity, gelu'(30) = 1."""
+    shape = _shape("gelu", D, D)
+    off = torch.from_numpy(OFF).to(DEV)
+    w1, w2 = torch.zeros((S, D, D), device=DEV), torch.eye(D, device=DEV).repeat(S, 1, 1)
+    z, dxp = torch.full((P, D), 30.0, device=DEV), torch.empty((P, D), device=DEV)
+    dw1, dw2 = torch.zeros((S, D, D), device=DEV), torch.zeros((S, D, D), device=DEV)
+    ws = torch.empty(lz.lz_train_workspace_bytes(shape), dtype=torch.uint8, device=DEV)
+    call = lz.lz_ffn_backward_accumulate if accumulate else lz.lz_ffn_backward
+    call(dyp, x, z, h, off, w1, w2, shape, dxp, dw1, dw2, ws, ws.numel())
+    return dw1, dw2
+
+
+def _rows64(x, w):
+    """x [P, K] against its slots' w [S, K, n], in fp64."""
+    return torch.cat([x[OFF[s]:OFF[s + 1]].double() @ w[s].double() for s in range(S)])
+
+
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_gradients_of_slots_of_a_few_rows(accumulate):
+    x, h, dyp = _normal(1, P, D), _normal(2, P, D), _normal(3, P, D)
+    dw1, dw2 = _gradients(x, h, dyp, accumulate)
+    for s in range(4):
+        a, b = OFF[s], OFF[s + 1]
+        for got, left in ((dw1, x), (dw2, h)):
+            want = left[a:b].double().T @ dyp[a:b].double()
+            size = left[a:b].double().abs().T @ dyp[a:b].double().abs()
+            assert float(((got[s].double() - want).abs() / size).max()) <= (b - a + (b - a > 1)) * ULP, s
+
+
+def test_sums_of_which_one_product_is_not_zero():
+    x, w1 = torch.zeros((P, D), device=DEV), _normal(4, S, D, FFN)
+    at = torch.arange(P, device=DEV) * 7 % D
+    x[torch.arange(P, device=DEV), at] = _normal(5, P)
+    z, _ = _up(x, w1)
+    want = _rows64(x, w1)
+    assert float(((z.double() - want).abs() / want.abs()).max()) <= ULP
