@@ -31,7 +31,11 @@ namespace {
 
 constexpr int kSplitRows = 64, kSplitCols = 128;  // of a tile
 
-// Two fp32 -> the three planes' dwords.
+// Operands are split at 2^24 times their size: the last bit of an fp32 number is 2^-149 or larger, so none of its parts is then
+// below the smallest normal number 2^-126.  Costs 48 multiplications of some 400 vector instructions a stage.
+constexpr float kSplitScale = 0x1p24f, kSplitUnscale = 0x1p-48f;
+
+// Two fp32 (scaled) -> the three planes' dwords.
 __device__ __forceinline__ void split_pair(float a, float b, uint32_t (&d)[3]) {
   const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
   d[0] = __builtin_amdgcn_perm(ub, ua, 0x07060302u);
@@ -49,7 +53,6 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(F32Args a) {
   constexpr int kPieces = TM * TK / 4 / 256;  // of A, per thread
   constexpr int kExchange = 4 * 2 * 4 * 64 * 16;  // [wave][row fragment][weight fragment][lane] partial sums
   __shared__ __attribute__((aligned(16))) char lds[TM * kPitch > kExchange ? TM * kPitch : kExchange];
-  __shared__ int s_range;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wn = wave & 1, wk = wave >> 1;
@@ -132,15 +135,10 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(F32Args a) {
 #pragma unroll
       for (int i = 0; i < 8; ++i) rw[i] = __builtin_amdgcn_raw_buffer_load_b128(buf, pw + i * a.ldw * 4, 0, 0);
     };
-    float largest_a = 0.f, largest_w = 0.f;  // magnitudes, NaNs aside
-    auto note = [](float& to, const f32x4& v) {  // fmaxf would quiet each operand first
-      asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(to) : "v"(v[0]), "v"(v[1]));
-      asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(to) : "v"(v[2]), "v"(v[3]));
-    };
     auto put_a = [&]() {
       f32x4 v[kPieces];
 #pragma unroll
-      for (int i = 0; i < kPieces; ++i) note(largest_a, v[i] = __builtin_bit_cast(f32x4, ra[i]));
+      for (int i = 0; i < kPieces; ++i) v[i] = __builtin_bit_cast(f32x4, ra[i]) * kSplitScale;
       auto store = [&](char* at, float v0, float v1, float v2, float v3) {
         uint32_t lo[3], hi[3];
         split_pair(v0, v1, lo);
@@ -165,12 +163,9 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(F32Args a) {
     const char* const read_a = lds + frag * kPitch + w_k * 2;
     const bool second_half = WGRAD || row0 + 32 < row_end;  // rows 32 to 63 are not all padding
     const int stages = (K + TK - 1) / TK;
-    if (tid == 0) s_range = 0;
     if (stages > 0) {
       fetch_a(0);
       fetch_w(0);
-    } else {
-      __syncthreads();
     }
     for (int s = 0; s < stages; ++s) {
       put_a();
@@ -178,13 +173,11 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(F32Args a) {
       fetch_a((s + 1) * TK);  // past the end: no valid piece
       u32x4_t w[4][3];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) note(largest_w, __builtin_bit_cast(f32x4, rw[i]));
-#pragma unroll
       for (int j = 0; j < 4; ++j)
 #pragma unroll
         for (int h = 0; h < 4; ++h) {
           uint32_t d[3];
-          split_pair(__uint_as_float(rw[2 * h][j]), __uint_as_float(rw[2 * h + 1][j]), d);
+          split_pair(__uint_as_float(rw[2 * h][j]) * kSplitScale, __uint_as_float(rw[2 * h + 1][j]) * kSplitScale, d);
 #pragma unroll
           for (int p = 0; p < 3; ++p) w[j][p][h] = d[p];
         }
@@ -218,25 +211,18 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(F32Args a) {
     // row within the tile and first of the 4 result columns of this lane's accumulators [0..3][f][t]
     auto tile_row = [&](int f) { return AKM ? 4 * frag + f : f * 16 + frag; };
     auto out_col = [&](int t) { return kGated ? (wn * 8 + (t & 1) * 4 + quad) * 4 : (wn * 16 + t * 4 + quad) * 4; };
-    // Infinities and products past the largest number, of which the split makes NaNs where fp32 does not, and operands
-    // so small that their last parts are no normal numbers: such a tile is summed again in fp32.
-    const int flags = (__any(largest_a >= 0x1p64f || largest_w >= 0x1p64f) ? 1 : 0) | (__any(largest_a >= 0x1p-100f) ? 2 : 0) |
-                      (__any(largest_w >= 0x1p-100f) ? 4 : 0) | (__any(largest_a > 0.f) ? 8 : 0) | (__any(largest_w > 0.f) ? 16 : 0);
-    if (lane == 0) atomicOr(&s_range, flags);
-    __syncthreads();
-    const int range = s_range;
-    bool again = (range & 6) != 6 && (range & 24) == 24;
-    if (range & 1) {
-      float bad = 0.f;
+    // Infinities and sums past the largest scaled number (2^80 unscaled), of which the split makes infinities and NaNs: such
+    // sums of a wave are made again in fp32.
+    float bad = 0.f;
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < 4; ++j)
 #pragma unroll
-        for (int f = 0; f < 4; ++f)
+      for (int f = 0; f < 4; ++f) {
+        acc[j][f] *= kSplitUnscale;
 #pragma unroll
-          for (int t = 0; t < 4; ++t) bad += acc[j][f][t] * 0.f;
-      again = again || __any(bad != bad);
-    }
-    if (again) {
+        for (int t = 0; t < 4; ++t) bad += acc[j][f][t] * 0.f;
+      }
+    if (__any(bad != bad)) {
       const float* at_a[4];
       const float* at_w[4];
 #pragma unroll

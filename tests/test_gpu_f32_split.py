@@ -106,7 +106,7 @@ def test_split_keeps_infinities_and_nans_where_fp32_has_them():
 
 @pytest.mark.parametrize("scale", [1e-30, 1e-33, 1e-36])
 def test_split_of_operands_near_the_smallest_normal_number(scale):
-    """Their last parts would be no normal numbers: such tiles are summed in fp32 (chains of 128: 2e-6)."""
+    """Their last parts would be no normal numbers if they were split as they are."""
     gen = torch.Generator(device=DEV).manual_seed(5)
     x = torch.randn((2048, 128), generator=gen, device=DEV) * scale
     w1, w2 = torch.randn((4, 128, 2048), generator=gen, device=DEV), torch.zeros((4, 2048, 128), device=DEV)

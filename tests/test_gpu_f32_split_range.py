@@ -1,10 +1,11 @@
-"""The fp32 GEMMs on split operands where their parts are easily lost: sums of one product.
-20 slots, 2400 rows, two 64 x 128 tiles a CU and more: every forward GEMM and both weight gradients run there
-(test_host_split_route.py holds them to that).
+"""The fp32 GEMMs on split operands where their parts are easily lost: sums of one product, small numbers
+beside ordinary ones.  20 slots, 2400 rows, two 64 x 128 tiles a CU and more: every forward GEMM and
+both weight gradients run there (test_host_split_route.py holds them to that).
 
 Bounds.  A product is rounded once, by 2^-24, and what is left out of it is below 2^-30: 2^-24 1.02.  A sum of n > 1 has n
 roundings and one more, of the matrix instruction, which adds its products at the scale of the largest: (n + 1) 2^-24 1.02
-of the sum of their magnitudes (found: 2.4 and 2.8 for n = 2 and 3; the fp32 instruction 1.9 and 2.5, of a larger rms)."""
+of the sum of their magnitudes (found: 2.4 and 2.8 for n = 2 and 3; the fp32 instruction 1.9 and 2.5, of a larger rms).
+Results below 2^-126 are multiples of 2^-149: two of those more, one for each half of the k."""
 import numpy as np
 import pytest
 import torch
@@ -15,6 +16,7 @@ from gpu_util import DEV
 
 pytestmark = pytest.mark.gpu
 ULP = 2.0 ** -24 * 1.02
+LEAST = 2 * 2.0 ** -149
 S, P, D, FFN = 20, 2400, 1412, 1500   # neither tiles nor stages divide the widths
 COUNTS = [1, 2, 3, 1, 0, 67, 129, 64] + [2133 // 12] * 12
 COUNTS[-1] += P - sum(COUNTS)
@@ -79,3 +81,42 @@ def test_sums_of_which_one_product_is_not_zero():
     z, _ = _up(x, w1)
     want = _rows64(x, w1)
     assert float(((z.double() - want).abs() / want.abs()).max()) <= ULP
+
+
+@pytest.mark.parametrize("scale", [1e-19, 1e-33, 1e-35, 1e-37, 1e-40])
+def test_small_rows_and_columns_beside_ordinary_ones(scale):
+    """Single rows of x and columns of w1: each is as exact as an ordinary one, by its own largest value (at 1e-19 also where
+    they meet: products of 1e-38).  A sum of 1412 products: a random walk of 44 steps of at most three roundings."""
+    x, w1 = _normal(6, P, D), _normal(7, S, D, FFN)
+    rows, cols = torch.arange(0, P, 5, device=DEV), torch.arange(0, FFN, 7, device=DEV)
+    x[rows] *= scale
+    w1[:, :, cols] *= scale
+    z, _ = _up(x, w1)
+    want, bound = _rows64(x, w1), 1e-6
+    other_cols = torch.tensor([c for c in range(FFN) if c % 7], device=DEV)
+    for part in (other_cols, cols):
+        err, big = (z[:, part].double() - want[:, part]).abs(), want[:, part].abs()
+        assert bool((err.amax(1) <= bound * big.amax(1) + LEAST).all())
+    other_rows = torch.tensor([r for r in range(P) if r % 5], device=DEV)
+    for part in (other_rows, rows):
+        err, big = (z[part].double() - want[part]).abs(), want[part].abs()
+        assert bool((err.amax(0) <= bound * big.amax(0) + LEAST).all())
+
+
+@pytest.mark.parametrize("accumulate", [False, True])
+@pytest.mark.parametrize("scale", [1e-33, 1e-36])
+def test_small_columns_of_the_gradients(scale, accumulate):
+    """A column of h is a row of dW2, a column of x one of dW1, a column of dyp one of both."""
+    x, h, dyp = _normal(8, P, D), _normal(9, P, D), _normal(10, P, D)
+    some = torch.arange(0, D, 9, device=DEV)
+    h[:, some] *= scale
+    x[:, some + 3] *= scale
+    dyp[:, some] *= scale
+    for got, left, small in zip(_gradients(x, h, dyp, accumulate), (x, h), (some + 3, some)):
+        for s in np.flatnonzero(COUNTS):
+            a, b = OFF[s], OFF[s + 1]
+            want = left[a:b].double().T @ dyp[a:b].double()
+            size = left[a:b].double().abs().T @ dyp[a:b].double().abs()
+            # of up to 180 products: three roundings in 32 k and one where the halves meet
+            bound = min(b - a + (b - a > 1), 3 * (-(-(b - a) // 32)) + 1) * ULP
+            assert bool(((got[s].double() - want).abs() <= bound * size + LEAST).all()), s
