@@ -54,14 +54,18 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(F32Args a) {
   constexpr int kExchange = 4 * 2 * 4 * 64 * 16;  // [wave][row fragment][weight fragment][lane] partial sums
   __shared__ __attribute__((aligned(16))) char lds[TM * kPitch > kExchange ? TM * kPitch : kExchange];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wn = wave & 1, wk = wave >> 1;
-  const int frag = lane & 15, quad = lane >> 4;
   constexpr int kOutCols = kGated ? TN / 2 : TN;
 
   const int n_row_tiles = WGRAD ? a.slots * a.m_tiles : a.t.header[0];
   const long long n_all = (long long)n_row_tiles * a.n_tiles;
   for (long long tile = blockIdx.x; tile < n_all; tile += gridDim.x) {
+    // The empty asm keeps the per-lane address arithmetic inside the tile: hoisted out of the loop it would be carried in
+    // registers through the stages and spill.
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wn = wave & 1, wk = wave >> 1;
+    const int frag = lane & 15, quad = lane >> 4;
     const int row_tile = int(tile / a.n_tiles), n0 = int(tile % a.n_tiles) * kOutCols;
     int slot, row0, row_end, K = a.K;
     const float* A = (const float*)a.A;
@@ -113,7 +117,8 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(F32Args a) {
     // wave are gates, the others the up projection of the same results.
     const int w_col = kGated ? (wn * 8 + (frag & 1) * 4 + (frag >> 2)) * 4 : (wn * 16 + (frag & 3) * 4 + (frag >> 2)) * 4;
     const int w_k = wk * 32 + quad * 8;
-    int pw = n0 + w_col < a.n_out ? (w_k * a.ldw + w_col + (kGated && (frag & 2) ? a.ffn : 0)) * 4 : kNowhere;
+    const int w_at = w_col + (kGated && (frag & 2) ? a.ffn : 0);
+    int pw = n0 + w_col < a.n_out ? (w_k * a.ldw + w_at) * 4 : kNowhere;
     u32x4_t ra[kPieces], rw[8];
     // A piece that is not there arrives as zeros: its offset is outside the descriptor, which for a k-major operand
     // ends with row K (the host checked that a stage spans less than 2 GiB).
@@ -211,81 +216,68 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(F32Args a) {
     // row within the tile and first of the 4 result columns of this lane's accumulators [0..3][f][t]
     auto tile_row = [&](int f) { return AKM ? 4 * frag + f : f * 16 + frag; };
     auto out_col = [&](int t) { return kGated ? (wn * 8 + (t & 1) * 4 + quad) * 4 : (wn * 16 + t * 4 + quad) * 4; };
-    // Infinities and sums past the largest scaled number (2^80 unscaled), of which the split makes infinities and NaNs: such
-    // sums of a wave are made again in fp32.
-    float bad = 0.f;
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int f = 0; f < 4; ++f) {
-        acc[j][f] *= kSplitUnscale;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) bad += acc[j][f][t] * 0.f;
-      }
-    if (__any(bad != bad)) {
-      const float* at_a[4];
-      const float* at_w[4];
-#pragma unroll
-      for (int f = 0; f < 4; ++f) {
-        const int r = tile_row(f);
-        const long long src = AKM ? (row0 + r < row_end ? r : -1) : source_row(r);
-        at_a[f] = src < 0 ? nullptr : AKM ? baseA + src : baseA + src * a.lda;
-      }
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int col = out_col(t);
-        at_w[t] = n0 + col >= a.n_out ? nullptr : baseW + col + (kGated && t >= 2 ? a.ffn : 0);
-      }
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int f = 0; f < 4; ++f) acc[j][f] = f32x4{0.f, 0.f, 0.f, 0.f};
-      for (int k = 0; k < K; ++k) {
-        if (k % TK / 32 != wk) continue;
-        float x[4];
-#pragma unroll
-        for (int f = 0; f < 4; ++f) x[f] = at_a[f] ? at_a[f][AKM ? (size_t)k * a.lda : (size_t)k] : 0.f;
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const float w = at_w[t] ? at_w[t][(size_t)k * a.ldw + j] : 0.f;
-#pragma unroll
-            for (int f = 0; f < 4; ++f) acc[j][f][t] = fmaf(x[f], w, acc[j][f][t]);
-          }
-      }
-    }
-
-    // The two waves of a column range exchange two row fragments each and emit the other two: 0 and 1 the wave of the
-    // first half of k.  The barrier lies between the branches, one for all waves.
+    // The two waves of a column range exchange two row fragments each and finish the other two: 0 and 1 the wave of the
+    // first half of k.  The barrier lies behind the branch, one for all waves.
     f32x4* const mine = (f32x4*)lds + wave * 8 * 64 + lane;
     const f32x4* const theirs = (const f32x4*)lds + (wave ^ 2) * 8 * 64 + lane;
+    f32x4 own[2][4];
     auto give = [&](auto f0_c) {
       constexpr int f0 = decltype(f0_c)::value;
 #pragma unroll
       for (int o = 0; o < 2; ++o)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) mine[(o * 4 + j) * 64] = acc[j][f0 + o];
+        for (int j = 0; j < 4; ++j) {
+          own[o][j] = acc[j][f0 + o];
+          mine[(o * 4 + j) * 64] = acc[j][2 - f0 + o];
+        }
     };
-    auto finish = [&](auto f0_c) {
-      constexpr int f0 = decltype(f0_c)::value;
-#pragma unroll
-      for (int o = 0; o < 2; ++o) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[j][f0 + o] += theirs[(o * 4 + j) * 64];
-        auto vec = [&](int t) { return f32x4{acc[0][f0 + o][t], acc[1][f0 + o][t], acc[2][f0 + o][t], acc[3][f0 + o][t]}; };
-#pragma unroll
-        for (int t = 0; t < (kGated ? 2 : 4); ++t)
-          f32_emit<float, EPI, WGRAD, true>(a, slot, row0 + tile_row(f0 + o), row_end, n0 + out_col(t), vec(t), vec(kGated ? t + 2 : t));
-      }
-    };
-    using F0 = std::integral_constant<int, 0>;
-    using F2 = std::integral_constant<int, 2>;
-    if (wk == 0) give(F2{});
-    else give(F0{});
+    if (wk == 0) give(std::integral_constant<int, 0>{});
+    else give(std::integral_constant<int, 2>{});
     __syncthreads();
-    if (wk == 0) finish(F0{});
-    else finish(F2{});
+#pragma unroll
+    for (int o = 0; o < 2; ++o) {
+      const int r = tile_row(2 * wk + o);
+      float bad = 0.f;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        own[o][j] = (own[o][j] + theirs[(o * 4 + j) * 64]) * kSplitUnscale;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) bad += own[o][j][t] * 0.f;
+      }
+      // Infinities, and sums past the largest scaled number (2^80 unscaled), make infinities and NaNs of the parts' products:
+      // those results, and no others, are taken from a sum by the fp32 instruction, so that a result is that of its own row
+      // and column whatever its neighbours hold.  16 rows at a time and without stages in LDS: a training step of 8192 rows,
+      // 8 slots, 1024 x 4096, takes 3150 us, 9100 if all of x is infinite.
+      if (__any(bad != bad)) {
+        const long long src = AKM ? (row0 + r < row_end ? r : -1) : source_row(r);
+        const float* const at_a = baseA + (AKM ? src : src * a.lda);  // of k = 0
+        f32x4 full[4] = {};
+        for (int k0 = 0; k0 < K; k0 += 16) {
+          float x[4];
+          f32x4 y[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int k = k0 + 4 * i + quad;
+            x[i] = k < K && src >= 0 ? at_a[AKM ? (size_t)k * a.lda : (size_t)k] : 0.f;
+            y[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (k < K && n0 + w_col < a.n_out) y[i] = *(const f32x4*)(baseW + (size_t)k * a.ldw + w_at);
+          }
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) full[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(y[i][j], x[i], full[j], 0, 0, 0);
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int t = 0; t < 4; ++t)
+            if (own[o][j][t] * 0.f != 0.f) own[o][j][t] = full[j][t];
+      }
+      auto vec = [&](int t) { return f32x4{own[o][0][t], own[o][1][t], own[o][2][t], own[o][3][t]}; };
+#pragma unroll
+      for (int t = 0; t < (kGated ? 2 : 4); ++t)
+        f32_emit<float, EPI, WGRAD, true>(a, slot, row0 + r, row_end, n0 + out_col(t), vec(t), vec(kGated ? t + 2 : t));
+    }
     __syncthreads();  // the partial sums are read: the next tile may fill the stage
   }
 }

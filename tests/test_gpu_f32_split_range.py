@@ -1,5 +1,5 @@
-"""The fp32 GEMMs on split operands where their parts are easily lost: sums of one product, small numbers
-beside ordinary ones.  20 slots, 2400 rows, two 64 x 128 tiles a CU and more: every forward GEMM and
+"""The fp32 GEMMs on split operands where their parts are easily lost: sums of one product, small numbers beside ordinary
+ones, infinities and numbers near the largest.  20 slots, 2400 rows, two 64 x 128 tiles a CU and more: every forward GEMM and
 both weight gradients run there (test_host_split_route.py holds them to that).
 
 Bounds.  A product is rounded once, by 2^-24, and what is left out of it is below 2^-30: 2^-24 1.02.  A sum of n > 1 has n
@@ -62,6 +62,10 @@ def _rows64(x, w):
     return torch.cat([x[OFF[s]:OFF[s + 1]].double() @ w[s].double() for s in range(S)])
 
 
+def _same_bits(a, b):
+    return torch.equal(a.view(torch.int32), b.view(torch.int32))
+
+
 @pytest.mark.parametrize("accumulate", [False, True])
 def test_gradients_of_slots_of_a_few_rows(accumulate):
     x, h, dyp = _normal(1, P, D), _normal(2, P, D), _normal(3, P, D)
@@ -120,3 +124,69 @@ def test_small_columns_of_the_gradients(scale, accumulate):
             # of up to 180 products: three roundings in 32 k and one where the halves meet
             bound = min(b - a + (b - a > 1), 3 * (-(-(b - a) // 32)) + 1) * ULP
             assert bool(((got[s].double() - want).abs() <= bound * size + LEAST).all()), s
+
+
+def _spoil(v, rows):
+    """Infinities, NaNs and numbers near the largest in the given rows of v; 1e30: finite, past the split's range."""
+    v = v.clone()
+    v[rows[0], 7], v[rows[1], 1], v[rows[2], 9] = float("inf"), float("-inf"), float("nan")
+    v[rows[3], 0], v[rows[3], 1] = float("inf"), float("-inf")
+    v[rows[4]] *= 1e30
+    v[rows[5]] = 3.0e38
+    return v
+
+
+def _check_spoiled(got, clean, want, rows, others):
+    """got: one row per row of the operand; want: fp64 of a fp32 operand in which infinities stand for themselves."""
+    assert _same_bits(got[others], clean[others])
+    for i in (0, 1, 2, 3, 5):
+        w = want[rows[i]].float()
+        assert torch.equal(w.isnan(), got[rows[i]].isnan())
+        assert torch.equal(w.isinf(), got[rows[i]].isinf())
+        assert torch.equal(torch.sign(w[w.isinf()]), torch.sign(got[rows[i]][w.isinf()]))
+    w = want[rows[4]]
+    assert float((got[rows[4]].double() - w).abs().max()) <= 2e-6 * float(w.abs().max())
+
+
+@pytest.mark.parametrize("act", ["gelu", "swiglu"])
+@pytest.mark.parametrize("gather", [False, True])
+def test_rows_past_the_splits_range_and_their_neighbours(act, gather):
+    n1 = FFN * (2 if act == "swiglu" else 1)
+    x, w1 = _normal(11, P, D), 0.5 + torch.rand((S, D, n1), generator=torch.Generator(device=DEV).manual_seed(12), device=DEV)
+    rows = [0, 5, 40, 76, 300, 2399]
+    others = torch.tensor([r for r in range(P) if r not in rows], device=DEV)
+    bad = _spoil(x, rows)
+    if not gather:
+        (z0, h0), (z, h) = _up(x, w1, act), _up(bad, w1, act)
+        _check_spoiled(z, z0, _rows64(bad, w1), rows, others)
+        assert _same_bits(h[others], h0[others])
+        return
+    # the same bits as of the reshuffled copy, whole layer: the second GEMM's tiles meet the rows' infinities too
+    shape, off = _shape(act), torch.from_numpy(OFF).to(DEV)
+    w2 = _normal(13, S, FFN, D)
+    perm = torch.from_numpy(np.random.default_rng(14).permutation(P).astype(np.int32)).to(DEV)
+    ws = torch.empty(lz.lz_ffn_workspace_bytes(shape), dtype=torch.uint8, device=DEV)
+    y = []
+    for v in (x, bad):
+        unpermuted = torch.empty_like(v)
+        unpermuted[perm.long()] = v
+        for fused in (False, True):
+            y.append(torch.full((P, D), 7.0, device=DEV))
+            if fused: lz.lz_expert_ffn_gather(unpermuted, perm, off, w1, w2, shape, y[-1], ws, ws.numel())
+            else: lz.lz_expert_ffn(v, off, w1, w2, shape, y[-1], ws, ws.numel())
+    assert _same_bits(y[0], y[1]) and _same_bits(y[2], y[3])
+    assert _same_bits(y[0][others], y[2][others])
+    assert y[0].isfinite().all() and not y[2][rows[0]].isfinite().any()
+
+
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_gradients_past_the_splits_range_and_their_neighbours(accumulate):
+    x, h = _normal(15, P, D), _normal(16, P, D)
+    dyp = 0.5 + torch.rand((P, D), generator=torch.Generator(device=DEV).manual_seed(17), device=DEV)
+    cols = [0, 5, 40, 76, 300, 1411]
+    others = torch.tensor([c for c in range(D) if c not in cols], device=DEV)
+    bad_h, bad_x = _spoil(h.T, cols).T.contiguous(), _spoil(x.T, cols).T.contiguous()
+    for got, clean, left in zip(_gradients(bad_x, bad_h, dyp, accumulate), _gradients(x, h, dyp, accumulate), (bad_x, bad_h)):
+        for s in np.flatnonzero(COUNTS):
+            a, b = OFF[s], OFF[s + 1]
+            _check_spoiled(got[s], clean[s], left[a:b].double().T @ dyp[a:b].double(), cols, others)
