@@ -107,6 +107,7 @@ int32_t generic_forward_train(const void* xp, const int32_t* slot_offsets, const
   a.ldw = a.ldz = n1;
   a.w_slot = (long long)d * n1;
   a.ldc = a.n_out = a.ffn = ffn;
+  a.gather_T = s->T;
   r = s->act == LZ_SWIGLU ? launch_f32_rows<Elem, EPI_SWIGLU_KEEP, true>(a, S, P, st)
                           : launch_f32_rows<Elem, EPI_GELU_KEEP, true>(a, S, P, st);
   if (r != LZ_OK) return r;

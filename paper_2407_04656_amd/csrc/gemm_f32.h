@@ -43,7 +43,7 @@ struct F32Args {
   TileTable t, t_split;  // of the kernel here; of gemm_split.h
   const int32_t* gather;  // row r of A is row gather[r] / gather_k (forward's first GEMM), or nullptr
   int gather_k;
-  long long gather_T;
+  long long gather_T;     // rows of x (first GEMM, gathered or not), 0 for the others
   const int32_t* slot_offsets;  // weight gradients
   long long P;
   int m_rows;           // weight gradients: rows of one slot's result

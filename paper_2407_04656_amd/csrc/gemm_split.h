@@ -320,7 +320,9 @@ int32_t launch_f32_rows(F32Args a, int S, long long P, hipStream_t st) {
   const long long used = P < S ? P : S;  // slots that can have rows, half a tile more each
   if constexpr (sizeof(Elem) == 4 && WKM) {
     const int cols = a.n_out * (EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_KEEP ? 2 : 1);
-    if (use_split_rows(P, S, cols, a.K) && whole_pieces(a)) {
+    // x past 31-bit offsets cannot be gathered: the calls that need not gather it take the same kernel and give the same bits
+    const bool x_fits = a.gather_T * a.lda * 4 < (1ll << 31);
+    if (use_split_rows(P, S, cols, a.K) && x_fits && whole_pieces(a)) {
       a.t = a.t_split;
       return launch_split<EPI, false>(a, cols, a.t.capacity, st);
     }

@@ -28,6 +28,21 @@ for P, S, d, ffn, w1 in ((2400, 20, 1408, 1408, A), (2400, 20, 1412, 1500, A), (
                    [[0, 0], [1, 1], "ffffff"], [[0, 0], [1, 1], "ffffff"], [[0, 0], [2, 1], "ffffff"]]
 
 
+def test_fused_unfused_and_training_forwards_run_on_the_same_kernels(tmp_path):
+    """They give the same bits, so where one cannot run on split operands (the fused one reads x through 31-bit offsets) none
+    does: the first GEMM's kernel depends on the size of x, not on the call."""
+    out = recorded(tmp_path, """
+A, W, out = At(1 << 20), At(1 << 30), []
+for T in ((1 << 19) - 1, 1 << 19):
+    s = lz.Shape(T, 1024, 1024, 8, 1, 1, 8, lz.LZ_F32, lz.LZ_GELU)
+    n = max(lz.lz_ffn_workspace_bytes(s), lz.lz_train_workspace_bytes(s))
+    for rc in (lambda: code(lz.lz_expert_ffn, A, A, A, A, s, A, W, n), lambda: code(lz.lz_expert_ffn_gather, A, A, A, A, A, s, A, W, n),
+               lambda: code(lz.lz_ffn_forward_train, A, A, A, A, s, A, A, A, W, n)):
+        out.append([rc(), "".join("s" if "gemm_split" in x else "f" for x in calls() if "gemm" in x)])
+""")
+    assert out == [[0, "ss"]] * 3 + [[0, "fs"]] * 3
+
+
 @pytest.mark.parametrize("epi,wgrad", [("EPI_SWIGLU_KEEP", "false"), ("EPI_ACCUM", "true")])
 def test_every_barrier_is_one_for_all_waves(tmp_path, epi, wgrad):
     """A barrier in code that is compiled once for each arm of a branch would be another one for the waves of each arm: the
