@@ -282,20 +282,22 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(F32Args a) {
   }
 }
 
-// Which fp32 GEMMs run here: those with two tiles a CU and more, columns and k (gradients: both widths) that fill three
-// quarters of their tiles, and 16 rows a slot on average.  us on the fp32 instruction and here: 4096 tokens, 1024 x 4096,
-// 8 slots, top-2: 644 -> 432, 656 -> 431, gradients 598 -> 390 and 383; 3000 tokens, 512 x 512 gated, top-6, 80 slots:
-// 213 -> 159, 106 -> 86, 114 -> 90, 221 -> 162; 1024 tokens, 512 x 2048, 16 slots: 63 -> 51, 61 -> 46; 256 tokens,
-// 1024 x 4096, 32 rows a slot: 74 -> 62, 120 -> 107.  Outside: 2 rows a slot 75 -> 84, 8 rows a slot 209 -> 231,
-// the down projection of 2048 x 512 at 160 tiles 59 -> 70.
+// Which fp32 GEMMs run here: those with two tiles a CU and more (gradients, whose tiles are often of one stage, four), columns
+// and k (gradients: both widths) that fill three quarters of their tiles, and 48 rows a slot on average.  us on the fp32
+// instruction and here: 4096 tokens, 1024 x 4096, 8 slots, top-2: 644 -> 490, 659 -> 524, gradients 596 -> 484 and 591 -> 478;
+// 3000 tokens, 512 x 512 gated, top-6, 80 slots: 217 -> 176, 108 -> 94, 116 -> 104, 225 -> 186; 1024 tokens, 512 x 2048,
+// 16 slots: 63 -> 60, 62 -> 55.  Of 300 layers drawn from S = 4 to 96, 16 to 600 rows a slot, d to 1300, ffn to 2600, within
+// the lines 388 GEMMs by 10 % (geometric mean; 18 slower by 3 to 14 %, just past a line); outside: 16 to 24 rows a
+// slot 3 % slower (forwards) and 6 % (gradients), 24 to 48 level, gradients of 512 to 1024 tiles 2 % slower, one tile a CU and
+// less 59 -> 70 (the down projection of 2048 x 512 at 160 tiles).
 // rows64: row tiles expected to hold rows;  fill: k, or a gradient's rows
-inline bool use_split(long long P, int S, long long rows64, int cols, int fill) {
+inline bool use_split(long long P, int S, long long rows64, int cols, int fill, int tiles_a_cu) {
   const long long padded = (long long)ceil_div(cols, kSplitCols) * kSplitCols * ceil_div(fill, 64) * 64;
-  return P >= 16ll * S && rows64 * ceil_div(cols, kSplitCols) >= 2ll * device_cus() && 4ll * cols * fill >= 3 * padded;
+  return P >= 48ll * S && rows64 * ceil_div(cols, kSplitCols) >= (long long)tiles_a_cu * device_cus() && 4ll * cols * fill >= 3 * padded;
 }
 inline bool use_split_rows(long long P, int S, int cols, int K) {
   const long long used = P < S ? P : S;  // slots that can have rows, half a tile more each
-  return use_split(P, S, P / kSplitRows + (used + 1) / 2, cols, K);
+  return use_split(P, S, P / kSplitRows + (used + 1) / 2, cols, K, 2);
 }
 // Whether a forward of this shape reads the table of 64-row tiles.
 inline bool split_forward(const lz_shape* s) {
@@ -347,7 +349,7 @@ int32_t launch_f32_wgrad(const void* A, int m_rows, const void* W, int n_out, co
   if constexpr (sizeof(Elem) == 4) {
     a.m_tiles = ceil_div(m_rows, kSplitRows);
     const long long tiles = (long long)S * a.m_tiles;
-    if (use_split(P, S, tiles, n_out, m_rows) && whole_pieces(a))
+    if (use_split(P, S, tiles, n_out, m_rows, 4) && whole_pieces(a))
       return Cacc ? launch_split<EPI_ACCUM, true>(a, n_out, tiles, st) : launch_split<EPI_NONE, true>(a, n_out, tiles, st);
   }
   a.m_tiles = ceil_div(m_rows, kF32Rows);

@@ -11,12 +11,13 @@ from hip_record import recorded
 
 
 def test_large_aligned_fp32_forwards_and_weight_gradients_are_split(tmp_path):
-    """The sizes of test_gpu_f32_split.py and test_gpu_f32_split_range.py run there; small batches, few rows a slot and unaligned tensors do not, and
-    only a forward that reads the table of 64-row tiles builds it (a workgroup per table of row tiles)."""
+    """The sizes of test_gpu_f32_split.py and test_gpu_f32_split_range.py run there; small batches, few rows a slot and
+    unaligned tensors do not, and only a forward that reads the table of 64-row tiles builds it (a workgroup per table)."""
     out = recorded(tmp_path, """
 A, U, out = At(1 << 20), At((1 << 20) + 4), []
-for P, S, d, ffn, w1 in ((2400, 20, 1408, 1408, A), (2400, 20, 1412, 1500, A), (2400, 20, 1412, 1412, A), (2048, 4, 128, 2048, A), (2400, 20, 1408, 1408, U),
-                         (256, 20, 1408, 1408, A), (256, 4, 128, 256, A), (2400, 20, 1409, 1408, A)):
+for P, S, d, ffn, w1 in ((2400, 20, 1408, 1408, A), (2400, 20, 1412, 1500, A), (2400, 20, 1412, 1412, A), (2048, 4, 128, 2048, A),
+                         (2400, 20, 1408, 1408, U), (256, 20, 1408, 1408, A), (256, 4, 128, 256, A), (2400, 20, 1409, 1408, A),
+                         (959, 20, 1408, 1408, A), (960, 20, 1408, 1408, A), (2048, 4, 1024, 1024, A), (2048, 8, 1024, 1024, A)):
     s = lz.Shape(P, d, ffn, S, 1, 1, S, lz.LZ_F32, lz.LZ_GELU)
     n = max(lz.lz_ffn_workspace_bytes(s), lz.lz_train_workspace_bytes(s))
     rc = [code(lz.lz_expert_ffn, A, A, w1, A, s, A, At(1 << 30), n), code(lz.lz_ffn_backward, A, A, A, A, A, w1, A, s, A, A, A, A, n)]
@@ -24,8 +25,9 @@ for P, S, d, ffn, w1 in ((2400, 20, 1408, 1408, A), (2400, 20, 1412, 1500, A), (
     out.append([rc, [int(x[2]) for x in c if "build_tiles" in x[1]], "".join("s" if "gemm_split" in x[1] else "f" for x in c if "gemm" in x[1])])
 """)
     # up, down, then dZ, dxp, dW2, dW1 of the backward
-    assert out == [[[0, 0], [2, 1], "ssffss"], [[0, 0], [2, 1], "ssffss"], [[0, 0], [2, 1], "ssffss"], [[0, 0], [2, 1], "sfffff"], [[0, 0], [2, 1], "fsffss"],
-                   [[0, 0], [1, 1], "ffffff"], [[0, 0], [1, 1], "ffffff"], [[0, 0], [2, 1], "ffffff"]]
+    assert out == [[[0, 0], [2, 1], "ssffss"], [[0, 0], [2, 1], "ssffss"], [[0, 0], [2, 1], "ssffss"], [[0, 0], [2, 1], "sfffff"],
+                   [[0, 0], [2, 1], "fsffss"], [[0, 0], [1, 1], "ffffff"], [[0, 0], [1, 1], "ffffff"], [[0, 0], [2, 1], "ffffff"],
+                   [[0, 0], [1, 1], "ffffff"], [[0, 0], [1, 1], "ffffss"], [[0, 0], [1, 1], "ffffff"], [[0, 0], [1, 1], "ffffss"]]
 
 
 def test_fused_unfused_and_training_forwards_run_on_the_same_kernels(tmp_path):
