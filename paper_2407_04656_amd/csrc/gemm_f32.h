@@ -197,7 +197,6 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(F32Args a) {
       slot = __builtin_amdgcn_readfirstlane(a.t.slot[row_tile]);  // the same in every lane: buffer bases are scalar
       row0 = __builtin_amdgcn_readfirstlane(a.t.row0[row_tile]);
       row_end = __builtin_amdgcn_readfirstlane(a.t.row_end[row_tile]);
-      if (slot < 0) continue;
       W += (size_t)slot * a.w_slot;
     }
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;

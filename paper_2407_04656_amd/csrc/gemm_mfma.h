@@ -1,10 +1,11 @@
-// Grouped bf16 GEMM on the gfx950 matrix cores and the row-tile table it draws its work from;
+// Grouped bf16 GEMM on the gfx950 matrix cores and the tables that it and the other grouped GEMMs draw their work from;
 // shared by the forward and the backward translation units (device code, not part of the C ABI).
 //
 //   C[rows of a slot, n] = epi( sum_k A(row, k) * W[slot](n, k) )
 //
-// Persistent kernel, one workgroup per CU, drawing 256x256 tiles from its XCD's queue.  4 waves
-// in 2x2, each wave a 128x128 patch = 8x8 v_mfma_f32_16x16x32_bf16 accumulators (fp32, 256
+// Persistent kernel, one workgroup per CU, drawing tiles of up to 256 rows (256, 192, 128 or 64 by the launch, a slot's last
+// one fewer) x 256 columns from its XCD's queue.  4 waves
+// in 2x2, each wave a 128x128 patch (of 256 rows) = 8x8 v_mfma_f32_16x16x32_bf16 accumulators (fp32, 256
 // AGPRs).  With every CU busy the chip is power-limited, and an MFMA-only loop of this shape
 // sustains 15 % more flops than one of v_mfma_f32_32x32x16_bf16 (2.03 against 1.76 PFLOP/s on
 // random operands; at a quarter of the CUs both reach the nominal rate).  Operand tiles are
@@ -145,8 +146,8 @@ constexpr int kTileThreads = 512, kTileWaves = kTileThreads / lz::kWave;  // of 
 
 // The unit lists: a wave each, a record a lane, 64 at a time; s_first: first group of every slot.  A record's slot is found
 // by bisection, a read of LDS per factor of two of the slots: runs of records a lane that step from slot to slot, and a
-// division per slot in sum_tile_costs below, took 20.4 us for the tables of 1024 slots where this takes 13.6, 8.7 for those of
-// 128 (7.9).
+// division per slot in sum_tile_costs below, took 20.4 us for a forward's tables of 1024 slots where this takes 13.6 (128 slots:
+// 8.7 and 7.9).
 __device__ __forceinline__ void deal_units(const SlotRows& slots, int S, const TileSpec& spec, int rows_per_tile,
                                            const int* s_first, int tid) {
   const int ncg = (spec.n_tiles + kGroupN - 1) / kGroupN;
@@ -353,24 +354,23 @@ __device__ __forceinline__ constexpr int a_stage_off(int s) { return s * kATile;
 __device__ __forceinline__ constexpr int w_stage_off(int w) { return 2 * kATile + w * kWTile; }
 
 struct MfmaArgs {
-  const uint16_t* A;    // MODE_NT, MODE_NN: [P, K];  MODE_TN: [k_rows, lda]
-  const uint16_t* W;    // MODE_NT: [S, w_rows, K];  MODE_NN: [S, K, ldw];  MODE_TN: [k_rows, ldw]
+  const uint16_t* A;    // MODE_NT, MODE_NN: [P, K];  MODE_TN: [rows of the batch, lda]
+  const uint16_t* W;    // MODE_NT: [S, w_rows, K];  MODE_NN: [S, K, ldw];  MODE_TN: [rows of the batch, ldw]
   uint16_t* C;          // [P, n_out]
   float* Cacc;          // EPI_ACCUM: [P, n_out] fp32, read, added to and written back
   long long P;          // rows of C (MODE_TN: S * rows_per_slot virtual rows)
-  int K;                // contraction length (MODE_TN: per slot, from slot_offsets)
+  int K;                // contraction length (MODE_TN: per slot, in its units' records)
   int w_rows;           // MODE_NT: weight rows per slot
   int n_out;            // output columns
   int up_row0;          // SwiGLU: offset of the up projection inside a slot's W (rows, or columns if k-major)
   int n_tiles;          // column tiles per row tile
   TileTable t;          // narrow kernel
   UnitTable u;          // wide kernel
-  // MODE_TN (weight gradients): slot s contracts over its rows of the batch (in its units' records)
-  // of both operands and owns rows_per_slot rows of C (row index = s * rows_per_slot + m, m =
-  // column of A).
   uint16_t* Z;          // *_KEEP epilogues: pre-activations [P, z_cols] (SwiGLU: gate columns, then up columns)
   int z_cols;
   int lda, ldw;         // row strides (elements) of the k-major operands
+  // MODE_TN (weight gradients): slot s contracts over its rows of the batch of both operands and owns rows_per_slot rows
+  // of C (row index = s * rows_per_slot + m, m = column of A)
   int rows_per_slot;
   // GATHER (forward only): A is x [gather_T, K] and row r of the permuted buffer is row
   // gather[r] / gather_k of it (gather = row_to_pair of the dispatcher)

@@ -24,7 +24,7 @@ constexpr int kNarrowLds = kNarrowStages * kNarrowStage;  // 64 KiB
 // row pairs 64 bytes and the second group 32 bytes apart: eight different bank groups.
 __device__ __forceinline__ int swz_narrow(int kr) { return (((kr >> 1) & 1) << 2) | (((kr >> 3) & 1) << 1); }
 
-// blockIdx.x = row tile of the table (64 rows, no padding entries) x column tile, columns fastest and padded
+// blockIdx.x = row tile of the table (64 rows) x column tile, columns fastest and padded
 // to a multiple of 8 from 8 on: the row tiles that share a column panel of W run on one XCD.
 template <int EPI, int MODE, bool GATHER, bool KTAIL>
 __global__ __launch_bounds__(256, 2) void gemm_narrow_kernel(MfmaArgs a) {
@@ -39,7 +39,6 @@ __global__ __launch_bounds__(256, 2) void gemm_narrow_kernel(MfmaArgs a) {
   const int slot = __builtin_amdgcn_readfirstlane(a.t.slot[row_tile]);
   const int row0 = __builtin_amdgcn_readfirstlane(a.t.row0[row_tile]);
   const int row_end = __builtin_amdgcn_readfirstlane(a.t.row_end[row_tile]);
-  if (slot < 0) return;
   const int n0 = col_tile * kNarrow;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave >> 1, wn = wave & 1;
