@@ -83,3 +83,61 @@ def test_units_of_the_persistent_kernel(counts):
         z = x[a:b].double() @ w1[s].double()
         ref = (torch.nn.functional.silu(z[:, :ffn]) * z[:, ffn:]) @ w2[s].double()
         assert float((out[0][a:b].double() - ref).abs().max()) <= 2e-2 * float(ref.abs().max())  # bf16 h and y
+
+
+def _round_up(n, to):
+    return -(-n // to) * to
+
+
+def _tile_rows(counts, d, ffn, act):
+    """Rows of a tile in the two GEMMs' unit tables, from the forward's workspace: hidden, then a table of the first GEMM and
+    one of the second; 0: none (narrow tiles)."""
+    S, P = len(counts), sum(counts)
+    c = next(c for c in range(64, 0, -1) if S % c == 0)
+    shape = lz.Shape(P, d, ffn, 1, 1, S // c, c, lz.LZ_BF16, act)
+    n = lz.lz_ffn_workspace_bytes(shape)
+    ws = torch.zeros(n, dtype=torch.uint8, device=DEV)
+    lz.lz_ffn_tiles(to_dev(np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)), shape, ws, n)
+    ints = ws.cpu().numpy().view(np.int32)
+    up = _round_up(P * ffn * 2, 256) // 4
+    units = -(-(P // 256 + S) * -(-_columns(d, ffn, act)[0] // 8) // 8)            # of an XCD's list; 8 ints each, after a
+    down = up + _round_up((64 + 17 * 32 + 8 * 8 * units) * 4, 256) // 4             # header of 64 ints and 17 lines of counters
+    return [int(ints[up + 16]), int(ints[down + 16])]
+
+
+def _columns(d, ffn, act):
+    return -(-ffn // (128 if act == lz.LZ_SWIGLU else 256)), -(-d // 256)
+
+
+def _first_to_end(counts, n_tiles):
+    """The height with which N tiles on the CUs end first: ceil(N / CUs) rounds of a tile's mean cost, a lower one only
+    if it gains 5 %."""
+    cost, cus = {0: 0, 1: 50, 2: 65, 3: 82, 4: 100}, torch.cuda.get_device_properties(0).multi_processor_count // 8 * 8
+    if sum(counts) / 256 * n_tiles > 16 * cus:
+        return 256
+    best = None
+    for h in (4, 3, 2, 1):
+        tiles = sum(-(-n // (64 * h)) for n in counts)
+        total = sum(n // (64 * h) * cost[h] + cost[-(-(n % (64 * h)) // 64)] for n in counts)
+        time = -(-tiles * n_tiles // cus) * total / tiles
+        if best is None or time < 0.95 * best[0]:
+            best = time, 64 * h
+    return best[1]
+
+
+@pytest.mark.parametrize("counts,d,ffn,act,want", [
+    ([683] * 60, 264, 2600, lz.LZ_SWIGLU, [256, 192]),        # the three of test_units_of_the_persistent_kernel
+    ([300, 301] * 15, 264, 2600, lz.LZ_SWIGLU, [256, 128]),
+    ([130] * 3, 264, 2600, lz.LZ_SWIGLU, [64, 0]),
+    ([130] * 40, 768, 768, lz.LZ_GELU, [128, 128]),
+    ([400] * 12, 2600, 2600, lz.LZ_GELU, [192, 192]),
+    ([16384], 4096, 4096, lz.LZ_GELU, [256, 256]),
+    ([0, 1, 63, 65, 129, 191, 193, 255, 257, 700] * 6, 768, 1304, lz.LZ_GELU, None),
+    ([(37 * i) % 500 for i in range(1024)], 512, 512, lz.LZ_GELU, None),
+])
+def test_tile_heights(counts, d, ffn, act, want):
+    got = _tile_rows(counts, d, ffn, act)
+    model = [_first_to_end(counts, n) if g else 0 for n, g in zip(_columns(d, ffn, act), got)]
+    assert got == model and any(got)
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert want is None or got == want

@@ -45,6 +45,20 @@ for T in ((1 << 19) - 1, 1 << 19):
     assert out == [[0, "ss"]] * 3 + [[0, "fs"]] * 3
 
 
+def test_gathered_gated_and_accumulating_calls_are_split_too(tmp_path):
+    """The calls of test_gpu_f32_split_range.py, both activations: 2400 rows, 20 slots."""
+    out = recorded(tmp_path, """
+A, W, out = At(1 << 20), At(1 << 30), []
+for act in (lz.LZ_GELU, lz.LZ_SWIGLU):
+    s = lz.Shape(2400, 1412, 1500, 20, 1, 1, 20, lz.LZ_F32, act)
+    n = max(lz.lz_ffn_workspace_bytes(s), lz.lz_train_workspace_bytes(s))
+    rc = [code(lz.lz_expert_ffn_gather, A, A, A, A, A, s, A, W, n), code(lz.lz_ffn_forward_train, A, A, A, A, s, A, A, A, W, n),
+          code(lz.lz_ffn_backward_accumulate, A, A, A, A, A, A, A, s, A, A, A, W, n)]
+    out.append([rc, "".join("s" if "gemm_split" in x else "f" for x in calls() if "gemm" in x)])
+""")
+    assert out == [[[0, 0, 0], "ss" + "ss" + "ffss"]] * 2
+
+
 @pytest.mark.parametrize("epi,wgrad", [("EPI_SWIGLU_KEEP", "false"), ("EPI_ACCUM", "true")])
 def test_every_barrier_is_one_for_all_waves(tmp_path, epi, wgrad):
     """A barrier in code that is compiled once for each arm of a branch would be another one for the waves of each arm: the
