@@ -16,14 +16,14 @@
 //
 // Tile: 64 rows x 128 columns, stages of 64 k, four waves: two column ranges of 64 times two halves of each stage's k,
 // added through LDS at the end.  A goes global -> registers (one stage ahead) -> split -> LDS, [row][plane][k] with a
-// pitch of 25 x 16 bytes, so that a fragment's 16 rows (one ds_read_b128 a lane) cover the banks once.  W no other
-// wave needs: it goes from global straight to the fragments, a lane loading 4 adjacent columns at its 8 k and splitting
-// the pairs of k in place; its four fragments are the columns 4 i + j, j = 0..3, and a lane's accumulators of them are
+// pitch of 25 x 16 bytes, so that a fragment's 16 rows (one ds_read_b128 a lane) cover the banks once.  W no other wave
+// needs: it goes from global straight to the fragments, a lane loading 4 adjacent columns at its 8 k and splitting the
+// pairs of k in place; its four fragments are the columns 4 i + j, j = 0..3, and a lane's accumulators of them are
 // adjacent columns again.  Two workgroups share a CU.  What bounds it: the split and the additions (some 400 vector
-// instructions to 128 MFMAs a stage) and the latency of a stage.  Tried: both operands through LDS (up projection of
-// 512 x 2048, 16 slots, 2048 rows 53 us against 49), column ranges of one wave (tiles of 64 x 256, all k: 54, and
-// 114 against 70 where tiles are few) or of four (64 x 64: 63), one run of tiles per XCD (level, gradients 20 % slower),
-// and the data gradients, whose W lies along k (65 us against 58 of the fp32 instruction).
+// instructions to 128 MFMAs a stage) and the latency of a stage.  Tried, with six products: both operands through LDS
+// (up projection of 512 x 2048, 16 slots, 2048 rows 53 us against 49), column ranges of one wave (tiles of 64 x 256,
+// all k: 54, and 114 against 70 where tiles are few) or of four (64 x 64: 63), one run of tiles per XCD (level,
+// gradients 20 % slower), and the data gradients, whose W lies along k (65 us against 58 of the fp32 instruction).
 #pragma once
 #include "gemm_f32.h"
 
