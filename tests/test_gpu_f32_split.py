@@ -1,6 +1,6 @@
 """The fp32 GEMM on split operands: the sizes that it takes (two 64 x 128 tiles a CU and more), at the edges of tiles,
-stages and fragments, against fp64.  Bound: each of K products is rounded below 2^-22, the sum at most twice in 32 k,
-with a random walk of K / 16 roundings of 2^-24: 2e-6 of the largest value at K <= 1500."""
+stages and fragments, against fp64.  Bound: the products are exact to 2^-30, the sum is rounded at most three times in 32 k,
+a random walk of 3 K / 32 roundings of 2^-24: 2e-6 of the largest value at K <= 1500."""
 import numpy as np
 import pytest
 import torch
