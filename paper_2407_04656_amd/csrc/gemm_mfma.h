@@ -142,17 +142,32 @@ struct SlotRows {
   int first[lz::kMaxN * lz::kMaxC], end[lz::kMaxN * lz::kMaxC];
 };
 
+// Inclusive scan of a wave by add(so far, lower lanes' part): a few cycles a step by DPP, where a shuffle through LDS takes 100.
+template <typename Add>
+__device__ __forceinline__ int wave_scan(int v, Add add) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  v = add(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false));  // row_shr 1, 2, 4, 8 within 16 lanes
+  v = add(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false));
+  v = add(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false));
+  v = add(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false));
+  v = add(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false));  // row_bcast 15 into rows 1 and 3
+  v = add(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false));  // row_bcast 31 into rows 2 and 3
+#endif
+  return v;
+}
+
 constexpr int kTileThreads = 512, kTileWaves = kTileThreads / lz::kWave;  // of a table: a wave per unit list
 
 // The unit lists: a wave each, a record a lane, 64 at a time; s_first: first group of every slot.  A record's slot is found
-// by bisection, a read of LDS per factor of two of the slots: runs of records a lane that step from slot to slot, and a
-// division per slot in sum_tile_costs below, took 20.4 us for a forward's tables of 1024 slots where this takes 13.6 (128 slots:
-// 8.7 and 7.9).
+// by bisection, a read of LDS per factor of two of the slots.  What bounds the tables is one chain of latencies: runs of records a
+// lane that step from slot to slot, a division per slot, scans by shuffles, tables of constants in memory and specs that every lane
+// reads from the kernel's arguments took 7.4, 8.7 and 20.4 us for a forward's tables of 16, 128 and 1024 slots, where this takes
+// 5.6, 6.3 and 11.3 (a launch of nothing: 4).
 __device__ __forceinline__ void deal_units(const SlotRows& slots, int S, const TileSpec& spec, int rows_per_tile,
                                            const int* s_first, int tid) {
   const int ncg = (spec.n_tiles + kGroupN - 1) / kGroupN;
   const int n_units = s_first[S] * ncg;
-  const int x = tid / lz::kWave, lane = tid % lz::kWave;
+  const int x = __builtin_amdgcn_readfirstlane(tid / lz::kWave), lane = tid % lz::kWave;
   static_assert(kTileWaves == 8, "one list per XCD");
   const int full = n_units / 8, count = full + (((full & 1) ? 7 - x : x) < n_units % 8 ? 1 : 0);
   const int cols = spec.n_tiles / ncg, more = spec.n_tiles % ncg;  // column groups of `cols`, the first `more` of one more
@@ -177,17 +192,12 @@ __device__ __forceinline__ void deal_units(const SlotRows& slots, int S, const T
     for (int i = 1; i < kGroupM; ++i) nr += b - row0 > i * rows_per_tile ? 1 : 0;
     const int nc = cols + (c < more ? 1 : 0);
     const int mine = in ? nr * nc : 0;
-    int incl = mine;
-#pragma unroll
-    for (int off = 1; off < lz::kWave; off <<= 1) {
-      const int n = __shfl_up(incl, off);
-      if (lane >= off) incl += n;
-    }
+    const int incl = wave_scan(mine, [](int x, int y) { return x + y; });
     if (in) {
       list[2 * r] = i32x4{tickets + incl - mine, s, row0, b};
       list[2 * r + 1] = i32x4{nr | nc << 8, c * cols + (c < more ? c : more), k0, k1};
     }
-    tickets += __shfl(incl, lz::kWave - 1);
+    tickets += __builtin_amdgcn_readlane(incl, lz::kWave - 1);
   }
   if (lane == 0) {
     spec.units.header[x] = tickets;
@@ -203,20 +213,19 @@ __device__ __forceinline__ void deal_units(const SlotRows& slots, int S, const T
 // 2.2 rounds of them (the down projection of 40960 tokens over 60 slots, 3072 x 768) 192 rows make 2.9 shorter ones:
 // that training step 1743 -> 1706 us, a forward of 3001 tokens (12 slots, 1000 x 2664, SwiGLU) 197 -> 186.
 // A row's result does not depend on the tile it is in.
-__device__ constexpr int kTileCost[5] = {0, 50, 65, 82, 100};  // by rows in 64s
+__device__ __forceinline__ int tile_cost(int n64) { return int(0x6452413200ull >> (8 * n64)) & 255; }  // by rows in 64s
 // Of a table's 512 threads each wave leaves one sum in s_sum: tiles (wave w < 4) or cost of tiles of 64 (w % 4 + 1) rows.
 template <typename RowsOf>
 __device__ __forceinline__ void sum_tile_costs(int S, int tid, unsigned* s_sum, RowsOf rows_of) {
-  const int lane = tid % lz::kWave, wave = tid / lz::kWave, n64 = wave % 4 + 1;
+  const int lane = tid % lz::kWave, wave = __builtin_amdgcn_readfirstlane(tid / lz::kWave), n64 = wave % 4 + 1;
   static_assert(kTileWaves == 8, "a wave per sum");
   unsigned sum = 0;
   for (int s = lane; s < S; s += lz::kWave) {
     const int all64 = (int)(((unsigned)rows_of(s) + 63) / 64), full = n64 == 3 ? all64 / 3 : all64 >> (n64 / 2), tail = all64 - full * n64;
-    sum += wave < 4 ? full + (tail > 0 ? 1 : 0) : full * kTileCost[n64] + kTileCost[tail];
+    sum += wave < 4 ? full + (tail > 0 ? 1 : 0) : full * tile_cost(n64) + tile_cost(tail);
   }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
-  if (lane == 0) s_sum[wave] = sum;
+  sum = wave_scan(sum, [](int x, int y) { return (int)((unsigned)x + (unsigned)y); });
+  if (lane == lz::kWave - 1) s_sum[wave] = sum;
 }
 __device__ __forceinline__ bool many_rounds(int S, const TileSpec& spec, int workgroups) {
   const float rows = spec.virtual_rows > 0 ? (float)S * (float)spec.virtual_rows : (float)spec.P;
@@ -245,7 +254,8 @@ __global__ __launch_bounds__(2 * kTileThreads) void build_tiles_kernel(const int
   __shared__ int s_firsts[2][lz::kMaxN * lz::kMaxC + 1];
   __shared__ int s_waves[2][kTileWaves];
   __shared__ unsigned s_sums[2][kTileWaves];
-  const int half = threadIdx.x / kTileThreads, tid = threadIdx.x % kTileThreads;
+  // scalar: so that a table's spec is read by scalar loads, not by every lane from the kernel's arguments
+  const int half = __builtin_amdgcn_readfirstlane(threadIdx.x / kTileThreads), tid = threadIdx.x % kTileThreads;
   const int unit_groups = (n_units + 1) / 2, b = blockIdx.x;
   const int table = b < unit_groups ? 2 * b + half : b - unit_groups + n_units;
   // a half without a table of its own follows the other's steps up to the barriers and writes nothing
@@ -256,7 +266,7 @@ __global__ __launch_bounds__(2 * kTileThreads) void build_tiles_kernel(const int
   const TileTable t = spec.rows;
   const bool units = spec.n_tiles > 0;
   const int capacity = units ? spec.units.groups : t.capacity;
-  const int lane = tid % lz::kWave, wave = tid / lz::kWave;
+  const int lane = tid % lz::kWave, wave = __builtin_amdgcn_readfirstlane(tid / lz::kWave);
   for (int s = threadIdx.x; s < S; s += blockDim.x) {
     long long a, b;
     clip_slot(slot_offsets, s, spec.P, &a, &b);  // the tables of a launch have one P
@@ -286,12 +296,7 @@ __global__ __launch_bounds__(2 * kTileThreads) void build_tiles_kernel(const int
     s_first[s] = mine;
     mine = add(mine, tiles < capacity ? tiles : capacity);
   }
-  int incl = mine;
-#pragma unroll
-  for (int off = 1; off < lz::kWave; off <<= 1) {
-    const int n = __shfl_up(incl, off);
-    if (lane >= off) incl = add(incl, n);
-  }
+  const int incl = wave_scan(mine, add);
   if (lane == lz::kWave - 1) s_wave[wave] = incl;
   const int before = __shfl_up(incl, 1);
   __syncthreads();
