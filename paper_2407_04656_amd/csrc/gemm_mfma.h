@@ -142,20 +142,6 @@ struct SlotRows {
   int first[lz::kMaxN * lz::kMaxC], end[lz::kMaxN * lz::kMaxC];
 };
 
-// Inclusive scan of a wave by add(so far, lower lanes' part): a few cycles a step by DPP, where a shuffle through LDS takes 100.
-template <typename Add>
-__device__ __forceinline__ int wave_scan(int v, Add add) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  v = add(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false));  // row_shr 1, 2, 4, 8 within 16 lanes
-  v = add(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false));
-  v = add(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false));
-  v = add(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false));
-  v = add(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false));  // row_bcast 15 into rows 1 and 3
-  v = add(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false));  // row_bcast 31 into rows 2 and 3
-#endif
-  return v;
-}
-
 constexpr int kTileThreads = 512, kTileWaves = kTileThreads / lz::kWave;  // of a table: a wave per unit list
 
 // The unit lists: a wave each, a record a lane, 64 at a time; s_first: first group of every slot.  A record's slot is found
@@ -192,7 +178,7 @@ __device__ __forceinline__ void deal_units(const SlotRows& slots, int S, const T
     for (int i = 1; i < kGroupM; ++i) nr += b - row0 > i * rows_per_tile ? 1 : 0;
     const int nc = cols + (c < more ? 1 : 0);
     const int mine = in ? nr * nc : 0;
-    const int incl = wave_scan(mine, [](int x, int y) { return x + y; });
+    const int incl = lz::wave_scan(mine, [](int x, int y) { return x + y; });
     if (in) {
       list[2 * r] = i32x4{tickets + incl - mine, s, row0, b};
       list[2 * r + 1] = i32x4{nr | nc << 8, c * cols + (c < more ? c : more), k0, k1};
@@ -224,7 +210,7 @@ __device__ __forceinline__ void sum_tile_costs(int S, int tid, unsigned* s_sum, 
     const int all64 = (int)(((unsigned)rows_of(s) + 63) / 64), full = n64 == 3 ? all64 / 3 : all64 >> (n64 / 2), tail = all64 - full * n64;
     sum += wave < 4 ? full + (tail > 0 ? 1 : 0) : full * tile_cost(n64) + tile_cost(tail);
   }
-  sum = wave_scan(sum, [](int x, int y) { return (int)((unsigned)x + (unsigned)y); });
+  sum = lz::wave_scan(sum, [](int x, int y) { return (int)((unsigned)x + (unsigned)y); });
   if (lane == lz::kWave - 1) s_sum[wave] = sum;
 }
 __device__ __forceinline__ bool many_rounds(int S, const TileSpec& spec, int workgroups) {
@@ -296,7 +282,7 @@ __global__ __launch_bounds__(2 * kTileThreads) void build_tiles_kernel(const int
     s_first[s] = mine;
     mine = add(mine, tiles < capacity ? tiles : capacity);
   }
-  const int incl = wave_scan(mine, add);
+  const int incl = lz::wave_scan(mine, add);
   if (lane == lz::kWave - 1) s_wave[wave] = incl;
   const int before = __shfl_up(incl, 1);
   __syncthreads();

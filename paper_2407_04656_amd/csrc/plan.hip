@@ -1,19 +1,21 @@
 // The flexible token dispatcher (Algorithm 1, Sec. 4.2) for all source ranks at once.
 //
-// Four kernels on one stream, no host synchronisation, no order-dependent atomics:
+// Three kernels on one stream, no host synchronisation, no order-dependent atomics:
 //   count    each wave owns a chunk of <= 128 consecutive pairs of ONE source rank and
-//            histograms their expert ids with LDS atomics (counts commute)
-//   schedule one workgroup per expert scans the chunk histograms into per-(expert, rank) list
-//            positions and evaluates the algorithm's counts in exact integers, in LDS; one
-//            more workgroup then cuts every (expert, rank) receive list over that rank's
-//            replicas and scans the slot sizes
-//   place    each wave revisits its chunk; a pair's position in its (expert, source rank)
+//            histograms their expert ids with LDS atomics (counts commute); a workgroup's chunks are neighbours of
+//            one rank, so that tables of (expert, chunk) are written and read in runs
+//   schedule one workgroup per expert scans the chunk counts into per-(expert, rank) list
+//            positions, evaluates the algorithm's counts in exact integers, in LDS, and cuts the expert's
+//            receive lists over its slots
+//   place    every workgroup scans the slot sizes; each wave revisits its chunk: a pair's position in its (expert, source rank)
 //            list is chunk base + ordered rank inside the chunk (wave ballots, one per
 //            bit of an expert index), which fixes destination rank, slot and row
-// Small batches take all of it in one workgroup (plan_small_kernel).
-// Each is a chain of dependent lookups over little data: latency bound.  32768 tokens, 256 experts, top-8, 32
-// ranks of 10 slots, the four kernels and the routing: 109 us -> 50 us with the lookups of a chunk's two halves
-// side by side, more waves on the chunk scans and the closed form of the assignments.
+// Where ids and experts are few enough the expert's workgroup counts its pairs itself, and small batches take all of it in one
+// workgroup (plan_small_kernel).
+// Each is a chain of dependent lookups over little data, and a launch of nothing takes 2.7 us: latency bound.  us of a plan, with a
+// launch of one workgroup for the slots, scans by shuffles, tables of (chunk, expert) and every lookup in memory, and now (chunks
+// a workgroup: 4, 8, 16): 16384 pairs, 8 experts, 8 ranks of 2 slots 18.7, now 13.3, 13.5, 14.4; 98304 pairs, 64 experts, 16 ranks of
+// 8 21.8, now 15.7, 15.4, 16.4; 262144 pairs, 256 experts, 32 ranks of 10 41.7, now 31.7, 28.3, 28.1.
 #include <mutex>
 
 #include "lz_common.h"
@@ -21,30 +23,28 @@
 namespace {
 
 constexpr int kChunk = 128;          // pairs per wave-chunk
-constexpr int kWavesPerBlock = 4;
+constexpr int kGroup = 8;            // chunks of a workgroup, a wave each, all of one source rank
 constexpr int kSchedThreads = 1024;
 
 struct PlanTables {
   // per chunk
-  int32_t* chunkcnt;   // [nch, E]
-  int32_t* chunkbase;  // [nch, E]  position of the chunk's first pair of e in its (e, rank) list
+  int nch;             // room for chunks
+  int32_t* chunkcnt;   // [E, nch]
+  int32_t* chunkbase;  // [E, nch]  position of the chunk's first pair of e in its (e, rank) list
   int32_t* chunkflag;  // [nch]
   // per (expert, rank)
-  int32_t* Tej;        // [E, N]
-  int32_t* R;          // [E, N]
-  int32_t* recv;       // [E, N]
-  int32_t* ejstart;    // [E, N]  index of the first slot of e in rank j's sorted slot list
+  int4* lists;         // [E, N]  pairs that rank j receives for e, its replicas of e, the first of those in its sorted slots
   int32_t* estatus;    // [E]     status bits raised while scheduling expert e
   // per (expert, src, dst)
-  int32_t* D;          // [E, N, N]
-  int32_t* cumDst;     // [E, N, N+1] prefix of D over dst
+  int32_t* cumDst;     // [N src, E, N+1] prefix of D over dst
   int32_t* preSrc;     // [E, N, N]   prefix of D over src
   // per slot
   int32_t* slot_sorted;  // [S] rank j's slots ordered by (expert, slot id)
   size_t total_bytes;
 };
 
-__host__ __device__ inline int max_chunks(long long P, int N) { return int((P + kChunk - 1) / kChunk) + N; }
+inline int max_chunks(long long P, int N) { return int((P + kChunk - 1) / kChunk) + N; }
+inline int max_groups(long long P, int N) { return int((P + kChunk * kGroup - 1) / (kChunk * kGroup)) + N; }
 
 PlanTables carve(void* ws, const lz_shape* s) {
   PlanTables t{};
@@ -57,15 +57,14 @@ PlanTables carve(void* ws, const lz_shape* s) {
     off += lz::align256(n_ints * sizeof(int32_t));
     return p;
   };
+  t.nch = (int)nch;
   t.chunkcnt = take(nch * E);
   t.chunkbase = take(nch * E);
   t.chunkflag = take(nch);
-  t.Tej = take(E * N);
-  t.R = take(E * N);
-  t.recv = take(E * N);
-  t.ejstart = take(E * N);
+  t.lists = (int4*)take(E * N);
+  for (int i = 1; i < 4; ++i) take(E * N);  // ... of four ints each
   t.estatus = take(E);
-  t.D = take(E * N * N);
+  take(E * N * N);  // room that no kernel uses: which shapes fit LZ_PLAN_NOALLOC_SCRATCH_BYTES is part of the interface
   t.cumDst = take(E * N * (N + 1));
   t.preSrc = take(E * N * N);
   t.slot_sorted = take(S);
@@ -73,33 +72,42 @@ PlanTables carve(void* ws, const lz_shape* s) {
   return t;
 }
 
+__device__ __forceinline__ int scan_sum(int v) {
+  return lz::wave_scan(v, [](int x, int y) { return x + y; });
+}
+__device__ __forceinline__ int last_lane(int v) { return __builtin_amdgcn_readlane(v, lz::kWave - 1); }
+// of the lane below, 0 in the first
+__device__ __forceinline__ int from_lane_below(int v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_update_dpp(0, v, 0x138, 0xF, 0xF, false);  // wave_shr 1
+#else
+  return v;
+#endif
+}
+
 // Sanitised batch split and the chunk table derived from it, rebuilt by every workgroup: called by its first
 // wave, lane i for the end of rank i (N <= 64).  An entry counts for at least its predecessors and at most T,
 // the last for T.  Returns true (in every lane) if rank_tok_off had to be repaired.
+// s_off: first tokens, s_cf: first chunks, s_gf (if any): first workgroups of the ranks.
 __device__ bool build_split(const int32_t* __restrict__ rank_tok_off, int T, int N, int k,
-                            int* s_off, int* s_cf) {
+                            int* s_off, int* s_cf, int* s_gf = nullptr) {
   const int lane = threadIdx.x;  // < 64
   const int raw = lane < N ? rank_tok_off[lane + 1] : T;
-  int v = lane < N - 1 ? (raw < 0 ? 0 : raw > T ? T : raw) : T;
-  const int own = v;
-#pragma unroll
-  for (int off = 1; off < lz::kWave; off <<= 1) {
-    const int n = __shfl_up(v, off);
-    if (lane >= off && n > v) v = n;
-  }
-  const int up = __shfl_up(v, 1);
-  const int prev = lane == 0 ? 0 : up;
+  const int own = lane < N - 1 ? (raw < 0 ? 0 : raw > T ? T : raw) : T;
+  const int v = lz::wave_scan(own, [](int x, int y) { return x > y ? x : y; });
+  const int prev = from_lane_below(v);
   const bool bad = lane < N - 1 ? raw < 0 || raw > T || own < prev : lane == N - 1 && raw != T;
-  int chunks = lane < N ? int(((long long)(v - prev) * k + kChunk - 1) / kChunk) : 0;
-#pragma unroll
-  for (int off = 1; off < lz::kWave; off <<= 1) {
-    const int n = __shfl_up(chunks, off);
-    if (lane >= off) chunks += n;
-  }
+  const int own_chunks = lane < N ? int(((long long)(v - prev) * k + kChunk - 1) / kChunk) : 0;
+  const int chunks = scan_sum(own_chunks);
   if (lane == 0) s_off[0] = s_cf[0] = 0;
   if (lane < N) {
     s_off[lane + 1] = v;
     s_cf[lane + 1] = chunks;
+  }
+  if (s_gf != nullptr) {
+    const int groups = scan_sum((own_chunks + kGroup - 1) / kGroup);
+    if (lane == 0) s_gf[0] = 0;
+    if (lane < N) s_gf[lane + 1] = groups;
   }
   return __any(bad) || rank_tok_off[0] != 0;
 }
@@ -121,32 +129,55 @@ __device__ __forceinline__ int chunk_range(int b, int N, int k, const int* s_off
   return i;
 }
 
-__global__ __launch_bounds__(256) void count_kernel(const int32_t* __restrict__ ids,
+// This workgroup's source rank, N if it has no chunks.
+__device__ __forceinline__ int group_rank(const int* s_gf, int N) {
+  const int lane = threadIdx.x % lz::kWave;
+  return __popcll(__ballot(lane < N && s_gf[lane + 1] <= (int)blockIdx.x));
+}
+
+// The chunk of wave w of this workgroup, whose rank is i: index (or -1) and pair range.
+__device__ __forceinline__ int group_chunk(int i, int w, int k, const int* s_off, const int* s_cf, const int* s_gf, long long* p0,
+                                           long long* p1) {
+  const int in_rank = ((int)blockIdx.x - s_gf[i]) * kGroup + w, b = s_cf[i] + in_rank;
+  if (b >= s_cf[i + 1]) return -1;
+  const long long begin = (long long)s_off[i] * k + (long long)in_rank * kChunk, end = (long long)s_off[i + 1] * k;
+  *p0 = begin;
+  *p1 = begin + kChunk < end ? begin + kChunk : end;
+  return b;
+}
+
+constexpr int kRowE = lz::kMaxE + 1;  // of LDS rows of experts, one a wave: a column's entries lie in different banks
+
+__global__ __launch_bounds__(kGroup * lz::kWave) void count_kernel(const int32_t* __restrict__ ids,
                                                     const int32_t* __restrict__ rank_tok_off, int T,
                                                     int E, int N, int k, PlanTables t,
                                                     int32_t* __restrict__ row_to_pair) {
-  __shared__ int s_off[lz::kMaxN + 1], s_cf[lz::kMaxN + 1];
-  __shared__ int s_cnt[kWavesPerBlock][lz::kMaxE];
-  const int lane = threadIdx.x % lz::kWave, w = threadIdx.x / lz::kWave;
-  if (threadIdx.x < lz::kWave) build_split(rank_tok_off, T, N, k, s_off, s_cf);
-  for (int e = lane; e < E; e += lz::kWave) s_cnt[w][e] = 0;
+  __shared__ int s_off[lz::kMaxN + 1], s_cf[lz::kMaxN + 1], s_gf[lz::kMaxN + 1];
+  __shared__ int s_cnt[kGroup * kRowE];
+  const int tid = threadIdx.x, lane = tid % lz::kWave, w = tid / lz::kWave;
+  int* const own = s_cnt + w * kRowE;
+  if (tid < lz::kWave) build_split(rank_tok_off, T, N, k, s_off, s_cf, s_gf);
+  for (int e = lane; e < E; e += lz::kWave) own[e] = 0;
   __syncthreads();
-  const int b = blockIdx.x * kWavesPerBlock + w;
+  const int i = group_rank(s_gf, N);
+  if (i == N) return;
   long long p0 = 0, p1 = 0;
-  const int rank = chunk_range(b, N, k, s_off, s_cf, &p0, &p1);
-  if (rank < 0) return;
+  const int b = group_chunk(i, w, k, s_off, s_cf, s_gf, &p0, &p1);
   int flag = 0;
   for (long long p = p0 + lane; p < p1; p += lz::kWave) {
     const int e = ids[p];
-    if (e >= 0 && e < E) atomicAdd(&s_cnt[w][e], 1);
+    if (e >= 0 && e < E) atomicAdd(&own[e], 1);
     else flag = LZ_PLAN_BAD_EXPERT_ID;
     row_to_pair[p] = -1;  // rows and pairs share the index range [0, P)
   }
   flag = __any(flag) ? LZ_PLAN_BAD_EXPERT_ID : 0;
-  // LDS atomics of this wave have completed before its own later LDS reads
-  __builtin_amdgcn_wave_barrier();
-  for (int e = lane; e < E; e += lz::kWave) t.chunkcnt[(size_t)b * E + e] = s_cnt[w][e];
-  if (lane == 0) t.chunkflag[b] = flag;
+  if (b >= 0 && lane == 0) t.chunkflag[b] = flag;
+  __syncthreads();
+  const int b0 = s_cf[i] + ((int)blockIdx.x - s_gf[i]) * kGroup, chunks = s_cf[i + 1] - b0 < kGroup ? s_cf[i + 1] - b0 : kGroup;
+  for (int x = tid; x < E * kGroup; x += kGroup * lz::kWave) {
+    const int e = x / kGroup, u = x % kGroup;
+    if (u < chunks) t.chunkcnt[(size_t)e * t.nch + b0 + u] = s_cnt[u * kRowE + e];
+  }
 }
 
 // a / b for a >= 0, b > 0; the 64-bit quotient costs several times the 32-bit one
@@ -162,29 +193,14 @@ struct Shares {
   bool uncovered;                     // pairs but no replica (the same in every lane)
 };
 __device__ __forceinline__ Shares shares_of(int R, int T) {
-  const int lane = threadIdx.x % lz::kWave;
-  long long hi = R, te = T;
-#pragma unroll
-  for (int off = 1; off < lz::kWave; off <<= 1) {
-    const long long nr = __shfl_up(hi, off), nt = __shfl_up(te, off);
-    if (lane >= off) {
-      hi += nr;
-      te += nt;
-    }
-  }
-  const long long re = __shfl(hi, lz::kWave - 1);
-  te = __shfl(te, lz::kWave - 1);
+  const long long hi = scan_sum(R), re = last_lane((int)hi);  // at most N c slots and P pairs
+  const long long te = last_lane(scan_sum(T));
   const long long lo = hi - R;
   const int cap = re > 0 ? int(div_floor(hi * te, re) - div_floor(lo * te, re)) : 0;
   Shares s;
   s.keep = cap < T ? cap : T;
   s.overflow = T - s.keep;
-  s.residual_upto = cap - s.keep;
-#pragma unroll
-  for (int off = 1; off < lz::kWave; off <<= 1) {
-    const int n = __shfl_up(s.residual_upto, off);
-    if (lane >= off) s.residual_upto += n;
-  }
+  s.residual_upto = scan_sum(cap - s.keep);
   s.uncovered = te > 0 && re == 0;
   return s;
 }
@@ -204,62 +220,104 @@ __device__ __forceinline__ int assignment(int i, int j, int N, const int* L, con
 
 // Algorithm 1 for one expert per workgroup.  Everything an expert needs (N counts, N x N
 // assignments) lives in LDS between the phases, so the chain of dependent steps costs barriers,
-// not global-memory round trips; the tables the other kernels read are written out once.
+// not global-memory round trips; the tables that place_kernel reads are written out once.
 // What bounds it is the latency of those steps: a wave per source rank for the chunk scans (up to 16 waves),
-// a thread per (source, destination) for the assignments, whose prefix over destinations has a closed form.
+// a thread per (source, destination) for the assignments, whose prefix over destinations has a closed form,
+// a wave per destination for the prefix over sources and the slots.
+// DIRECT: the expert's pairs of every chunk are counted here, by ballots, where count_kernel would be a launch before.
+constexpr int kDirectPairs = 8192, kDirectChunks = kDirectPairs / kChunk + lz::kMaxN;
+
+template <bool DIRECT>
 __global__ __launch_bounds__(1024) void schedule_expert_kernel(
-    const int32_t* __restrict__ rank_tok_off, const int32_t* __restrict__ slot_expert, int T, int E,
-    int N, int c, int k, PlanTables t, int32_t* __restrict__ Tej_opt, int32_t* __restrict__ D_opt) {
+    const int32_t* __restrict__ ids, const int32_t* __restrict__ rank_tok_off, const int32_t* __restrict__ slot_expert, int T,
+    int E, int N, int c, int k, PlanTables t, int32_t* __restrict__ slot_counts, int32_t* __restrict__ row_to_pair,
+    int32_t* __restrict__ Tej_opt, int32_t* __restrict__ D_opt) {
   __shared__ int s_off[lz::kMaxN + 1], s_cf[lz::kMaxN + 1];
-  __shared__ int s_R[lz::kMaxN], s_T[lz::kMaxN], s_L[lz::kMaxN], s_P[lz::kMaxN + 1], s_O[lz::kMaxN];
-  __shared__ int s_D[lz::kMaxN * lz::kMaxN];
+  __shared__ int s_T[lz::kMaxN], s_L[lz::kMaxN], s_P[lz::kMaxN + 1], s_O[lz::kMaxN];
+  __shared__ int s_before[lz::kMaxN];                 // slots of rank j with a lower expert
+  __shared__ unsigned long long s_mine[lz::kMaxN];    // slots of rank j with this one, a bit each (c <= 64)
+  __shared__ int s_D[lz::kMaxN * (lz::kMaxN + 1)];
+  __shared__ int s_count[DIRECT ? kDirectChunks : 1];
+  __shared__ int s_status;
   const int e = blockIdx.x;
-  const int tid = threadIdx.x, lane = tid % lz::kWave, w = tid / lz::kWave, n_waves = blockDim.x / lz::kWave;
-  if (tid < lz::kWave) build_split(rank_tok_off, T, N, k, s_off, s_cf);
+  const int tid = threadIdx.x, lane = tid % lz::kWave, w = __builtin_amdgcn_readfirstlane(tid / lz::kWave), n_waves = blockDim.x / lz::kWave;
+  const int pitch = N | 1;  // of s_D: a column's entries lie in different banks
+  if (tid == 0) s_status = 0;
+  if (w == 0) build_split(rank_tok_off, T, N, k, s_off, s_cf);
+  int flag = 0;
+  for (int j = w; j < N; j += n_waves) {
+    const int se = lane < c ? slot_expert[j * c + lane] : -1;
+    const unsigned long long own = __ballot(lane < c && se == e), lower = __ballot(lane < c && se >= 0 && se < e);
+    if (lane == 0) {
+      s_mine[j] = own;
+      s_before[j] = __popcll(lower);
+    }
+    if (e == 0 && lane < c && (se < 0 || se >= E)) {  // a slot of no expert
+      slot_counts[j * c + lane] = 0;
+      flag = LZ_PLAN_BAD_EXPERT_ID;
+    }
+  }
   __syncthreads();
 
-  // ---- per source rank j (one wave each): positions of the chunks in the (e, j) list, T[e,j],
-  // the replicas of e on rank j and the index of their first slot in j's sorted slot list
+  if constexpr (DIRECT) {
+    const int P = T * k;
+    // lane m looks up the wave's m-th chunk, n_waves apart
+    const int chunks = s_cf[N], own = chunks > w ? (chunks - w + n_waves - 1) / n_waves : 0;  // at most 64
+    long long p0 = 0, p1 = 0;
+    chunk_range(w + n_waves * lane, N, k, s_off, s_cf, &p0, &p1);
+    constexpr int kAhead = 4;  // chunks whose ids are loaded before the first is counted
+    for (int m0 = 0; m0 < own; m0 += kAhead) {
+      int id[kAhead][2];
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        const int m = m0 + u < own ? m0 + u : own - 1;
+        const int from = __builtin_amdgcn_readlane((int)p0, m), to = m0 + u < own ? __builtin_amdgcn_readlane((int)p1, m) : 0;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int p = from + h * lz::kWave + lane;
+          id[u][h] = p < to ? ids[p] : E;
+          // (E: none; an id that is E is caught here)
+          if (p < to && (id[u][h] < 0 || id[u][h] >= E)) flag = LZ_PLAN_BAD_EXPERT_ID;
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        const int n = __popcll(__ballot(id[u][0] == e)) + __popcll(__ballot(id[u][1] == e));
+        if (lane == 0 && m0 + u < own) s_count[w + n_waves * (m0 + u)] = n;
+      }
+    }
+    for (int p = e * blockDim.x + tid; p < P; p += gridDim.x * blockDim.x) row_to_pair[p] = -1;  // rows and pairs share [0, P)
+    __syncthreads();
+  }
+  if (flag) atomicOr(&s_status, flag);
+
+  // ---- per source rank j (one wave each): positions of the chunks in the (e, j) list, T[e,j]
   for (int j = w; j < N; j += n_waves) {
     const int b_end = s_cf[j + 1];
+    auto count_of = [&](int b) {
+      if constexpr (DIRECT) return b < b_end ? s_count[b] : 0;
+      else return b < b_end ? t.chunkcnt[(size_t)e * t.nch + b] : 0;
+    };
     int running = 0, b = s_cf[j] + lane;
-    int v = b < b_end ? t.chunkcnt[(size_t)b * E + e] : 0;
-    int reps = 0, before = 0;
-    for (int l0 = 0; l0 < c; l0 += lz::kWave) {
-      const int l = l0 + lane;
-      const int se = l < c ? slot_expert[j * c + l] : -1;
-      reps += __popcll(__ballot(l < c && se == e));
-      before += __popcll(__ballot(l < c && se >= 0 && se < e));
-    }
+    int v = count_of(b);
     for (int b0 = s_cf[j]; b0 < b_end; b0 += lz::kWave) {
-      const int b_next = b + lz::kWave;
-      const int v_next = b_next < b_end ? t.chunkcnt[(size_t)b_next * E + e] : 0;
-      int incl = v;
-#pragma unroll
-      for (int off = 1; off < lz::kWave; off <<= 1) {
-        const int n = __shfl_up(incl, off);
-        if (lane >= off) incl += n;
-      }
-      if (b < b_end) t.chunkbase[(size_t)b * E + e] = running + incl - v;
-      running += __shfl(incl, lz::kWave - 1);
-      b = b_next;
+      const int v_next = count_of(b + lz::kWave);
+      const int incl = scan_sum(v);
+      if (b < b_end) t.chunkbase[(size_t)e * t.nch + b] = running + incl - v;
+      running += last_lane(incl);
+      b += lz::kWave;
       v = v_next;
     }
     if (lane == 0) {
-      const int idx = e * N + j;
       s_T[j] = running;
-      s_R[j] = reps;
-      t.Tej[idx] = running;
-      if (Tej_opt) Tej_opt[idx] = running;
-      t.R[idx] = reps;
-      t.ejstart[idx] = before;
+      if (Tej_opt) Tej_opt[e * N + j] = running;
     }
   }
   __syncthreads();
 
   // ---- one wave, lane = rank: capacity, local share, residual and its prefix over ranks, overflow
   if (w == 0) {
-    const Shares sh = shares_of(lane < N ? s_R[lane] : 0, lane < N ? s_T[lane] : 0);
+    const Shares sh = shares_of(lane < N ? __popcll(s_mine[lane]) : 0, lane < N ? s_T[lane] : 0);
     if (lane < N) {
       s_L[lane] = sh.keep;
       s_P[lane + 1] = sh.residual_upto;
@@ -267,109 +325,60 @@ __global__ __launch_bounds__(1024) void schedule_expert_kernel(
     }
     if (lane == 0) {
       s_P[0] = 0;
-      t.estatus[e] = sh.uncovered ? LZ_PLAN_UNCOVERED_EXPERT : 0;
+      t.estatus[e] = s_status | (sh.uncovered ? LZ_PLAN_UNCOVERED_EXPERT : 0);
     }
   }
   __syncthreads();
 
   // ---- D[e, i, j] and its prefix over destinations
   for (int ij = tid; ij < N * N; ij += blockDim.x) {
-    const int i = ij / N, j = ij % N, idx = e * N + i;
+    const int i = ij / N, j = ij % N;
     int cum;
     const int dval = assignment(i, j, N, s_L, s_P, s_O, &cum);
-    s_D[ij] = dval;
-    t.D[(size_t)idx * N + j] = dval;
-    if (D_opt) D_opt[(size_t)idx * N + j] = dval;
-    t.cumDst[(size_t)idx * (N + 1) + j] = cum;
-    if (j == N - 1) t.cumDst[(size_t)idx * (N + 1) + N] = cum + dval;
+    s_D[i * pitch + j] = dval;
+    if (D_opt) D_opt[(size_t)(e * N + i) * N + j] = dval;
+    int32_t* const row = t.cumDst + (size_t)(i * E + e) * (N + 1);
+    row[j] = cum;
+    if (j == N - 1) row[N] = cum + dval;
   }
   __syncthreads();
 
-  // ---- receive side: prefix over source ranks, recv[e, j]
-  if (tid < N) {
-    const int j = tid;
-    int running = 0;
-    for (int i = 0; i < N; ++i) {
-      t.preSrc[((size_t)(e * N + i)) * N + j] = running;
-      running += s_D[i * N + j];
+  // ---- per destination rank j (one wave each): prefix over source ranks, the received pairs, and their balanced
+  // cut over the rank's slots of e
+  for (int j = w; j < N; j += n_waves) {
+    const int v = lane < N ? s_D[lane * pitch + j] : 0;
+    const int incl = scan_sum(v), n = last_lane(incl);
+    if (lane < N) t.preSrc[(size_t)(e * N + lane) * N + j] = incl - v;
+    const unsigned long long own = s_mine[j];
+    const int reps = __popcll(own), before = s_before[j];
+    if (own >> lane & 1) {
+      const long long m = __popcll(own & ((1ull << lane) - 1ull));
+      slot_counts[j * c + lane] = int(div_floor((m + 1) * n, reps) - div_floor(m * n, reps));
+      t.slot_sorted[j * c + before + (int)m] = j * c + lane;
     }
-    t.recv[e * N + j] = running;
+    if (lane == 0) t.lists[e * N + j] = int4{n, reps, before, 0};
   }
 }
 
-// Slot order inside every rank, slot sizes (balanced cut of the (e, j) receive list over its
-// R[e, j] slots), their exclusive scan, and the status word.  One workgroup.
-__global__ __launch_bounds__(kSchedThreads) void schedule_slots_kernel(
-    const int32_t* __restrict__ rank_tok_off, const int32_t* __restrict__ slot_expert, int T, int E,
-    int N, int c, int k, PlanTables t, int32_t* __restrict__ slot_counts,
-    int32_t* __restrict__ slot_offsets, int32_t* __restrict__ status_opt) {
-  __shared__ int s_off[lz::kMaxN + 1], s_cf[lz::kMaxN + 1];
-  __shared__ int s_status;
-  __shared__ int s_wave[kSchedThreads / lz::kWave];
-  __shared__ int s_expert[lz::kMaxN * lz::kMaxC], s_count[lz::kMaxN * lz::kMaxC];
-  const int tid = threadIdx.x, lane = tid % lz::kWave, w = tid / lz::kWave;
-  const int S = N * c;
-  for (int s = tid; s < S; s += kSchedThreads) {
-    const int se = slot_expert[s];
-    s_expert[s] = se >= 0 && se < E ? se : E;
-  }
-  if (tid < lz::kWave) {
-    const bool bad = build_split(rank_tok_off, T, N, k, s_off, s_cf);
-    if (tid == 0) s_status = bad ? LZ_PLAN_BAD_RANK_SPLIT : 0;
-  }
-  __syncthreads();
-  int flag = 0;
-  for (int b = tid; b < s_cf[N]; b += kSchedThreads) flag |= t.chunkflag[b];
-  for (int e = tid; e < E; e += kSchedThreads) flag |= t.estatus[e];
-  for (int s = tid; s < S; s += kSchedThreads) {
-    const int j = s / c, se = s_expert[s];
-    if (se == E) flag |= LZ_PLAN_BAD_EXPERT_ID;
-    int pos = 0;
-    for (int s2 = j * c; s2 < j * c + c; ++s2) pos += s_expert[s2] < se || (s_expert[s2] == se && s2 < s);
-    t.slot_sorted[j * c + pos] = s;
-    int cnt = 0;
-    if (se < E) {
-      const int ej = se * N + j;
-      const long long m = pos - t.ejstart[ej];
-      const long long n = t.recv[ej], reps = t.R[ej];
-      cnt = int(div_floor((m + 1) * n, reps) - div_floor(m * n, reps));
-    }
-    slot_counts[s] = cnt;
-    s_count[s] = cnt;
-  }
-  if (flag) atomicOr(&s_status, flag);
-  __syncthreads();
+// The tables of place_chunk for one source rank: prefix of D over destinations (an expert's row every cum_stride), over
+// sources, {received, replicas, first slot} of an (expert, rank) list, a rank's slots in order, first rows of slots.
+template <typename Cum, typename Pre, typename List, typename Sorted, typename First>
+struct PlaceTables {
+  Cum cum;
+  Pre pre;
+  List list;
+  Sorted sorted;
+  First first;
+};
+template <typename Cum, typename Pre, typename List, typename Sorted, typename First>
+__device__ PlaceTables(Cum, Pre, List, Sorted, First) -> PlaceTables<Cum, Pre, List, Sorted, First>;
 
-  // ---- exclusive scan over slot id (each thread owns a run of consecutive slots)
-  const int per = (S + kSchedThreads - 1) / kSchedThreads;
-  const int first = tid * per;
-  int local = 0;
-  for (int s = first; s < first + per && s < S; ++s) local += s_count[s];
-  int incl = local;
-#pragma unroll
-  for (int off = 1; off < lz::kWave; off <<= 1) {
-    const int n = __shfl_up(incl, off);
-    if (lane >= off) incl += n;
-  }
-  if (lane == lz::kWave - 1) s_wave[w] = incl;
-  __syncthreads();
-  for (int w2 = 0; w2 < w; ++w2) incl += s_wave[w2];
-  int running = incl - local;
-  for (int s = first; s < first + per && s < S; ++s) {
-    slot_offsets[s] = running;
-    running += s_count[s];
-  }
-  if (tid == kSchedThreads - 1) slot_offsets[S] = incl;
-  if (tid == 0 && status_opt) *status_opt = s_status;
-}
-
-// One wave places the pairs [p0, p1) of a chunk of source rank i; run[e]: position of its first pair of e in the
-// (e, i) list, advanced here.
-__device__ __forceinline__ void place_chunk(const int32_t* __restrict__ ids, long long p0, long long p1, int i, int* run, int E,
-                                            int N, int c, long long P, const int32_t* cumDst, const int32_t* preSrc,
-                                            const int32_t* recv, const int32_t* R, const int32_t* ejstart,
-                                            const int32_t* slot_sorted, const int32_t* slot_offsets,
-                                            int32_t* __restrict__ pair_to_row, int32_t* __restrict__ row_to_pair) {
+// One wave places the pairs [p0, p1) of a chunk; run[e]: position of its first pair of e in the
+// (e, source rank) list, advanced here.
+template <typename Tables>
+__device__ __forceinline__ void place_chunk(const int32_t* __restrict__ ids, long long p0, long long p1, int* run, int E,
+                                            int N, int c, long long P, const Tables& t, int32_t* __restrict__ pair_to_row,
+                                            int32_t* __restrict__ row_to_pair) {
   const int lane = threadIdx.x % lz::kWave;
   const unsigned long long lower = (1ull << lane) - 1ull;
   const int e_bits = 32 - __clz(E - 1 | 1);
@@ -399,13 +408,11 @@ __device__ __forceinline__ void place_chunk(const int32_t* __restrict__ ids, lon
   }
   int row[kPairs], dst[kPairs];
   bool ok[kPairs];
-  const int32_t* cum[kPairs];
 #pragma unroll
   for (int u = 0; u < kPairs; ++u) {
-    cum[u] = cumDst + (size_t)((ex[u] < 0 ? 0 : ex[u]) * N + i) * (N + 1);
     row[u] = -1;
     dst[u] = 0;
-    ok[u] = ex[u] >= 0 && q[u] < cum[u][N];
+    ok[u] = ex[u] >= 0 && q[u] < t.cum(ex[u] < 0 ? 0 : ex[u], N);
   }
   // destination rank: the last j with cum[j] <= q (cum[0] = 0)
   int step = 1;
@@ -414,21 +421,22 @@ __device__ __forceinline__ void place_chunk(const int32_t* __restrict__ ids, lon
 #pragma unroll
     for (int u = 0; u < kPairs; ++u) {
       const int j = dst[u] + step;
-      if (j < N && cum[u][j] <= q[u]) dst[u] = j;
+      if (j < N && t.cum(ex[u] < 0 ? 0 : ex[u], j) <= q[u]) dst[u] = j;
     }
   }
 #pragma unroll
   for (int u = 0; u < kPairs; ++u) {
     if (ok[u]) {
-      const int ei = ex[u] * N + i, j = dst[u], ej = ex[u] * N + j;
-      const long long pos = preSrc[(size_t)ei * N + j] + (q[u] - cum[u][j]);
-      const long long n = recv[ej], reps = R[ej];
+      const int j = dst[u];
+      const int3 list = t.list(ex[u], j);
+      const long long pos = t.pre(ex[u], j) + (q[u] - t.cum(ex[u], j));
+      const long long n = list.x, reps = list.y;
       if (n > 0 && reps > 0) {
         // slot m of the (e, j) list holds positions [floor(m*n/reps), floor((m+1)*n/reps))
         long long m = div_floor((pos + 1) * reps - 1, n);
         m = m < reps ? m : reps - 1;
-        const int s = slot_sorted[j * c + ejstart[ej] + (int)m];
-        const long long r = slot_offsets[s] + pos - div_floor(m * n, reps);
+        const int s = t.sorted(j * c + list.z + (int)m);
+        const long long r = t.first(s) + pos - div_floor(m * n, reps);
         if (r >= 0 && r < P) row[u] = (int)r;
       }
     }
@@ -441,39 +449,114 @@ __device__ __forceinline__ void place_chunk(const int32_t* __restrict__ ids, lon
   }
 }
 
-__global__ __launch_bounds__(256) void place_kernel(const int32_t* __restrict__ ids,
-                                                    const int32_t* __restrict__ rank_tok_off, int T,
-                                                    int E, int N, int c, int k, PlanTables t,
-                                                    const int32_t* __restrict__ slot_offsets,
-                                                    int32_t* __restrict__ pair_to_row,
-                                                    int32_t* __restrict__ row_to_pair) {
-  __shared__ int s_off[lz::kMaxN + 1], s_cf[lz::kMaxN + 1];
-  __shared__ int s_run[kWavesPerBlock][lz::kMaxE];
-  const int lane = threadIdx.x % lz::kWave, w = threadIdx.x / lz::kWave;
-  if (threadIdx.x < lz::kWave) build_split(rank_tok_off, T, N, k, s_off, s_cf);
+// First rows of the slots from their sizes, by a whole workgroup (each thread a run of consecutive slots); returns their sum
+// in the last thread.  s_first may be written when the workgroup has passed its first barrier.
+__device__ __forceinline__ int scan_slots(const int32_t* __restrict__ slot_counts, int S, int* s_first, int* s_wave) {
+  const int tid = threadIdx.x, lane = tid % lz::kWave, w = tid / lz::kWave;
+  const int per = (S + (int)blockDim.x - 1) / (int)blockDim.x, first = tid * per;
+  int own = 0;
+  for (int s = first; s < first + per && s < S; ++s) own += slot_counts[s];
+  const int incl = scan_sum(own);
+  if (lane == lz::kWave - 1) s_wave[w] = incl;
   __syncthreads();
-  const int b = blockIdx.x * kWavesPerBlock + w;
+  int running = incl - own;
+  for (int v = 0; v < w; ++v) running += s_wave[v];
+  const int end = running + own;
+  for (int s = first; s < first + per && s < S; ++s) {
+    s_first[s] = running;
+    running += slot_counts[s];
+  }
+  return end;
+}
+
+// The first rows of all slots are scanned by every workgroup, which is cheaper than a launch of one workgroup for them (5 us
+// of a plan).  What bounds it is latency, and with many experts the lookups of single entries: what a workgroup's chunks need of the
+// tables is fetched at the start, all at once, but for the entries of the pairs' lists; the prefix over destinations of the
+// workgroup's rank is searched in LDS where it fits.
+constexpr int kCumSlice = 8448;  // 256 experts, 32 ranks
+
+__global__ __launch_bounds__(kGroup * lz::kWave) void place_kernel(const int32_t* __restrict__ ids,
+                                                    const int32_t* __restrict__ rank_tok_off, int T,
+                                                    int E, int N, int c, int k, PlanTables t, bool counted,
+                                                    const int32_t* __restrict__ slot_counts,
+                                                    int32_t* __restrict__ slot_offsets,
+                                                    int32_t* __restrict__ pair_to_row,
+                                                    int32_t* __restrict__ row_to_pair, int32_t* __restrict__ status_opt) {
+  constexpr int kThreads = kGroup * lz::kWave;
+  __shared__ int s_off[lz::kMaxN + 1], s_cf[lz::kMaxN + 1], s_gf[lz::kMaxN + 1];
+  __shared__ int s_run[kGroup * kRowE];
+  __shared__ int s_cum[kCumSlice];
+  __shared__ int s_first[lz::kMaxN * lz::kMaxC], s_wave[kGroup];
+  __shared__ unsigned short s_sorted[lz::kMaxN * lz::kMaxC];
+  __shared__ int s_status;
+  const int tid = threadIdx.x, w = tid / lz::kWave;
+  const int S = N * c;
+  if (tid < lz::kWave) {
+    const bool bad = build_split(rank_tok_off, T, N, k, s_off, s_cf, s_gf);
+    if (tid == 0) s_status = bad ? LZ_PLAN_BAD_RANK_SPLIT : 0;
+  }
+  for (int s = tid; s < S; s += kThreads) s_sorted[s] = (unsigned short)t.slot_sorted[s];
+  const int end = scan_slots(slot_counts, S, s_first, s_wave);
+  if (blockIdx.x == 0) {
+    int flag = 0;
+    for (int e = tid; e < E; e += kThreads) flag |= t.estatus[e];
+    if (counted)
+      for (int b = tid; b < s_cf[N]; b += kThreads) flag |= t.chunkflag[b];
+    if (flag) atomicOr(&s_status, flag);
+  }
+  const int i = group_rank(s_gf, N), slice = E * (N + 1);
+  if (i < N) {
+    const int b0 = s_cf[i] + ((int)blockIdx.x - s_gf[i]) * kGroup, chunks = s_cf[i + 1] - b0 < kGroup ? s_cf[i + 1] - b0 : kGroup;
+#pragma unroll 4
+    for (int x = tid; x < E * kGroup; x += kThreads) {
+      const int e = x / kGroup, u = x % kGroup;
+      if (u < chunks) s_run[u * kRowE + e] = t.chunkbase[(size_t)e * t.nch + b0 + u];
+    }
+    if (slice <= kCumSlice) {
+#pragma unroll 9
+      for (int x = tid; x < slice; x += kThreads) s_cum[x] = t.cumDst[(size_t)i * slice + x];
+    }
+  }
+  __syncthreads();
+  if (blockIdx.x == 0) {
+    for (int s = tid; s < S; s += kThreads) slot_offsets[s] = s_first[s];
+    if (tid == kThreads - 1) slot_offsets[S] = end;
+    if (tid == 0 && status_opt) *status_opt = s_status;
+  }
+  if (i == N) return;
   long long p0 = 0, p1 = 0;
-  const int i = chunk_range(b, N, k, s_off, s_cf, &p0, &p1);
-  if (i < 0) return;
-  for (int e = lane; e < E; e += lz::kWave) s_run[w][e] = t.chunkbase[(size_t)b * E + e];
-  __builtin_amdgcn_wave_barrier();
-  place_chunk(ids, p0, p1, i, s_run[w], E, N, c, (long long)T * k, t.cumDst, t.preSrc, t.recv, t.R, t.ejstart, t.slot_sorted,
-              slot_offsets, pair_to_row, row_to_pair);
+  if (group_chunk(i, w, k, s_off, s_cf, s_gf, &p0, &p1) < 0) return;
+  int* const run = s_run + w * kRowE;
+  auto pre = [&](int e, int j) { return t.preSrc[(size_t)(e * N + i) * N + j]; };
+  auto list = [&](int e, int j) {
+    const int4 v = t.lists[e * N + j];
+    return int3{v.x, v.y, v.z};
+  };
+  auto sorted = [&](int at) { return (int)s_sorted[at]; };
+  auto first = [&](int s) { return s_first[s]; };
+  if (slice <= kCumSlice) {
+    const PlaceTables tables{[&](int e, int j) { return s_cum[e * (N + 1) + j]; }, pre, list, sorted, first};
+    place_chunk(ids, p0, p1, run, E, N, c, (long long)T * k, tables, pair_to_row, row_to_pair);
+  } else {
+    const int32_t* const cum = t.cumDst + (size_t)i * slice;
+    const PlaceTables tables{[=](int e, int j) { return cum[e * (N + 1) + j]; }, pre, list, sorted, first};
+    place_chunk(ids, p0, p1, run, E, N, c, (long long)T * k, tables, pair_to_row, row_to_pair);
+  }
 }
 
 // ------------------------------------------------------------------------------------------
 // The whole dispatcher in one workgroup, tables in LDS: small batches, where the four launches and the trips of
 // their tables through memory are the time.  Same steps, same results.
 // ------------------------------------------------------------------------------------------
-constexpr int kSmallPairs = 4096, kSmallCounts = 4096, kSmallTriples = 2048, kSmallLists = 512, kSmallSlots = 512;
+constexpr int kSmallPairs = 2048, kSmallExperts = 24;
+constexpr int kSmallCounts = 2048, kSmallTriples = 2048, kSmallLists = 512, kSmallSlots = 512;
 
-// Where one workgroup is the faster dispatcher.  Measured (us, this kernel against the four): 128 pairs, 8 experts, 8
-// ranks 9.6, 17.8; 2048 pairs 11.1, 18.8; 4096 pairs 15.0, 19.2; 16 experts 16.7, 19.3; 32 experts, 2048 pairs 15.9,
-// 19.5; 60 experts, 3600 pairs 23.4, 20.6; 128 experts, 120 pairs 28.1, 18.9.  The other bounds are the LDS tables'.
+// Where one workgroup is the faster dispatcher.  Measured (us, this kernel against two launches, 8 ranks): 64 pairs, 8 experts
+// 8.0, 11.0; 2048 pairs, 8, 16, 24, 32 experts 9.5, 10.5, 11.3, 12.8 against 11.6, 11.9, 12.1, 12.5; 3072 pairs 11.8, 13.0, 13.9,
+// 15.4 against 11.7 to 12.2.  The other bounds are the LDS tables'.
 inline bool small_plan(const lz_shape* s) {
   const long long P = (long long)s->T * s->k;
-  return P > 0 && P <= kSmallPairs && s->E <= 32 && (long long)max_chunks(P, s->N) * s->E <= kSmallCounts &&
+  return P > 0 && P <= kSmallPairs && s->E <= kSmallExperts && (long long)max_chunks(P, s->N) * s->E <= kSmallCounts &&
          s->E * s->N * s->N <= kSmallTriples && s->E * s->N <= kSmallLists && s->N * s->c <= kSmallSlots;
 }
 
@@ -593,12 +676,7 @@ __global__ __launch_bounds__(kSchedThreads) void plan_small_kernel(
     }
     slot_counts[tid] = count;
   }
-  int incl = count;
-#pragma unroll
-  for (int off = 1; off < lz::kWave; off <<= 1) {
-    const int n = __shfl_up(incl, off);
-    if (lane >= off) incl += n;
-  }
+  int incl = scan_sum(count);
   if (lane == lz::kWave - 1) s_wave[w] = incl;
   __syncthreads();
   for (int w2 = 0; w2 < w; ++w2) incl += s_wave[w2];
@@ -614,8 +692,11 @@ __global__ __launch_bounds__(kSchedThreads) void plan_small_kernel(
   for (int b = w; b < chunks; b += kWaves) {
     long long p0 = 0, p1 = 0;
     const int i = chunk_range(b, N, k, s_off, s_cf, &p0, &p1);
-    place_chunk(ids, p0, p1, i, s_cnt + b * E, E, N, c, P, s_cum, s_D, s_recv, s_R, s_start, s_sorted, s_first, pair_to_row,
-                row_to_pair);
+    const PlaceTables tables{[=](int e, int j) { return s_cum[(e * N + i) * (N + 1) + j]; },
+                             [=](int e, int j) { return s_D[(e * N + i) * N + j]; },
+                             [=](int e, int j) { return int3{s_recv[e * N + j], s_R[e * N + j], s_start[e * N + j]}; },
+                             [=](int at) { return s_sorted[at]; }, [=](int s) { return s_first[s]; }};
+    place_chunk(ids, p0, p1, s_cnt + b * E, E, N, c, P, tables, pair_to_row, row_to_pair);
   }
 }
 
@@ -628,7 +709,15 @@ extern "C" size_t lz_plan_workspace_bytes(const lz_shape* shape) {
 
 namespace {
 
-// The four launches of the dispatcher on tables carved from `ws` (already checked by the caller).
+// Whether the expert's workgroups count their pairs themselves, each reading all ids.  us, so and with a launch that counts: 2000 pairs,
+// 8 and 53 experts 11.4, 12.9 and 12.6, 14.2; 8000 pairs, 16 experts 12.9, 13.7; 16384 pairs, 8 experts 14.4, 13.5; 32768 pairs,
+// 32 experts 18.0, 13.9.
+inline bool direct_counts(const lz_shape* s) {
+  const long long P = (long long)s->T * s->k;
+  return P <= kDirectPairs;
+}
+
+// The launches of the dispatcher on tables carved from `ws` (already checked by the caller).
 int32_t enqueue_plan(const int32_t* topk_ids, const lz_shape* shape, const int32_t* rank_tok_off,
                      const int32_t* slot_expert, int32_t* slot_counts, int32_t* slot_offsets,
                      int32_t* pair_to_row, int32_t* row_to_pair, int32_t* Tej_opt, int32_t* D_opt,
@@ -640,21 +729,22 @@ int32_t enqueue_plan(const int32_t* topk_ids, const lz_shape* shape, const int32
                        D_opt, status_opt);
     return lz::launch_status();
   }
-  const int nch = max_chunks(P, shape->N);
-  const unsigned blocks = unsigned((nch + kWavesPerBlock - 1) / kWavesPerBlock);
-  if (P > 0)
-    hipLaunchKernelGGL(count_kernel, dim3(blocks), dim3(256), 0, st, topk_ids, rank_tok_off, shape->T,
-                       shape->E, shape->N, shape->k, t, row_to_pair);
-  const int expert_waves = shape->N < 4 ? 4 : shape->N < 16 ? shape->N : 16;  // one per source rank
-  hipLaunchKernelGGL(schedule_expert_kernel, dim3(shape->E), dim3(lz::kWave * expert_waves), 0, st, rank_tok_off,
-                     slot_expert, shape->T, shape->E, shape->N, shape->c, shape->k, t, Tej_opt, D_opt);
-  hipLaunchKernelGGL(schedule_slots_kernel, dim3(1), dim3(kSchedThreads), 0, st, rank_tok_off, slot_expert,
-                     shape->T, shape->E, shape->N, shape->c, shape->k, t, slot_counts, slot_offsets,
-                     status_opt);
-  if (P > 0)
-    hipLaunchKernelGGL(place_kernel, dim3(blocks), dim3(256), 0, st, topk_ids, rank_tok_off, shape->T,
-                       shape->E, shape->N, shape->c, shape->k, t, slot_offsets, pair_to_row,
-                       row_to_pair);
+  const unsigned blocks = P > 0 ? (unsigned)max_groups(P, shape->N) : 1;
+  constexpr int threads = kGroup * lz::kWave;
+  const bool direct = direct_counts(shape);
+  if (direct) {
+    hipLaunchKernelGGL(schedule_expert_kernel<true>, dim3(shape->E), dim3(1024), 0, st, topk_ids, rank_tok_off, slot_expert,
+                       shape->T, shape->E, shape->N, shape->c, shape->k, t, slot_counts, row_to_pair, Tej_opt, D_opt);
+  } else {
+    if (P > 0)
+      hipLaunchKernelGGL(count_kernel, dim3(blocks), dim3(threads), 0, st, topk_ids, rank_tok_off, shape->T,
+                         shape->E, shape->N, shape->k, t, row_to_pair);
+    const int expert_waves = shape->N < 4 ? 4 : shape->N < 16 ? shape->N : 16;  // one per source rank
+    hipLaunchKernelGGL(schedule_expert_kernel<false>, dim3(shape->E), dim3(lz::kWave * expert_waves), 0, st, topk_ids, rank_tok_off,
+                       slot_expert, shape->T, shape->E, shape->N, shape->c, shape->k, t, slot_counts, row_to_pair, Tej_opt, D_opt);
+  }
+  hipLaunchKernelGGL(place_kernel, dim3(blocks), dim3(threads), 0, st, topk_ids, rank_tok_off, shape->T, shape->E, shape->N, shape->c,
+                     shape->k, t, !direct, slot_counts, slot_offsets, pair_to_row, row_to_pair, status_opt);
   return lz::launch_status();
 }
 
