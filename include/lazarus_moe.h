@@ -300,6 +300,38 @@ int32_t lz_reduce_replica_grads(const void* dw_slot, const int32_t* slot_expert,
 int32_t lz_reduce_replica_grads_dtype(const void* dw_slot, const int32_t* slot_expert, int32_t S, int32_t E,
                                       int64_t elems_per_slot, int32_t dtype, void* dw, void* stream);
 
+/* ---------------------------------------------------------------- the whole layer in one call
+ *
+ * The buffers of a layer, as the single calls take them (device memory; the struct itself is host memory, read during the call
+ * only).  Those that a call does not use may be NULL. */
+typedef struct {
+  const int32_t *rank_tok_off, *slot_expert;
+  const void *w1, *w2;
+  int32_t* topk_ids;
+  float* topk_gates;
+  int32_t *slot_counts, *slot_offsets, *pair_to_row, *row_to_pair, *Tej_opt, *D_opt, *status_opt;
+  void *xp, *yp, *y;
+  void *plan_ws, *ffn_ws, *train_ws;
+  size_t plan_ws_bytes, ffn_ws_bytes, train_ws_bytes;
+  void *z, *h, *dyp, *dxp, *dx;
+  float *dgates, *dlogits;
+  void *dw1_slot, *dw2_slot; /* lz_layer_backward with accumulate: the fp32 accumulators */
+  void *dw1, *dw2;
+} lz_layer_buffers;
+
+/* lz_route, lz_plan_dispatch, lz_permute_scatter and lz_expert_ffn (fused: lz_expert_ffn_gather instead of the two, xp unused), then
+ * lz_unpermute_combine.  The first step that is refused ends the call with
+ * its status; steps before it may have run. */
+int32_t lz_layer_forward(const lz_shape* shape, const lz_layer_buffers* buffers, const float* logits, const void* x,
+                         int32_t fused, void* stream);
+/* lz_route, lz_plan_dispatch, lz_permute_scatter, lz_ffn_forward_train, lz_unpermute_combine. */
+int32_t lz_layer_forward_train(const lz_shape* shape, const lz_layer_buffers* buffers, const float* logits, const void* x,
+                               void* stream);
+/* lz_combine_backward, lz_ffn_backward (accumulate: lz_ffn_backward_accumulate), lz_permute_backward, lz_route_backward and, unless
+ * accumulating, lz_reduce_replica_grads_dtype of both matrices. */
+int32_t lz_layer_backward(const lz_shape* shape, const lz_layer_buffers* buffers, const void* dy, int32_t accumulate,
+                          void* stream);
+
 /* ---------------------------------------------------------------- host planning */
 
 /* Replica allocation, Eq. 1 (Sec. 4.1): experts in ascending load t_e (ties: lower id)

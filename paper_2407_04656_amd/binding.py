@@ -16,6 +16,7 @@ __all__ = [
     "lz_pack_weights", "lz_train_workspace_bytes", "lz_ffn_forward_train", "lz_combine_backward",
     "lz_ffn_backward", "lz_ffn_backward_accumulate", "lz_permute_backward", "lz_route_backward", "lz_reduce_replica_grads",
     "lz_reduce_replica_grads_dtype", "lz_debug_xcc_ids",
+    "lz_layer_forward", "lz_layer_forward_train", "lz_layer_backward",
 ]
 
 LZ_F32, LZ_BF16 = 0, 1
@@ -36,6 +37,14 @@ class _Shape(C.Structure):
 
 class _Transfer(C.Structure):
     _fields_ = [(n, C.c_int32) for n in ("dst_slot", "src_slot", "expert", "remote")]
+
+
+class _LayerBuffers(C.Structure):
+    _fields_ = [(n, C.c_void_p) for n in (
+        "rank_tok_off", "slot_expert", "w1", "w2", "topk_ids", "topk_gates", "slot_counts", "slot_offsets", "pair_to_row",
+        "row_to_pair", "Tej_opt", "D_opt", "status_opt", "xp", "yp", "y", "plan_ws", "ffn_ws", "train_ws")] + [
+        (n, C.c_size_t) for n in ("plan_ws_bytes", "ffn_ws_bytes", "train_ws_bytes")] + [
+        (n, C.c_void_p) for n in ("z", "h", "dyp", "dxp", "dx", "dgates", "dlogits", "dw1_slot", "dw2_slot", "dw1", "dw2")]
 
 
 @dataclass(frozen=True)
@@ -138,6 +147,9 @@ def _load():
         "lz_reduce_replica_grads": (i32, [vp, vp, i32, i32, C.c_int64, vp, vp]),
         "lz_reduce_replica_grads_dtype": (i32, [vp, vp, i32, i32, C.c_int64, i32, vp, vp]),
         "lz_debug_xcc_ids": (i32, [vp, i32, vp]),
+        "lz_layer_forward": (i32, [sp, vp, vp, vp, i32, vp]),
+        "lz_layer_forward_train": (i32, [sp, vp, vp, vp, vp]),
+        "lz_layer_backward": (i32, [sp, vp, vp, i32, vp]),
     }
     for name, (res, args) in sig.items():
         fn = getattr(L, name)
@@ -328,6 +340,22 @@ def lz_debug_xcc_ids(xcc_of_workgroup, n_workgroups, stream=None):
            "lz_debug_xcc_ids")
 
 
+# ------------------------------------------------------------------ the whole layer in one call (buffers: a _LayerBuffers)
+def lz_layer_forward(shape, buffers, logits, x, fused=False, stream=None):
+    _check(lib.lz_layer_forward(shape._arg(), C.addressof(buffers), _ptr(logits), _ptr(x), fused,
+                                _stream() if stream is None else stream), "lz_layer_forward")
+
+
+def lz_layer_forward_train(shape, buffers, logits, x, stream=None):
+    _check(lib.lz_layer_forward_train(shape._arg(), C.addressof(buffers), _ptr(logits), _ptr(x),
+                                      _stream() if stream is None else stream), "lz_layer_forward_train")
+
+
+def lz_layer_backward(shape, buffers, dy, accumulate=False, stream=None):
+    _check(lib.lz_layer_backward(shape._arg(), C.addressof(buffers), _ptr(dy), accumulate,
+                                 _stream() if stream is None else stream), "lz_layer_backward")
+
+
 # ------------------------------------------------------------------ host planning
 def _i64(a):
     return np.ascontiguousarray(np.asarray(a, dtype=np.int64))
@@ -492,7 +520,27 @@ class MoELayer:
     def unpermute_combine(self):
         lz_unpermute_combine(self.yp, self.pair_to_row, self.topk_gates, self.shape, self.y)
 
+    # The passes below are one call each, which takes the addresses of the buffers as they are now.  A layer with steps of its
+    # own (a subclass's, or set on the object) keeps to them.
+    _STEPS = frozenset(("route", "plan_dispatch", "permute", "expert_ffn", "unpermute_combine"))
+
+    def _own_steps(self):
+        cls = type(self)
+        return not self._STEPS.isdisjoint(self.__dict__) or (
+            cls is not MoELayer and any(getattr(cls, n) is not getattr(MoELayer, n) for n in self._STEPS))
+
+    def _forward_buffers(self, train_ws=None, train_ws_bytes=0, z=None, h=None):
+        return _LayerBuffers(
+            _ptr(self.rank_tok_off), _ptr(self.slot_expert), _ptr(self.w1), _ptr(self.w2), _ptr(self.topk_ids),
+            _ptr(self.topk_gates), _ptr(self.slot_counts), _ptr(self.slot_offsets), _ptr(self.pair_to_row),
+            _ptr(self.row_to_pair), _ptr(self.Tej), _ptr(self.D), _ptr(self.status), _ptr(self.xp), _ptr(self.yp),
+            _ptr(self.y), _ptr(self.plan_ws), _ptr(self.ffn_ws), _ptr(train_ws), self.plan_ws_bytes,
+            self.ffn_ws_bytes, train_ws_bytes, _ptr(z), _ptr(h))
+
     def forward(self, logits, x):
+        if not self._own_steps():
+            lz_layer_forward(self.shape, self._forward_buffers(), logits, x)
+            return self.y
         self.route(logits)
         self.plan_dispatch()
         self.permute(x)
@@ -525,6 +573,9 @@ class MoELayer:
 
     def forward_fused(self, logits, x):
         """The same pass with the reshuffle done by the first GEMM's loads (no permute call, xp unused)."""
+        if not self._own_steps():
+            lz_layer_forward(self.shape, self._forward_buffers(), logits, x, True)
+            return self.y
         self.route(logits)
         self.plan_dispatch()
         lz_expert_ffn_gather(x, self.row_to_pair, self.slot_offsets, self.w1, self.w2, self.shape, self.yp,
@@ -533,6 +584,10 @@ class MoELayer:
         return self.y
 
     def forward_train(self, logits, x):
+        if not self._own_steps():
+            lz_layer_forward_train(self.shape, self._forward_buffers(self.train_ws, self.train_ws_bytes, self.z, self.h),
+                                   logits, x)
+            return self.y
         self.route(logits)
         self.plan_dispatch()
         self.permute(x)
@@ -551,12 +606,7 @@ class MoELayer:
 
     def backward_accumulate(self, dy):
         """One micro-batch: data gradients as in backward(), weight gradients added to the fp32 accumulators."""
-        s = self.shape
-        lz_combine_backward(dy, self.yp, self.pair_to_row, self.topk_gates, s, self.dyp, self.dgates)
-        lz_ffn_backward_accumulate(self.dyp, self.xp, self.z, self.h, self.slot_offsets, self.w1, self.w2, s,
-                                   self.dxp, self.dw1_acc, self.dw2_acc, self.train_ws, self.train_ws_bytes)
-        lz_permute_backward(self.dxp, self.pair_to_row, s, self.dx)
-        lz_route_backward(self.dgates, self.topk_gates, self.topk_ids, s, self.dlogits)
+        lz_layer_backward(self.shape, self._backward_buffers(self.dw1_acc, self.dw2_acc), dy, True)
         return self.dx
 
     def reduce_accumulated(self):
@@ -568,15 +618,15 @@ class MoELayer:
                                       self.dw2_sum)
         return self.dw1_sum, self.dw2_sum
 
+    def _backward_buffers(self, dw1_slot, dw2_slot, dw1=None, dw2=None):
+        return _LayerBuffers(
+            slot_expert=_ptr(self.slot_expert), w1=_ptr(self.w1), w2=_ptr(self.w2), topk_ids=_ptr(self.topk_ids),
+            topk_gates=_ptr(self.topk_gates), slot_offsets=_ptr(self.slot_offsets), pair_to_row=_ptr(self.pair_to_row),
+            xp=_ptr(self.xp), yp=_ptr(self.yp), train_ws=_ptr(self.train_ws), train_ws_bytes=self.train_ws_bytes,
+            z=_ptr(self.z), h=_ptr(self.h), dyp=_ptr(self.dyp), dxp=_ptr(self.dxp), dx=_ptr(self.dx),
+            dgates=_ptr(self.dgates), dlogits=_ptr(self.dlogits), dw1_slot=_ptr(dw1_slot), dw2_slot=_ptr(dw2_slot),
+            dw1=_ptr(dw1), dw2=_ptr(dw2))
+
     def backward(self, dy):
-        s = self.shape
-        lz_combine_backward(dy, self.yp, self.pair_to_row, self.topk_gates, s, self.dyp, self.dgates)
-        lz_ffn_backward(self.dyp, self.xp, self.z, self.h, self.slot_offsets, self.w1, self.w2, s, self.dxp,
-                        self.dw1_slot, self.dw2_slot, self.train_ws, self.train_ws_bytes)
-        lz_permute_backward(self.dxp, self.pair_to_row, s, self.dx)
-        lz_route_backward(self.dgates, self.topk_gates, self.topk_ids, s, self.dlogits)
-        lz_reduce_replica_grads_dtype(self.dw1_slot, self.slot_expert, s.S, s.E, self.dw1_slot[0].numel(), s.dtype,
-                                      self.dw1)
-        lz_reduce_replica_grads_dtype(self.dw2_slot, self.slot_expert, s.S, s.E, self.dw2_slot[0].numel(), s.dtype,
-                                      self.dw2)
+        lz_layer_backward(self.shape, self._backward_buffers(self.dw1_slot, self.dw2_slot, self.dw1, self.dw2), dy)
         return self.dx

@@ -1,0 +1,61 @@
+// The whole layer in one call: the single calls in their order, on the caller's buffers.  A caller of small batches pays for the calls:
+// from Python a forward of 256 tokens spent 34 us on five of them and seven launches, 30 on one.
+#include "lz_common.h"
+
+namespace {
+
+int32_t route_and_plan(const lz_shape* shape, const lz_layer_buffers& b, const float* logits, void* stream) {
+  if (!shape) return LZ_ESHAPE;
+  const int32_t rc = lz_route(logits, shape->T, shape->E, shape->k, b.topk_ids, b.topk_gates, stream);
+  if (rc != LZ_OK) return rc;
+  return lz_plan_dispatch(b.topk_ids, shape, b.rank_tok_off, b.slot_expert, b.slot_counts, b.slot_offsets, b.pair_to_row,
+                          b.row_to_pair, b.Tej_opt, b.D_opt, b.status_opt, b.plan_ws, b.plan_ws_bytes, stream);
+}
+
+}  // namespace
+
+extern "C" int32_t lz_layer_forward(const lz_shape* shape, const lz_layer_buffers* buffers, const float* logits, const void* x,
+                                    int32_t fused, void* stream) {
+  if (!buffers) return LZ_EINVAL;
+  const lz_layer_buffers& b = *buffers;
+  int32_t rc = route_and_plan(shape, b, logits, stream);
+  if (rc != LZ_OK) return rc;
+  if (!fused && (rc = lz_permute_scatter(x, b.pair_to_row, shape, b.xp, stream)) != LZ_OK) return rc;
+  rc = fused ? lz_expert_ffn_gather(x, b.row_to_pair, b.slot_offsets, b.w1, b.w2, shape, b.yp, b.ffn_ws, b.ffn_ws_bytes, stream)
+             : lz_expert_ffn(b.xp, b.slot_offsets, b.w1, b.w2, shape, b.yp, b.ffn_ws, b.ffn_ws_bytes, stream);
+  if (rc != LZ_OK) return rc;
+  return lz_unpermute_combine(b.yp, b.pair_to_row, b.topk_gates, shape, b.y, stream);
+}
+
+extern "C" int32_t lz_layer_forward_train(const lz_shape* shape, const lz_layer_buffers* buffers, const float* logits, const void* x,
+                                          void* stream) {
+  if (!buffers) return LZ_EINVAL;
+  const lz_layer_buffers& b = *buffers;
+  int32_t rc = route_and_plan(shape, b, logits, stream);
+  if (rc != LZ_OK) return rc;
+  if ((rc = lz_permute_scatter(x, b.pair_to_row, shape, b.xp, stream)) != LZ_OK) return rc;
+  rc = lz_ffn_forward_train(b.xp, b.slot_offsets, b.w1, b.w2, shape, b.z, b.h, b.yp, b.train_ws, b.train_ws_bytes, stream);
+  if (rc != LZ_OK) return rc;
+  return lz_unpermute_combine(b.yp, b.pair_to_row, b.topk_gates, shape, b.y, stream);
+}
+
+extern "C" int32_t lz_layer_backward(const lz_shape* shape, const lz_layer_buffers* buffers, const void* dy, int32_t accumulate,
+                                     void* stream) {
+  if (!buffers) return LZ_EINVAL;
+  const lz_layer_buffers& b = *buffers;
+  int32_t rc = lz_combine_backward(dy, b.yp, b.pair_to_row, b.topk_gates, shape, b.dyp, b.dgates, stream);
+  if (rc != LZ_OK) return rc;
+  rc = accumulate ? lz_ffn_backward_accumulate(b.dyp, b.xp, b.z, b.h, b.slot_offsets, b.w1, b.w2, shape, b.dxp, (float*)b.dw1_slot,
+                                               (float*)b.dw2_slot, b.train_ws, b.train_ws_bytes, stream)
+                  : lz_ffn_backward(b.dyp, b.xp, b.z, b.h, b.slot_offsets, b.w1, b.w2, shape, b.dxp, b.dw1_slot, b.dw2_slot,
+                                    b.train_ws, b.train_ws_bytes, stream);
+  if (rc != LZ_OK) return rc;
+  if ((rc = lz_permute_backward(b.dxp, b.pair_to_row, shape, b.dx, stream)) != LZ_OK) return rc;
+  if ((rc = lz_route_backward(b.dgates, b.topk_gates, b.topk_ids, shape, b.dlogits, stream)) != LZ_OK) return rc;
+  if (accumulate) return LZ_OK;
+  const int S = shape->N * shape->c;
+  const int64_t elems = (int64_t)shape->d * shape->ffn, elems1 = elems * (shape->act == LZ_SWIGLU ? 2 : 1);
+  if ((rc = lz_reduce_replica_grads_dtype(b.dw1_slot, b.slot_expert, S, shape->E, elems1, shape->dtype, b.dw1, stream)) != LZ_OK)
+    return rc;
+  return lz_reduce_replica_grads_dtype(b.dw2_slot, b.slot_expert, S, shape->E, elems, shape->dtype, b.dw2, stream);
+}
