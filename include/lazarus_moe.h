@@ -320,7 +320,7 @@ typedef struct {
 } lz_layer_buffers;
 
 /* lz_route, lz_plan_dispatch, lz_permute_scatter and lz_expert_ffn (fused: lz_expert_ffn_gather instead of the two, xp unused), then
- * lz_unpermute_combine.  The first step that is refused ends the call with
+ * lz_unpermute_combine: the same results in all buffers, in fewer launches.  The first step that is refused ends the call with
  * its status; steps before it may have run. */
 int32_t lz_layer_forward(const lz_shape* shape, const lz_layer_buffers* buffers, const float* logits, const void* x,
                          int32_t fused, void* stream);

@@ -21,6 +21,7 @@
 // from slot_offsets.
 #include "backward_generic.h"
 #include "gemm_narrow.h"
+#include "layer.h"
 
 namespace {
 
@@ -373,19 +374,49 @@ extern "C" size_t lz_train_workspace_bytes(const lz_shape* shape) {
   return bytes > generic || train_whole_tiles(shape) ? bytes : generic;
 }
 
-extern "C" int32_t lz_ffn_forward_train(const void* xp, const int32_t* slot_offsets, const void* w1, const void* w2,
-                                        const lz_shape* shape, void* z, void* h, void* yp, void* ws,
-                                        size_t ws_bytes, void* stream) {
+namespace {
+
+// Whether the bf16 kernels serve the call.
+bool on_mfma(const lz_shape* shape, bool aligned) { return train_shape(shape) && (aligned || train_whole_tiles(shape)); }
+
+TileSpecs forward_tables(const TrainWorkspace& w, const lz_shape* shape) {
+  const long long P = (long long)shape->T * shape->k;
+  const int S = shape->N * shape->c, n_up = ceil_div(shape->ffn, shape->act == LZ_SWIGLU ? BN / 2 : BN), n_d = ceil_div(shape->d, BN);
+  TileSpecs specs{};
+  if (!w.narrow_up) add_units(specs, n_up, 0, P, carve_units(w.units_up, P, S, n_up));
+  if (!w.narrow_d) add_units(specs, n_d, 0, P, carve_units(w.units_d, P, S, n_d));
+  if (w.narrow_up || w.narrow_d) add_rows(specs, kNarrow, P, narrow_tiles(w, S, P));
+  return specs;
+}
+
+}  // namespace
+
+TileSpecs lz::train_tables(const lz_shape* shape, const void* const* tensors, int n_tensors, void* ws, size_t ws_bytes) {
+  bool aligned = true;
+  for (int i = 0; i < n_tensors; ++i) aligned = aligned && aligned16(tensors[i]);
+  if (!lz::shape_ok(shape) || (long long)shape->T * shape->k == 0) return TileSpecs{};
+  if (on_mfma(shape, aligned)) {
+    TrainWorkspace w;
+    return check_train(shape, ws, ws_bytes, &w) == LZ_OK ? forward_tables(w, shape) : TileSpecs{};
+  }
+  GenericTrainWorkspace w;
+  F32Args a{};
+  if (check_train_generic(shape, ws, ws_bytes, &w) != LZ_OK) return TileSpecs{};
+  return generic_tables(a, shape->N * shape->c, (long long)shape->T * shape->k, w, split_forward(shape));
+}
+
+int32_t lz::ffn_forward_train(const void* xp, const int32_t* slot_offsets, const void* w1, const void* w2, const lz_shape* shape,
+                              void* z, void* h, void* yp, void* ws, size_t ws_bytes, bool tables_built, void* stream) {
   const bool aligned = aligned16(z) && aligned16(h) && aligned16(yp) && aligned16(xp) && aligned16(w1) && aligned16(w2);
-  if (!train_shape(shape) || (!aligned && !train_whole_tiles(shape))) {
+  if (!on_mfma(shape, aligned)) {
     GenericTrainWorkspace gw;
     const int32_t grc = check_train_generic(shape, ws, ws_bytes, &gw);
     if (grc != LZ_OK) return grc;
     if ((long long)shape->T * shape->k == 0) return LZ_OK;
     if (!xp || !slot_offsets || !w1 || !w2 || !z || !h || !yp) return LZ_EINVAL;
     return shape->dtype == LZ_F32
-               ? generic_forward_train<float>(xp, slot_offsets, w1, w2, shape, z, h, yp, gw, (hipStream_t)stream)
-               : generic_forward_train<uint16_t>(xp, slot_offsets, w1, w2, shape, z, h, yp, gw, (hipStream_t)stream);
+               ? generic_forward_train<float>(xp, slot_offsets, w1, w2, shape, z, h, yp, gw, tables_built, (hipStream_t)stream)
+               : generic_forward_train<uint16_t>(xp, slot_offsets, w1, w2, shape, z, h, yp, gw, tables_built, (hipStream_t)stream);
   }
   TrainWorkspace w;
   const int32_t rc = check_train(shape, ws, ws_bytes, &w);
@@ -400,11 +431,7 @@ extern "C" int32_t lz_ffn_forward_train(const void* xp, const int32_t* slot_offs
   const int n_up = ceil_div(shape->ffn, swiglu ? BN / 2 : BN);
   const UnitTable u_up = carve_units(w.units_up, P, S, n_up);
   const UnitTable u_d = carve_units(w.units_d, P, S, ceil_div(shape->d, BN));
-  TileSpecs specs{};
-  if (!w.narrow_up) add_units(specs, n_up, 0, P, u_up);
-  if (!w.narrow_d) add_units(specs, ceil_div(shape->d, BN), 0, P, u_d);
-  if (w.narrow_up || w.narrow_d) add_rows(specs, kNarrow, P, narrow_tiles(w, S, P));
-  int32_t r = launch_build_tiles(slot_offsets, S, specs, st);
+  int32_t r = tables_built ? LZ_OK : launch_build_tiles(slot_offsets, S, forward_tables(w, shape), st);
   if (r != LZ_OK) return r;
   // z = xp W1 and h = act(z) from one epilogue
   MfmaArgs g{};
@@ -426,6 +453,12 @@ extern "C" int32_t lz_ffn_forward_train(const void* xp, const int32_t* slot_offs
   if (r != LZ_OK) return r;
   return gemm_nn((const uint16_t*)h, (const uint16_t*)w2, (uint16_t*)yp, P, shape->ffn, shape->d, u_d,
                  w.narrow_d, w, S, st);
+}
+
+extern "C" int32_t lz_ffn_forward_train(const void* xp, const int32_t* slot_offsets, const void* w1, const void* w2,
+                                        const lz_shape* shape, void* z, void* h, void* yp, void* ws,
+                                        size_t ws_bytes, void* stream) {
+  return lz::ffn_forward_train(xp, slot_offsets, w1, w2, shape, z, h, yp, ws, ws_bytes, false, stream);
 }
 
 extern "C" int32_t lz_combine_backward(const void* dy, const void* yp, const int32_t* pair_to_row,

@@ -76,9 +76,8 @@ inline GenericTrainWorkspace carve_train_generic(void* ws, const lz_shape* s) {
   return w;
 }
 
-// The tables of a GEMM's arguments; `split`: that of the 64-row tiles too.
-inline int32_t generic_tiles(F32Args& a, const int32_t* slot_offsets, int S, long long P, const GenericTrainWorkspace& w,
-                             bool split, hipStream_t st) {
+// The tables of a GEMM's arguments, to be built; `split`: that of the 64-row tiles too.
+inline TileSpecs generic_tables(F32Args& a, int S, long long P, const GenericTrainWorkspace& w, bool split) {
   TileSpecs specs{};
   a.t = carve_tiles(w.tiles, P, S, kF32Rows);
   add_rows(specs, kF32Rows, P, a.t);
@@ -86,18 +85,19 @@ inline int32_t generic_tiles(F32Args& a, const int32_t* slot_offsets, int S, lon
     a.t_split = carve_tiles(w.tiles_split, P, S, kSplitRows);
     add_rows(specs, kSplitRows, P, a.t_split);
   }
-  return launch_build_tiles(slot_offsets, S, specs, st);
+  return specs;
 }
 
 template <typename Elem>
 int32_t generic_forward_train(const void* xp, const int32_t* slot_offsets, const void* w1, const void* w2,
                               const lz_shape* s, void* z, void* h, void* yp, const GenericTrainWorkspace& w,
-                              hipStream_t st) {
+                              bool tables_built, hipStream_t st) {
   const long long P = (long long)s->T * s->k;
   const int S = s->N * s->c, d = s->d, ffn = s->ffn, n1 = w.n1;
   // z = xp W1 and h = act(z) from one epilogue   (W1[s] = [d, n1])
   F32Args a{};
-  int32_t r = generic_tiles(a, slot_offsets, S, P, w, split_forward(s), st);
+  const TileSpecs tables = generic_tables(a, S, P, w, split_forward(s));
+  int32_t r = tables_built ? LZ_OK : launch_build_tiles(slot_offsets, S, tables, st);
   if (r != LZ_OK) return r;
   a.A = xp;
   a.W = w1;
@@ -135,8 +135,8 @@ int32_t generic_ffn_backward(const void* dyp, const void* xp, const void* z, con
   if (P > 0) {
     // dZ = (dyp W2^T) * act'(Z): W2[s] [ffn, d] along its rows
     F32Args a{};
-    r = generic_tiles(a, slot_offsets, S, P, w, false, st);  // the data gradients stay on the 32-row tiles
-    if (r != LZ_OK) return r;
+    const TileSpecs tables = generic_tables(a, S, P, w, false);  // the data gradients stay on the 32-row tiles
+    if ((r = launch_build_tiles(slot_offsets, S, tables, st)) != LZ_OK) return r;
     a.A = dyp;
     a.W = w2;
     a.C = w.dz;

@@ -13,6 +13,7 @@
 // fp32 tensors, and bf16 rows that are no whole 16-byte pieces: the fp32 matrix-core kernel of gemm_f32.h.
 #include "gemm_split.h"
 #include "gemm_narrow.h"
+#include "layer.h"
 
 namespace {
 
@@ -108,15 +109,10 @@ int32_t check_ffn(const lz_shape* shape, void* ws, size_t ws_bytes, FfnWorkspace
 
 }  // namespace
 
-extern "C" int32_t lz_ffn_tiles(const int32_t* slot_offsets, const lz_shape* shape, void* ws,
-                                size_t ws_bytes, void* stream) {
-  FfnWorkspace w;
-  const int32_t rc = check_ffn(shape, ws, ws_bytes, &w);
-  if (rc != LZ_OK) return rc;
+namespace {
+
+TileSpecs tables_of(const FfnWorkspace& w, const lz_shape* shape) {
   const long long P = (long long)shape->T * shape->k;
-  if (P == 0) return LZ_OK;
-  if (!slot_offsets) return LZ_EINVAL;
-  const int S = shape->N * shape->c;
   TileSpecs specs{};
   if (mfma_shape(shape)) {
     if (!w.narrow_up) add_units(specs, w.n_up, 0, P, units_up_of(w, shape));
@@ -126,7 +122,25 @@ extern "C" int32_t lz_ffn_tiles(const int32_t* slot_offsets, const lz_shape* sha
   // the calls that follow may bring unaligned tensors where that is allowed
   if (!mfma_shape(shape) || !whole_tiles(shape)) add_rows(specs, kF32Rows, P, f32_tiles_of(w, shape));
   if (split_forward(shape)) add_rows(specs, kSplitRows, P, split_tiles_of(w, shape));
-  return launch_build_tiles(slot_offsets, S, specs, (hipStream_t)stream);
+  return specs;
+}
+
+}  // namespace
+
+TileSpecs lz::ffn_tables(const lz_shape* shape, void* ws, size_t ws_bytes) {
+  FfnWorkspace w;
+  if (check_ffn(shape, ws, ws_bytes, &w) != LZ_OK || (long long)shape->T * shape->k == 0) return TileSpecs{};
+  return tables_of(w, shape);
+}
+
+extern "C" int32_t lz_ffn_tiles(const int32_t* slot_offsets, const lz_shape* shape, void* ws,
+                                size_t ws_bytes, void* stream) {
+  FfnWorkspace w;
+  const int32_t rc = check_ffn(shape, ws, ws_bytes, &w);
+  if (rc != LZ_OK) return rc;
+  if ((long long)shape->T * shape->k == 0) return LZ_OK;
+  if (!slot_offsets) return LZ_EINVAL;
+  return launch_build_tiles(slot_offsets, shape->N * shape->c, tables_of(w, shape), (hipStream_t)stream);
 }
 
 namespace {

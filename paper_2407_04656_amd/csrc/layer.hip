@@ -1,15 +1,25 @@
-// The whole layer in one call: the single calls in their order, on the caller's buffers.  A caller of small batches pays for the calls:
-// from Python a forward of 256 tokens spent 34 us on five of them and seven launches, 30 on one.
-#include "lz_common.h"
+// The whole layer in one call: the steps of the single calls in their order, on the caller's buffers.  What a caller of small batches
+// pays for is launches and calls (from Python a forward of 256 tokens spent 34 us of the host on five calls, 30 on one): the dispatcher's
+// launches also build the tables of the grouped GEMMs, and route where the batch is
+// small enough for one workgroup.
+#include "layer.h"
 
 namespace {
 
-int32_t route_and_plan(const lz_shape* shape, const lz_layer_buffers& b, const float* logits, void* stream) {
+lz::Dispatch dispatch_of(const lz_shape* shape, const lz_layer_buffers& b) {
+  return lz::Dispatch{shape, b.topk_ids, b.rank_tok_off, b.slot_expert, b.slot_counts, b.slot_offsets, b.pair_to_row, b.row_to_pair,
+                      b.Tej_opt, b.D_opt, b.status_opt, b.plan_ws, b.plan_ws_bytes};
+}
+
+// lz_route, lz_plan_dispatch and `tables`
+int32_t route_and_plan(const lz_shape* shape, const lz_layer_buffers& b, const float* logits, const TileSpecs& tables, void* stream) {
   if (!shape) return LZ_ESHAPE;
-  const int32_t rc = lz_route(logits, shape->T, shape->E, shape->k, b.topk_ids, b.topk_gates, stream);
-  if (rc != LZ_OK) return rc;
-  return lz_plan_dispatch(b.topk_ids, shape, b.rank_tok_off, b.slot_expert, b.slot_counts, b.slot_offsets, b.pair_to_row,
-                          b.row_to_pair, b.Tej_opt, b.D_opt, b.status_opt, b.plan_ws, b.plan_ws_bytes, stream);
+  const bool in_plan = lz::plan_routes(shape) && logits && b.topk_ids && b.topk_gates;
+  if (!in_plan) {
+    const int32_t rc = lz_route(logits, shape->T, shape->E, shape->k, b.topk_ids, b.topk_gates, stream);
+    if (rc != LZ_OK) return rc;
+  }
+  return lz::plan_dispatch(dispatch_of(shape, b), in_plan ? logits : nullptr, b.topk_gates, tables, (hipStream_t)stream);
 }
 
 }  // namespace
@@ -18,12 +28,21 @@ extern "C" int32_t lz_layer_forward(const lz_shape* shape, const lz_layer_buffer
                                     int32_t fused, void* stream) {
   if (!buffers) return LZ_EINVAL;
   const lz_layer_buffers& b = *buffers;
-  int32_t rc = route_and_plan(shape, b, logits, stream);
+  const TileSpecs tables = lz::ffn_tables(shape, b.ffn_ws, b.ffn_ws_bytes);
+  int32_t rc = route_and_plan(shape, b, logits, tables, stream);
   if (rc != LZ_OK) return rc;
   if (!fused && (rc = lz_permute_scatter(x, b.pair_to_row, shape, b.xp, stream)) != LZ_OK) return rc;
-  rc = fused ? lz_expert_ffn_gather(x, b.row_to_pair, b.slot_offsets, b.w1, b.w2, shape, b.yp, b.ffn_ws, b.ffn_ws_bytes, stream)
-             : lz_expert_ffn(b.xp, b.slot_offsets, b.w1, b.w2, shape, b.yp, b.ffn_ws, b.ffn_ws_bytes, stream);
-  if (rc != LZ_OK) return rc;
+  if (tables.n == 0) {  // no rows, or a workspace that is refused
+    rc = fused ? lz_expert_ffn_gather(x, b.row_to_pair, b.slot_offsets, b.w1, b.w2, shape, b.yp, b.ffn_ws, b.ffn_ws_bytes, stream)
+               : lz_expert_ffn(b.xp, b.slot_offsets, b.w1, b.w2, shape, b.yp, b.ffn_ws, b.ffn_ws_bytes, stream);
+    if (rc != LZ_OK) return rc;
+  } else {
+    if (!(fused ? x : b.xp) || !b.w1 || !b.w2 || !b.yp) return LZ_EINVAL;
+    rc = fused ? lz_ffn_up_gather(x, b.row_to_pair, b.w1, shape, b.ffn_ws, b.ffn_ws_bytes, stream)
+               : lz_ffn_up(b.xp, b.w1, shape, b.ffn_ws, b.ffn_ws_bytes, stream);
+    if (rc != LZ_OK) return rc;
+    if ((rc = lz_ffn_down(b.w2, shape, b.yp, b.ffn_ws, b.ffn_ws_bytes, stream)) != LZ_OK) return rc;
+  }
   return lz_unpermute_combine(b.yp, b.pair_to_row, b.topk_gates, shape, b.y, stream);
 }
 
@@ -31,10 +50,12 @@ extern "C" int32_t lz_layer_forward_train(const lz_shape* shape, const lz_layer_
                                           void* stream) {
   if (!buffers) return LZ_EINVAL;
   const lz_layer_buffers& b = *buffers;
-  int32_t rc = route_and_plan(shape, b, logits, stream);
+  const void* const tensors[] = {b.z, b.h, b.yp, b.xp, b.w1, b.w2};
+  const TileSpecs tables = lz::train_tables(shape, tensors, 6, b.train_ws, b.train_ws_bytes);
+  int32_t rc = route_and_plan(shape, b, logits, tables, stream);
   if (rc != LZ_OK) return rc;
   if ((rc = lz_permute_scatter(x, b.pair_to_row, shape, b.xp, stream)) != LZ_OK) return rc;
-  rc = lz_ffn_forward_train(b.xp, b.slot_offsets, b.w1, b.w2, shape, b.z, b.h, b.yp, b.train_ws, b.train_ws_bytes, stream);
+  rc = lz::ffn_forward_train(b.xp, b.slot_offsets, b.w1, b.w2, shape, b.z, b.h, b.yp, b.train_ws, b.train_ws_bytes, tables.n > 0, stream);
   if (rc != LZ_OK) return rc;
   return lz_unpermute_combine(b.yp, b.pair_to_row, b.topk_gates, shape, b.y, stream);
 }

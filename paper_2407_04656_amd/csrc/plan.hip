@@ -18,7 +18,8 @@
 // 8 21.8, now 15.7, 15.4, 16.4; 262144 pairs, 256 experts, 32 ranks of 10 41.7, now 31.7, 28.3, 28.1.
 #include <mutex>
 
-#include "lz_common.h"
+#include "layer.h"
+#include "route.h"
 
 namespace {
 
@@ -451,7 +452,9 @@ __device__ __forceinline__ void place_chunk(const int32_t* __restrict__ ids, lon
 
 // First rows of the slots from their sizes, by a whole workgroup (each thread a run of consecutive slots); returns their sum
 // in the last thread.  s_first may be written when the workgroup has passed its first barrier.
-__device__ __forceinline__ int scan_slots(const int32_t* __restrict__ slot_counts, int S, int* s_first, int* s_wave) {
+// end_of(slot, end of its rows): to be kept by the caller.
+template <typename EndOf>
+__device__ __forceinline__ int scan_slots(const int32_t* __restrict__ slot_counts, int S, int* s_first, int* s_wave, EndOf end_of) {
   const int tid = threadIdx.x, lane = tid % lz::kWave, w = tid / lz::kWave;
   const int per = (S + (int)blockDim.x - 1) / (int)blockDim.x, first = tid * per;
   int own = 0;
@@ -465,6 +468,7 @@ __device__ __forceinline__ int scan_slots(const int32_t* __restrict__ slot_count
   for (int s = first; s < first + per && s < S; ++s) {
     s_first[s] = running;
     running += slot_counts[s];
+    end_of(s, running);
   }
   return end;
 }
@@ -475,28 +479,52 @@ __device__ __forceinline__ int scan_slots(const int32_t* __restrict__ slot_count
 // workgroup's rank is searched in LDS where it fits.
 constexpr int kCumSlice = 8448;  // 256 experts, 32 ranks
 
+struct PlaceLds {
+  int run[kGroup * kRowE];
+  int cum[kCumSlice];
+  int first[kMostSlots];
+  unsigned short sorted[kMostSlots];
+};
+struct TableLds {
+  SlotRows<kMostSlots> slots;
+  TableScratch<kMostSlots> scratch;
+};
+
+// Workgroups from place_groups on build a table of the grouped GEMMs each, from the slot sizes too: a launch of their own
+// behind this one took 5 us of every forward.
 __global__ __launch_bounds__(kGroup * lz::kWave) void place_kernel(const int32_t* __restrict__ ids,
                                                     const int32_t* __restrict__ rank_tok_off, int T,
                                                     int E, int N, int c, int k, PlanTables t, bool counted,
                                                     const int32_t* __restrict__ slot_counts,
                                                     int32_t* __restrict__ slot_offsets,
                                                     int32_t* __restrict__ pair_to_row,
-                                                    int32_t* __restrict__ row_to_pair, int32_t* __restrict__ status_opt) {
+                                                    int32_t* __restrict__ row_to_pair, int32_t* __restrict__ status_opt,
+                                                    int place_groups, TileSpecs tables, int workgroups) {
   constexpr int kThreads = kGroup * lz::kWave;
+  static_assert(kThreads == kTileThreads, "a table a workgroup");
   __shared__ int s_off[lz::kMaxN + 1], s_cf[lz::kMaxN + 1], s_gf[lz::kMaxN + 1];
-  __shared__ int s_run[kGroup * kRowE];
-  __shared__ int s_cum[kCumSlice];
-  __shared__ int s_first[lz::kMaxN * lz::kMaxC], s_wave[kGroup];
-  __shared__ unsigned short s_sorted[lz::kMaxN * lz::kMaxC];
+  __shared__ __attribute__((aligned(16))) char lds[sizeof(PlaceLds) > sizeof(TableLds) ? sizeof(PlaceLds) : sizeof(TableLds)];
+  __shared__ int s_wave[kGroup];
   __shared__ int s_status;
   const int tid = threadIdx.x, w = tid / lz::kWave;
   const int S = N * c;
+  if ((int)blockIdx.x >= place_groups) {
+    TableLds& m = *(TableLds*)lds;
+    scan_slots(slot_counts, S, m.slots.first, s_wave, [&](int s, int end) { m.slots.end[s] = end; });
+    __syncthreads();
+    build_table(tables.spec[blockIdx.x - place_groups], false, m.slots, S, m.scratch, tid, workgroups);
+    return;
+  }
+  int* const s_run = ((PlaceLds*)lds)->run;
+  int* const s_cum = ((PlaceLds*)lds)->cum;
+  int* const s_first = ((PlaceLds*)lds)->first;
+  unsigned short* const s_sorted = ((PlaceLds*)lds)->sorted;
   if (tid < lz::kWave) {
     const bool bad = build_split(rank_tok_off, T, N, k, s_off, s_cf, s_gf);
     if (tid == 0) s_status = bad ? LZ_PLAN_BAD_RANK_SPLIT : 0;
   }
   for (int s = tid; s < S; s += kThreads) s_sorted[s] = (unsigned short)t.slot_sorted[s];
-  const int end = scan_slots(slot_counts, S, s_first, s_wave);
+  const int end = scan_slots(slot_counts, S, s_first, s_wave, [](int, int) {});
   if (blockIdx.x == 0) {
     int flag = 0;
     for (int e = tid; e < E; e += kThreads) flag |= t.estatus[e];
@@ -535,12 +563,12 @@ __global__ __launch_bounds__(kGroup * lz::kWave) void place_kernel(const int32_t
   auto sorted = [&](int at) { return (int)s_sorted[at]; };
   auto first = [&](int s) { return s_first[s]; };
   if (slice <= kCumSlice) {
-    const PlaceTables tables{[&](int e, int j) { return s_cum[e * (N + 1) + j]; }, pre, list, sorted, first};
-    place_chunk(ids, p0, p1, run, E, N, c, (long long)T * k, tables, pair_to_row, row_to_pair);
+    const PlaceTables lookups{[&](int e, int j) { return s_cum[e * (N + 1) + j]; }, pre, list, sorted, first};
+    place_chunk(ids, p0, p1, run, E, N, c, (long long)T * k, lookups, pair_to_row, row_to_pair);
   } else {
     const int32_t* const cum = t.cumDst + (size_t)i * slice;
-    const PlaceTables tables{[=](int e, int j) { return cum[e * (N + 1) + j]; }, pre, list, sorted, first};
-    place_chunk(ids, p0, p1, run, E, N, c, (long long)T * k, tables, pair_to_row, row_to_pair);
+    const PlaceTables lookups{[=](int e, int j) { return cum[e * (N + 1) + j]; }, pre, list, sorted, first};
+    place_chunk(ids, p0, p1, run, E, N, c, (long long)T * k, lookups, pair_to_row, row_to_pair);
   }
 }
 
@@ -560,11 +588,14 @@ inline bool small_plan(const lz_shape* s) {
          s->E * s->N * s->N <= kSmallTriples && s->E * s->N <= kSmallLists && s->N * s->c <= kSmallSlots;
 }
 
+// G > 0: it routes the tokens first, G lanes each (logits to ids and gates); tables: it then builds those of the grouped GEMMs.
+template <int G>
 __global__ __launch_bounds__(kSchedThreads) void plan_small_kernel(
-    const int32_t* __restrict__ ids, const int32_t* __restrict__ rank_tok_off, const int32_t* __restrict__ slot_expert,
+    const float* __restrict__ logits, float* __restrict__ gates, int32_t* __restrict__ ids, const int32_t* __restrict__ rank_tok_off,
+    const int32_t* __restrict__ slot_expert,
     int T, int E, int N, int c, int k, int32_t* __restrict__ slot_counts, int32_t* __restrict__ slot_offsets,
     int32_t* __restrict__ pair_to_row, int32_t* __restrict__ row_to_pair, int32_t* __restrict__ Tej_opt,
-    int32_t* __restrict__ D_opt, int32_t* __restrict__ status_opt) {
+    int32_t* __restrict__ D_opt, int32_t* __restrict__ status_opt, TileSpecs tables, int workgroups) {
   constexpr int kWaves = kSchedThreads / lz::kWave;
   __shared__ int s_off[lz::kMaxN + 1], s_cf[lz::kMaxN + 1];
   __shared__ int s_cnt[kSmallCounts];                       // [chunk][e] counts, then positions of the first pair
@@ -575,9 +606,22 @@ __global__ __launch_bounds__(kSchedThreads) void plan_small_kernel(
   __shared__ int s_expert[kSmallSlots], s_sorted[kSmallSlots], s_first[kSmallSlots];
   __shared__ int s_wave[kWaves];
   __shared__ int s_status;
+  __shared__ int s_ids[kSmallPairs];
+  __shared__ SlotRows<kSmallSlots> s_rows;
+  __shared__ TableScratch<kSmallSlots> s_scratch[2];
   const int tid = threadIdx.x, lane = tid % lz::kWave, w = tid / lz::kWave;
   const int S = N * c;
   const long long P = (long long)T * k;
+  if constexpr (G > 0) {
+    for (int t0 = 0; t0 < T; t0 += kSchedThreads / G)
+      route_token<G, 4, false, false>(logits, t0 + tid / G, T, E, k, [&](long long t, int kk, int id, float gate) {
+        ids[t * k + kk] = id;
+        gates[t * k + kk] = gate;
+        s_ids[t * k + kk] = id;
+      });
+  } else {
+    for (int p = tid; p < (int)P; p += kSchedThreads) s_ids[p] = ids[p];
+  }
   if (tid < lz::kWave) {
     const bool bad = build_split(rank_tok_off, T, N, k, s_off, s_cf);
     if (tid == 0) s_status = bad ? LZ_PLAN_BAD_RANK_SPLIT : 0;
@@ -597,7 +641,7 @@ __global__ __launch_bounds__(kSchedThreads) void plan_small_kernel(
     long long p0 = 0, p1 = 0;
     chunk_range(b, N, k, s_off, s_cf, &p0, &p1);
     for (long long p = p0 + lane; p < p1; p += lz::kWave) {
-      const int e = ids[p];
+      const int e = s_ids[p];
       if (e >= 0 && e < E) atomicAdd(&s_cnt[b * E + e], 1);
       else flag |= LZ_PLAN_BAD_EXPERT_ID;
       row_to_pair[p] = -1;  // rows and pairs share the index range [0, P)
@@ -683,6 +727,8 @@ __global__ __launch_bounds__(kSchedThreads) void plan_small_kernel(
   if (tid < S) {
     s_first[tid] = incl - count;
     slot_offsets[tid] = incl - count;
+    s_rows.first[tid] = incl - count;
+    s_rows.end[tid] = incl;
   }
   if (tid == kSchedThreads - 1) slot_offsets[S] = incl;
   if (tid == 0 && status_opt) *status_opt = s_status;
@@ -692,11 +738,19 @@ __global__ __launch_bounds__(kSchedThreads) void plan_small_kernel(
   for (int b = w; b < chunks; b += kWaves) {
     long long p0 = 0, p1 = 0;
     const int i = chunk_range(b, N, k, s_off, s_cf, &p0, &p1);
-    const PlaceTables tables{[=](int e, int j) { return s_cum[(e * N + i) * (N + 1) + j]; },
+    const PlaceTables lookups{[=](int e, int j) { return s_cum[(e * N + i) * (N + 1) + j]; },
                              [=](int e, int j) { return s_D[(e * N + i) * N + j]; },
                              [=](int e, int j) { return int3{s_recv[e * N + j], s_R[e * N + j], s_start[e * N + j]}; },
                              [=](int at) { return s_sorted[at]; }, [=](int s) { return s_first[s]; }};
-    place_chunk(ids, p0, p1, s_cnt + b * E, E, N, c, P, tables, pair_to_row, row_to_pair);
+    place_chunk(s_ids, p0, p1, s_cnt + b * E, E, N, c, P, lookups, pair_to_row, row_to_pair);
+  }
+
+  // ---- tables, two at a time
+  for (int i = 0; i < tables.n; i += 2) {
+    const int half = __builtin_amdgcn_readfirstlane(tid / kTileThreads);
+    if (i > 0) __syncthreads();  // the scratch has been read
+    build_table(tables.spec[i + half < tables.n ? i + half : i], i + half >= tables.n, s_rows, S, s_scratch[half], tid % kTileThreads,
+                workgroups);
   }
 }
 
@@ -709,6 +763,9 @@ extern "C" size_t lz_plan_workspace_bytes(const lz_shape* shape) {
 
 namespace {
 
+// Lanes of a token where the one workgroup routes, four logits each.
+inline int route_lanes(int E) { return E <= 4 ? 1 : E <= 8 ? 2 : E <= 16 ? 4 : 8; }
+
 // Whether the expert's workgroups count their pairs themselves, each reading all ids.  us, so and with a launch that counts: 2000 pairs,
 // 8 and 53 experts 11.4, 12.9 and 12.6, 14.2; 8000 pairs, 16 experts 12.9, 13.7; 16384 pairs, 8 experts 14.4, 13.5; 32768 pairs,
 // 32 experts 18.0, 13.9.
@@ -717,61 +774,77 @@ inline bool direct_counts(const lz_shape* s) {
   return P <= kDirectPairs;
 }
 
-// The launches of the dispatcher on tables carved from `ws` (already checked by the caller).
-int32_t enqueue_plan(const int32_t* topk_ids, const lz_shape* shape, const int32_t* rank_tok_off,
-                     const int32_t* slot_expert, int32_t* slot_counts, int32_t* slot_offsets,
-                     int32_t* pair_to_row, int32_t* row_to_pair, int32_t* Tej_opt, int32_t* D_opt,
-                     int32_t* status_opt, const PlanTables& t, hipStream_t st) {
-  const long long P = (long long)shape->T * shape->k;
-  if (small_plan(shape)) {
-    hipLaunchKernelGGL(plan_small_kernel, dim3(1), dim3(kSchedThreads), 0, st, topk_ids, rank_tok_off, slot_expert, shape->T,
-                       shape->E, shape->N, shape->c, shape->k, slot_counts, slot_offsets, pair_to_row, row_to_pair, Tej_opt,
-                       D_opt, status_opt);
+// The launches of the dispatcher on tables carved from its workspace (already checked by the caller); with logits (where
+// plan_routes says so) the routing too, and the tables of the grouped GEMMs that `tables` lists.
+int32_t enqueue_plan(const lz::Dispatch& d, const float* logits, float* topk_gates, const TileSpecs& tables, const PlanTables& t,
+                     hipStream_t st) {
+  const lz_shape* const s = d.shape;
+  const long long P = (long long)s->T * s->k;
+  const int workgroups = tables.n > 0 ? device_cus() : 0;
+  if (tables.n > 0 && workgroups == 0) return LZ_EHIP;
+  if (small_plan(s)) {
+    const int g = logits == nullptr ? 0 : route_lanes(s->E);
+    auto* const kern = g == 0 ? plan_small_kernel<0> : g == 1 ? plan_small_kernel<1> : g == 2 ? plan_small_kernel<2>
+                       : g == 4 ? plan_small_kernel<4> : plan_small_kernel<8>;
+    hipLaunchKernelGGL(kern, dim3(1), dim3(kSchedThreads), 0, st, logits, topk_gates, d.topk_ids, d.rank_tok_off, d.slot_expert,
+                       s->T, s->E, s->N, s->c, s->k, d.slot_counts, d.slot_offsets, d.pair_to_row, d.row_to_pair, d.Tej_opt,
+                       d.D_opt, d.status_opt, tables, workgroups);
     return lz::launch_status();
   }
-  const unsigned blocks = P > 0 ? (unsigned)max_groups(P, shape->N) : 1;
+  const unsigned blocks = P > 0 ? (unsigned)max_groups(P, s->N) : 1;
   constexpr int threads = kGroup * lz::kWave;
-  const bool direct = direct_counts(shape);
+  const bool direct = direct_counts(s);
   if (direct) {
-    hipLaunchKernelGGL(schedule_expert_kernel<true>, dim3(shape->E), dim3(1024), 0, st, topk_ids, rank_tok_off, slot_expert,
-                       shape->T, shape->E, shape->N, shape->c, shape->k, t, slot_counts, row_to_pair, Tej_opt, D_opt);
+    hipLaunchKernelGGL(schedule_expert_kernel<true>, dim3(s->E), dim3(1024), 0, st, d.topk_ids, d.rank_tok_off, d.slot_expert,
+                       s->T, s->E, s->N, s->c, s->k, t, d.slot_counts, d.row_to_pair, d.Tej_opt, d.D_opt);
   } else {
     if (P > 0)
-      hipLaunchKernelGGL(count_kernel, dim3(blocks), dim3(threads), 0, st, topk_ids, rank_tok_off, shape->T,
-                         shape->E, shape->N, shape->k, t, row_to_pair);
-    const int expert_waves = shape->N < 4 ? 4 : shape->N < 16 ? shape->N : 16;  // one per source rank
-    hipLaunchKernelGGL(schedule_expert_kernel<false>, dim3(shape->E), dim3(lz::kWave * expert_waves), 0, st, topk_ids, rank_tok_off,
-                       slot_expert, shape->T, shape->E, shape->N, shape->c, shape->k, t, slot_counts, row_to_pair, Tej_opt, D_opt);
+      hipLaunchKernelGGL(count_kernel, dim3(blocks), dim3(threads), 0, st, d.topk_ids, d.rank_tok_off, s->T, s->E, s->N, s->k, t,
+                         d.row_to_pair);
+    const int expert_waves = s->N < 4 ? 4 : s->N < 16 ? s->N : 16;  // one per source rank
+    hipLaunchKernelGGL(schedule_expert_kernel<false>, dim3(s->E), dim3(lz::kWave * expert_waves), 0, st, d.topk_ids, d.rank_tok_off,
+                       d.slot_expert, s->T, s->E, s->N, s->c, s->k, t, d.slot_counts, d.row_to_pair, d.Tej_opt, d.D_opt);
   }
-  hipLaunchKernelGGL(place_kernel, dim3(blocks), dim3(threads), 0, st, topk_ids, rank_tok_off, shape->T, shape->E, shape->N, shape->c,
-                     shape->k, t, !direct, slot_counts, slot_offsets, pair_to_row, row_to_pair, status_opt);
+  hipLaunchKernelGGL(place_kernel, dim3(blocks + tables.n), dim3(threads), 0, st, d.topk_ids, d.rank_tok_off, s->T, s->E, s->N, s->c,
+                     s->k, t, !direct, d.slot_counts, d.slot_offsets, d.pair_to_row, d.row_to_pair, d.status_opt, (int)blocks, tables,
+                     workgroups);
   return lz::launch_status();
 }
 
-int32_t check_plan_args(const int32_t* topk_ids, const lz_shape* shape, const int32_t* rank_tok_off,
-                        const int32_t* slot_expert, const int32_t* slot_counts, const int32_t* slot_offsets,
-                        const int32_t* pair_to_row, const int32_t* row_to_pair) {
-  if (!lz::shape_ok(shape)) return LZ_ESHAPE;
-  if (!rank_tok_off || !slot_expert || !slot_counts || !slot_offsets) return LZ_EINVAL;
-  const long long P = (long long)shape->T * shape->k;
-  if (P > 0 && (!topk_ids || !pair_to_row || !row_to_pair)) return LZ_EINVAL;
+int32_t check_plan_args(const lz::Dispatch& d) {
+  if (!lz::shape_ok(d.shape)) return LZ_ESHAPE;
+  if (!d.rank_tok_off || !d.slot_expert || !d.slot_counts || !d.slot_offsets) return LZ_EINVAL;
+  const long long P = (long long)d.shape->T * d.shape->k;
+  if (P > 0 && (!d.topk_ids || !d.pair_to_row || !d.row_to_pair)) return LZ_EINVAL;
   return LZ_OK;
 }
 
 }  // namespace
+
+namespace lz {
+
+// Where the one workgroup routes its tokens in one go.  us of a forward (64 x 64, top-2), routing launched before and inside: 64 and 512
+// tokens of 8 experts 22.5, 21.2 and 23.8, 22.8; 256 of 16 experts 24.3, 23.0; two goes, 512 of them, 25.0, 25.2; four 26.2, 29.1.
+bool plan_routes(const lz_shape* s) { return shape_ok(s) && small_plan(s) && s->T * route_lanes(s->E) <= kSchedThreads; }
+
+int32_t plan_dispatch(const Dispatch& d, const float* logits, float* topk_gates, const TileSpecs& tables, hipStream_t st) {
+  const int32_t rc = check_plan_args(d);
+  if (rc != LZ_OK) return rc;
+  const PlanTables t = carve(d.ws, d.shape);
+  if (!d.ws || (uintptr_t)d.ws % 256 != 0 || d.ws_bytes < t.total_bytes) return LZ_EWORKSPACE;
+  return enqueue_plan(d, logits, topk_gates, tables, t, st);
+}
+
+}  // namespace lz
 
 extern "C" int32_t lz_plan_dispatch(const int32_t* topk_ids, const lz_shape* shape,
                                     const int32_t* rank_tok_off, const int32_t* slot_expert,
                                     int32_t* slot_counts, int32_t* slot_offsets, int32_t* pair_to_row,
                                     int32_t* row_to_pair, int32_t* Tej_opt, int32_t* D_opt,
                                     int32_t* status_opt, void* ws, size_t ws_bytes, void* stream) {
-  const int32_t rc = check_plan_args(topk_ids, shape, rank_tok_off, slot_expert, slot_counts, slot_offsets,
-                                     pair_to_row, row_to_pair);
-  if (rc != LZ_OK) return rc;
-  PlanTables t = carve(ws, shape);
-  if (!ws || (uintptr_t)ws % 256 != 0 || ws_bytes < t.total_bytes) return LZ_EWORKSPACE;
-  return enqueue_plan(topk_ids, shape, rank_tok_off, slot_expert, slot_counts, slot_offsets, pair_to_row,
-                      row_to_pair, Tej_opt, D_opt, status_opt, t, (hipStream_t)stream);
+  const lz::Dispatch d{shape, const_cast<int32_t*>(topk_ids), rank_tok_off, slot_expert, slot_counts, slot_offsets, pair_to_row,
+                       row_to_pair, Tej_opt, D_opt, status_opt, ws, ws_bytes};
+  return lz::plan_dispatch(d, nullptr, nullptr, TileSpecs{}, (hipStream_t)stream);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -782,7 +855,6 @@ static __device__ __align__(256) unsigned char scratch[LZ_PLAN_NOALLOC_SCRATCH_B
 
 namespace {
 
-constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mutex;
 void* g_scratch_ptr[kMaxDevices] = {};  // device address of `scratch` on each GPU, looked up once
 
@@ -808,8 +880,9 @@ extern "C" int32_t lz_plan_dispatch_noalloc(const int32_t* topk_ids, const lz_sh
                                             int32_t* slot_counts, int32_t* slot_offsets,
                                             int32_t* pair_to_row, int32_t* row_to_pair, int32_t* Tej_opt,
                                             int32_t* D_opt, int32_t* status_opt, void* stream) {
-  const int32_t rc = check_plan_args(topk_ids, shape, rank_tok_off, slot_expert, slot_counts, slot_offsets,
-                                     pair_to_row, row_to_pair);
+  const lz::Dispatch d{shape, const_cast<int32_t*>(topk_ids), rank_tok_off, slot_expert, slot_counts, slot_offsets, pair_to_row,
+                       row_to_pair, Tej_opt, D_opt, status_opt, nullptr, 0};
+  const int32_t rc = check_plan_args(d);
   if (rc != LZ_OK) return rc;
   if (carve(nullptr, shape).total_bytes > (size_t)LZ_PLAN_NOALLOC_SCRATCH_BYTES) return LZ_EWORKSPACE;
   void* base = nullptr;
@@ -818,6 +891,5 @@ extern "C" int32_t lz_plan_dispatch_noalloc(const int32_t* topk_ids, const lz_sh
   // Every table entry a kernel reads was written earlier in the same call, so what the previous
   // call left in the array does not matter and nothing has to be cleared.
   const PlanTables t = carve(base, shape);
-  return enqueue_plan(topk_ids, shape, rank_tok_off, slot_expert, slot_counts, slot_offsets, pair_to_row,
-                      row_to_pair, Tej_opt, D_opt, status_opt, t, (hipStream_t)stream);
+  return enqueue_plan(d, nullptr, nullptr, TileSpecs{}, t, (hipStream_t)stream);
 }
