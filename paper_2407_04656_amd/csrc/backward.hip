@@ -25,7 +25,6 @@
 
 namespace {
 
-constexpr int kRowsPerBlock = 4;  // streaming kernels: one wave per row
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ float wave_sum(float v) {
@@ -52,17 +51,31 @@ __device__ __forceinline__ u32x4 pack8(const float* f) {
   return o;
 }
 
+// the elements of a 16-byte piece
+__device__ __forceinline__ void unpack(const u32x4& v, float* f, uint16_t) { unpack8(v, f); }
+__device__ __forceinline__ void unpack(const u32x4& v, float* f, float) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) f[q] = __uint_as_float(v[q]);
+}
+__device__ __forceinline__ u32x4 pack(const float* f, uint16_t) { return pack8(f); }
+__device__ __forceinline__ u32x4 pack(const float* f, float) {
+  return u32x4{__float_as_uint(f[0]), __float_as_uint(f[1]), __float_as_uint(f[2]), __float_as_uint(f[3])};
+}
+
 // ---- combine backward: one wave per token.  dy[t] is read once, every yp row once, every
 // dyp row written once; the k dot products are reduced over the wave at the end.
-__global__ __launch_bounds__(256) void combine_backward_kernel(const u32x4* __restrict__ dy,
+template <typename Elem>
+__global__ __launch_bounds__(kCombineThreads) void combine_backward_kernel(const u32x4* __restrict__ dy,
                                                                const u32x4* __restrict__ yp,
                                                                const int32_t* __restrict__ pair_to_row,
                                                                const float* __restrict__ gates, int T, int k,
                                                                long long P, int vec_per_row,
                                                                u32x4* __restrict__ dyp,
-                                                               float* __restrict__ dgates) {
+                                                               float* __restrict__ dgates, WithCombine with) {
+  __shared__ CombineLds lds;
+  if (table_workgroup(with, lds)) return;
   const int lane = threadIdx.x % lz::kWave;
-  const long long t = (long long)blockIdx.x * kRowsPerBlock + threadIdx.x / lz::kWave;
+  const long long t = ((long long)blockIdx.x - with.tables.n) * kTokensPerBlock + threadIdx.x / lz::kWave;
   if (t >= T) return;
   long long rows[lz::kMaxK];
   float g[lz::kMaxK], dot[lz::kMaxK];
@@ -78,8 +91,9 @@ __global__ __launch_bounds__(256) void combine_backward_kernel(const u32x4* __re
     }
   }
   for (int v = lane; v < vec_per_row; v += lz::kWave) {
-    float gy[8];
-    unpack8(__builtin_nontemporal_load(dy + (size_t)t * vec_per_row + v), gy);
+    constexpr int kElems = 16 / sizeof(Elem);
+    float gy[kElems];
+    unpack(__builtin_nontemporal_load(dy + (size_t)t * vec_per_row + v), gy, Elem{});
     u32x4 in[lz::kMaxK];
 #pragma unroll
     for (int kk = 0; kk < lz::kMaxK; ++kk)
@@ -87,22 +101,23 @@ __global__ __launch_bounds__(256) void combine_backward_kernel(const u32x4* __re
 #pragma unroll
     for (int kk = 0; kk < lz::kMaxK; ++kk)
       if (kk < k && rows[kk] >= 0) {
-        float y8[8], o[8];
-        unpack8(in[kk], y8);
+        float y[kElems], o[kElems];
+        unpack(in[kk], y, Elem{});
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          dot[kk] = fmaf(gy[q], y8[q], dot[kk]);
+        for (int q = 0; q < kElems; ++q) {
+          dot[kk] = fmaf(gy[q], y[q], dot[kk]);
           o[q] = g[kk] * gy[q];
         }
-        __builtin_nontemporal_store(pack8(o), dyp + (size_t)rows[kk] * vec_per_row + v);
+        __builtin_nontemporal_store(pack(o, Elem{}), dyp + (size_t)rows[kk] * vec_per_row + v);
       }
   }
 #pragma unroll
   for (int kk = 0; kk < lz::kMaxK; ++kk)
     if (kk < k) {
-      const float s = wave_sum(dot[kk]);
-      if (lane == 0) dgates[t * k + kk] = s;
+      dot[kk] = wave_sum(dot[kk]);
+      if (lane == 0) dgates[t * k + kk] = dot[kk];
     }
+  if (with.dlogits != nullptr) gate_backward(with, t, k, g, dot);
 }
 
 // ---- gate backward: thread per (token, expert)
@@ -204,12 +219,21 @@ __device__ __forceinline__ u32x4 sum_vec(const float* acc, float) {
 }
 __device__ __forceinline__ u32x4 sum_vec(const float* acc, uint16_t) { return pack8(acc); }
 
+// One matrix of every slot; a launch sums one or two.
+struct ReducePart {
+  const u32x4* dw_slot;
+  u32x4* dw;
+  long long vec_per_slot;
+};
 template <typename Elem, int AHEAD>
-__global__ __launch_bounds__(256) void reduce_replicas_kernel(const u32x4* __restrict__ dw_slot,
-                                                              const int32_t* __restrict__ slot_expert, int S,
-                                                              long long vec_per_slot, u32x4* __restrict__ dw) {
+__global__ __launch_bounds__(256) void reduce_replicas_kernel(ReducePart part0, ReducePart part1, unsigned blocks0,
+                                                              const int32_t* __restrict__ slot_expert, int S) {
   const int e = blockIdx.y, lane = threadIdx.x % lz::kWave;
-  const long long v = (long long)blockIdx.x * 256 + threadIdx.x;
+  const bool second = blockIdx.x >= blocks0;
+  const u32x4* __restrict__ const dw_slot = second ? part1.dw_slot : part0.dw_slot;
+  u32x4* __restrict__ const dw = second ? part1.dw : part0.dw;
+  const long long vec_per_slot = second ? part1.vec_per_slot : part0.vec_per_slot;
+  const long long v = (long long)(blockIdx.x - (second ? blocks0 : 0)) * 256 + threadIdx.x;
   const bool live = v < vec_per_slot;
   float acc[16 / sizeof(Elem)] = {};
   for (int s0 = 0; s0 < S; s0 += lz::kWave) {
@@ -461,30 +485,46 @@ extern "C" int32_t lz_ffn_forward_train(const void* xp, const int32_t* slot_offs
   return lz::ffn_forward_train(xp, slot_offsets, w1, w2, shape, z, h, yp, ws, ws_bytes, false, stream);
 }
 
-extern "C" int32_t lz_combine_backward(const void* dy, const void* yp, const int32_t* pair_to_row,
-                                       const float* topk_gates, const lz_shape* shape, void* dyp, float* dgates,
-                                       void* stream) {
+namespace {
+
+int32_t combine_backward(const void* dy, const void* yp, const int32_t* pair_to_row, const float* topk_gates, const lz_shape* shape,
+                         void* dyp, float* dgates, const WithCombine& with, hipStream_t st) {
   if (!lz::shape_ok(shape)) return LZ_ESHAPE;
   if (shape->T == 0) return LZ_OK;
   if (!dy || !yp || !pair_to_row || !topk_gates || !dyp || !dgates) return LZ_EINVAL;
   const long long P = (long long)shape->T * shape->k;
-  const unsigned blocks = unsigned((shape->T + kRowsPerBlock - 1) / kRowsPerBlock);
-  if (shape->dtype != LZ_BF16 || shape->d % 8 != 0 || !aligned16(dy) || !aligned16(yp) || !aligned16(dyp)) {
-    // element-wise kernel: fp32 tensors, rows that are not a multiple of 16 bytes, unaligned buffers
-    if (shape->dtype == LZ_F32)
-      hipLaunchKernelGGL(combine_backward_generic_kernel<float>, dim3(blocks), dim3(256), 0, (hipStream_t)stream,
-                         (const float*)dy, (const float*)yp, pair_to_row, topk_gates, shape->T, shape->k, P,
-                         shape->d, (float*)dyp, dgates);
+  const dim3 grid((unsigned)((shape->T + kTokensPerBlock - 1) / kTokensPerBlock + with.tables.n)), threads(kCombineThreads);
+  const size_t row_bytes = (size_t)shape->d * lz::elem_bytes(shape->dtype);
+  const bool whole = row_bytes % 16 == 0 && aligned16(dy) && aligned16(yp) && aligned16(dyp);
+  auto launch = [&](auto elem) {
+    using Elem = decltype(elem);
+    if (whole)
+      hipLaunchKernelGGL(combine_backward_kernel<Elem>, grid, threads, 0, st, (const u32x4*)dy, (const u32x4*)yp, pair_to_row, topk_gates,
+                         shape->T, shape->k, P, int(row_bytes / 16), (u32x4*)dyp, dgates, with);
     else
-      hipLaunchKernelGGL(combine_backward_generic_kernel<uint16_t>, dim3(blocks), dim3(256), 0, (hipStream_t)stream,
-                         (const uint16_t*)dy, (const uint16_t*)yp, pair_to_row, topk_gates, shape->T, shape->k, P,
-                         shape->d, (uint16_t*)dyp, dgates);
-    return lz::launch_status();
-  }
-  hipLaunchKernelGGL(combine_backward_kernel, dim3(blocks), dim3(256), 0, (hipStream_t)stream, (const u32x4*)dy,
-                     (const u32x4*)yp, pair_to_row, topk_gates, shape->T, shape->k, P, shape->d / 8, (u32x4*)dyp,
-                     dgates);
+      hipLaunchKernelGGL(combine_backward_generic_kernel<Elem>, grid, threads, 0, st, (const Elem*)dy, (const Elem*)yp, pair_to_row,
+                         topk_gates, shape->T, shape->k, P, shape->d, (Elem*)dyp, dgates, with);
+  };
+  if (shape->dtype == LZ_F32) launch(float{});
+  else launch(uint16_t{});
   return lz::launch_status();
+}
+
+}  // namespace
+
+extern "C" int32_t lz_combine_backward(const void* dy, const void* yp, const int32_t* pair_to_row,
+                                       const float* topk_gates, const lz_shape* shape, void* dyp, float* dgates,
+                                       void* stream) {
+  return combine_backward(dy, yp, pair_to_row, topk_gates, shape, dyp, dgates, WithCombine{}, (hipStream_t)stream);
+}
+
+int32_t lz::combine_backward_with(const void* dy, const lz_shape* shape, const lz_layer_buffers& b, bool gate, const TileSpecs& tables,
+                                  void* stream) {
+  const int workgroups = device_cus();
+  if (workgroups == 0) return LZ_EHIP;
+  const WithCombine with{b.topk_ids, shape ? shape->E : 0, gate ? b.dlogits : nullptr, b.slot_offsets, shape ? shape->N * shape->c : 0,
+                         workgroups, tables};
+  return combine_backward(dy, b.yp, b.pair_to_row, b.topk_gates, shape, b.dyp, b.dgates, with, (hipStream_t)stream);
 }
 
 extern "C" int32_t lz_route_backward(const float* dgates, const float* topk_gates, const int32_t* topk_ids,
@@ -500,13 +540,43 @@ extern "C" int32_t lz_route_backward(const float* dgates, const float* topk_gate
 
 namespace {
 
+TileSpecs backward_tables(const TrainWorkspace& w, const lz_shape* shape, bool accumulate) {
+  const long long P = (long long)shape->T * shape->k;
+  const int S = shape->N * shape->c, d = shape->d, ffn = shape->ffn;
+  const int n_ffn = ceil_div(ffn, BN), n_d = ceil_div(d, BN), n_n1 = ceil_div(w.n1, BN);
+  TileSpecs specs{};
+  if (!w.narrow_ffn) add_units(specs, n_ffn, 0, P, carve_units(w.units_ffn, P, S, n_ffn));
+  if (!w.narrow_d) add_units(specs, n_d, 0, P, carve_units(w.units_d, P, S, n_d));
+  add_units(specs, n_d, ffn, P, carve_units(w.units_w2, (long long)S * ffn, S, n_d), accumulate);
+  add_units(specs, n_n1, d, P, carve_units(w.units_w1, (long long)S * d, S, n_n1), accumulate);
+  if (w.narrow_ffn || w.narrow_d) add_rows(specs, kNarrow, P, narrow_tiles(w, S, P));
+  return specs;
+}
+
+}  // namespace
+
+TileSpecs lz::backward_tables(const lz_shape* shape, const void* const* tensors, int n_tensors, void* ws, size_t ws_bytes,
+                              bool accumulate) {
+  bool aligned = true;
+  for (int i = 0; i < n_tensors; ++i) aligned = aligned && aligned16(tensors[i]);
+  if (!lz::shape_ok(shape) || shape->N * shape->c > kTableSlots || shape->T == 0) return TileSpecs{};
+  if (on_mfma(shape, aligned)) {
+    TrainWorkspace w;
+    return check_train(shape, ws, ws_bytes, &w) == LZ_OK ? ::backward_tables(w, shape, accumulate) : TileSpecs{};
+  }
+  GenericTrainWorkspace w;
+  F32Args a{};
+  if (check_train_generic(shape, ws, ws_bytes, &w) != LZ_OK) return TileSpecs{};
+  return generic_tables(a, shape->N * shape->c, (long long)shape->T * shape->k, w, false);
+}
+
 // dw1 / dw2 are bf16 gradients (accumulate == false: overwritten) or fp32 sums (accumulate == true: added to)
-int32_t ffn_backward(const void* dyp, const void* xp, const void* z, const void* h, const int32_t* slot_offsets,
-                     const void* w1, const void* w2, const lz_shape* shape, void* dxp, void* dw1, void* dw2,
-                     bool accumulate, void* ws, size_t ws_bytes, void* stream) {
+int32_t lz::ffn_backward(const void* dyp, const void* xp, const void* z, const void* h, const int32_t* slot_offsets,
+                         const void* w1, const void* w2, const lz_shape* shape, void* dxp, void* dw1, void* dw2,
+                         bool accumulate, void* ws, size_t ws_bytes, bool tables_built, void* stream) {
   const bool aligned = aligned16(dyp) && aligned16(xp) && aligned16(z) && aligned16(h) && aligned16(dxp) &&
                        aligned16(w1) && aligned16(w2) && aligned16(dw1) && aligned16(dw2);
-  if (!train_shape(shape) || (!aligned && !train_whole_tiles(shape))) {
+  if (!on_mfma(shape, aligned)) {
     GenericTrainWorkspace gw;
     const int32_t grc = check_train_generic(shape, ws, ws_bytes, &gw);
     if (grc != LZ_OK) return grc;
@@ -514,9 +584,9 @@ int32_t ffn_backward(const void* dyp, const void* xp, const void* z, const void*
     if ((long long)shape->T * shape->k > 0 && (!dyp || !xp || !z || !h || !w1 || !w2 || !dxp)) return LZ_EINVAL;
     return shape->dtype == LZ_F32
                ? generic_ffn_backward<float>(dyp, xp, z, h, slot_offsets, w1, w2, shape, dxp, dw1, dw2, accumulate,
-                                             gw, (hipStream_t)stream)
+                                             gw, tables_built, (hipStream_t)stream)
                : generic_ffn_backward<uint16_t>(dyp, xp, z, h, slot_offsets, w1, w2, shape, dxp, dw1, dw2,
-                                                accumulate, gw, (hipStream_t)stream);
+                                                accumulate, gw, tables_built, (hipStream_t)stream);
   }
   TrainWorkspace w;
   const int32_t rc = check_train(shape, ws, ws_bytes, &w);
@@ -537,13 +607,7 @@ int32_t ffn_backward(const void* dyp, const void* xp, const void* z, const void*
   const long long rows_w2 = (long long)S * ffn, rows_w1 = (long long)S * d;
   const UnitTable u_ffn = carve_units(w.units_ffn, P, S, n_ffn), u_d = carve_units(w.units_d, P, S, n_d);
   const UnitTable u_w2 = carve_units(w.units_w2, rows_w2, S, n_d), u_w1 = carve_units(w.units_w1, rows_w1, S, n_n1);
-  TileSpecs specs{};
-  if (!w.narrow_ffn) add_units(specs, n_ffn, 0, P, u_ffn);
-  if (!w.narrow_d) add_units(specs, n_d, 0, P, u_d);
-  add_units(specs, n_d, ffn, P, u_w2, accumulate);
-  add_units(specs, n_n1, d, P, u_w1, accumulate);
-  if (w.narrow_ffn || w.narrow_d) add_rows(specs, kNarrow, P, narrow_tiles(w, S, P));
-  int32_t r = launch_build_tiles(slot_offsets, S, specs, st);
+  int32_t r = tables_built ? LZ_OK : launch_build_tiles(slot_offsets, S, ::backward_tables(w, shape, accumulate), st);
   if (r != LZ_OK) return r;
 
   if (P > 0) {
@@ -570,48 +634,58 @@ int32_t ffn_backward(const void* dyp, const void* xp, const void* z, const void*
                     accumulate ? (float*)dw1 : nullptr, S, P, d, n1, u_w1, st);
 }
 
-}  // namespace
-
 extern "C" int32_t lz_ffn_backward(const void* dyp, const void* xp, const void* z, const void* h,
                                    const int32_t* slot_offsets, const void* w1, const void* w2,
                                    const lz_shape* shape, void* dxp, void* dw1, void* dw2, void* ws,
                                    size_t ws_bytes, void* stream) {
-  return ffn_backward(dyp, xp, z, h, slot_offsets, w1, w2, shape, dxp, dw1, dw2, false, ws, ws_bytes, stream);
+  return lz::ffn_backward(dyp, xp, z, h, slot_offsets, w1, w2, shape, dxp, dw1, dw2, false, ws, ws_bytes, false, stream);
 }
 
 extern "C" int32_t lz_ffn_backward_accumulate(const void* dyp, const void* xp, const void* z, const void* h,
                                               const int32_t* slot_offsets, const void* w1, const void* w2,
                                               const lz_shape* shape, void* dxp, float* dw1_acc, float* dw2_acc,
                                               void* ws, size_t ws_bytes, void* stream) {
-  return ffn_backward(dyp, xp, z, h, slot_offsets, w1, w2, shape, dxp, dw1_acc, dw2_acc, true, ws, ws_bytes,
-                      stream);
+  return lz::ffn_backward(dyp, xp, z, h, slot_offsets, w1, w2, shape, dxp, dw1_acc, dw2_acc, true, ws, ws_bytes, false, stream);
 }
 
 namespace {
 
-// 16-byte aligned tensors whose slots are whole 16-byte vectors
+// 16-byte aligned tensors whose slots are whole 16-byte vectors; elems1 = 0: one matrix
 template <typename Elem>
-int32_t reduce_vectors(const void* dw_slot, const int32_t* slot_expert, int32_t S, int32_t E, int64_t elems_per_slot,
-                       void* dw, void* stream) {
-  const long long vec = elems_per_slot / (16 / (int)sizeof(Elem));
-  const long long blocks = (vec + 255) / 256;
+int32_t reduce_vectors(const void* dw_slot0, int64_t elems0, void* dw0, const void* dw_slot1, int64_t elems1, void* dw1,
+                       const int32_t* slot_expert, int32_t S, int32_t E, void* stream) {
+  auto part = [](const void* in, int64_t elems, void* out) { return ReducePart{(const u32x4*)in, (u32x4*)out, elems / (16 / (int)sizeof(Elem))}; };
+  const ReducePart p0 = part(dw_slot0, elems0, dw0), p1 = part(dw_slot1, elems1, dw1);
+  const long long blocks0 = (p0.vec_per_slot + 255) / 256, blocks = blocks0 + (p1.vec_per_slot + 255) / 256;
   if (blocks > 0x7FFFFFFFll) return LZ_ESHAPE;
-  void (*kern)(const u32x4*, const int32_t*, int, long long, u32x4*) = reduce_replicas_kernel<Elem, kReduceAhead>;
+  auto* kern = reduce_replicas_kernel<Elem, kReduceAhead>;
   if constexpr (sizeof(Elem) == 4)
     if (E <= kReduceFewExperts && blocks * E < kReduceFewBlocks) kern = reduce_replicas_kernel<Elem, kReduceAheadFew>;
-  hipLaunchKernelGGL(kern, dim3((unsigned)blocks, (unsigned)E), dim3(256), 0, (hipStream_t)stream,
-                     (const u32x4*)dw_slot, slot_expert, S, vec, (u32x4*)dw);
+  hipLaunchKernelGGL(kern, dim3((unsigned)blocks, (unsigned)E), dim3(256), 0, (hipStream_t)stream, p0, p1, (unsigned)blocks0, slot_expert, S);
   return lz::launch_status();
 }
 
 }  // namespace
+
+int32_t lz::reduce_pair(const lz_shape* s, const lz_layer_buffers& b, int64_t elems1, int64_t elems2, void* stream) {
+  const int S = s->N * s->c, per = s->dtype == LZ_F32 ? 4 : 8;
+  const bool whole = elems1 % per == 0 && elems2 % per == 0 && aligned16(b.dw1_slot) && aligned16(b.dw2_slot) && aligned16(b.dw1) &&
+                     aligned16(b.dw2) && (elems1 + elems2) / per / 256 < 0x7FFFFFF0ll;
+  if (whole && b.dw1_slot && b.dw2_slot && b.dw1 && b.dw2 && b.slot_expert)
+    return s->dtype == LZ_F32
+               ? reduce_vectors<float>(b.dw1_slot, elems1, b.dw1, b.dw2_slot, elems2, b.dw2, b.slot_expert, S, s->E, stream)
+               : reduce_vectors<uint16_t>(b.dw1_slot, elems1, b.dw1, b.dw2_slot, elems2, b.dw2, b.slot_expert, S, s->E, stream);
+  const int32_t rc = lz_reduce_replica_grads_dtype(b.dw1_slot, b.slot_expert, S, s->E, elems1, s->dtype, b.dw1, stream);
+  if (rc != LZ_OK) return rc;
+  return lz_reduce_replica_grads_dtype(b.dw2_slot, b.slot_expert, S, s->E, elems2, s->dtype, b.dw2, stream);
+}
 
 extern "C" int32_t lz_reduce_replica_grads(const void* dw_slot, const int32_t* slot_expert, int32_t S, int32_t E,
                                            int64_t elems_per_slot, void* dw, void* stream) {
   if (S < 1 || E < 1 || E > 65535 || elems_per_slot < 0 || elems_per_slot % 8 != 0) return LZ_ESHAPE;
   if (elems_per_slot == 0) return LZ_OK;
   if (!dw_slot || !slot_expert || !dw || !aligned16(dw_slot) || !aligned16(dw)) return LZ_EINVAL;
-  return reduce_vectors<uint16_t>(dw_slot, slot_expert, S, E, elems_per_slot, dw, stream);
+  return reduce_vectors<uint16_t>(dw_slot, elems_per_slot, dw, nullptr, 0, nullptr, slot_expert, S, E, stream);
 }
 
 extern "C" int32_t lz_reduce_replica_grads_dtype(const void* dw_slot, const int32_t* slot_expert, int32_t S,
@@ -624,7 +698,7 @@ extern "C" int32_t lz_reduce_replica_grads_dtype(const void* dw_slot, const int3
   if (elems_per_slot == 0) return LZ_OK;
   if (!dw_slot || !slot_expert || !dw) return LZ_EINVAL;
   if (dtype == LZ_F32 && elems_per_slot % 4 == 0 && aligned16(dw_slot) && aligned16(dw))
-    return reduce_vectors<float>(dw_slot, slot_expert, S, E, elems_per_slot, dw, stream);
+    return reduce_vectors<float>(dw_slot, elems_per_slot, dw, nullptr, 0, nullptr, slot_expert, S, E, stream);
   if ((elems_per_slot + 255) / 256 > 0x7FFFFFFFll) return LZ_ESHAPE;
   const dim3 grid((unsigned)((elems_per_slot + 255) / 256), (unsigned)E);
   if (dtype == LZ_F32)

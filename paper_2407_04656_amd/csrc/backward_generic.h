@@ -8,22 +8,83 @@
 
 namespace {
 
-// combine backward, one wave per token: dgates[t,kk] = <dy[t], yp[row]>, dyp[row] = gates[t,kk] dy[t]
+// What a whole backward pass does in the launch of the combine backward: the gates', whose input that is (dlogits given), and
+// the tables of the grouped GEMMs, by the first tables.n workgroups.  Each was a launch of 3 to 6 us.
+struct WithCombine {
+  const int32_t* ids;
+  int E;
+  float* dlogits;
+  const int32_t* slot_offsets;
+  int S, workgroups;
+  TileSpecs tables;
+};
+constexpr int kTableSlots = 512;      // more slots get a launch of their own: LDS that all workgroups would carry
+constexpr int kCombineThreads = kTileThreads, kTokensPerBlock = kCombineThreads / lz::kWave;
+struct CombineLds {
+  SlotRows<kTableSlots> slots;
+  TableScratch<kTableSlots> scratch;
+};
+// true: this workgroup has built a table
+__device__ __forceinline__ bool table_workgroup(const WithCombine& with, CombineLds& m) {
+  if ((int)blockIdx.x >= with.tables.n) return false;
+  const TileSpec& spec = with.tables.spec[blockIdx.x];
+  for (int s = threadIdx.x; s < with.S; s += kCombineThreads) {
+    long long a, b;
+    clip_slot(with.slot_offsets, s, spec.P, &a, &b);
+    m.slots.first[s] = int(a);
+    m.slots.end[s] = int(b);
+  }
+  __syncthreads();
+  build_table(spec, false, m.slots, with.S, m.scratch, threadIdx.x, with.workgroups);
+  return true;
+}
+
+// A token's gates' gradients by its whole wave, lane by lane an expert: dlogits[e] = g_e (dg_e - sum_i g_i dg_i).
+__device__ __forceinline__ void gate_backward(const WithCombine& with, long long t, int k, const float* g, const float* dg) {
+  const int lane = threadIdx.x % lz::kWave;
+  float inner = 0.f;
+  int id[lz::kMaxK];
+#pragma unroll
+  for (int kk = 0; kk < lz::kMaxK; ++kk)
+    if (kk < k) {
+      inner = fmaf(g[kk], dg[kk], inner);
+      id[kk] = with.ids[t * k + kk];
+    }
+  for (int e = lane; e < with.E; e += lz::kWave) {
+    float mine_g = 0.f, mine_dg = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < lz::kMaxK; ++kk)
+      if (kk < k && id[kk] == e) {
+        mine_g = g[kk];
+        mine_dg = dg[kk];
+      }
+    with.dlogits[t * with.E + e] = mine_g * (mine_dg - inner);  // an expert the token did not select has mine_g = 0
+  }
+}
+
+// combine backward, one wave per token, by elements (rows that are no whole 16-byte pieces, unaligned tensors):
+// dgates[t,kk] = <dy[t], yp[row]>, dyp[row] = gates[t,kk] dy[t]
 template <typename Elem>
-__global__ __launch_bounds__(256) void combine_backward_generic_kernel(const Elem* __restrict__ dy,
+__global__ __launch_bounds__(kCombineThreads) void combine_backward_generic_kernel(const Elem* __restrict__ dy,
                                                                        const Elem* __restrict__ yp,
                                                                        const int32_t* __restrict__ pair_to_row,
                                                                        const float* __restrict__ gates, int T, int k,
                                                                        long long P, int d, Elem* __restrict__ dyp,
-                                                                       float* __restrict__ dgates) {
+                                                                       float* __restrict__ dgates, WithCombine with) {
+  __shared__ CombineLds lds;
+  if (table_workgroup(with, lds)) return;
   const int lane = threadIdx.x % lz::kWave;
-  const long long t = (long long)blockIdx.x * 4 + threadIdx.x / lz::kWave;
+  const long long t = ((long long)blockIdx.x - with.tables.n) * kTokensPerBlock + threadIdx.x / lz::kWave;
   if (t >= T) return;
-  for (int kk = 0; kk < k; ++kk) {
+  float gate[lz::kMaxK], grad[lz::kMaxK];
+#pragma unroll
+  for (int kk = 0; kk < lz::kMaxK; ++kk) {
+    gate[kk] = grad[kk] = 0.f;
+    if (kk >= k) continue;
     const int r = pair_to_row[t * k + kk];
+    const float g = gates[t * k + kk];
     float dot = 0.f;
     if (r >= 0 && r < P) {
-      const float g = gates[t * k + kk];
       for (int v = lane; v < d; v += lz::kWave) {
         const float gy = load_elem<Elem>(dy + (size_t)t * d + v);
         dot = fmaf(gy, load_elem<Elem>(yp + (size_t)r * d + v), dot);
@@ -33,7 +94,10 @@ __global__ __launch_bounds__(256) void combine_backward_generic_kernel(const Ele
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) dot += __shfl_xor(dot, off, 64);
     if (lane == 0) dgates[t * k + kk] = dot;
+    gate[kk] = g;
+    grad[kk] = dot;
   }
+  if (with.dlogits != nullptr) gate_backward(with, t, k, gate, grad);
 }
 
 // dW[e] = sum over the slots holding e, ascending slot, fp32 sum, one rounding
@@ -128,7 +192,7 @@ template <typename Elem>
 int32_t generic_ffn_backward(const void* dyp, const void* xp, const void* z, const void* h,
                              const int32_t* slot_offsets, const void* w1, const void* w2, const lz_shape* s,
                              void* dxp, void* dw1, void* dw2, bool accumulate, const GenericTrainWorkspace& w,
-                             hipStream_t st) {
+                             bool tables_built, hipStream_t st) {
   const long long P = (long long)s->T * s->k;
   const int S = s->N * s->c, d = s->d, ffn = s->ffn, n1 = w.n1;
   int32_t r;
@@ -136,7 +200,7 @@ int32_t generic_ffn_backward(const void* dyp, const void* xp, const void* z, con
     // dZ = (dyp W2^T) * act'(Z): W2[s] [ffn, d] along its rows
     F32Args a{};
     const TileSpecs tables = generic_tables(a, S, P, w, false);  // the data gradients stay on the 32-row tiles
-    if ((r = launch_build_tiles(slot_offsets, S, tables, st)) != LZ_OK) return r;
+    if (!tables_built && (r = launch_build_tiles(slot_offsets, S, tables, st)) != LZ_OK) return r;
     a.A = dyp;
     a.W = w2;
     a.C = w.dz;

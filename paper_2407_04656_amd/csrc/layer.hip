@@ -64,19 +64,17 @@ extern "C" int32_t lz_layer_backward(const lz_shape* shape, const lz_layer_buffe
                                      void* stream) {
   if (!buffers) return LZ_EINVAL;
   const lz_layer_buffers& b = *buffers;
-  int32_t rc = lz_combine_backward(dy, b.yp, b.pair_to_row, b.topk_gates, shape, b.dyp, b.dgates, stream);
+  const bool gate = shape && shape->T > 0 && b.topk_ids && b.dlogits;
+  const void* const tensors[] = {b.dyp, b.xp, b.z, b.h, b.dxp, b.w1, b.w2, b.dw1_slot, b.dw2_slot};
+  const TileSpecs tables = b.slot_offsets ? lz::backward_tables(shape, tensors, 9, b.train_ws, b.train_ws_bytes, accumulate) : TileSpecs{};
+  int32_t rc = lz::combine_backward_with(dy, shape, b, gate, tables, stream);
   if (rc != LZ_OK) return rc;
-  rc = accumulate ? lz_ffn_backward_accumulate(b.dyp, b.xp, b.z, b.h, b.slot_offsets, b.w1, b.w2, shape, b.dxp, (float*)b.dw1_slot,
-                                               (float*)b.dw2_slot, b.train_ws, b.train_ws_bytes, stream)
-                  : lz_ffn_backward(b.dyp, b.xp, b.z, b.h, b.slot_offsets, b.w1, b.w2, shape, b.dxp, b.dw1_slot, b.dw2_slot,
-                                    b.train_ws, b.train_ws_bytes, stream);
+  rc = lz::ffn_backward(b.dyp, b.xp, b.z, b.h, b.slot_offsets, b.w1, b.w2, shape, b.dxp, b.dw1_slot, b.dw2_slot, accumulate, b.train_ws,
+                        b.train_ws_bytes, tables.n > 0, stream);
   if (rc != LZ_OK) return rc;
   if ((rc = lz_permute_backward(b.dxp, b.pair_to_row, shape, b.dx, stream)) != LZ_OK) return rc;
-  if ((rc = lz_route_backward(b.dgates, b.topk_gates, b.topk_ids, shape, b.dlogits, stream)) != LZ_OK) return rc;
+  if (!gate && (rc = lz_route_backward(b.dgates, b.topk_gates, b.topk_ids, shape, b.dlogits, stream)) != LZ_OK) return rc;
   if (accumulate) return LZ_OK;
-  const int S = shape->N * shape->c;
-  const int64_t elems = (int64_t)shape->d * shape->ffn, elems1 = elems * (shape->act == LZ_SWIGLU ? 2 : 1);
-  if ((rc = lz_reduce_replica_grads_dtype(b.dw1_slot, b.slot_expert, S, shape->E, elems1, shape->dtype, b.dw1, stream)) != LZ_OK)
-    return rc;
-  return lz_reduce_replica_grads_dtype(b.dw2_slot, b.slot_expert, S, shape->E, elems, shape->dtype, b.dw2, stream);
+  const int64_t elems = (int64_t)shape->d * shape->ffn;
+  return lz::reduce_pair(shape, b, elems * (shape->act == LZ_SWIGLU ? 2 : 1), elems, stream);
 }
