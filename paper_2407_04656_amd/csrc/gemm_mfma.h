@@ -385,18 +385,46 @@ constexpr int kFirstLoads = 32;  // of which the first half belong to step 0
 // and more however small it was.
 //
 // Wave 0 draws; the ticket goes to the other waves through LDS, and each looks its tile up by itself.
+//
+// A launch of one or two rounds, a small batch's, feels every trip to memory on the way: the records of the first unit are fetched with the
+// list's header, before it is known that they exist, the first ticket needs no exchange, and a workgroup that has found all queues empty
+// says so ahead of its last epilogue.  (Counters read with every draw, to know of that earlier, keep the draws waiting: 1 to 5 % slower.)
 struct Draws {
   const UnitTable u;
-  const int per_xcd, xcd, tile_rows;
+  const int per_xcd, xcd;
+  int tile_rows;
   int q, tickets, units;  // the queue it draws from, tickets and units in it
   int ticket, drawn;      // drawn: what the atomic returned (lane 0 of wave 0)
+  int total, taken;       // wave 0, lane h < 8: tickets in queue h, drawn from it when last looked at
+  int others_left;        // lane 0 of wave 0: workgroups of this XCD that had left before, once this one has
   i32x4 rec[2];           // lane l: record `at` + l of queue q
   int at;
 
-  __device__ __forceinline__ Draws(const UnitTable& table)
+  // takes the first ticket, the workgroup's index in its XCD's queue
+  __device__ __forceinline__ Draws(const UnitTable& table, char* smem)
       : u(table), per_xcd(gridDim.x / 8), xcd(blockIdx.x % 8),  // workgroups are dealt round-robin to the 8 XCDs
-        tile_rows(__builtin_amdgcn_readfirstlane(table.header[kTileRows])) {
-    set_queue(xcd);
+        taken(0), others_left(0) {
+    const int lane = (int)(threadIdx.x & 63);
+    const int rows = u.header[kTileRows], n_tickets = u.header[xcd], n_units = u.header[8 + xcd];
+    total = u.header[lane & 7];
+    const int i = lane < u.cap ? lane : u.cap - 1;
+    const i32x4* const from = (const i32x4*)(u.records + ((size_t)xcd * u.cap + i) * kRecord);
+    rec[0] = from[0];
+    rec[1] = from[1];
+    q = xcd;
+    tile_rows = __builtin_amdgcn_readfirstlane(rows);
+    tickets = __builtin_amdgcn_readfirstlane(n_tickets);
+    units = __builtin_amdgcn_readfirstlane(n_units);
+    ticket = blockIdx.x / 8;
+    at = 0;
+    if (lane >= units) rec[0].x = 0x7FFFFFFF;
+    if (ticket >= tickets) {  // the same in all waves
+      if (mine()) publish_ticket(ticket, smem);
+      receive(smem);
+    } else if (ticket >= kGroupM * kGroupN) {
+      at = ticket / (kGroupM * kGroupN);
+      load_records();
+    }
   }
   static __device__ __forceinline__ bool mine() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x) == 0; }
   __device__ __forceinline__ int* counter(int x) const { return u.header + kTicket + x * kLine; }
@@ -405,6 +433,7 @@ struct Draws {
     tickets = __builtin_amdgcn_readfirstlane(u.header[x]);
     units = __builtin_amdgcn_readfirstlane(u.header[8 + x]);
   }
+  __device__ __forceinline__ void look() { taken = __hip_atomic_load(counter(threadIdx.x & 7), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
   // asks for the next ticket of the queue
   __device__ __forceinline__ void request() {
     if (mine()) {
@@ -419,18 +448,14 @@ struct Draws {
   __device__ __forceinline__ void publish_ticket(int t, char* to) {
     while (t >= tickets) {
       // the first queue from this XCD's on with a ticket left (counters only grow: one that reads as empty is)
-      int taken[8], left = -1;
-#pragma unroll
-      for (int h = 0; h < 8; ++h) taken[h] = __hip_atomic_load(counter(h), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-      for (int h = 0; h < 8; ++h)
-        if (per_xcd + taken[h] < u.header[h] && (left < 0 || ((h - xcd) & 7) < ((left - xcd) & 7))) left = h;
-      left = __builtin_amdgcn_readfirstlane(left);
-      if (left < 0) {
+      look();
+      const unsigned some = (unsigned)__ballot(per_xcd + taken < total) & 255u;
+      if (some == 0) {
         t = -1;
         break;
       }
-      set_queue(left);
+      const unsigned from_own = (some >> xcd | some << (8 - xcd)) & 255u;
+      set_queue((xcd + __ffs((int)from_own) - 1) & 7);
       request();
       t = per_xcd + __builtin_amdgcn_readfirstlane(drawn);
     }
@@ -443,9 +468,21 @@ struct Draws {
     ticket = __builtin_amdgcn_readfirstlane(v.x);
     const int from_q = __builtin_amdgcn_readfirstlane(v.y);
     __syncthreads();  // the place may be written again
+    if (ticket < 0) {
+      leave();
+      return;
+    }
     if (from_q != q) set_queue(from_q);
-    at = ticket < 0 ? 0 : ticket / (kGroupM * kGroupN);  // a unit has at most that many tiles
+    at = ticket / (kGroupM * kGroupN);  // a unit has at most that many tiles
     load_records();
+  }
+  // This workgroup draws no more.  The last one to leave resets the counters (finish(), once it has nothing else to do).
+  __device__ __forceinline__ void leave() {
+    if (threadIdx.x == 0) others_left = atomicAdd(counter(8 + xcd), 1);
+  }
+  __device__ __forceinline__ void finish() {
+    if (threadIdx.x == 0 && others_left == per_xcd - 1 && atomicAdd(counter(16), 1) == 7)
+      for (int i = 0; i < 17; ++i) *counter(i) = 0;
   }
   __device__ __forceinline__ void load_records() {
     const int i = at + (int)(threadIdx.x & 63), last = units > 0 ? units - 1 : 0;
@@ -879,9 +916,7 @@ template <int EPI, int MODE, bool GATHER, bool KTAIL>
 __global__ __launch_bounds__(256, 1) void gemm_mfma_kernel(MfmaArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub, not the gfx950 builtins
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  Draws draws(a.u);
-  if (Draws::mine()) draws.publish_ticket(blockIdx.x / 8, smem);
-  draws.receive(smem);
+  Draws draws(a.u, smem);
   Tile tile = draws.tile(kOutCols<EPI>);
   Operands<EPI, MODE, GATHER, KTAIL> ops;
   ops.set(a, smem, tile);
@@ -899,9 +934,7 @@ __global__ __launch_bounds__(256, 1) void gemm_mfma_kernel(MfmaArgs a) {
     else tile = gemm_tile<EPI, 1, MODE, GATHER, KTAIL>(a, smem, tile, ops, draws);
   }
   __builtin_amdgcn_s_waitcnt(0x0F70);  // the loads of no tile are done with LDS
-  // the last workgroup to finish leaves the counters at zero for the next launch on this table
-  if (threadIdx.x == 0 && atomicAdd(draws.counter(8 + draws.xcd), 1) == draws.per_xcd - 1 && atomicAdd(draws.counter(16), 1) == 7)
-    for (int i = 0; i < 17; ++i) *draws.counter(i) = 0;
+  draws.finish();  // (a workgroup ends when it has received no tile, and has left then)
 #endif
 }
 
