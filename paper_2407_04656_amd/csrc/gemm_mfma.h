@@ -388,14 +388,15 @@ constexpr int kFirstLoads = 32;  // of which the first half belong to step 0
 //
 // A launch of one or two rounds, a small batch's, feels every trip to memory on the way: the records of the first unit are fetched with the
 // list's header, before it is known that they exist, the first ticket needs no exchange, and a workgroup that has found all queues empty
-// says so ahead of its last epilogue.  (Counters read with every draw, to know of that earlier, keep the draws waiting: 1 to 5 % slower.)
+// says so ahead of its last epilogue.  A launch of one round draws nothing and counts nobody.  (Counters read with every draw, to know of that earlier, keep the draws waiting: 1 to 5 % slower.)
 struct Draws {
   const UnitTable u;
   const int per_xcd, xcd;
   int tile_rows;
   int q, tickets, units;  // the queue it draws from, tickets and units in it
   int ticket, drawn;      // drawn: what the atomic returned (lane 0 of wave 0)
-  int total, taken;       // wave 0, lane h < 8: tickets in queue h, drawn from it when last looked at
+  int total, taken;       // lane h < 8: tickets in queue h, and, wave 0, drawn from it when last looked at
+  bool one_round;         // no queue has more tickets than workgroups: none is ever drawn
   int others_left;        // lane 0 of wave 0: workgroups of this XCD that had left before, once this one has
   i32x4 rec[2];           // lane l: record `at` + l of queue q
   int at;
@@ -417,8 +418,11 @@ struct Draws {
     units = __builtin_amdgcn_readfirstlane(n_units);
     ticket = blockIdx.x / 8;
     at = 0;
+    one_round = (__ballot(total > per_xcd) & 255) == 0;
     if (lane >= units) rec[0].x = 0x7FFFFFFF;
-    if (ticket >= tickets) {  // the same in all waves
+    if (ticket >= tickets && one_round) {
+      ticket = -1;
+    } else if (ticket >= tickets) {  // the same in all waves
       if (mine()) publish_ticket(ticket, smem);
       receive(smem);
     } else if (ticket >= kGroupM * kGroupN) {
@@ -436,14 +440,14 @@ struct Draws {
   __device__ __forceinline__ void look() { taken = __hip_atomic_load(counter(threadIdx.x & 7), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
   // asks for the next ticket of the queue
   __device__ __forceinline__ void request() {
-    if (mine()) {
+    if (mine() && !one_round) {
       drawn = 0;
       if (threadIdx.x == 0) drawn = atomicAdd(counter(q), 1);
     }
   }
   // the ticket asked for, or one of another queue, -1 when no queue has one left, to `to` in LDS
   __device__ __forceinline__ void publish(char* to) {
-    if (mine()) publish_ticket(per_xcd + __builtin_amdgcn_readfirstlane(drawn), to);
+    if (mine() && !one_round) publish_ticket(per_xcd + __builtin_amdgcn_readfirstlane(drawn), to);
   }
   __device__ __forceinline__ void publish_ticket(int t, char* to) {
     while (t >= tickets) {
@@ -464,6 +468,10 @@ struct Draws {
   // what was published goes to every wave, which loads the records the ticket may belong to
   __device__ __forceinline__ void receive(const char* from) {
     __syncthreads();
+    if (one_round) {
+      ticket = -1;
+      return;
+    }
     const int2 v = *(const int2*)from;
     ticket = __builtin_amdgcn_readfirstlane(v.x);
     const int from_q = __builtin_amdgcn_readfirstlane(v.y);
@@ -481,7 +489,7 @@ struct Draws {
     if (threadIdx.x == 0) others_left = atomicAdd(counter(8 + xcd), 1);
   }
   __device__ __forceinline__ void finish() {
-    if (threadIdx.x == 0 && others_left == per_xcd - 1 && atomicAdd(counter(16), 1) == 7)
+    if (threadIdx.x == 0 && !one_round && others_left == per_xcd - 1 && atomicAdd(counter(16), 1) == 7)
       for (int i = 0; i < 17; ++i) *counter(i) = 0;
   }
   __device__ __forceinline__ void load_records() {
