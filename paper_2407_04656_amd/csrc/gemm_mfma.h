@@ -172,6 +172,7 @@ __device__ __forceinline__ int swz_kmajor(int kr) { return ((kr & 3) << 2) | (((
 // A tile: rows [row0, row_end) of a slot, at most 256, output columns from n0; weight gradients: the rows [k0, k1) of the batch that the slot contracts over.  slot < 0: none.
 struct Tile {
   int slot, row0, row_end, n0, k0, k1;
+  int part;  // of a pair of GEMMs in one launch: which
 };
 
 // Where a tile's operands lie, and their direct-to-LDS loads.
@@ -389,11 +390,16 @@ constexpr int kFirstLoads = 32;  // of which the first half belong to step 0
 // A launch of one or two rounds, a small batch's, feels every trip to memory on the way: the records of the first unit are fetched with the
 // list's header, before it is known that they exist, the first ticket needs no exchange, and a workgroup that has found all queues empty
 // says so ahead of its last epilogue.  A launch of one round draws nothing and counts nobody.  (Counters read with every draw, to know of that earlier, keep the draws waiting: 1 to 5 % slower.)
+//
+// PAIR: two GEMMs in one launch, the lists of one behind those of the other; the counters of the first serve both.
+template <bool PAIR>
 struct Draws {
-  const UnitTable u;
+  const UnitTable u, u1;
   const int per_xcd, xcd;
-  int tile_rows;
-  int q, tickets, units;  // the queue it draws from, tickets and units in it
+  int tile_rows, tile_rows1;
+  int q, tickets, units, units1;  // the queue it draws from, tickets and units in it
+  int first1;                     // PAIR: tickets from here on belong to the second list
+  int part, local;                // of the ticket: its list, its index there
   int ticket, drawn;      // drawn: what the atomic returned (lane 0 of wave 0)
   int total, taken;       // lane h < 8: tickets in queue h, and, wave 0, drawn from it when last looked at
   bool one_round;         // no queue has more tickets than workgroups: none is ever drawn
@@ -401,23 +407,34 @@ struct Draws {
   i32x4 rec[2];           // lane l: record `at` + l of queue q
   int at;
 
-  // takes the first ticket, the workgroup's index in its XCD's queue
-  __device__ __forceinline__ Draws(const UnitTable& table, char* smem)
-      : u(table), per_xcd(gridDim.x / 8), xcd(blockIdx.x % 8),  // workgroups are dealt round-robin to the 8 XCDs
-        taken(0), others_left(0) {
+  // takes the first ticket, the workgroup's index in its XCD's queue (workgroups are dealt round-robin to the 8 XCDs)
+  __device__ __forceinline__ Draws(const UnitTable& table, const UnitTable& table1, char* smem)
+      : u(table), u1(table1), per_xcd(gridDim.x / 8), xcd(blockIdx.x % 8), taken(0), others_left(0) {
     const int lane = (int)(threadIdx.x & 63);
     const int rows = u.header[kTileRows], n_tickets = u.header[xcd], n_units = u.header[8 + xcd];
     total = u.header[lane & 7];
+    int rows1 = 0, n_tickets1 = 0, n_units1 = 0;
+    if constexpr (PAIR) {
+      rows1 = u1.header[kTileRows], n_tickets1 = u1.header[xcd], n_units1 = u1.header[8 + xcd];
+      total += u1.header[lane & 7];
+    }
     const int i = lane < u.cap ? lane : u.cap - 1;
     const i32x4* const from = (const i32x4*)(u.records + ((size_t)xcd * u.cap + i) * kRecord);
     rec[0] = from[0];
     rec[1] = from[1];
     q = xcd;
     tile_rows = __builtin_amdgcn_readfirstlane(rows);
-    tickets = __builtin_amdgcn_readfirstlane(n_tickets);
+    first1 = __builtin_amdgcn_readfirstlane(n_tickets);
     units = __builtin_amdgcn_readfirstlane(n_units);
+    tickets = first1;
+    if constexpr (PAIR) {
+      tile_rows1 = __builtin_amdgcn_readfirstlane(rows1);
+      tickets += __builtin_amdgcn_readfirstlane(n_tickets1);
+      units1 = __builtin_amdgcn_readfirstlane(n_units1);
+    }
     ticket = blockIdx.x / 8;
-    at = 0;
+    part = at = 0;
+    local = ticket;
     one_round = (__ballot(total > per_xcd) & 255) == 0;
     if (lane >= units) rec[0].x = 0x7FFFFFFF;
     if (ticket >= tickets && one_round) {
@@ -425,17 +442,21 @@ struct Draws {
     } else if (ticket >= tickets) {  // the same in all waves
       if (mine()) publish_ticket(ticket, smem);
       receive(smem);
-    } else if (ticket >= kGroupM * kGroupN) {
-      at = ticket / (kGroupM * kGroupN);
-      load_records();
+    } else if (ticket >= kGroupM * kGroupN || (PAIR && ticket >= first1)) {
+      locate();
     }
   }
   static __device__ __forceinline__ bool mine() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x) == 0; }
   __device__ __forceinline__ int* counter(int x) const { return u.header + kTicket + x * kLine; }
   __device__ __forceinline__ void set_queue(int x) {
     q = x;
-    tickets = __builtin_amdgcn_readfirstlane(u.header[x]);
+    first1 = __builtin_amdgcn_readfirstlane(u.header[x]);
     units = __builtin_amdgcn_readfirstlane(u.header[8 + x]);
+    tickets = first1;
+    if constexpr (PAIR) {
+      tickets += __builtin_amdgcn_readfirstlane(u1.header[x]);
+      units1 = __builtin_amdgcn_readfirstlane(u1.header[8 + x]);
+    }
   }
   __device__ __forceinline__ void look() { taken = __hip_atomic_load(counter(threadIdx.x & 7), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
   // asks for the next ticket of the queue
@@ -481,7 +502,12 @@ struct Draws {
       return;
     }
     if (from_q != q) set_queue(from_q);
-    at = ticket / (kGroupM * kGroupN);  // a unit has at most that many tiles
+    locate();
+  }
+  __device__ __forceinline__ void locate() {
+    part = PAIR && ticket >= first1 ? 1 : 0;
+    local = ticket - (part ? first1 : 0);
+    at = local / (kGroupM * kGroupN);  // a unit has at most that many tiles
     load_records();
   }
   // This workgroup draws no more.  The last one to leave resets the counters (finish(), once it has nothing else to do).
@@ -493,26 +519,28 @@ struct Draws {
       for (int i = 0; i < 17; ++i) *counter(i) = 0;
   }
   __device__ __forceinline__ void load_records() {
-    const int i = at + (int)(threadIdx.x & 63), last = units > 0 ? units - 1 : 0;
-    const i32x4* const from = (const i32x4*)(u.records + ((size_t)q * u.cap + (i < last ? i : last)) * kRecord);
+    const bool second = PAIR && part != 0;
+    const int n = second ? units1 : units, i = at + (int)(threadIdx.x & 63), last = n > 0 ? n - 1 : 0;
+    const int32_t* const list = second ? u1.records + (size_t)q * u1.cap * kRecord : u.records + (size_t)q * u.cap * kRecord;
+    const i32x4* const from = (const i32x4*)(list + (size_t)(i < last ? i : last) * kRecord);
     rec[0] = from[0];
     rec[1] = from[1];
     if (i > last) rec[0].x = 0x7FFFFFFF;
   }
   __device__ __forceinline__ Tile tile(int n_out_cols) {
-    if (ticket < 0) return Tile{-1, 0, 0, 0, 0, 0};
+    if (ticket < 0) return Tile{-1, 0, 0, 0, 0, 0, 0};
     unsigned long long le;
-    while ((le = __ballot(rec[0].x <= ticket)) == ~0ull) {
+    while ((le = __ballot(rec[0].x <= local)) == ~0ull) {
       at += 63;
       load_records();
     }
     const int l = __popcll(le) - 1;  // the unit: the last that starts at or before the ticket
     auto of = [&](int v) { return __builtin_amdgcn_readlane(v, l); };
-    const int within = ticket - of(rec[0].x), nr = of(rec[1].x) & 255;
+    const int within = local - of(rec[0].x), nr = of(rec[1].x) & 255, rows = PAIR && part ? tile_rows1 : tile_rows;
     const int col = within / nr;
-    const int row0 = of(rec[0].z) + (within - col * nr) * tile_rows, end = of(rec[0].w);
-    return Tile{of(rec[0].y), row0, end - row0 < tile_rows ? end : row0 + tile_rows, (of(rec[1].y) + col) * n_out_cols,
-                of(rec[1].z), of(rec[1].w)};
+    const int row0 = of(rec[0].z) + (within - col * nr) * rows, end = of(rec[0].w);
+    return Tile{of(rec[0].y), row0, end - row0 < rows ? end : row0 + rows, (of(rec[1].y) + col) * n_out_cols, of(rec[1].z), of(rec[1].w),
+                part};
   }
 };
 
@@ -525,9 +553,10 @@ constexpr int kOutCols = (EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_KEEP) ? BN / 2 
 //
 // ops: the tile's operands, whose first loads are under way.  The next tile is drawn while the last K steps run; its operands
 // go to ops and its first loads out within the epilogue.
-template <int EPI, int XF, int MODE, bool GATHER, bool KTAIL>
-__device__ __forceinline__ Tile gemm_tile(const MfmaArgs& a, char* smem, const Tile tile, Operands<EPI, MODE, GATHER, KTAIL>& ops,
-                                          Draws& draws) {
+template <int EPI, int XF, int MODE, bool GATHER, bool KTAIL, bool PAIR>
+__device__ __forceinline__ Tile gemm_tile(const MfmaArgs* args, char* smem, const Tile tile, Operands<EPI, MODE, GATHER, KTAIL>& ops,
+                                          Draws<PAIR>& draws) {
+  const MfmaArgs& a = args[PAIR ? __builtin_amdgcn_readfirstlane(tile.part) : 0];
   constexpr bool TA = MODE == MODE_TN || MODE == MODE_TN_WIDE, TB = MODE != MODE_NT;  // k-major left / right operand
   constexpr bool kGated = EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_KEEP;
   constexpr int KS = BK / 32;             // 32-wide MFMA slices per stage
@@ -774,9 +803,9 @@ __device__ __forceinline__ Tile gemm_tile(const MfmaArgs& a, char* smem, const T
   auto begin_pass = [&](int p) {
     if (p == kTurn) {
       next = draws.tile(kOutCols<EPI>);
-      ops.set(a, smem, next);
+      ops.set(args[PAIR ? __builtin_amdgcn_readfirstlane(next.part) : 0], smem, next);
     }
-    if (p == kFeed0) ops.gather_rows(a);
+    if (p == kFeed0) ops.gather_rows(args[0]);
     __builtin_amdgcn_sched_barrier(0);
   };
   // after cell c of n of pass p's writes
@@ -920,15 +949,20 @@ __device__ __forceinline__ Tile gemm_tile(const MfmaArgs& a, char* smem, const T
 // its own pace.  (The hardware hands the workgroups of an ordinary launch to the XCDs strictly
 // in order of their index: there an XCD whose tiles take longer holds back the workgroups
 // queued behind it for every other XCD, which costs 10-40 % on ragged plans.)
-template <int EPI, int MODE, bool GATHER, bool KTAIL>
-__global__ __launch_bounds__(256, 1) void gemm_mfma_kernel(MfmaArgs a) {
+template <bool PAIR>
+struct MfmaLaunch {
+  MfmaArgs gemm[PAIR ? 2 : 1];
+};
+template <int EPI, int MODE, bool GATHER, bool KTAIL, bool PAIR>
+__global__ __launch_bounds__(256, 1) void gemm_mfma_kernel(MfmaLaunch<PAIR> launch) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub, not the gfx950 builtins
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  Draws draws(a.u, smem);
+  const MfmaArgs* const args = launch.gemm;
+  Draws<PAIR> draws(args[0].u, args[PAIR ? 1 : 0].u, smem);
   Tile tile = draws.tile(kOutCols<EPI>);
   Operands<EPI, MODE, GATHER, KTAIL> ops;
-  ops.set(a, smem, tile);
-  ops.gather_rows(a);
+  ops.set(args[PAIR ? __builtin_amdgcn_readfirstlane(tile.part) : 0], smem, tile);
+  ops.gather_rows(args[0]);
   if (tile.slot >= 0) {
 #pragma unroll
     for (int l = 0; l < kFirstLoads; ++l) ops.load_first(l);
@@ -936,20 +970,20 @@ __global__ __launch_bounds__(256, 1) void gemm_mfma_kernel(MfmaArgs a) {
   }
   while (tile.slot >= 0) {
     const int rows = tile.row_end - tile.row0;  // 1..256
-    if (rows > 192) tile = gemm_tile<EPI, 4, MODE, GATHER, KTAIL>(a, smem, tile, ops, draws);
-    else if (rows > 128) tile = gemm_tile<EPI, 3, MODE, GATHER, KTAIL>(a, smem, tile, ops, draws);
-    else if (rows > 64) tile = gemm_tile<EPI, 2, MODE, GATHER, KTAIL>(a, smem, tile, ops, draws);
-    else tile = gemm_tile<EPI, 1, MODE, GATHER, KTAIL>(a, smem, tile, ops, draws);
+    if (rows > 192) tile = gemm_tile<EPI, 4, MODE, GATHER, KTAIL, PAIR>(args, smem, tile, ops, draws);
+    else if (rows > 128) tile = gemm_tile<EPI, 3, MODE, GATHER, KTAIL, PAIR>(args, smem, tile, ops, draws);
+    else if (rows > 64) tile = gemm_tile<EPI, 2, MODE, GATHER, KTAIL, PAIR>(args, smem, tile, ops, draws);
+    else tile = gemm_tile<EPI, 1, MODE, GATHER, KTAIL, PAIR>(args, smem, tile, ops, draws);
   }
   __builtin_amdgcn_s_waitcnt(0x0F70);  // the loads of no tile are done with LDS
   draws.finish();  // (a workgroup ends when it has received no tile, and has left then)
 #endif
 }
 
-template <int EPI, int MODE, bool GATHER, bool KTAIL>
-int32_t launch_mfma_kernel(const MfmaArgs& a, hipStream_t st) {
+template <int EPI, int MODE, bool GATHER, bool KTAIL, bool PAIR = false>
+int32_t launch_mfma_kernel(const MfmaLaunch<PAIR>& a, hipStream_t st) {
   static_assert(!GATHER || MODE == MODE_NN, "the gather is part of the forward's first GEMM only");
-  void (*kern)(MfmaArgs) = gemm_mfma_kernel<EPI, MODE, GATHER, KTAIL>;
+  void (*kern)(MfmaLaunch<PAIR>) = gemm_mfma_kernel<EPI, MODE, GATHER, KTAIL, PAIR>;
   // per device: the LDS attribute is set on the first launch there (idempotent, so two threads racing through
   // the set-up do the same thing twice)
   static std::atomic<int> workgroups_of_device[kMaxDevices];
@@ -971,9 +1005,15 @@ int32_t launch_mfma_kernel(const MfmaArgs& a, hipStream_t st) {
 template <int EPI, int MODE = MODE_NT, bool GATHER = false>
 int32_t launch_mfma(const MfmaArgs& a, hipStream_t st) {
   if constexpr (MODE == MODE_NT || MODE == MODE_NN) {
-    if (a.K % BK != 0) return launch_mfma_kernel<EPI, MODE, GATHER, true>(a, st);
+    if (a.K % BK != 0) return launch_mfma_kernel<EPI, MODE, GATHER, true>(MfmaLaunch<false>{{a}}, st);
   }
-  return launch_mfma_kernel<EPI, MODE, GATHER, false>(a, st);
+  return launch_mfma_kernel<EPI, MODE, GATHER, false>(MfmaLaunch<false>{{a}}, st);
+}
+
+// Both weight gradients of a backward pass in one launch.
+template <int EPI>
+int32_t launch_mfma_pair(const MfmaArgs& a0, const MfmaArgs& a1, hipStream_t st) {
+  return launch_mfma_kernel<EPI, MODE_TN, false, false, true>(MfmaLaunch<true>{{a0, a1}}, st);
 }
 
 // bf16 shapes the MFMA kernel takes: rows of whole 16-byte pieces, one slot's weights and one 256-row

@@ -30,10 +30,10 @@ TileSpecs backward_tables(const lz_shape* shape, const void* const* tensors, int
 // lz_combine_backward, in the same launch lz_route_backward (gate) and the tables.
 int32_t combine_backward_with(const void* dy, const lz_shape* shape, const lz_layer_buffers& b, bool gate, const TileSpecs& tables,
                               void* stream);
-// lz_ffn_backward, lz_ffn_backward_accumulate, their tables built already or not.
+// lz_ffn_backward, lz_ffn_backward_accumulate, their tables built already or not; in_pass: as part of a whole backward pass.
 int32_t ffn_backward(const void* dyp, const void* xp, const void* z, const void* h, const int32_t* slot_offsets, const void* w1,
                      const void* w2, const lz_shape* shape, void* dxp, void* dw1, void* dw2, bool accumulate, void* ws,
-                     size_t ws_bytes, bool tables_built, void* stream);
+                     size_t ws_bytes, bool tables_built, bool in_pass, void* stream);
 // lz_reduce_replica_grads_dtype of both matrices, of elems1 and elems2 a slot, in one launch where both are whole 16-byte pieces.
 int32_t reduce_pair(const lz_shape* shape, const lz_layer_buffers& b, int64_t elems1, int64_t elems2, void* stream);
 

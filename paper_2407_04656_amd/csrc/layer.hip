@@ -70,7 +70,7 @@ extern "C" int32_t lz_layer_backward(const lz_shape* shape, const lz_layer_buffe
   int32_t rc = lz::combine_backward_with(dy, shape, b, gate, tables, stream);
   if (rc != LZ_OK) return rc;
   rc = lz::ffn_backward(b.dyp, b.xp, b.z, b.h, b.slot_offsets, b.w1, b.w2, shape, b.dxp, b.dw1_slot, b.dw2_slot, accumulate, b.train_ws,
-                        b.train_ws_bytes, tables.n > 0, stream);
+                        b.train_ws_bytes, tables.n > 0, true, stream);
   if (rc != LZ_OK) return rc;
   if ((rc = lz_permute_backward(b.dxp, b.pair_to_row, shape, b.dx, stream)) != LZ_OK) return rc;
   if (!gate && (rc = lz_route_backward(b.dgates, b.topk_gates, b.topk_ids, shape, b.dlogits, stream)) != LZ_OK) return rc;

@@ -80,6 +80,8 @@ CASES = [
     (1500, 512, 768, 12, 4, 4, 4, lz.LZ_BF16, lz.LZ_SWIGLU),     # tables beside the placing workgroups
     (3000, 72, 130, 40, 3, 16, 64, lz.LZ_BF16, lz.LZ_GELU),      # 1024 slots, rows of no whole pieces
     (9000, 256, 512, 6, 2, 3, 4, lz.LZ_BF16, lz.LZ_GELU),
+    (5000, 768, 1088, 16, 2, 8, 8, lz.LZ_BF16, lz.LZ_GELU),      # both weight gradients in one launch: several rounds,
+    (400, 264, 328, 20, 2, 5, 5, lz.LZ_BF16, lz.LZ_SWIGLU),      # one round, lists of unlike lengths
 ]
 
 
