@@ -2,6 +2,8 @@
 // (Algorithm 1's h -> h') and its inverse fused with the gate-weighted combine (Sec. 2.1).
 // Both are pure HBM streaming: one wave per row, 16-byte accesses per lane, several rows'
 // worth of loads in flight before the first store.
+#include <type_traits>
+
 #include "lz_common.h"
 
 namespace {
@@ -112,7 +114,7 @@ __global__ __launch_bounds__(256) void permute_scatter_elem_kernel(const Elem* _
   }
 }
 
-__device__ __forceinline__ void fma8(float* acc, const u32x4& v, float g) {
+__device__ __forceinline__ void fma_vec(float* acc, const u32x4& v, float g, uint16_t) {
   const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
@@ -120,13 +122,28 @@ __device__ __forceinline__ void fma8(float* acc, const u32x4& v, float g) {
     acc[2 * q + 1] = fmaf(g, __uint_as_float(w[q] & 0xFFFF0000u), acc[2 * q + 1]);
   }
 }
+__device__ __forceinline__ void fma_vec(float* acc, const u32x4& v, float g, float) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) acc[q] = fmaf(g, __uint_as_float(v[q]), acc[q]);
+}
+__device__ __forceinline__ u32x4 pack_vec(const float* acc, uint16_t) {
+  u32x4 out;
+  out.x = uint32_t(lz::f32_to_bf16(acc[0])) | (uint32_t(lz::f32_to_bf16(acc[1])) << 16);
+  out.y = uint32_t(lz::f32_to_bf16(acc[2])) | (uint32_t(lz::f32_to_bf16(acc[3])) << 16);
+  out.z = uint32_t(lz::f32_to_bf16(acc[4])) | (uint32_t(lz::f32_to_bf16(acc[5])) << 16);
+  out.w = uint32_t(lz::f32_to_bf16(acc[6])) | (uint32_t(lz::f32_to_bf16(acc[7])) << 16);
+  return out;
+}
+__device__ __forceinline__ u32x4 pack_vec(const float* acc, float) {
+  return u32x4{__float_as_uint(acc[0]), __float_as_uint(acc[1]), __float_as_uint(acc[2]), __float_as_uint(acc[3])};
+}
 
-// y[t, :] = sum_kk gate[t, kk] * yp[pair_to_row[t*k+kk], :]   bf16, 8 elements per lane-vector
+// y[t, :] = sum_kk gate[t, kk] * yp[pair_to_row[t*k+kk], :]   16 bytes per lane-vector: 8 bf16 or 4 fp32 elements
 // (gates == nullptr: all gates 1, the backward of the reshuffle).  K = top-k (compile time, so the
 // row indices and loaded vectors stay in registers); U lane-vectors of every row are loaded before
 // the first is used, K * U 16-byte loads in flight per lane.
-template <int K, int U>
-__global__ __launch_bounds__(256) void combine_bf16_kernel(const u32x4* __restrict__ yp,
+template <typename Elem, int K, int U>
+__global__ __launch_bounds__(256) void combine_vec_kernel(const u32x4* __restrict__ yp,
                                                            const int32_t* __restrict__ pair_to_row,
                                                            const float* __restrict__ gates, int T,
                                                            long long P, int vec_per_row,
@@ -144,14 +161,7 @@ __global__ __launch_bounds__(256) void combine_bf16_kernel(const u32x4* __restri
     src[kk] = yp + (size_t)(ok[kk] ? r : 0) * vec_per_row;
     g[kk] = gates ? gates[t * K + kk] : 1.f;
   }
-  auto pack = [](const float* acc) {
-    u32x4 out;
-    out.x = uint32_t(lz::f32_to_bf16(acc[0])) | (uint32_t(lz::f32_to_bf16(acc[1])) << 16);
-    out.y = uint32_t(lz::f32_to_bf16(acc[2])) | (uint32_t(lz::f32_to_bf16(acc[3])) << 16);
-    out.z = uint32_t(lz::f32_to_bf16(acc[4])) | (uint32_t(lz::f32_to_bf16(acc[5])) << 16);
-    out.w = uint32_t(lz::f32_to_bf16(acc[6])) | (uint32_t(lz::f32_to_bf16(acc[7])) << 16);
-    return out;
-  };
+  constexpr int kElems = 16 / sizeof(Elem);
   u32x4* const dst = y + (size_t)t * vec_per_row;
   int v = lane;
   for (; v + (U - 1) * lz::kWave < vec_per_row; v += U * lz::kWave) {
@@ -163,23 +173,23 @@ __global__ __launch_bounds__(256) void combine_bf16_kernel(const u32x4* __restri
         if (ok[kk]) in[u][kk] = __builtin_nontemporal_load(src[kk] + v + u * lz::kWave);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      float acc[kElems] = {};
 #pragma unroll
       for (int kk = 0; kk < K; ++kk)
-        if (ok[kk]) fma8(acc, in[u][kk], g[kk]);
-      dst[v + u * lz::kWave] = pack(acc);
+        if (ok[kk]) fma_vec(acc, in[u][kk], g[kk], Elem{});
+      dst[v + u * lz::kWave] = pack_vec(acc, Elem{});
     }
   }
   for (; v < vec_per_row; v += lz::kWave) {
-    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    float acc[kElems] = {};
 #pragma unroll
     for (int kk = 0; kk < K; ++kk)
-      if (ok[kk]) fma8(acc, __builtin_nontemporal_load(src[kk] + v), g[kk]);
-    dst[v] = pack(acc);
+      if (ok[kk]) fma_vec(acc, __builtin_nontemporal_load(src[kk] + v), g[kk], Elem{});
+    dst[v] = pack_vec(acc, Elem{});
   }
 }
 
-// generic element-wise combine (fp32 tensors, or bf16 rows not a multiple of 16 bytes)
+// element-wise combine (rows that are not a multiple of 16 bytes, unaligned tensors)
 template <bool BF16>
 __global__ __launch_bounds__(256) void combine_elem_kernel(const void* __restrict__ yp_,
                                                            const int32_t* __restrict__ pair_to_row,
@@ -254,47 +264,49 @@ extern "C" int32_t lz_permute_scatter(const void* x, const int32_t* pair_to_row,
 
 namespace {
 
+// Rows of whole 16-byte pieces.
+template <typename Elem>
+int32_t combine_vec(const void* yp, const int32_t* pair_to_row, const float* gates, const lz_shape* s, void* y, hipStream_t st) {
+  const u32x4* const src = (const u32x4*)yp;
+  u32x4* const dst = (u32x4*)y;
+  const int vec = s->d / (16 / (int)sizeof(Elem));
+  // lane-vectors of a row loaded ahead: 4 (measured: 5.7 TB/s against 5.2 with one; 8 is no
+  // faster), fewer only for rows shorter than that
+  const int ahead = vec >= 4 * lz::kWave ? 4 : (vec >= 2 * lz::kWave ? 2 : 1);
+  auto launch = [&](auto k_c) -> int32_t {
+    constexpr int K = decltype(k_c)::value;
+    auto* const kern = ahead == 4 ? combine_vec_kernel<Elem, K, 4> : ahead == 2 ? combine_vec_kernel<Elem, K, 2> : combine_vec_kernel<Elem, K, 1>;
+    hipLaunchKernelGGL(kern, dim3(unsigned((s->T + kRowsPerBlock - 1) / kRowsPerBlock)), dim3(256), 0, st, src, pair_to_row, gates, s->T,
+                       (long long)s->T * s->k, vec, dst);
+    return lz::launch_status();
+  };
+  switch (s->k) {  // 1 <= k <= kMaxK = 8, checked by shape_ok
+    case 1: return launch(std::integral_constant<int, 1>{});
+    case 2: return launch(std::integral_constant<int, 2>{});
+    case 3: return launch(std::integral_constant<int, 3>{});
+    case 4: return launch(std::integral_constant<int, 4>{});
+    case 5: return launch(std::integral_constant<int, 5>{});
+    case 6: return launch(std::integral_constant<int, 6>{});
+    case 7: return launch(std::integral_constant<int, 7>{});
+    case 8: return launch(std::integral_constant<int, 8>{});
+    default: return LZ_ESHAPE;
+  }
+}
+
 int32_t combine(const void* yp, const int32_t* pair_to_row, const float* topk_gates, const lz_shape* shape,
                 void* y, void* stream) {
   hipStream_t st = (hipStream_t)stream;
   const long long P = (long long)shape->T * shape->k;
   const unsigned blocks = unsigned((shape->T + kRowsPerBlock - 1) / kRowsPerBlock);
-  if (shape->dtype == LZ_BF16 && shape->d % 8 == 0 && aligned16(yp) && aligned16(y)) {
-    const u32x4* src = (const u32x4*)yp;
-    u32x4* dst = (u32x4*)y;
-    const int T = shape->T, vec = shape->d / 8;
-    // lane-vectors of a row loaded ahead: 4 (measured: 5.7 TB/s against 5.2 with one; 8 is no
-    // faster), fewer only for rows shorter than that
-    const int ahead = vec >= 4 * lz::kWave ? 4 : (vec >= 2 * lz::kWave ? 2 : 1);
-#define LZ_COMBINE_U(K, U)                                                                                    \
-  hipLaunchKernelGGL((combine_bf16_kernel<K, U>), dim3(blocks), dim3(256), 0, st, src, pair_to_row, topk_gates, \
-                     T, P, vec, dst)
-#define LZ_COMBINE(K)                       \
-  case K:                                   \
-    if (ahead == 4) LZ_COMBINE_U(K, 4);     \
-    else if (ahead == 2) LZ_COMBINE_U(K, 2); \
-    else LZ_COMBINE_U(K, 1);                \
-    break
-    switch (shape->k) {  // 1 <= k <= kMaxK = 8, checked by shape_ok
-      LZ_COMBINE(1);
-      LZ_COMBINE(2);
-      LZ_COMBINE(3);
-      LZ_COMBINE(4);
-      LZ_COMBINE(5);
-      LZ_COMBINE(6);
-      LZ_COMBINE(7);
-      LZ_COMBINE(8);
-      default: return LZ_ESHAPE;
-    }
-#undef LZ_COMBINE
-#undef LZ_COMBINE_U
-  } else if (shape->dtype == LZ_BF16) {
+  if ((size_t)shape->d * lz::elem_bytes(shape->dtype) % 16 == 0 && aligned16(yp) && aligned16(y))
+    return shape->dtype == LZ_BF16 ? combine_vec<uint16_t>(yp, pair_to_row, topk_gates, shape, y, st)
+                                   : combine_vec<float>(yp, pair_to_row, topk_gates, shape, y, st);
+  if (shape->dtype == LZ_BF16)
     hipLaunchKernelGGL(combine_elem_kernel<true>, dim3(blocks), dim3(256), 0, st, yp, pair_to_row,
                        topk_gates, shape->T, shape->k, P, shape->d, y);
-  } else {
+  else
     hipLaunchKernelGGL(combine_elem_kernel<false>, dim3(blocks), dim3(256), 0, st, yp, pair_to_row,
                        topk_gates, shape->T, shape->k, P, shape->d, y);
-  }
   return lz::launch_status();
 }
 
