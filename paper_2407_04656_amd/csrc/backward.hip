@@ -597,9 +597,9 @@ int32_t lz::ffn_backward(const void* dyp, const void* xp, const void* z, const v
     if ((long long)shape->T * shape->k > 0 && (!dyp || !xp || !z || !h || !w1 || !w2 || !dxp)) return LZ_EINVAL;
     return shape->dtype == LZ_F32
                ? generic_ffn_backward<float>(dyp, xp, z, h, slot_offsets, w1, w2, shape, dxp, dw1, dw2, accumulate,
-                                             gw, tables_built, (hipStream_t)stream)
+                                             gw, tables_built, in_pass, (hipStream_t)stream)
                : generic_ffn_backward<uint16_t>(dyp, xp, z, h, slot_offsets, w1, w2, shape, dxp, dw1, dw2,
-                                                accumulate, gw, tables_built, (hipStream_t)stream);
+                                                accumulate, gw, tables_built, in_pass, (hipStream_t)stream);
   }
   TrainWorkspace w;
   const int32_t rc = check_train(shape, ws, ws_bytes, &w);

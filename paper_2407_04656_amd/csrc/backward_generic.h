@@ -192,7 +192,7 @@ template <typename Elem>
 int32_t generic_ffn_backward(const void* dyp, const void* xp, const void* z, const void* h,
                              const int32_t* slot_offsets, const void* w1, const void* w2, const lz_shape* s,
                              void* dxp, void* dw1, void* dw2, bool accumulate, const GenericTrainWorkspace& w,
-                             bool tables_built, hipStream_t st) {
+                             bool tables_built, bool in_pass, hipStream_t st) {
   const long long P = (long long)s->T * s->k;
   const int S = s->N * s->c, d = s->d, ffn = s->ffn, n1 = w.n1;
   int32_t r;
@@ -224,10 +224,9 @@ int32_t generic_ffn_backward(const void* dyp, const void* xp, const void* z, con
     if ((r = launch_f32_rows<Elem, EPI_NONE, false>(b, S, P, st)) != LZ_OK) return r;
   }
   // dW2[s] = H_s^T dyp_s  [ffn, d],   dW1[s] = xp_s^T dZ_s  [d, n1]
-  r = launch_f32_wgrad<Elem>(h, ffn, dyp, d, slot_offsets, S, P, accumulate ? nullptr : dw2, accumulate ? (float*)dw2 : nullptr, st);
-  if (r != LZ_OK) return r;
-  return launch_f32_wgrad<Elem>(xp, d, w.dz, n1, slot_offsets, S, P, accumulate ? nullptr : dw1,
-                                accumulate ? (float*)dw1 : nullptr, st);
+  const F32Wgrad g2 = f32_wgrad<Elem>(h, ffn, dyp, d, slot_offsets, S, P, accumulate ? nullptr : dw2, accumulate ? (float*)dw2 : nullptr);
+  const F32Wgrad g1 = f32_wgrad<Elem>(xp, d, w.dz, n1, slot_offsets, S, P, accumulate ? nullptr : dw1, accumulate ? (float*)dw1 : nullptr);
+  return accumulate ? launch_f32_wgrads<Elem, EPI_ACCUM>(g2, g1, in_pass, st) : launch_f32_wgrads<Elem, EPI_NONE>(g2, g1, in_pass, st);
 }
 
 }  // namespace

@@ -160,8 +160,15 @@ __device__ __forceinline__ void f32_emit(const F32Args& a, int slot, int row, in
 // by WKM.  Persistent: the grid is what fits the chip at once and a workgroup strides over the tiles, columns
 // fastest (an XCD meets the same columns of a slot's weights again).  Against
 // one workgroup per tile: 4-8 % on the 32 x 32 tiles, level on the wide ones.
-template <typename Elem, int EPI, bool WGRAD, bool WKM, int NW, bool VEC>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(F32Args a) {
+// PAIR: two of them in one launch, the tiles of one behind those of the other.
+template <bool PAIR>
+struct F32Launch {
+  F32Args gemm[PAIR ? 2 : 1];
+  // a weight gradient's tiles
+  static __device__ __forceinline__ long long tiles(const F32Args& a) { return (long long)a.slots * a.m_tiles * a.n_tiles; }
+};
+template <typename Elem, int EPI, bool WGRAD, bool WKM, int NW, bool VEC, bool PAIR>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(F32Launch<PAIR> launch) {
   constexpr int KSPLIT = 4 / NW, TM = kF32Rows, TN = 32 * NW, TK = NW == 4 ? 32 : 64;
   constexpr int kBlocks = TK / KSPLIT / 16;  // 16-k blocks of a stage per wave
   constexpr bool kGated = EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_KEEP;
@@ -175,9 +182,14 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(F32Args a) {
   static_assert(2 * (kSizeA + kSizeW) >= KSPLIT * 32 * (TN + 4), "the K split's partial sums reuse the stages");
 
   constexpr int kOutCols = kGated ? TN / 2 : TN;
-  const int n_row_tiles = WGRAD ? a.slots * a.m_tiles : a.t.header[0];
-  const long long n_all = (long long)n_row_tiles * a.n_tiles;
-  for (long long tile = blockIdx.x; tile < n_all; tile += gridDim.x) {
+  static_assert(WGRAD || !PAIR, "pairs are of weight gradients");
+  const F32Args* const args = launch.gemm;
+  const long long n_first = WGRAD ? F32Launch<PAIR>::tiles(args[0]) : (long long)args[0].t.header[0] * args[0].n_tiles;
+  const long long n_all = n_first + (PAIR ? F32Launch<PAIR>::tiles(args[PAIR ? 1 : 0]) : 0);
+  for (long long t = blockIdx.x; t < n_all; t += gridDim.x) {
+    const int part = PAIR && t >= n_first ? 1 : 0;
+    const F32Args& a = args[part];
+    const long long tile = t - (part ? n_first : 0);
     const int row_tile = int(tile / a.n_tiles), n0 = int(tile % a.n_tiles) * kOutCols;
     int slot, row0, row_end, K = a.K;
     const Elem* A = (const Elem*)a.A;
@@ -439,16 +451,19 @@ inline bool whole_pieces(const F32Args& a) {
          aligned16(a.W) && aligned16(a.C) && aligned16(a.Z) && aligned16(a.Cacc);
 }
 
-template <typename Elem, int EPI, bool WGRAD, bool WKM, int NW>
-void launch_f32_waves(const F32Args& a, dim3 grid, bool vec, hipStream_t st) {
+template <typename Elem, int EPI, bool WGRAD, bool WKM, int NW, bool PAIR = false>
+void launch_f32_waves(const F32Launch<PAIR>& a, dim3 grid, bool vec, hipStream_t st) {
   if constexpr (sizeof(Elem) == 4) {
     if (vec) {
-      hipLaunchKernelGGL((gemm_f32_kernel<Elem, EPI, WGRAD, WKM, NW, true>), grid, dim3(256), 0, st, a);
+      hipLaunchKernelGGL((gemm_f32_kernel<Elem, EPI, WGRAD, WKM, NW, true, PAIR>), grid, dim3(256), 0, st, a);
       return;
     }
   }
-  hipLaunchKernelGGL((gemm_f32_kernel<Elem, EPI, WGRAD, WKM, NW, false>), grid, dim3(256), 0, st, a);
+  hipLaunchKernelGGL((gemm_f32_kernel<Elem, EPI, WGRAD, WKM, NW, false, PAIR>), grid, dim3(256), 0, st, a);
 }
+
+// workgroups that the LDS of the chip holds; 0 on an error
+inline long long f32_resident(int nw) { return (long long)device_cus() * (nw == 1 ? 4 : 3); }
 
 // rows32: 32-row tiles expected to hold rows; max_rows32: those the grid may have to cover
 template <typename Elem, int EPI, bool WGRAD, bool WKM>
@@ -456,13 +471,12 @@ int32_t launch_f32(F32Args a, long long rows32, long long max_rows32, hipStream_
   const int cols = a.n_out * (EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_KEEP ? 2 : 1);
   const int nw = f32_waves(rows32 * ceil_div(cols, 32));
   a.n_tiles = ceil_div(cols, 32 * nw);
-  const int cus = device_cus();
-  if (cus == 0) return LZ_EHIP;
-  const long long resident = (long long)cus * (nw == 1 ? 4 : 3);  // what the LDS of a CU holds
+  const long long resident = f32_resident(nw);
+  if (resident == 0) return LZ_EHIP;
   const dim3 grid((unsigned)(max_rows32 * a.n_tiles < resident ? max_rows32 * a.n_tiles : resident));
   const bool vec = whole_pieces(a);
-  if (nw == 4) launch_f32_waves<Elem, EPI, WGRAD, WKM, 4>(a, grid, vec, st);
-  else launch_f32_waves<Elem, EPI, WGRAD, WKM, 1>(a, grid, vec, st);
+  if (nw == 4) launch_f32_waves<Elem, EPI, WGRAD, WKM, 4>(F32Launch<false>{{a}}, grid, vec, st);
+  else launch_f32_waves<Elem, EPI, WGRAD, WKM, 1>(F32Launch<false>{{a}}, grid, vec, st);
   return lz::launch_status();
 }
 

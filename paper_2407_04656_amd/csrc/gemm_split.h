@@ -44,8 +44,8 @@ __device__ __forceinline__ void split_pair(float a, float b, uint32_t (&d)[3]) {
   d[2] = pack_bf16x2(ra - __uint_as_float(d[1] << 16), rb - __uint_as_float(d[1] & 0xFFFF0000u));
 }
 
-template <int EPI, bool WGRAD>
-__global__ __launch_bounds__(256, 2) void gemm_split_kernel(F32Args a) {
+template <int EPI, bool WGRAD, bool PAIR>
+__global__ __launch_bounds__(256, 2) void gemm_split_kernel(F32Launch<PAIR> launch) {
   constexpr int TM = kSplitRows, TN = kSplitCols, TK = 64;
   constexpr bool kGated = EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_KEEP;
   constexpr bool AKM = WGRAD;
@@ -56,9 +56,13 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(F32Args a) {
 
   constexpr int kOutCols = kGated ? TN / 2 : TN;
 
-  const int n_row_tiles = WGRAD ? a.slots * a.m_tiles : a.t.header[0];
-  const long long n_all = (long long)n_row_tiles * a.n_tiles;
-  for (long long tile = blockIdx.x; tile < n_all; tile += gridDim.x) {
+  const F32Args* const args = launch.gemm;
+  const long long n_first = WGRAD ? F32Launch<PAIR>::tiles(args[0]) : (long long)args[0].t.header[0] * args[0].n_tiles;
+  const long long n_all = n_first + (PAIR ? F32Launch<PAIR>::tiles(args[PAIR ? 1 : 0]) : 0);
+  for (long long t = blockIdx.x; t < n_all; t += gridDim.x) {
+    const int part = PAIR && t >= n_first ? 1 : 0;
+    const F32Args& a = args[part];
+    const long long tile = t - (part ? n_first : 0);
     // The empty asm keeps the per-lane address arithmetic inside the tile: hoisted out of the loop it would be carried in
     // registers through the stages and spill.
     int tid = threadIdx.x;
@@ -312,7 +316,8 @@ int32_t launch_split(F32Args a, int cols, long long max_rows64, hipStream_t st) 
   if (cus == 0) return LZ_EHIP;
   a.n_tiles = ceil_div(cols, kSplitCols);
   const long long resident = 2ll * cus, tiles = max_rows64 * a.n_tiles;
-  hipLaunchKernelGGL((gemm_split_kernel<EPI, WGRAD>), dim3((unsigned)(tiles < resident ? tiles : resident)), dim3(256), 0, st, a);
+  hipLaunchKernelGGL((gemm_split_kernel<EPI, WGRAD, false>), dim3((unsigned)(tiles < resident ? tiles : resident)), dim3(256), 0, st,
+                     F32Launch<false>{{a}});
   return lz::launch_status();
 }
 
@@ -332,11 +337,18 @@ int32_t launch_f32_rows(F32Args a, int S, long long P, hipStream_t st) {
   return launch_f32<Elem, EPI, false, WKM>(a, P / kF32Rows + (used + 1) / 2, a.t.capacity, st);
 }
 
-// The weight gradients of all slots: C[s] [m_rows, n_out] = A[rows of s]^T W[rows of s], or added to Cacc.
+// A weight gradient of all slots, C[s] [m_rows, n_out] = A[rows of s]^T W[rows of s], or added to Cacc, and how it is launched.
+struct F32Wgrad {
+  F32Args a;
+  bool split, vec;
+  int nw;           // of the fp32 kernel
+  long long tiles;  // of the kernel that serves it
+};
 template <typename Elem>
-int32_t launch_f32_wgrad(const void* A, int m_rows, const void* W, int n_out, const int32_t* slot_offsets, int S, long long P,
-                         void* C, float* Cacc, hipStream_t st) {
-  F32Args a{};
+F32Wgrad f32_wgrad(const void* A, int m_rows, const void* W, int n_out, const int32_t* slot_offsets, int S, long long P, void* C,
+                   float* Cacc) {
+  F32Wgrad g{};
+  F32Args& a = g.a;
   a.A = A;
   a.W = W;
   a.C = C;
@@ -346,16 +358,42 @@ int32_t launch_f32_wgrad(const void* A, int m_rows, const void* W, int n_out, co
   a.slot_offsets = slot_offsets;
   a.P = P;
   a.slots = S;
-  if constexpr (sizeof(Elem) == 4) {
-    a.m_tiles = ceil_div(m_rows, kSplitRows);
-    const long long tiles = (long long)S * a.m_tiles;
-    if (use_split(P, S, tiles, n_out, m_rows, 4) && whole_pieces(a))
-      return Cacc ? launch_split<EPI_ACCUM, true>(a, n_out, tiles, st) : launch_split<EPI_NONE, true>(a, n_out, tiles, st);
+  g.vec = whole_pieces(a);
+  g.split = sizeof(Elem) == 4 && g.vec && use_split(P, S, (long long)S * ceil_div(m_rows, kSplitRows), n_out, m_rows, 4);
+  a.m_tiles = ceil_div(m_rows, g.split ? kSplitRows : kF32Rows);
+  g.nw = f32_waves((long long)S * a.m_tiles * ceil_div(n_out, 32));
+  a.n_tiles = ceil_div(n_out, g.split ? kSplitCols : 32 * g.nw);
+  g.tiles = (long long)S * a.m_tiles * a.n_tiles;
+  return g;
+}
+
+template <typename Elem, int EPI>
+int32_t launch_f32_wgrad(const F32Wgrad& g, hipStream_t st) {
+  const long long rows = (long long)g.a.slots * g.a.m_tiles;
+  if constexpr (sizeof(Elem) == 4)
+    if (g.split) return launch_split<EPI, true>(g.a, g.a.n_out, rows, st);
+  return launch_f32<Elem, EPI, true, true>(g.a, rows, rows, st);
+}
+
+// Both of a backward pass; pair: in one launch where one kernel serves both, see gemm_wgrads() of the bf16 kernels.
+template <typename Elem, int EPI>
+int32_t launch_f32_wgrads(const F32Wgrad& g0, const F32Wgrad& g1, bool pair, hipStream_t st) {
+  if (pair && g0.split == g1.split && g0.vec == g1.vec && (g0.split || g0.nw == g1.nw)) {
+    const F32Launch<true> both{{g0.a, g1.a}};
+    const long long tiles = g0.tiles + g1.tiles, resident = g0.split ? 2ll * device_cus() : f32_resident(g0.nw);
+    if (resident == 0) return LZ_EHIP;
+    const dim3 grid((unsigned)(tiles < resident ? tiles : resident));
+    if (g0.split) {
+      if constexpr (sizeof(Elem) == 4) hipLaunchKernelGGL((gemm_split_kernel<EPI, true, true>), grid, dim3(256), 0, st, both);
+    } else if (g0.nw == 4) {
+      launch_f32_waves<Elem, EPI, true, true, 4>(both, grid, g0.vec, st);
+    } else {
+      launch_f32_waves<Elem, EPI, true, true, 1>(both, grid, g0.vec, st);
+    }
+    return lz::launch_status();
   }
-  a.m_tiles = ceil_div(m_rows, kF32Rows);
-  const long long tiles = (long long)S * a.m_tiles;
-  return Cacc ? launch_f32<Elem, EPI_ACCUM, true, true>(a, tiles, tiles, st)
-              : launch_f32<Elem, EPI_NONE, true, true>(a, tiles, tiles, st);
+  const int32_t r = launch_f32_wgrad<Elem, EPI>(g0, st);
+  return r != LZ_OK ? r : launch_f32_wgrad<Elem, EPI>(g1, st);
 }
 
 }  // namespace
