@@ -44,7 +44,7 @@ __device__ __forceinline__ void split_pair(float a, float b, uint32_t (&d)[3]) {
   d[2] = pack_bf16x2(ra - __uint_as_float(d[1] << 16), rb - __uint_as_float(d[1] & 0xFFFF0000u));
 }
 
-template <int EPI, bool WGRAD, bool PAIR>
+template <int EPI, bool WGRAD, bool PAIR = false>
 __global__ __launch_bounds__(256, 2) void gemm_split_kernel(F32Launch<PAIR> launch) {
   constexpr int TM = kSplitRows, TN = kSplitCols, TK = 64;
   constexpr bool kGated = EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_KEEP;
