@@ -20,8 +20,8 @@ namespace {
 // Shapes on the MFMA kernels: every bf16 shape whose rows are whole 16-byte pieces.  Where a size is no
 // multiple of the tile the kernel computes the tile's padding too and stores the real part; a forward
 // of T = 3001, d = 1000, ffn = 2664, top-2 over 12 slots, SwiGLU: 2413 us on an fp32-FMA kernel, 200 us here.
-// Their activations are this kernel's (hardware exp2 and rcp, a rational erf), not the fp32 kernel's erff and expf:
-// before the rounding to bf16 GELU is off by up to 4.7e-7 against 4.5e-7, after it both have the same error.
+// Their activations are this kernel's (hardware exp2 and rcp, see gelu_fast), not the fp32 kernel's erff and expf: after the
+// rounding to bf16 both have the same error.
 // Sizes that are not whole_tiles additionally accept unaligned tensors (on the fp32 kernel) and fused gathers of any
 // x; the MFMA gather's 32-bit offsets hold x up to 2 GiB there, and a shape decides for all its calls.
 inline bool whole_tiles(const lz_shape* s) {

@@ -1,4 +1,4 @@
-// Grouped bf16 GEMM on the gfx950 matrix cores and the tables that it and the other grouped GEMMs draw their work from;
+// Grouped bf16 GEMM on the gfx950 matrix cores, drawing its work from the tables of tiles.h;
 // shared by the forward and the backward translation units (device code, not part of the C ABI).
 //
 //   C[rows of a slot, n] = epi( sum_k A(row, k) * W[slot](n, k) )

@@ -145,17 +145,16 @@ __device__ __forceinline__ void route_token(const float* __restrict__ logits, lo
   typename std::conditional<SORTED, double, uint32_t>::type key[V];
 #pragma unroll
   for (int q = 0; q < V / 4; ++q) {
-    float x[4] = {0.f, 0.f, 0.f, 0.f};
+    // Absent logits read the row's first: loads under a test would each be waited for before the next (256 experts, top-8, with the
+    // plan 35.7 -> 38.4 us).
+    float x[4];
     const int e = e0 + expert_of(4 * q);
     if constexpr (VEC) {
-      if (e < E) {
-        const float4 f = *(const float4*)(row + e);
-        x[0] = f.x, x[1] = f.y, x[2] = f.z, x[3] = f.w;
-      }
+      const float4 f = *(const float4*)(row + (e < E ? e : 0));
+      x[0] = f.x, x[1] = f.y, x[2] = f.z, x[3] = f.w;
     } else {
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (e + i < E) x[i] = row[e + i];
+      for (int i = 0; i < 4; ++i) x[i] = row[e + i < E ? e + i : 0];
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
