@@ -62,25 +62,35 @@ __device__ __forceinline__ u32x4 pack(const float* f, float) {
   return u32x4{__float_as_uint(f[0]), __float_as_uint(f[1]), __float_as_uint(f[2]), __float_as_uint(f[3])};
 }
 
+template <bool STREAM>
+__device__ __forceinline__ u32x4 load_piece(const u32x4* p) {
+  if constexpr (STREAM) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+template <bool STREAM>
+__device__ __forceinline__ void store_piece(const u32x4& v, u32x4* p) {
+  if constexpr (STREAM) __builtin_nontemporal_store(v, p);
+  else *p = v;
+}
+
 // ---- combine backward: one wave per token.  dy[t] is read once, every yp row once, every
 // dyp row written once; the k dot products are reduced over the wave at the end.
-template <typename Elem>
-__global__ __launch_bounds__(kCombineThreads) void combine_backward_kernel(const u32x4* __restrict__ dy,
-                                                               const u32x4* __restrict__ yp,
-                                                               const int32_t* __restrict__ pair_to_row,
-                                                               const float* __restrict__ gates, int T, int k,
-                                                               long long P, int vec_per_row,
-                                                               u32x4* __restrict__ dyp,
-                                                               float* __restrict__ dgates, WithCombine with) {
-  __shared__ CombineLds lds;
-  if (table_workgroup(with, lds)) return;
+// MAXK: the most choices a token can have.  Room for eight of them is 100 registers and four waves a SIMD, which costs an fp32 row,
+// whose elements' kernel runs eight: us for 40000 tokens of 128 columns, top-2, elements 20.5, this kernel with room for eight 32.4, for
+// two 22.0; 10897 of 368, top-4, 32.0, 30.0, and 27.1 for four; 5448 of 320, top-1, 4.4, 6.0, and 4.4 for one.
+// STREAM: past the caches.  fp32, 40000 tokens of 384 columns, top-4 (553 MB) 117 us, 125 through them; 8000 of 1024, top-2 (164 MB, left in
+// the caches by the call before) 38 and 27.
+template <typename Elem, bool WITH, int MAXK, bool STREAM>
+__global__ __launch_bounds__(kCombineThreads<WITH>) void combine_backward_kernel(
+    const u32x4* __restrict__ dy, const u32x4* __restrict__ yp, const int32_t* __restrict__ pair_to_row, const float* __restrict__ gates,
+    int T, int k, long long P, int vec_per_row, u32x4* __restrict__ dyp, float* __restrict__ dgates, CombineExtra<WITH> with) {
   const int lane = threadIdx.x % lz::kWave;
-  const long long t = ((long long)blockIdx.x - with.tables.n) * kTokensPerBlock + threadIdx.x / lz::kWave;
-  if (t >= T) return;
-  long long rows[lz::kMaxK];
-  float g[lz::kMaxK], dot[lz::kMaxK];
+  const long long t = combine_token<WITH>(T, with);
+  if (t < 0) return;
+  long long rows[MAXK];
+  float g[MAXK], dot[MAXK];
 #pragma unroll
-  for (int kk = 0; kk < lz::kMaxK; ++kk) {
+  for (int kk = 0; kk < MAXK; ++kk) {
     rows[kk] = -1;
     g[kk] = 0.f;
     dot[kk] = 0.f;
@@ -93,13 +103,13 @@ __global__ __launch_bounds__(kCombineThreads) void combine_backward_kernel(const
   for (int v = lane; v < vec_per_row; v += lz::kWave) {
     constexpr int kElems = 16 / sizeof(Elem);
     float gy[kElems];
-    unpack(__builtin_nontemporal_load(dy + (size_t)t * vec_per_row + v), gy, Elem{});
-    u32x4 in[lz::kMaxK];
+    unpack(load_piece<STREAM>(dy + (size_t)t * vec_per_row + v), gy, Elem{});
+    u32x4 in[MAXK];
 #pragma unroll
-    for (int kk = 0; kk < lz::kMaxK; ++kk)
-      if (kk < k && rows[kk] >= 0) in[kk] = __builtin_nontemporal_load(yp + (size_t)rows[kk] * vec_per_row + v);
+    for (int kk = 0; kk < MAXK; ++kk)
+      if (kk < k && rows[kk] >= 0) in[kk] = load_piece<STREAM>(yp + (size_t)rows[kk] * vec_per_row + v);
 #pragma unroll
-    for (int kk = 0; kk < lz::kMaxK; ++kk)
+    for (int kk = 0; kk < MAXK; ++kk)
       if (kk < k && rows[kk] >= 0) {
         float y[kElems], o[kElems];
         unpack(in[kk], y, Elem{});
@@ -108,16 +118,22 @@ __global__ __launch_bounds__(kCombineThreads) void combine_backward_kernel(const
           dot[kk] = fmaf(gy[q], y[q], dot[kk]);
           o[q] = g[kk] * gy[q];
         }
-        __builtin_nontemporal_store(pack(o, Elem{}), dyp + (size_t)rows[kk] * vec_per_row + v);
+        store_piece<STREAM>(pack(o, Elem{}), dyp + (size_t)rows[kk] * vec_per_row + v);
       }
   }
 #pragma unroll
-  for (int kk = 0; kk < lz::kMaxK; ++kk)
+  for (int kk = 0; kk < MAXK; ++kk)
     if (kk < k) {
       dot[kk] = wave_sum(dot[kk]);
       if (lane == 0) dgates[t * k + kk] = dot[kk];
     }
-  if (with.dlogits != nullptr) gate_backward(with, t, k, g, dot);
+  if constexpr (WITH)
+    if (with.dlogits != nullptr) {
+      int id[MAXK];
+#pragma unroll
+      for (int kk = 0; kk < MAXK; ++kk) id[kk] = kk < k ? with.ids[t * k + kk] : 0;
+      gate_backward<MAXK>(with, t, k, id, g, dot);
+    }
 }
 
 // ---- gate backward: thread per (token, expert)
@@ -500,23 +516,53 @@ extern "C" int32_t lz_ffn_forward_train(const void* xp, const int32_t* slot_offs
 
 namespace {
 
+// Bytes of the combine backward's rows that the memory-side cache holds.
+constexpr long long kCachedBytes = 256ll << 20;
+
+// Which of fp32 rows of whole 16-byte pieces the vector kernel takes; bits of dgates depend on it.  Rows of fewer than 24 pieces leave lanes
+// without work, and more than four choices their room for eight (see the kernel), which few tokens and rows from memory do not feel.
+// us by elements, by vectors: 16000 tokens of 32 columns, top-4 8.6, 11.1; 8000 of 96, top-4 8.0, 8.3; 8000 of 256, top-6 18.6, 23.1;
+// 4096 of them 14.5, 11.8; 1000 of 96, top-8 7.0, 6.5; 40000 of 128, top-8 (348 MB) 107, 87.
+inline bool vectors_f32(const lz_shape* s, long long bytes) {
+  return s->d >= 96 && (s->k <= 4 || s->T <= 4096 || bytes > kCachedBytes);
+}
+
+template <typename Elem, bool WITH>
+auto combine_kernel_of(int k, bool stream) {
+  if constexpr (sizeof(Elem) == 2) return combine_backward_kernel<Elem, WITH, lz::kMaxK, true>;
+  else
+    return stream ? (k > 4   ? combine_backward_kernel<Elem, WITH, lz::kMaxK, true>
+                     : k > 2 ? combine_backward_kernel<Elem, WITH, 4, true>
+                     : k > 1 ? combine_backward_kernel<Elem, WITH, 2, true>
+                             : combine_backward_kernel<Elem, WITH, 1, true>)
+                  : (k > 4   ? combine_backward_kernel<Elem, WITH, lz::kMaxK, false>
+                     : k > 2 ? combine_backward_kernel<Elem, WITH, 4, false>
+                     : k > 1 ? combine_backward_kernel<Elem, WITH, 2, false>
+                             : combine_backward_kernel<Elem, WITH, 1, false>);
+}
+
+template <bool WITH>
 int32_t combine_backward(const void* dy, const void* yp, const int32_t* pair_to_row, const float* topk_gates, const lz_shape* shape,
-                         void* dyp, float* dgates, const WithCombine& with, hipStream_t st) {
+                         void* dyp, float* dgates, const CombineExtra<WITH>& with, hipStream_t st) {
   if (!lz::shape_ok(shape)) return LZ_ESHAPE;
   if (shape->T == 0) return LZ_OK;
   if (!dy || !yp || !pair_to_row || !topk_gates || !dyp || !dgates) return LZ_EINVAL;
   const long long P = (long long)shape->T * shape->k;
-  const dim3 grid((unsigned)((shape->T + kTokensPerBlock - 1) / kTokensPerBlock + with.tables.n)), threads(kCombineThreads);
+  int tokens = kTokensAlone, first = 0;
+  if constexpr (WITH) tokens = with.tokens, first = with.tables.n;
+  const dim3 grid((unsigned)((shape->T + tokens - 1) / tokens + first)), threads(kCombineThreads<WITH>);
   const size_t row_bytes = (size_t)shape->d * lz::elem_bytes(shape->dtype);
-  const bool whole = row_bytes % 16 == 0 && aligned16(dy) && aligned16(yp) && aligned16(dyp);
+  const long long bytes = (2 * P + shape->T) * (long long)row_bytes;
+  const bool whole = row_bytes % 16 == 0 && aligned16(dy) && aligned16(yp) && aligned16(dyp) &&
+                     (shape->dtype == LZ_BF16 || vectors_f32(shape, bytes));
   auto launch = [&](auto elem) {
     using Elem = decltype(elem);
     if (whole)
-      hipLaunchKernelGGL(combine_backward_kernel<Elem>, grid, threads, 0, st, (const u32x4*)dy, (const u32x4*)yp, pair_to_row, topk_gates,
-                         shape->T, shape->k, P, int(row_bytes / 16), (u32x4*)dyp, dgates, with);
+      hipLaunchKernelGGL((combine_kernel_of<Elem, WITH>(shape->k, bytes > kCachedBytes)), grid, threads, 0, st, (const u32x4*)dy,
+                         (const u32x4*)yp, pair_to_row, topk_gates, shape->T, shape->k, P, int(row_bytes / 16), (u32x4*)dyp, dgates, with);
     else
-      hipLaunchKernelGGL(combine_backward_generic_kernel<Elem>, grid, threads, 0, st, (const Elem*)dy, (const Elem*)yp, pair_to_row,
-                         topk_gates, shape->T, shape->k, P, shape->d, (Elem*)dyp, dgates, with);
+      hipLaunchKernelGGL((combine_backward_generic_kernel<Elem, WITH>), grid, threads, 0, st, (const Elem*)dy, (const Elem*)yp,
+                         pair_to_row, topk_gates, shape->T, shape->k, P, shape->d, (Elem*)dyp, dgates, with);
   };
   if (shape->dtype == LZ_F32) launch(float{});
   else launch(uint16_t{});
@@ -528,16 +574,19 @@ int32_t combine_backward(const void* dy, const void* yp, const int32_t* pair_to_
 extern "C" int32_t lz_combine_backward(const void* dy, const void* yp, const int32_t* pair_to_row,
                                        const float* topk_gates, const lz_shape* shape, void* dyp, float* dgates,
                                        void* stream) {
-  return combine_backward(dy, yp, pair_to_row, topk_gates, shape, dyp, dgates, WithCombine{}, (hipStream_t)stream);
+  return combine_backward<false>(dy, yp, pair_to_row, topk_gates, shape, dyp, dgates, CombineAlone{}, (hipStream_t)stream);
 }
 
 int32_t lz::combine_backward_with(const void* dy, const lz_shape* shape, const lz_layer_buffers& b, bool gate, const TileSpecs& tables,
                                   void* stream) {
+  if (!gate && tables.n == 0) return lz_combine_backward(dy, b.yp, b.pair_to_row, b.topk_gates, shape, b.dyp, b.dgates, stream);
   const int workgroups = device_cus();
   if (workgroups == 0) return LZ_EHIP;
-  const WithCombine with{b.topk_ids, shape ? shape->E : 0, gate ? b.dlogits : nullptr, b.slot_offsets, shape ? shape->N * shape->c : 0,
-                         workgroups, tables};
-  return combine_backward(dy, b.yp, b.pair_to_row, b.topk_gates, shape, b.dyp, b.dgates, with, (hipStream_t)stream);
+  // Four tokens a workgroup while that gives no CU a second one: us for 225 tokens, top-8, 3944 bf16 columns 29 with eight, 21 with
+  // four; 2450, top-6, 672 17 and 18; 40960, top-1, 768 52 and 66.
+  const WithCombine with{b.topk_ids, shape->E, gate ? b.dlogits : nullptr, b.slot_offsets, shape->N * shape->c, workgroups,
+                         shape->T <= 4 * workgroups ? 4 : kTileThreads / lz::kWave, tables};
+  return combine_backward<true>(dy, b.yp, b.pair_to_row, b.topk_gates, shape, b.dyp, b.dgates, with, (hipStream_t)stream);
 }
 
 extern "C" int32_t lz_route_backward(const float* dgates, const float* topk_gates, const int32_t* topk_ids,

@@ -4,6 +4,8 @@
 // to the tensor type; the fp32 path uses erff / expf so that it meets the fp32 error bar.
 // Device code, not part of the C ABI; included by backward.hip.
 #pragma once
+#include <type_traits>
+
 #include "gemm_split.h"
 
 namespace {
@@ -16,10 +18,16 @@ struct WithCombine {
   float* dlogits;
   const int32_t* slot_offsets;
   int S, workgroups;
+  int tokens;  // of a workgroup, a wave each; its other waves are there for the tables
   TileSpecs tables;
 };
-constexpr int kTableSlots = 512;      // more slots get a launch of their own: LDS that all workgroups would carry
-constexpr int kCombineThreads = kTileThreads, kTokensPerBlock = kCombineThreads / lz::kWave;
+struct CombineAlone {};  // lz_combine_backward: none of it, in arguments and LDS neither
+template <bool WITH>
+using CombineExtra = typename std::conditional<WITH, WithCombine, CombineAlone>::type;
+constexpr int kTableSlots = 512;  // more slots get a launch of their own: LDS that all workgroups would carry
+constexpr int kTokensAlone = 4;
+template <bool WITH>
+constexpr int kCombineThreads = WITH ? kTileThreads : kTokensAlone * lz::kWave;
 struct CombineLds {
   SlotRows<kTableSlots> slots;
   TableScratch<kTableSlots> scratch;
@@ -28,7 +36,7 @@ struct CombineLds {
 __device__ __forceinline__ bool table_workgroup(const WithCombine& with, CombineLds& m) {
   if ((int)blockIdx.x >= with.tables.n) return false;
   const TileSpec& spec = with.tables.spec[blockIdx.x];
-  for (int s = threadIdx.x; s < with.S; s += kCombineThreads) {
+  for (int s = threadIdx.x; s < with.S; s += kTileThreads) {
     long long a, b;
     clip_slot(with.slot_offsets, s, spec.P, &a, &b);
     m.slots.first[s] = int(a);
@@ -38,22 +46,33 @@ __device__ __forceinline__ bool table_workgroup(const WithCombine& with, Combine
   build_table(spec, false, m.slots, with.S, m.scratch, threadIdx.x, with.workgroups);
   return true;
 }
+// The token of this wave, -1: none.
+template <bool WITH>
+__device__ __forceinline__ long long combine_token(int T, const CombineExtra<WITH>& with) {
+  const int w = threadIdx.x / lz::kWave;
+  if constexpr (WITH) {
+    __shared__ CombineLds lds;
+    if (table_workgroup(with, lds) || w >= with.tokens) return -1;
+    const long long t = ((long long)blockIdx.x - with.tables.n) * with.tokens + w;
+    return t < T ? t : -1;
+  } else {
+    const long long t = (long long)blockIdx.x * kTokensAlone + w;
+    return t < T ? t : -1;
+  }
+}
 
 // A token's gates' gradients by its whole wave, lane by lane an expert: dlogits[e] = g_e (dg_e - sum_i g_i dg_i).
-__device__ __forceinline__ void gate_backward(const WithCombine& with, long long t, int k, const float* g, const float* dg) {
+template <int MAXK>
+__device__ __forceinline__ void gate_backward(const WithCombine& with, long long t, int k, const int* id, const float* g, const float* dg) {
   const int lane = threadIdx.x % lz::kWave;
   float inner = 0.f;
-  int id[lz::kMaxK];
 #pragma unroll
-  for (int kk = 0; kk < lz::kMaxK; ++kk)
-    if (kk < k) {
-      inner = fmaf(g[kk], dg[kk], inner);
-      id[kk] = with.ids[t * k + kk];
-    }
+  for (int kk = 0; kk < MAXK; ++kk)
+    if (kk < k) inner = fmaf(g[kk], dg[kk], inner);
   for (int e = lane; e < with.E; e += lz::kWave) {
     float mine_g = 0.f, mine_dg = 0.f;
 #pragma unroll
-    for (int kk = 0; kk < lz::kMaxK; ++kk)
+    for (int kk = 0; kk < MAXK; ++kk)
       if (kk < k && id[kk] == e) {
         mine_g = g[kk];
         mine_dg = dg[kk];
@@ -64,27 +83,25 @@ __device__ __forceinline__ void gate_backward(const WithCombine& with, long long
 
 // combine backward, one wave per token, by elements (rows that are no whole 16-byte pieces, unaligned tensors):
 // dgates[t,kk] = <dy[t], yp[row]>, dyp[row] = gates[t,kk] dy[t]
-template <typename Elem>
-__global__ __launch_bounds__(kCombineThreads) void combine_backward_generic_kernel(const Elem* __restrict__ dy,
-                                                                       const Elem* __restrict__ yp,
-                                                                       const int32_t* __restrict__ pair_to_row,
-                                                                       const float* __restrict__ gates, int T, int k,
-                                                                       long long P, int d, Elem* __restrict__ dyp,
-                                                                       float* __restrict__ dgates, WithCombine with) {
-  __shared__ CombineLds lds;
-  if (table_workgroup(with, lds)) return;
+template <typename Elem, bool WITH>
+__global__ __launch_bounds__(kCombineThreads<WITH>) void combine_backward_generic_kernel(
+    const Elem* __restrict__ dy, const Elem* __restrict__ yp, const int32_t* __restrict__ pair_to_row, const float* __restrict__ gates,
+    int T, int k, long long P, int d, Elem* __restrict__ dyp, float* __restrict__ dgates, CombineExtra<WITH> with) {
   const int lane = threadIdx.x % lz::kWave;
-  const long long t = ((long long)blockIdx.x - with.tables.n) * kTokensPerBlock + threadIdx.x / lz::kWave;
-  if (t >= T) return;
-  float gate[lz::kMaxK], grad[lz::kMaxK];
-#pragma unroll
-  for (int kk = 0; kk < lz::kMaxK; ++kk) {
-    gate[kk] = grad[kk] = 0.f;
-    if (kk >= k) continue;
+  const long long t = combine_token<WITH>(T, with);
+  if (t < 0) return;
+  int own_id = 0;  // lane kk: the kk-th choice, its gate and that one's gradient
+  float own_gate = 0.f, own = 0.f;
+  if constexpr (WITH)
+    if (with.dlogits != nullptr && lane < k) {
+      own_id = with.ids[t * k + lane];
+      own_gate = gates[t * k + lane];
+    }
+  for (int kk = 0; kk < k; ++kk) {
     const int r = pair_to_row[t * k + kk];
-    const float g = gates[t * k + kk];
     float dot = 0.f;
     if (r >= 0 && r < P) {
+      const float g = gates[t * k + kk];
       for (int v = lane; v < d; v += lz::kWave) {
         const float gy = load_elem<Elem>(dy + (size_t)t * d + v);
         dot = fmaf(gy, load_elem<Elem>(yp + (size_t)r * d + v), dot);
@@ -94,10 +111,21 @@ __global__ __launch_bounds__(kCombineThreads) void combine_backward_generic_kern
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) dot += __shfl_xor(dot, off, 64);
     if (lane == 0) dgates[t * k + kk] = dot;
-    gate[kk] = g;
-    grad[kk] = dot;
+    if constexpr (WITH) own = lane == kk ? dot : own;
   }
-  if (with.dlogits != nullptr) gate_backward(with, t, k, gate, grad);
+  if constexpr (WITH) {
+    if (with.dlogits == nullptr) return;
+    auto of = [](float v, int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); };
+    int id[lz::kMaxK];
+    float g[lz::kMaxK], dg[lz::kMaxK];
+#pragma unroll
+    for (int kk = 0; kk < lz::kMaxK; ++kk) {
+      id[kk] = __builtin_amdgcn_readlane(own_id, kk);
+      g[kk] = of(own_gate, kk);
+      dg[kk] = of(own, kk);
+    }
+    gate_backward<lz::kMaxK>(with, t, k, id, g, dg);
+  }
 }
 
 // dW[e] = sum over the slots holding e, ascending slot, fp32 sum, one rounding
