@@ -521,13 +521,14 @@ class MoELayer:
         lz_unpermute_combine(self.yp, self.pair_to_row, self.topk_gates, self.shape, self.y)
 
     # The passes below are one call each, which takes the addresses of the buffers as they are now.  A layer with steps of its
-    # own (a subclass's, or set on the object) keeps to them.
-    _STEPS = frozenset(("route", "plan_dispatch", "permute", "expert_ffn", "unpermute_combine"))
+    # own (a subclass's, set on the object, or put in this class's place) keeps to them.
+    _STEPS = dict(route=route, plan_dispatch=plan_dispatch, permute=permute, expert_ffn=expert_ffn,
+                  unpermute_combine=unpermute_combine)
 
     def _own_steps(self):
         cls = type(self)
-        return not self._STEPS.isdisjoint(self.__dict__) or (
-            cls is not MoELayer and any(getattr(cls, n) is not getattr(MoELayer, n) for n in self._STEPS))
+        return not self._STEPS.keys().isdisjoint(self.__dict__) or any(
+            getattr(cls, n) is not step for n, step in self._STEPS.items())
 
     def _forward_buffers(self, train_ws=None, train_ws_bytes=0, z=None, h=None):
         return _LayerBuffers(
