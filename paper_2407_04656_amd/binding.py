@@ -530,17 +530,18 @@ class MoELayer:
         return not self._STEPS.keys().isdisjoint(self.__dict__) or any(
             getattr(cls, n) is not step for n, step in self._STEPS.items())
 
-    def _forward_buffers(self, train_ws=None, train_ws_bytes=0, z=None, h=None):
+    def _forward_buffers(self, xp, ffn_ws=None, ffn_ws_bytes=0, train_ws=None, train_ws_bytes=0, z=None, h=None):
+        """Those of every forward, and what this one uses: a buffer that a program has given up is not asked for by the others."""
         return _LayerBuffers(
             _ptr(self.rank_tok_off), _ptr(self.slot_expert), _ptr(self.w1), _ptr(self.w2), _ptr(self.topk_ids),
             _ptr(self.topk_gates), _ptr(self.slot_counts), _ptr(self.slot_offsets), _ptr(self.pair_to_row),
-            _ptr(self.row_to_pair), _ptr(self.Tej), _ptr(self.D), _ptr(self.status), _ptr(self.xp), _ptr(self.yp),
-            _ptr(self.y), _ptr(self.plan_ws), _ptr(self.ffn_ws), _ptr(train_ws), self.plan_ws_bytes,
-            self.ffn_ws_bytes, train_ws_bytes, _ptr(z), _ptr(h))
+            _ptr(self.row_to_pair), _ptr(self.Tej), _ptr(self.D), _ptr(self.status), _ptr(xp), _ptr(self.yp),
+            _ptr(self.y), _ptr(self.plan_ws), _ptr(ffn_ws), _ptr(train_ws), self.plan_ws_bytes,
+            ffn_ws_bytes, train_ws_bytes, _ptr(z), _ptr(h))
 
     def forward(self, logits, x):
         if not self._own_steps():
-            lz_layer_forward(self.shape, self._forward_buffers(), logits, x)
+            lz_layer_forward(self.shape, self._forward_buffers(self.xp, self.ffn_ws, self.ffn_ws_bytes), logits, x)
             return self.y
         self.route(logits)
         self.plan_dispatch()
@@ -575,7 +576,7 @@ class MoELayer:
     def forward_fused(self, logits, x):
         """The same pass with the reshuffle done by the first GEMM's loads (no permute call, xp unused)."""
         if not self._own_steps():
-            lz_layer_forward(self.shape, self._forward_buffers(), logits, x, True)
+            lz_layer_forward(self.shape, self._forward_buffers(None, self.ffn_ws, self.ffn_ws_bytes), logits, x, True)
             return self.y
         self.route(logits)
         self.plan_dispatch()
@@ -586,8 +587,8 @@ class MoELayer:
 
     def forward_train(self, logits, x):
         if not self._own_steps():
-            lz_layer_forward_train(self.shape, self._forward_buffers(self.train_ws, self.train_ws_bytes, self.z, self.h),
-                                   logits, x)
+            buffers = self._forward_buffers(self.xp, train_ws=self.train_ws, train_ws_bytes=self.train_ws_bytes, z=self.z, h=self.h)
+            lz_layer_forward_train(self.shape, buffers, logits, x)
             return self.y
         self.route(logits)
         self.plan_dispatch()

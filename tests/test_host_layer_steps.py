@@ -50,3 +50,25 @@ for step in {STEPS}:
         train = step != "expert_ffn"
         assert counts == [1, 1 + fused, 1 + fused + train], step
         assert launches == 5        # routing and tables in the dispatcher's launch
+
+
+def test_a_pass_asks_for_its_own_buffers_only(tmp_path):
+    """xp is not used by a fused forward, ffn_ws by no training step, the plan's other buffers by no backward."""
+    out = recorded(tmp_path, LAYER + """
+out = []
+def without(names, *passes):
+    l = layer_of()
+    l.forward_train(logits, x)
+    for n in names:
+        delattr(l, n)
+    for name, *args in passes:
+        calls()
+        getattr(l, name)(*args)
+        out.append(len(calls()))
+without(["xp", "train_ws", "z", "h"], ("forward_fused", logits, x))
+without(["train_ws", "z", "h", "dyp", "dw1_slot"], ("forward", logits, x))
+without(["ffn_ws"], ("forward_train", logits, x))
+without(["ffn_ws", "plan_ws", "row_to_pair", "slot_counts", "Tej", "D", "status", "y", "dw1_acc"], ("backward", x))
+without(["ffn_ws", "plan_ws", "dw1", "dw1_slot"], ("backward_accumulate", x))
+""")
+    assert all(out) and len(out) == 5
