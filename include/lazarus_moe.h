@@ -332,6 +332,10 @@ int32_t lz_layer_forward_train(const lz_shape* shape, const lz_layer_buffers* bu
 int32_t lz_layer_backward(const lz_shape* shape, const lz_layer_buffers* buffers, const void* dy, int32_t accumulate,
                           void* stream);
 
+/* The single call that these three stand for and that was refused when one of them last returned an error in this thread (their own name
+ * where no buffers were given).  A string of the library; "" before any refusal. */
+const char* lz_layer_refused(void);
+
 /* ---------------------------------------------------------------- host planning */
 
 /* Replica allocation, Eq. 1 (Sec. 4.1): experts in ascending load t_e (ties: lower id)

@@ -150,6 +150,7 @@ def _load():
         "lz_layer_forward": (i32, [sp, vp, vp, vp, i32, vp]),
         "lz_layer_forward_train": (i32, [sp, vp, vp, vp, vp]),
         "lz_layer_backward": (i32, [sp, vp, vp, i32, vp]),
+        "lz_layer_refused": (C.c_char_p, []),
     }
     for name, (res, args) in sig.items():
         fn = getattr(L, name)
@@ -341,19 +342,24 @@ def lz_debug_xcc_ids(xcc_of_workgroup, n_workgroups, stream=None):
 
 
 # ------------------------------------------------------------------ the whole layer in one call (buffers: a _LayerBuffers)
+def _check_layer(code):
+    if code != LZ_OK:
+        raise LzError(code, lib.lz_layer_refused().decode())
+
+
 def lz_layer_forward(shape, buffers, logits, x, fused=False, stream=None):
-    _check(lib.lz_layer_forward(shape._arg(), C.addressof(buffers), _ptr(logits), _ptr(x), fused,
-                                _stream() if stream is None else stream), "lz_layer_forward")
+    _check_layer(lib.lz_layer_forward(shape._arg(), C.addressof(buffers), _ptr(logits), _ptr(x), fused,
+                                      _stream() if stream is None else stream))
 
 
 def lz_layer_forward_train(shape, buffers, logits, x, stream=None):
-    _check(lib.lz_layer_forward_train(shape._arg(), C.addressof(buffers), _ptr(logits), _ptr(x),
-                                      _stream() if stream is None else stream), "lz_layer_forward_train")
+    _check_layer(lib.lz_layer_forward_train(shape._arg(), C.addressof(buffers), _ptr(logits), _ptr(x),
+                                            _stream() if stream is None else stream))
 
 
 def lz_layer_backward(shape, buffers, dy, accumulate=False, stream=None):
-    _check(lib.lz_layer_backward(shape._arg(), C.addressof(buffers), _ptr(dy), accumulate,
-                                 _stream() if stream is None else stream), "lz_layer_backward")
+    _check_layer(lib.lz_layer_backward(shape._arg(), C.addressof(buffers), _ptr(dy), accumulate,
+                                       _stream() if stream is None else stream))
 
 
 # ------------------------------------------------------------------ host planning

@@ -72,3 +72,48 @@ without(["ffn_ws", "plan_ws", "row_to_pair", "slot_counts", "Tej", "D", "status"
 without(["ffn_ws", "plan_ws", "dw1", "dw1_slot"], ("backward_accumulate", x))
 """)
     assert all(out) and len(out) == 5
+
+
+def test_a_refusal_names_its_step(tmp_path):
+    out = recorded(tmp_path, LAYER + """
+out = []
+def refused(name, change, *args):
+    l = layer_of()
+    if change: setattr(l, *change)
+    try:
+        getattr(l, name)(*args)
+    except lz.LzError as e:
+        out.append((str(e).split(":")[0], e.code))
+    else:
+        out.append(None)
+big = lz.Shape(64, 64, 64, 8, 9, 4, 4, lz.LZ_BF16, lz.LZ_GELU)
+for name in ("forward", "forward_fused", "forward_train"):
+    refused(name, None, None, x)
+    refused(name, ("slot_expert", None), logits, x)
+    refused(name, ("plan_ws_bytes", 64), logits, x)
+    refused(name, None, logits, None)
+    refused(name, ("train_ws_bytes" if name == "forward_train" else "ffn_ws_bytes", 64), logits, x)
+    refused(name, ("w1", None), logits, x)
+    refused(name, ("y", None), logits, x)
+    refused(name, ("shape", big), logits, x)
+for name in ("backward", "backward_accumulate"):
+    refused(name, None, None)
+    refused(name, ("w1", None), x)
+    refused(name, ("train_ws_bytes", 64), x)
+    refused(name, ("dx", None), x)
+    refused(name, ("dlogits", None), x)
+refused("backward", ("dw1", None), x)
+from paper_2407_04656_amd import binding
+out.append((binding.lib.lz_layer_forward(layer_of().shape._arg(), None, 64, 64, 0, 0), binding.lib.lz_layer_refused().decode()))
+""")
+    EINVAL, ESHAPE, EWORKSPACE = -1, -2, -3
+    want = []
+    for ffn in ("lz_expert_ffn", "lz_expert_ffn_gather", "lz_ffn_forward_train"):
+        want += [("lz_route", EINVAL), ("lz_plan_dispatch", EINVAL), ("lz_plan_dispatch", EWORKSPACE),
+                 (ffn if ffn.endswith("gather") else "lz_permute_scatter", EINVAL), (ffn, EWORKSPACE), (ffn, EINVAL),
+                 ("lz_unpermute_combine", EINVAL), ("lz_route", ESHAPE)]
+    for ffn in ("lz_ffn_backward", "lz_ffn_backward_accumulate"):
+        want += [("lz_combine_backward", EINVAL), (ffn, EINVAL), (ffn, EWORKSPACE), ("lz_permute_backward", EINVAL),
+                 ("lz_route_backward", EINVAL)]
+    want += [("lz_reduce_replica_grads_dtype", EINVAL), (EINVAL, "lz_layer_forward")]
+    assert [tuple(o) for o in out] == want
