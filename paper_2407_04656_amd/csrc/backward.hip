@@ -541,12 +541,17 @@ auto combine_kernel_of(int k, bool stream) {
                              : combine_backward_kernel<Elem, WITH, 1, false>);
 }
 
+int32_t check_combine(const void* dy, const void* yp, const int32_t* pair_to_row, const float* topk_gates, const lz_shape* shape,
+                      const void* dyp, const float* dgates) {
+  if (!lz::shape_ok(shape)) return LZ_ESHAPE;
+  return shape->T == 0 || (dy && yp && pair_to_row && topk_gates && dyp && dgates) ? LZ_OK : LZ_EINVAL;
+}
+
 template <bool WITH>
 int32_t combine_backward(const void* dy, const void* yp, const int32_t* pair_to_row, const float* topk_gates, const lz_shape* shape,
                          void* dyp, float* dgates, const CombineExtra<WITH>& with, hipStream_t st) {
-  if (!lz::shape_ok(shape)) return LZ_ESHAPE;
-  if (shape->T == 0) return LZ_OK;
-  if (!dy || !yp || !pair_to_row || !topk_gates || !dyp || !dgates) return LZ_EINVAL;
+  const int32_t rc = check_combine(dy, yp, pair_to_row, topk_gates, shape, dyp, dgates);
+  if (rc != LZ_OK || shape->T == 0) return rc;
   const long long P = (long long)shape->T * shape->k;
   int tokens = kTokensAlone, first = 0;
   if constexpr (WITH) tokens = with.tokens, first = with.tables.n;
@@ -580,6 +585,8 @@ extern "C" int32_t lz_combine_backward(const void* dy, const void* yp, const int
 int32_t lz::combine_backward_with(const void* dy, const lz_shape* shape, const lz_layer_buffers& b, bool gate, const TileSpecs& tables,
                                   void* stream) {
   if (!gate && tables.n == 0) return lz_combine_backward(dy, b.yp, b.pair_to_row, b.topk_gates, shape, b.dyp, b.dgates, stream);
+  const int32_t rc = check_combine(dy, b.yp, b.pair_to_row, b.topk_gates, shape, b.dyp, b.dgates);
+  if (rc != LZ_OK) return rc;
   const int workgroups = device_cus();
   if (workgroups == 0) return LZ_EHIP;
   // Four tokens a workgroup while that gives no CU a second one: us for 225 tokens, top-8, 3944 bf16 columns 29 with eight, 21 with

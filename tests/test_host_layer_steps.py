@@ -117,3 +117,22 @@ out.append((binding.lib.lz_layer_forward(layer_of().shape._arg(), None, 64, 64, 
                  ("lz_route_backward", EINVAL)]
     want += [("lz_reduce_replica_grads_dtype", EINVAL), (EINVAL, "lz_layer_forward")]
     assert [tuple(o) for o in out] == want
+
+
+def test_a_call_is_refused_before_the_device_is_asked_for():
+    """Bad arguments are that on a host without a GPU too, as the calls by themselves have it."""
+    import paper_2407_04656_amd as lz
+    from paper_2407_04656_amd import binding
+
+    class At:
+        def __init__(self, address): self.address = address
+        def data_ptr(self): return self.address
+        def is_contiguous(self): return True
+    fields = {n: 1 << 20 for n, _ in binding._LayerBuffers._fields_}
+    for k, missing, want in ((9, None, -2), (2, "yp", -1), (2, "dgates", -1)):
+        shape = lz.Shape(64, 64, 64, 8, k, 4, 4, lz.LZ_BF16, lz.LZ_GELU)
+        buffers = binding._LayerBuffers(**{n: v for n, v in fields.items() if n != missing})
+        buffers.train_ws_bytes = lz.lz_train_workspace_bytes(shape)
+        with pytest.raises(lz.LzError) as e:
+            binding.lz_layer_backward(shape, buffers, At(1 << 20), stream=0)
+        assert (e.value.code, str(e.value).split(":")[0]) == (want, "lz_combine_backward")
