@@ -394,17 +394,26 @@ MfmaArgs wgrad_args(const uint16_t* A, const uint16_t* W, uint16_t* C, float* Ca
   return g;
 }
 
-// pair: one launch for both, of a whole backward pass.  The second's tiles fill what the first's last round leaves idle, and where
+// 32-bit byte offsets do if no operand reaches 4 GiB, the K steps past a slot's end included
+inline bool wgrad_is_wide(long long P, int lda, int ldw) {
+  return ((unsigned long long)P + 4 * BK) * (unsigned)(lda > ldw ? lda : ldw) * 2ull > 0xFFFFFFFFull;
+}
+
+// Whether a whole pass has both weight gradients in one launch.  The second's tiles fill what the first's last round leaves idle, and where
 // tiles are few they run side by side: a training step of 73 tokens over 33 slots, 768 x 2240, 318 -> 302 us, of 40960 tokens, top-1,
-// 768 x 3072, over 60 slots 1691 -> 1673.
+// 768 x 3072, over 60 slots 1691 -> 1673.  Backward passes of 2573 drawn layers, geometric mean by the rounds of 256 x 256 tiles of both:
+// below 1 round 0.87 of two launches' time, to 4 0.93, 16 0.96, 32 0.99, and from there on, with 128 rows a slot and more, 0.994; with
+// fewer 0.999, at the worst 1.024 (276 tokens, 42 slots, 1920 x 3136; 429 tokens over 50 slots, 3072 x 3840, 1.007): two launches.
+inline bool pair_wgrads(const lz_shape* s) {
+  const long long P = (long long)s->T * s->k, slots = (long long)s->N * s->c;
+  const int n1 = s->act == LZ_SWIGLU ? 2 * s->ffn : s->ffn;
+  const long long tiles = slots * ceil_div(s->d, BN) * (ceil_div(s->ffn, BM) + ceil_div(n1, BN));
+  return (tiles < 32ll * device_cus() || P >= 128 * slots) && !wgrad_is_wide(P, s->ffn, s->d) && !wgrad_is_wide(P, s->d, n1);
+}
 int32_t gemm_wgrads(const MfmaArgs& g0, const MfmaArgs& g1, long long P, bool accumulate, bool pair, hipStream_t st) {
-  // 32-bit byte offsets do if no operand reaches 4 GiB, the K steps past a slot's end included
-  auto wide = [&](const MfmaArgs& g) {
-    return ((unsigned long long)P + 4 * BK) * (unsigned)(g.lda > g.ldw ? g.lda : g.ldw) * 2ull > 0xFFFFFFFFull;
-  };
-  if (pair && !wide(g0) && !wide(g1)) return accumulate ? launch_mfma_pair<EPI_ACCUM>(g0, g1, st) : launch_mfma_pair<EPI_NONE>(g0, g1, st);
+  if (pair) return accumulate ? launch_mfma_pair<EPI_ACCUM>(g0, g1, st) : launch_mfma_pair<EPI_NONE>(g0, g1, st);
   auto one = [&](const MfmaArgs& g) {
-    if (wide(g)) return accumulate ? launch_mfma<EPI_ACCUM, MODE_TN_WIDE>(g, st) : launch_mfma<EPI_NONE, MODE_TN_WIDE>(g, st);
+    if (wgrad_is_wide(P, g.lda, g.ldw)) return accumulate ? launch_mfma<EPI_ACCUM, MODE_TN_WIDE>(g, st) : launch_mfma<EPI_NONE, MODE_TN_WIDE>(g, st);
     return accumulate ? launch_mfma<EPI_ACCUM, MODE_TN>(g, st) : launch_mfma<EPI_NONE, MODE_TN>(g, st);
   };
   const int32_t r = one(g0);
@@ -609,7 +618,7 @@ extern "C" int32_t lz_route_backward(const float* dgates, const float* topk_gate
 
 namespace {
 
-TileSpecs backward_tables(const TrainWorkspace& w, const lz_shape* shape, bool accumulate) {
+TileSpecs backward_tables(const TrainWorkspace& w, const lz_shape* shape, bool accumulate, bool pair) {
   const long long P = (long long)shape->T * shape->k;
   const int S = shape->N * shape->c, d = shape->d, ffn = shape->ffn;
   const int n_ffn = ceil_div(ffn, BN), n_d = ceil_div(d, BN), n_n1 = ceil_div(w.n1, BN);
@@ -618,6 +627,7 @@ TileSpecs backward_tables(const TrainWorkspace& w, const lz_shape* shape, bool a
   if (!w.narrow_d) add_units(specs, n_d, 0, P, carve_units(w.units_d, P, S, n_d));
   add_units(specs, n_d, ffn, P, carve_units(w.units_w2, (long long)S * ffn, S, n_d), accumulate);
   add_units(specs, n_n1, d, P, carve_units(w.units_w1, (long long)S * d, S, n_n1), accumulate);
+  if (pair) share_launch(specs);
   if (w.narrow_ffn || w.narrow_d) add_rows(specs, kNarrow, P, narrow_tiles(w, S, P));
   return specs;
 }
@@ -631,7 +641,7 @@ TileSpecs lz::backward_tables(const lz_shape* shape, const void* const* tensors,
   if (!lz::shape_ok(shape) || shape->N * shape->c > kTableSlots || shape->T == 0) return TileSpecs{};
   if (on_mfma(shape, aligned)) {
     TrainWorkspace w;
-    return check_train(shape, ws, ws_bytes, &w) == LZ_OK ? ::backward_tables(w, shape, accumulate) : TileSpecs{};
+    return check_train(shape, ws, ws_bytes, &w) == LZ_OK ? ::backward_tables(w, shape, accumulate, pair_wgrads(shape)) : TileSpecs{};
   }
   GenericTrainWorkspace w;
   F32Args a{};
@@ -676,7 +686,8 @@ int32_t lz::ffn_backward(const void* dyp, const void* xp, const void* z, const v
   const long long rows_w2 = (long long)S * ffn, rows_w1 = (long long)S * d;
   const UnitTable u_ffn = carve_units(w.units_ffn, P, S, n_ffn), u_d = carve_units(w.units_d, P, S, n_d);
   const UnitTable u_w2 = carve_units(w.units_w2, rows_w2, S, n_d), u_w1 = carve_units(w.units_w1, rows_w1, S, n_n1);
-  int32_t r = tables_built ? LZ_OK : launch_build_tiles(slot_offsets, S, ::backward_tables(w, shape, accumulate), st);
+  const bool pair = in_pass && pair_wgrads(shape);
+  int32_t r = tables_built ? LZ_OK : launch_build_tiles(slot_offsets, S, ::backward_tables(w, shape, accumulate, pair), st);
   if (r != LZ_OK) return r;
 
   if (P > 0) {
@@ -701,7 +712,7 @@ int32_t lz::ffn_backward(const void* dyp, const void* xp, const void* z, const v
                                 accumulate ? (float*)dw2 : nullptr, S, ffn, d, u_w2),
                      wgrad_args((const uint16_t*)xp, w.dz, accumulate ? none : (uint16_t*)dw1, accumulate ? (float*)dw1 : nullptr, S, d,
                                 n1, u_w1),
-                     P, accumulate, in_pass, st);
+                     P, accumulate, pair, st);
 }
 
 extern "C" int32_t lz_ffn_backward(const void* dyp, const void* xp, const void* z, const void* h,

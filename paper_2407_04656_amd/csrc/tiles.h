@@ -81,6 +81,7 @@ struct TileSpec {
   int n_tiles;       // column tiles; 0: row tiles for `rows`, else units for `units`
   int virtual_rows;  // > 0: every slot has this many rows (weight gradients)
   bool skip_empty;   // those of slots without rows of the batch have no units: nothing is added to their sums
+  int with_tiles, with_rows;  // > 0: n_tiles and virtual_rows of a list that shares this one's launch
   long long P;       // rows of the batch
   TileTable rows;
   UnitTable units;
@@ -90,10 +91,16 @@ struct TileSpecs {
   int n;
 };
 inline void add_rows(TileSpecs& specs, int rows, long long P, const TileTable& t) {
-  specs.spec[specs.n++] = TileSpec{rows, 0, 0, false, P, t, UnitTable{}};
+  specs.spec[specs.n++] = TileSpec{rows, 0, 0, false, 0, 0, P, t, UnitTable{}};
 }
 inline void add_units(TileSpecs& specs, int n_tiles, int virtual_rows, long long P, const UnitTable& u, bool skip_empty = false) {
-  specs.spec[specs.n++] = TileSpec{0, n_tiles, virtual_rows, skip_empty, P, TileTable{}, u};
+  specs.spec[specs.n++] = TileSpec{0, n_tiles, virtual_rows, skip_empty, 0, 0, P, TileTable{}, u};
+}
+// The two lists added last share a launch.
+inline void share_launch(TileSpecs& specs) {
+  TileSpec &a = specs.spec[specs.n - 2], &b = specs.spec[specs.n - 1];
+  a.with_tiles = b.n_tiles, a.with_rows = b.virtual_rows;
+  b.with_tiles = a.n_tiles, b.with_rows = a.virtual_rows;
 }
 
 }  // namespace lz
@@ -178,31 +185,43 @@ __device__ __forceinline__ void deal_units(const SlotRows<SLOTS>& slots, int S, 
 // 2.2 rounds of them (the down projection of 40960 tokens over 60 slots, 3072 x 768) 192 rows make 2.9 shorter ones:
 // that training step 1743 -> 1706 us, a forward of 3001 tokens (12 slots, 1000 x 2664, SwiGLU) 197 -> 186.
 // A row's result does not depend on the tile it is in.
+// Two lists that share a launch get the rows that suit their sum: what one's last round leaves idle the other fills.  Backward
+// passes of 1093 drawn layers below 1, 4 and 16 rounds of both weight gradients, with rows that suit each list alone 0.918, 0.939 and 0.966
+// of two launches' time, with these 0.863, 0.925 and 0.961, none above 1.  Of 895 that accumulate 9 are above 1.01 (36 before), those of
+// a K step and short launches: what the costs are measured on is long ones.  Worst: 97 tokens, top-2, 11 slots, 768 x 768, 53 -> 62 us.
 __device__ __forceinline__ int tile_cost(int n64) { return int(0x6452413200ull >> (8 * n64)) & 255; }  // by rows in 64s
 // Of a table's 512 threads each wave leaves one sum in s_sum: tiles (wave w < 4) or cost of tiles of 64 (w % 4 + 1) rows.
+// rows_of(slot, virtual rows of the list)
 template <typename RowsOf>
-__device__ __forceinline__ void sum_tile_costs(int S, int tid, unsigned* s_sum, RowsOf rows_of) {
+__device__ __forceinline__ void sum_tile_costs(const TileSpec& spec, int S, int tid, unsigned* s_sum, RowsOf rows_of) {
   const int lane = tid % lz::kWave, wave = __builtin_amdgcn_readfirstlane(tid / lz::kWave), n64 = wave % 4 + 1;
   static_assert(kTileWaves == 8, "a wave per sum");
-  unsigned sum = 0;
-  for (int s = lane; s < S; s += lz::kWave) {
-    const int all64 = (int)(((unsigned)rows_of(s) + 63) / 64), full = n64 == 3 ? all64 / 3 : all64 >> (n64 / 2), tail = all64 - full * n64;
-    sum += wave < 4 ? full + (tail > 0 ? 1 : 0) : full * tile_cost(n64) + tile_cost(tail);
-  }
+  auto sum_of = [&](int virtual_rows) {
+    unsigned sum = 0;
+    for (int s = lane; s < S; s += lz::kWave) {
+      const int all64 = (int)(((unsigned)rows_of(s, virtual_rows) + 63) / 64), full = n64 == 3 ? all64 / 3 : all64 >> (n64 / 2),
+                tail = all64 - full * n64;
+      sum += wave < 4 ? full + (tail > 0 ? 1 : 0) : full * tile_cost(n64) + tile_cost(tail);
+    }
+    return sum;
+  };
+  unsigned sum = spec.n_tiles * sum_of(spec.virtual_rows);
+  if (spec.with_tiles > 0) sum += spec.with_tiles * sum_of(spec.with_rows);
   sum = lz::wave_scan(sum, [](int x, int y) { return (int)((unsigned)x + (unsigned)y); });
   if (lane == lz::kWave - 1) s_sum[wave] = sum;
 }
 __device__ __forceinline__ bool many_rounds(int S, const TileSpec& spec, int workgroups) {
   const float rows = spec.virtual_rows > 0 ? (float)S * (float)spec.virtual_rows : (float)spec.P;
-  return rows / 256.f * (float)spec.n_tiles > 16.f * (float)workgroups;
+  const float tiles = rows / 256.f * (float)spec.n_tiles + (float)S * (float)spec.with_rows / 256.f * (float)spec.with_tiles;
+  return tiles > 16.f * (float)workgroups;
 }
-__device__ __forceinline__ int choose_tile_rows(const TileSpec& spec, int workgroups, const unsigned* s_sum) {
-  const float n_tiles = (float)spec.n_tiles, one_round = (float)workgroups;
+__device__ __forceinline__ int choose_tile_rows(int workgroups, const unsigned* s_sum) {
+  const float one_round = (float)workgroups;
   int best = 256;
   float best_time = 0.f;
 #pragma unroll
   for (int c = 3; c >= 0; --c) {
-    const float n = (float)s_sum[c], rounds = ceilf(n * n_tiles / one_round);
+    const float n = (float)s_sum[c], rounds = ceilf(n / one_round);
     const float time = n > 0.f ? rounds * (float)s_sum[4 + c] / n : 0.f;
     if (c == 3 || time < 0.95f * best_time) {
       best = 64 * (c + 1);
@@ -230,14 +249,14 @@ __device__ __forceinline__ void build_table(const TileSpec& spec, bool idle, con
   const int lane = tid % lz::kWave, wave = __builtin_amdgcn_readfirstlane(tid / lz::kWave);
   // Without skip_empty the sums of empty slots are read and written back: two micro-batches of 50 rows on 90 slots,
   // 768 x 1792, 1423 us a step, 927 with it.
-  auto rows_of = [&](int s) {
+  auto rows_of = [&](int s, int virtual_rows) {
     const int own = slots.end[s] - slots.first[s];
-    return spec.virtual_rows > 0 && (own > 0 || !spec.skip_empty) ? spec.virtual_rows : own;
+    return virtual_rows > 0 && (own > 0 || !spec.skip_empty) ? virtual_rows : own;
   };
   const bool choose = units && !many_rounds(S, spec, workgroups);
-  if (choose) sum_tile_costs(S, tid, scratch.sum, rows_of);
+  if (choose) sum_tile_costs(spec, S, tid, scratch.sum, rows_of);
   __syncthreads();
-  const int rows = !units ? spec.rows_per_tile : choose ? choose_tile_rows(spec, workgroups, scratch.sum) : 256;
+  const int rows = !units ? spec.rows_per_tile : choose ? choose_tile_rows(workgroups, scratch.sum) : 256;
   const unsigned group_rows = units ? rows * kGroupM : rows;
   // tile or group count of every slot and its exclusive sum: each thread owns a run of consecutive slots.  The sums
   // end at the table's capacity, which the slots of ascending offsets stay within: offsets that fall again make
@@ -246,7 +265,7 @@ __device__ __forceinline__ void build_table(const TileSpec& spec, bool idle, con
   const int per = (S + kTileThreads - 1) / kTileThreads, first = tid * per;
   int mine = 0;
   for (int s = first; s < first + per && s < S; ++s) {
-    const int tiles = int(((unsigned)rows_of(s) + group_rows - 1) / group_rows);
+    const int tiles = int(((unsigned)rows_of(s, spec.virtual_rows) + group_rows - 1) / group_rows);
     scratch.first[s] = mine;
     mine = add(mine, tiles < capacity ? tiles : capacity);
   }
