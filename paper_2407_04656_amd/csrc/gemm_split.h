@@ -375,10 +375,20 @@ int32_t launch_f32_wgrad(const F32Wgrad& g, hipStream_t st) {
   return launch_f32<Elem, EPI, true, true>(g.a, rows, rows, st);
 }
 
-// Both of a backward pass; pair: in one launch where one kernel serves both, see gemm_wgrads() of the bf16 kernels.
+// Both of a backward pass; in_pass: as part of a whole one, in one launch where one kernel serves both and that is no slower.  Backward
+// passes of 1350 drawn fp32 layers, geometric mean and worst against two launches, by rounds of the chip's workgroups: split
+// kernel and four waves side by side up to 48 rounds 0.96, 1.013, past them 1.002, 1.018; one wave, up to 512 rows a slot 0.94, 1.0;
+// more rows, up to 1.5 rounds 0.88, 1.014, above 0.99, 1.072 (22074 tokens, top-4, 22 slots, 192 x 384 719 -> 771 us: a workgroup's tiles
+// are fixed, and the few that are left over for a last round are long).
+inline bool pair_f32_wgrads(const F32Wgrad& g0, const F32Wgrad& g1) {
+  if (g0.split != g1.split || g0.vec != g1.vec || (!g0.split && g0.nw != g1.nw)) return false;
+  const long long tiles = g0.tiles + g1.tiles, resident = g0.split ? 2ll * device_cus() : f32_resident(g0.nw);
+  if (!g0.split && g0.nw == 1 && g0.a.P >= 512ll * g0.a.slots) return 2 * tiles <= 3 * resident;
+  return tiles <= 48 * resident;
+}
 template <typename Elem, int EPI>
-int32_t launch_f32_wgrads(const F32Wgrad& g0, const F32Wgrad& g1, bool pair, hipStream_t st) {
-  if (pair && g0.split == g1.split && g0.vec == g1.vec && (g0.split || g0.nw == g1.nw)) {
+int32_t launch_f32_wgrads(const F32Wgrad& g0, const F32Wgrad& g1, bool in_pass, hipStream_t st) {
+  if (in_pass && pair_f32_wgrads(g0, g1)) {
     const F32Launch<true> both{{g0.a, g1.a}};
     const long long tiles = g0.tiles + g1.tiles, resident = g0.split ? 2ll * device_cus() : f32_resident(g0.nw);
     if (resident == 0) return LZ_EHIP;
