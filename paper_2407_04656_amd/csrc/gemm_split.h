@@ -61,7 +61,7 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(F32Launch<PAIR> laun
   const long long n_all = n_first + (PAIR ? F32Launch<PAIR>::tiles(args[PAIR ? 1 : 0]) : 0);
   for (long long t = blockIdx.x; t < n_all; t += gridDim.x) {
     const int part = PAIR && t >= n_first ? 1 : 0;
-    const F32Args& a = args[part];
+    const F32Args a = PAIR && part ? args[PAIR ? 1 : 0] : args[0];  // by value, as in gemm_f32_kernel
     const long long tile = t - (part ? n_first : 0);
     // The empty asm keeps the per-lane address arithmetic inside the tile: hoisted out of the loop it would be carried in
     // registers through the stages and spill.
@@ -375,20 +375,15 @@ int32_t launch_f32_wgrad(const F32Wgrad& g, hipStream_t st) {
   return launch_f32<Elem, EPI, true, true>(g.a, rows, rows, st);
 }
 
-// Both of a backward pass; in_pass: as part of a whole one, in one launch where one kernel serves both and that is no slower.  Backward
-// passes of 1350 drawn fp32 layers, geometric mean and worst against two launches, by rounds of the chip's workgroups: split
-// kernel and four waves side by side up to 48 rounds 0.96, 1.013, past them 1.002, 1.018; one wave, up to 512 rows a slot 0.94, 1.0;
-// more rows, up to 1.5 rounds 0.88, 1.014, above 0.99, 1.072 (22074 tokens, top-4, 22 slots, 192 x 384 719 -> 771 us: a workgroup's tiles
-// are fixed, and the few that are left over for a last round are long).
-inline bool pair_f32_wgrads(const F32Wgrad& g0, const F32Wgrad& g1) {
-  if (g0.split != g1.split || g0.vec != g1.vec || (!g0.split && g0.nw != g1.nw)) return false;
-  const long long tiles = g0.tiles + g1.tiles, resident = g0.split ? 2ll * device_cus() : f32_resident(g0.nw);
-  if (!g0.split && g0.nw == 1 && g0.a.P >= 512ll * g0.a.slots) return 2 * tiles <= 3 * resident;
-  return tiles <= 48 * resident;
-}
+// Both of a backward pass; in_pass: as part of a whole one, in one launch where one kernel serves both.  Backward passes of 2700 drawn
+// fp32 layers, whole pieces and odd sizes, half of them with skewed loads, geometric mean and worst of two launches' time: 32-column tiles of
+// slots of under 512 rows 0.94 and 1.01, of 128 columns and split 0.96 and 1.01 (past 16 rounds of the chip's workgroups 0.99).  Slots of
+// more rows on 32-column tiles: below 1.5 rounds 0.89, 1.02, above 0.95, from 0.73 (12715 tokens, top-3, 36 slots, 120 x 256,
+// 388 -> 282 us) to 1.08 (11952, top-6, 36 slots, 216 x 192, 629 -> 681): a workgroup's tiles are fixed, and which of them get two
+// of the fullest slot's is luck with one launch and with two.
 template <typename Elem, int EPI>
 int32_t launch_f32_wgrads(const F32Wgrad& g0, const F32Wgrad& g1, bool in_pass, hipStream_t st) {
-  if (in_pass && pair_f32_wgrads(g0, g1)) {
+  if (in_pass && g0.split == g1.split && g0.vec == g1.vec && (g0.split || g0.nw == g1.nw)) {
     const F32Launch<true> both{{g0.a, g1.a}};
     const long long tiles = g0.tiles + g1.tiles, resident = g0.split ? 2ll * device_cus() : f32_resident(g0.nw);
     if (resident == 0) return LZ_EHIP;

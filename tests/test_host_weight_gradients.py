@@ -7,11 +7,8 @@ CASES = [
     ((500, 2048, 3840, 8, 2, 4, 8, 1, 0), 1), ((500, 2048, 4096, 8, 2, 4, 8, 1, 0), 2),     # 7680 and 8192 tiles of 256 x 256
     ((2048, 2048, 4096, 8, 2, 4, 8, 1, 0), 1), ((2047, 2048, 4096, 8, 2, 4, 8, 1, 0), 2),   # 128 rows a slot
     ((261887, 64, 8192, 1, 1, 1, 1, 1, 0), 1), ((261888, 64, 8192, 1, 1, 1, 1, 1, 0), 2),   # an operand of 4 GiB
-    ((22074, 192, 384, 5, 4, 11, 2, 0, 0), 2),
-    ((11263, 192, 384, 5, 1, 11, 2, 0, 0), 1), ((11264, 192, 384, 5, 1, 11, 2, 0, 0), 2),   # 512 rows a slot
-    ((20000, 192, 384, 5, 1, 10, 1, 0, 0), 1), ((20000, 192, 384, 5, 1, 11, 1, 0, 0), 2),   # 1440 and 1584 tiles of 32 x 32
-    ((500, 1024, 1024, 8, 2, 9, 8, 0, 0), 1), ((500, 1024, 1024, 8, 2, 10, 8, 0, 0), 2),    # 36864 and 40960 of 32 x 128
-    ((8000, 512, 2048, 8, 2, 12, 8, 0, 0), 1), ((16000, 512, 2048, 8, 2, 13, 16, 0, 0), 2),  # 24576 and 53248 of 64 x 128
+    ((22074, 192, 384, 5, 4, 11, 2, 0, 0), 1), ((14091, 137, 128, 60, 1, 2, 32, 0, 1), 1),  # fp32 kernel: one wave, by elements,
+    ((500, 1024, 1024, 8, 2, 10, 8, 0, 0), 1), ((16000, 512, 2048, 8, 2, 13, 16, 0, 0), 1),   # four side by side, split
     ((300, 112, 128, 62, 3, 10, 11, 0, 1), 2),                                              # kernels of their own
 ]
 
