@@ -627,7 +627,9 @@ TileSpecs backward_tables(const TrainWorkspace& w, const lz_shape* shape, bool a
   if (!w.narrow_d) add_units(specs, n_d, 0, P, carve_units(w.units_d, P, S, n_d));
   add_units(specs, n_d, ffn, P, carve_units(w.units_w2, (long long)S * ffn, S, n_d), accumulate);
   add_units(specs, n_n1, d, P, carve_units(w.units_w1, (long long)S * d, S, n_n1), accumulate);
-  if (pair) share_launch(specs);
+  // Longer slots keep the rows that suit each list: there the tiles of the fullest slot, which few rows make short, end last (30617 tokens,
+  // top-2, over 66 slots of unlike loads, 256 x 256: a training step 484 us with rows for both, 435).
+  if (pair && P < 128ll * S) share_launch(specs);
   if (w.narrow_ffn || w.narrow_d) add_rows(specs, kNarrow, P, narrow_tiles(w, S, P));
   return specs;
 }

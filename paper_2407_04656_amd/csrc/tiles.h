@@ -185,10 +185,11 @@ __device__ __forceinline__ void deal_units(const SlotRows<SLOTS>& slots, int S, 
 // 2.2 rounds of them (the down projection of 40960 tokens over 60 slots, 3072 x 768) 192 rows make 2.9 shorter ones:
 // that training step 1743 -> 1706 us, a forward of 3001 tokens (12 slots, 1000 x 2664, SwiGLU) 197 -> 186.
 // A row's result does not depend on the tile it is in.
-// Two lists that share a launch get the rows that suit their sum: what one's last round leaves idle the other fills.  Backward
-// passes of 1093 drawn layers below 1, 4 and 16 rounds of both weight gradients, with rows that suit each list alone 0.918, 0.939 and 0.966
-// of two launches' time, with these 0.863, 0.925 and 0.961, none above 1.  Of 895 that accumulate 9 are above 1.01 (36 before), those of
-// a K step and short launches: what the costs are measured on is long ones.  Worst: 97 tokens, top-2, 11 slots, 768 x 768, 53 -> 62 us.
+// Two lists that share a launch (with_tiles) get the rows that suit their sum: what one's last round leaves idle the other fills.  Backward
+// passes of some 550 drawn layers of up to 128 rows a slot, below 1, 4 and 16 rounds of both weight gradients, with rows that suit each
+// list alone 0.93, 0.95 and 0.97 of two launches' time, with these 0.89, 0.93 and 0.96, none above 1.005.  Accumulating passes of one K step and
+// a round or two: 9 of 300 are above 1.01 (28 before): the costs are those of longer loops.  Worst: 97 tokens, top-2, 11 slots,
+// 768 x 768, 53 -> 62 us.
 __device__ __forceinline__ int tile_cost(int n64) { return int(0x6452413200ull >> (8 * n64)) & 255; }  // by rows in 64s
 // Of a table's 512 threads each wave leaves one sum in s_sum: tiles (wave w < 4) or cost of tiles of 64 (w % 4 + 1) rows.
 // rows_of(slot, virtual rows of the list)
