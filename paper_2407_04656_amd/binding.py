@@ -528,13 +528,13 @@ class MoELayer:
 
     # The passes below are one call each, which takes the addresses of the buffers as they are now.  A layer with steps of its
     # own (a subclass's, set on the object, or put in this class's place) keeps to them.
-    _STEPS = dict(route=route, plan_dispatch=plan_dispatch, permute=permute, expert_ffn=expert_ffn,
-                  unpermute_combine=unpermute_combine)
+    _NAMES = frozenset(("route", "plan_dispatch", "permute", "expert_ffn", "unpermute_combine"))
+    _STEPS = (route, plan_dispatch, permute, expert_ffn, unpermute_combine)
 
     def _own_steps(self):
         cls = type(self)
-        return not self._STEPS.keys().isdisjoint(self.__dict__) or any(
-            getattr(cls, n) is not step for n, step in self._STEPS.items())
+        return (cls.route, cls.plan_dispatch, cls.permute, cls.expert_ffn, cls.unpermute_combine) != self._STEPS or (
+            not self._NAMES.isdisjoint(self.__dict__))
 
     def _forward_buffers(self, xp, ffn_ws=None, ffn_ws_bytes=0, train_ws=None, train_ws_bytes=0, z=None, h=None):
         """Those of every forward, and what this one uses: a buffer that a program has given up is not asked for by the others."""
