@@ -753,7 +753,7 @@ int32_t reduce_vectors(const void* dw_slot0, int64_t elems0, void* dw0, const vo
 int32_t lz::reduce_pair(const lz_shape* s, const lz_layer_buffers& b, int64_t elems1, int64_t elems2, void* stream) {
   const int S = s->N * s->c, per = s->dtype == LZ_F32 ? 4 : 8;
   const bool whole = elems1 % per == 0 && elems2 % per == 0 && aligned16(b.dw1_slot) && aligned16(b.dw2_slot) && aligned16(b.dw1) &&
-                     aligned16(b.dw2) && (elems1 + elems2) / per / 256 < 0x7FFFFFF0ll;
+                     aligned16(b.dw2) && (elems1 + elems2) / per + 512 < 1ll << 32;  // a grid's threads in x
   if (whole && b.dw1_slot && b.dw2_slot && b.dw1 && b.dw2 && b.slot_expert)
     return s->dtype == LZ_F32
                ? reduce_vectors<float>(b.dw1_slot, elems1, b.dw1, b.dw2_slot, elems2, b.dw2, b.slot_expert, S, s->E, stream)

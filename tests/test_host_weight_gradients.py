@@ -28,3 +28,19 @@ for case in {[s for s, _ in CASES]}:
     for i, (case, want) in enumerate(CASES):
         for rc, gemms in out[2 * i:2 * i + 2]:
             assert rc == 0 and len(gemms) == 2 + want, (case, rc, gemms)        # with those of dH and dxp
+
+
+def test_sums_that_one_grid_cannot_hold_are_two_launches(tmp_path):
+    """A grid has fewer than 2^32 threads in x, a 16-byte piece each: slots of 2^31 pieces a matrix fit one by one."""
+    out = recorded(tmp_path, """
+from paper_2407_04656_amd.binding import _LayerBuffers, lz_layer_backward
+out = []
+for d in ((1 << 17) - 64, 1 << 17):
+    s = lz.Shape(1, d, 1 << 17, 1, 1, 1, 1, lz.LZ_BF16, lz.LZ_GELU)
+    b = _LayerBuffers(**{n: 1 << 20 for n, t in _LayerBuffers._fields_})
+    b.train_ws_bytes = lz.lz_train_workspace_bytes(s)
+    rc = code(lz_layer_backward, s, b, At(1 << 20))
+    out.append((rc, [int(c.split()[3]) for c in calls() if "reduce_replicas" in c]))
+""")
+    for (rc, threads), launches in zip(out, (1, 2)):
+        assert rc == 0 and len(threads) == launches and all(n < 2 ** 32 for n in threads), (rc, threads)
