@@ -453,11 +453,9 @@ TileSpecs forward_tables(const TrainWorkspace& w, const lz_shape* shape) {
 
 }  // namespace
 
-TileSpecs lz::train_tables(const lz_shape* shape, const void* const* tensors, int n_tensors, void* ws, size_t ws_bytes) {
-  bool aligned = true;
-  for (int i = 0; i < n_tensors; ++i) aligned = aligned && aligned16(tensors[i]);
+TileSpecs lz::train_tables(const lz_shape* shape, const FfnTrain& t, void* ws, size_t ws_bytes) {
   if (!lz::shape_ok(shape) || (long long)shape->T * shape->k == 0) return TileSpecs{};
-  if (on_mfma(shape, aligned)) {
+  if (on_mfma(shape, t.aligned())) {
     TrainWorkspace w;
     return check_train(shape, ws, ws_bytes, &w) == LZ_OK ? forward_tables(w, shape) : TileSpecs{};
   }
@@ -467,9 +465,10 @@ TileSpecs lz::train_tables(const lz_shape* shape, const void* const* tensors, in
   return generic_tables(a, shape->N * shape->c, (long long)shape->T * shape->k, w, split_forward(shape));
 }
 
-int32_t lz::ffn_forward_train(const void* xp, const int32_t* slot_offsets, const void* w1, const void* w2, const lz_shape* shape,
-                              void* z, void* h, void* yp, void* ws, size_t ws_bytes, bool tables_built, void* stream) {
-  const bool aligned = aligned16(z) && aligned16(h) && aligned16(yp) && aligned16(xp) && aligned16(w1) && aligned16(w2);
+int32_t lz::ffn_forward_train(const lz_shape* shape, const FfnTrain& t, const int32_t* slot_offsets, void* ws, size_t ws_bytes,
+                              bool tables_built, void* stream) {
+  const auto [xp, w1, w2, z, h, yp] = t;
+  const bool aligned = t.aligned();
   if (!on_mfma(shape, aligned)) {
     GenericTrainWorkspace gw;
     const int32_t grc = check_train_generic(shape, ws, ws_bytes, &gw);
@@ -520,7 +519,7 @@ int32_t lz::ffn_forward_train(const void* xp, const int32_t* slot_offsets, const
 extern "C" int32_t lz_ffn_forward_train(const void* xp, const int32_t* slot_offsets, const void* w1, const void* w2,
                                         const lz_shape* shape, void* z, void* h, void* yp, void* ws,
                                         size_t ws_bytes, void* stream) {
-  return lz::ffn_forward_train(xp, slot_offsets, w1, w2, shape, z, h, yp, ws, ws_bytes, false, stream);
+  return lz::ffn_forward_train(shape, lz::FfnTrain{xp, w1, w2, z, h, yp}, slot_offsets, ws, ws_bytes, false, stream);
 }
 
 namespace {
@@ -636,12 +635,9 @@ TileSpecs backward_tables(const TrainWorkspace& w, const lz_shape* shape, bool a
 
 }  // namespace
 
-TileSpecs lz::backward_tables(const lz_shape* shape, const void* const* tensors, int n_tensors, void* ws, size_t ws_bytes,
-                              bool accumulate) {
-  bool aligned = true;
-  for (int i = 0; i < n_tensors; ++i) aligned = aligned && aligned16(tensors[i]);
+TileSpecs lz::backward_tables(const lz_shape* shape, const FfnBackward& t, void* ws, size_t ws_bytes, bool accumulate) {
   if (!lz::shape_ok(shape) || shape->N * shape->c > kTableSlots || shape->T == 0) return TileSpecs{};
-  if (on_mfma(shape, aligned)) {
+  if (on_mfma(shape, t.aligned())) {
     TrainWorkspace w;
     return check_train(shape, ws, ws_bytes, &w) == LZ_OK ? ::backward_tables(w, shape, accumulate, pair_wgrads(shape)) : TileSpecs{};
   }
@@ -652,11 +648,10 @@ TileSpecs lz::backward_tables(const lz_shape* shape, const void* const* tensors,
 }
 
 // dw1 / dw2 are bf16 gradients (accumulate == false: overwritten) or fp32 sums (accumulate == true: added to)
-int32_t lz::ffn_backward(const void* dyp, const void* xp, const void* z, const void* h, const int32_t* slot_offsets,
-                         const void* w1, const void* w2, const lz_shape* shape, void* dxp, void* dw1, void* dw2,
-                         bool accumulate, void* ws, size_t ws_bytes, bool tables_built, bool in_pass, void* stream) {
-  const bool aligned = aligned16(dyp) && aligned16(xp) && aligned16(z) && aligned16(h) && aligned16(dxp) &&
-                       aligned16(w1) && aligned16(w2) && aligned16(dw1) && aligned16(dw2);
+int32_t lz::ffn_backward(const lz_shape* shape, const FfnBackward& t, const int32_t* slot_offsets, bool accumulate, void* ws,
+                         size_t ws_bytes, bool tables_built, bool in_pass, void* stream) {
+  const auto [dyp, xp, z, h, w1, w2, dxp, dw1, dw2] = t;
+  const bool aligned = t.aligned();
   if (!on_mfma(shape, aligned)) {
     GenericTrainWorkspace gw;
     const int32_t grc = check_train_generic(shape, ws, ws_bytes, &gw);
@@ -721,14 +716,16 @@ extern "C" int32_t lz_ffn_backward(const void* dyp, const void* xp, const void* 
                                    const int32_t* slot_offsets, const void* w1, const void* w2,
                                    const lz_shape* shape, void* dxp, void* dw1, void* dw2, void* ws,
                                    size_t ws_bytes, void* stream) {
-  return lz::ffn_backward(dyp, xp, z, h, slot_offsets, w1, w2, shape, dxp, dw1, dw2, false, ws, ws_bytes, false, false, stream);
+  return lz::ffn_backward(shape, lz::FfnBackward{dyp, xp, z, h, w1, w2, dxp, dw1, dw2}, slot_offsets, false, ws, ws_bytes, false, false,
+                          stream);
 }
 
 extern "C" int32_t lz_ffn_backward_accumulate(const void* dyp, const void* xp, const void* z, const void* h,
                                               const int32_t* slot_offsets, const void* w1, const void* w2,
                                               const lz_shape* shape, void* dxp, float* dw1_acc, float* dw2_acc,
                                               void* ws, size_t ws_bytes, void* stream) {
-  return lz::ffn_backward(dyp, xp, z, h, slot_offsets, w1, w2, shape, dxp, dw1_acc, dw2_acc, true, ws, ws_bytes, false, false, stream);
+  return lz::ffn_backward(shape, lz::FfnBackward{dyp, xp, z, h, w1, w2, dxp, dw1_acc, dw2_acc}, slot_offsets, true, ws, ws_bytes, false,
+                          false, stream);
 }
 
 namespace {

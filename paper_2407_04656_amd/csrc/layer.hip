@@ -63,12 +63,12 @@ extern "C" int32_t lz_layer_forward_train(const lz_shape* shape, const lz_layer_
                                           void* stream) {
   if (!buffers) return of("lz_layer_forward_train", LZ_EINVAL);
   const lz_layer_buffers& b = *buffers;
-  const void* const tensors[] = {b.z, b.h, b.yp, b.xp, b.w1, b.w2};
-  const TileSpecs tables = lz::train_tables(shape, tensors, 6, b.train_ws, b.train_ws_bytes);
+  const lz::FfnTrain ffn{b.xp, b.w1, b.w2, b.z, b.h, b.yp};
+  const TileSpecs tables = lz::train_tables(shape, ffn, b.train_ws, b.train_ws_bytes);
   int32_t rc = route_and_plan(shape, b, logits, tables, stream);
   if (rc != LZ_OK) return rc;
   if ((rc = of("lz_permute_scatter", lz_permute_scatter(x, b.pair_to_row, shape, b.xp, stream))) != LZ_OK) return rc;
-  rc = lz::ffn_forward_train(b.xp, b.slot_offsets, b.w1, b.w2, shape, b.z, b.h, b.yp, b.train_ws, b.train_ws_bytes, tables.n > 0, stream);
+  rc = lz::ffn_forward_train(shape, ffn, b.slot_offsets, b.train_ws, b.train_ws_bytes, tables.n > 0, stream);
   if (of("lz_ffn_forward_train", rc) != LZ_OK) return rc;
   return of("lz_unpermute_combine", lz_unpermute_combine(b.yp, b.pair_to_row, b.topk_gates, shape, b.y, stream));
 }
@@ -78,12 +78,11 @@ extern "C" int32_t lz_layer_backward(const lz_shape* shape, const lz_layer_buffe
   if (!buffers) return of("lz_layer_backward", LZ_EINVAL);
   const lz_layer_buffers& b = *buffers;
   const bool gate = shape && shape->T > 0 && b.topk_ids && b.dlogits;
-  const void* const tensors[] = {b.dyp, b.xp, b.z, b.h, b.dxp, b.w1, b.w2, b.dw1_slot, b.dw2_slot};
-  const TileSpecs tables = b.slot_offsets ? lz::backward_tables(shape, tensors, 9, b.train_ws, b.train_ws_bytes, accumulate) : TileSpecs{};
+  const lz::FfnBackward ffn{b.dyp, b.xp, b.z, b.h, b.w1, b.w2, b.dxp, b.dw1_slot, b.dw2_slot};
+  const TileSpecs tables = b.slot_offsets ? lz::backward_tables(shape, ffn, b.train_ws, b.train_ws_bytes, accumulate) : TileSpecs{};
   int32_t rc = of("lz_combine_backward", lz::combine_backward_with(dy, shape, b, gate, tables, stream));
   if (rc != LZ_OK) return rc;
-  rc = lz::ffn_backward(b.dyp, b.xp, b.z, b.h, b.slot_offsets, b.w1, b.w2, shape, b.dxp, b.dw1_slot, b.dw2_slot, accumulate, b.train_ws,
-                        b.train_ws_bytes, tables.n > 0, true, stream);
+  rc = lz::ffn_backward(shape, ffn, b.slot_offsets, accumulate, b.train_ws, b.train_ws_bytes, tables.n > 0, true, stream);
   if (of(accumulate ? "lz_ffn_backward_accumulate" : "lz_ffn_backward", rc) != LZ_OK) return rc;
   if ((rc = of("lz_permute_backward", lz_permute_backward(b.dxp, b.pair_to_row, shape, b.dx, stream))) != LZ_OK) return rc;
   if (!gate) {
