@@ -129,8 +129,9 @@ __device__ __forceinline__ void mfma_then_load16_to_lds(f32x4& acc, const bf16x8
 // weighted least squares, reweighted until the errors of u 2^P(u) are level; P falls without end past it, so that large
 // u give exactly v / 2 + |v| / 2, and infinities and NaNs what those two terms make of them.  What bounds it is the vector unit,
 // one wave a SIMD with the matrix cores idle: a quarter-rate instruction counts as four, 15 slots where Abramowitz-Stegun
-// 7.1.26 (four steps, exp2 and rcp) takes 21.  Largest and rms error against fp64 over [-8, 8]: 3.1e-7 and 0.45e-7, 3.8e-7 and
-// 0.80e-7 by that; of negative v 0.8e-7 and 2.6e-7; relative, v > 0: 1.8e-7 and 5.2e-7.
+// 7.1.26 (four steps, exp2 and rcp) takes 21.  Largest and rms error against fp64 at 2^20 + 1 even points of [-8, 8], in fp32 with
+// exp2 and rcp rounded correctly: 3.1e-7 and 0.56e-7, by that 3.8e-7 and 0.96e-7 (the exact value rounded 2.4e-7 and 0.51e-7); largest
+// of negative v 0.8e-7 and 2.6e-7; relative, v > 0: 1.8e-7 and 5.3e-7.
 __device__ __forceinline__ float silu_fast(float v) {
   return v * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.44269504088896341f * v));
 }
