@@ -24,7 +24,10 @@ struct WithCombine {
 struct CombineAlone {};  // lz_combine_backward: none of it, in arguments and LDS neither
 template <bool WITH>
 using CombineExtra = typename std::conditional<WITH, WithCombine, CombineAlone>::type;
-constexpr int kTableSlots = 512;  // more slots get a launch of their own: LDS that all workgroups would carry
+// More slots get a launch of their own: 6 KB of LDS that every workgroup carries; with 48 KB for all 4096 training steps of 528
+// slots gain what the launch costs (763 -> 748 us, 2000 tokens 301 -> 295), those of many short rows lose as much (30000 tokens, 64 fp32
+// columns 213 -> 216, 60000 of 33 513 -> 518).  Beside the combine up to here: 64 slots 95.6, by themselves 101.2.
+constexpr int kTableSlots = 512;
 constexpr int kTokensAlone = 4;
 template <bool WITH>
 constexpr int kCombineThreads = WITH ? kTileThreads : kTokensAlone * lz::kWave;

@@ -10,7 +10,7 @@
 //   place    every workgroup scans the slot sizes; each wave revisits its chunk: a pair's position in its (expert, source rank)
 //            list is chunk base + ordered rank inside the chunk (wave ballots, one per
 //            bit of an expert index), which fixes destination rank, slot and row
-// Where ids and experts are few enough the expert's workgroup counts its pairs itself, and small batches take all of it in one
+// Up to 8192 pairs the expert's workgroup counts its pairs itself (direct_counts), and small batches take all of it in one
 // workgroup (plan_small_kernel).
 // Each is a chain of dependent lookups over little data, and a launch of nothing takes 2.7 us: latency bound.  us of a plan, with a
 // launch of one workgroup for the slots, scans by shuffles, tables of (chunk, expert) and every lookup in memory, and now (chunks
@@ -63,7 +63,7 @@ PlanTables carve(void* ws, const lz_shape* s) {
   t.chunkbase = take(nch * E);
   t.chunkflag = take(nch);
   t.lists = (int4*)take(E * N);
-  for (int i = 1; i < 4; ++i) take(E * N);  // ... of four ints each
+  for (int i = 1; i < 4; ++i) take(E * N);  // ... of four ints each: what is taken follows on, with room to spare by its rounding up
   t.estatus = take(E);
   take(E * N * N);  // room that no kernel uses: which shapes fit LZ_PLAN_NOALLOC_SCRATCH_BYTES is part of the interface
   t.cumDst = take(E * N * (N + 1));
@@ -477,7 +477,10 @@ __device__ __forceinline__ int scan_slots(const int32_t* __restrict__ slot_count
 // of a plan).  What bounds it is latency, and with many experts the lookups of single entries: what a workgroup's chunks need of the
 // tables is fetched at the start, all at once, but for the entries of the pairs' lists; the prefix over destinations of the
 // workgroup's rank is searched in LDS where it fits.
-constexpr int kCumSlice = 8448;  // 256 experts, 32 ranks
+// What fits beside the other tables with two workgroups a CU.  us of a plan of 262144 pairs, top-8: 256 experts, 32 ranks 28.6, searched in
+// memory 29.1; with room for 16640 entries and one workgroup a CU, 33 ranks (in memory so) 37.0 -> 39.5, 200 experts, 42 ranks
+// 35.8 -> 39.6, 64 experts, 16 ranks 16.7 -> 18.0.
+constexpr int kCumSlice = 8448;
 
 struct PlaceLds {
   int run[kGroup * kRowE];
@@ -541,7 +544,7 @@ __global__ __launch_bounds__(kGroup * lz::kWave) void place_kernel(const int32_t
       if (u < chunks) s_run[u * kRowE + e] = t.chunkbase[(size_t)e * t.nch + b0 + u];
     }
     if (slice <= kCumSlice) {
-#pragma unroll 9
+#pragma unroll 4  // (9: 256 experts, 32 ranks, 16384, 65536 and 262144 pairs 20.0, 22.4, 27.7 -> 21.0, 23.2, 28.6 us)
       for (int x = tid; x < slice; x += kThreads) s_cum[x] = t.cumDst[(size_t)i * slice + x];
     }
   }
@@ -573,7 +576,7 @@ __global__ __launch_bounds__(kGroup * lz::kWave) void place_kernel(const int32_t
 }
 
 // ------------------------------------------------------------------------------------------
-// The whole dispatcher in one workgroup, tables in LDS: small batches, where the four launches and the trips of
+// The whole dispatcher in one workgroup, tables in LDS: small batches, where two launches and the trips of
 // their tables through memory are the time.  Same steps, same results.
 // ------------------------------------------------------------------------------------------
 constexpr int kSmallPairs = 2048, kSmallExperts = 24;
@@ -613,12 +616,12 @@ __global__ __launch_bounds__(kSchedThreads) void plan_small_kernel(
   const int S = N * c;
   const long long P = (long long)T * k;
   if constexpr (G > 0) {
-    for (int t0 = 0; t0 < T; t0 += kSchedThreads / G)
-      route_token<G, 4, false, false>(logits, t0 + tid / G, T, E, k, [&](long long t, int kk, int id, float gate) {
-        ids[t * k + kk] = id;
-        gates[t * k + kk] = gate;
-        s_ids[t * k + kk] = id;
-      });
+    // (one go: plan_routes)
+    route_token<G, 4, false, false>(logits, tid / G, T, E, k, [&](long long t, int kk, int id, float gate) {
+      ids[t * k + kk] = id;
+      gates[t * k + kk] = gate;
+      s_ids[t * k + kk] = id;
+    });
   } else {
     for (int p = tid; p < (int)P; p += kSchedThreads) s_ids[p] = ids[p];
   }
@@ -767,8 +770,8 @@ namespace {
 inline int route_lanes(int E) { return E <= 4 ? 1 : E <= 8 ? 2 : E <= 16 ? 4 : 8; }
 
 // Whether the expert's workgroups count their pairs themselves, each reading all ids.  us, so and with a launch that counts: 2000 pairs,
-// 8 and 53 experts 11.4, 12.9 and 12.6, 14.2; 8000 pairs, 16 experts 12.9, 13.7; 16384 pairs, 8 experts 14.4, 13.5; 32768 pairs,
-// 32 experts 18.0, 13.9.
+// 8 and 53 experts 11.4, 12.9 and 12.6, 14.2; 8000 pairs, 16 experts 12.9, 13.7; 8192 pairs, 128 and 256 experts on 4 ranks 14.1, 14.8
+// and 15.2, 15.9, on 32 ranks 18.1, 19.1 and 19.2, 20.3; 16384 pairs, 8 experts 14.4, 13.5; 32768 pairs, 32 experts 18.0, 13.9.
 inline bool direct_counts(const lz_shape* s) {
   const long long P = (long long)s->T * s->k;
   return P <= kDirectPairs;
