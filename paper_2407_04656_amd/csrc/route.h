@@ -8,8 +8,8 @@
 // it (the tie rule), both with DPP moves inside a row of 16 lanes.  Few lanes per token: four tokens or more
 // share each of those moves.
 //
-// SORTED, from 5 choices on: a logit and its expert are one key of 40 bits, the image above 255 minus the expert, so that one
-// maximum decides by both.  The keys are mantissas of doubles between 1 and 2, whose order is theirs: v_max_f64 is one instruction
+// SORTED, from 5 choices on (the line is drawn in route.hip): a logit and its expert are one key of 40 bits, the image above 255
+// minus the expert, so that one maximum decides by both.  The keys are mantissas of doubles between 1 and 2, whose order is theirs: v_max_f64 is one instruction
 // where a maximum of 64-bit integers is three.  A lane sorts its keys by a network and keeps the first; a round is a maximum over
 // the group's heads, and the lane it came from steps to its next key.  us for 32768 tokens of 256 experts, top-1, 2, 4 and 8: 5.6, 6.7,
 // 9.0 and 13.3 the first way, 5.9, 7.9, 9.0 and 10.5 this way; of 64 experts 3.2, 3.6, 4.6, 6.3 and 3.3, 3.8, 4.6, 5.8; 256 tokens of
