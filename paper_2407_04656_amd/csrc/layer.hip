@@ -1,6 +1,6 @@
 // The whole layer in one call: the steps of the single calls in their order, on the caller's buffers.  What a caller of small batches
-// pays for is launches and calls (from Python a forward of 256 tokens spent 34 us of the host on five calls, 30 on one): the dispatcher's
-// launches also build the tables of the grouped GEMMs, and route where the batch is
+// pays for is launches and calls (from Python a forward of 256 fp32 tokens, 20 in a row, takes 30 us of the host as five calls of seven
+// launches, 23 to 24 as one of five): the dispatcher's launches also build the tables of the grouped GEMMs, and route where the batch is
 // small enough for one workgroup.
 #include "layer.h"
 
