@@ -36,18 +36,16 @@ class SingleCalls(lz.MoELayer):
         return self.backward(dy, True)
 
 
-def _pair(T, d, ffn, E, k, N, c, dtype, act, seed=0, plan=None, off=None):
+def _pair(T, d, ffn, E, k, N, c, dtype, act, seed=0):
     """Two layers of one shape, plan and weights, one pass by pass, one call by call; and a batch."""
     gen = torch.Generator(device=DEV)
     gen.manual_seed(seed + T)
     rng = np.random.default_rng(seed + T)
     shape = lz.Shape(T, d, ffn, E, k, N, c, dtype, act)
     tdt = torch.float32 if dtype == lz.LZ_F32 else torch.bfloat16
-    if plan is None:
-        plan = np.concatenate([np.arange(E), rng.integers(0, E, size=N * c - E)]).astype(np.int32)
-        rng.shuffle(plan)
-    if off is None:
-        off = np.concatenate([[0], np.sort(rng.integers(0, T + 1, size=N - 1)), [T]]).astype(np.int32)
+    plan = np.concatenate([np.arange(E), rng.integers(0, E, size=N * c - E)]).astype(np.int32)
+    rng.shuffle(plan)
+    off = np.concatenate([[0], np.sort(rng.integers(0, T + 1, size=N - 1)), [T]]).astype(np.int32)
 
     def normal(*size):
         return torch.randn(size, generator=gen, device=DEV).to(tdt)
@@ -67,8 +65,7 @@ def _pair(T, d, ffn, E, k, N, c, dtype, act, seed=0, plan=None, off=None):
 def _same(a, b, names):
     for name in names:
         x, y = getattr(a, name), getattr(b, name)
-        width = torch.int32 if x.element_size() == 4 else torch.int16       # (an unaligned view has no bytes of its own)
-        assert torch.equal(x.view(width), y.view(width)), name
+        assert torch.equal(x.view(torch.uint8), y.view(torch.uint8)), name
 
 
 CASES = [
@@ -88,65 +85,25 @@ CASES = [
 ]
 
 
-def _check_passes(one, single, logits, x, dy):
-    for layer in (one, single):
-        layer.forward(logits, x)
-    _same(one, single, FORWARD)
-    for layer in (one, single):
-        layer.y.zero_()
-        layer.forward_fused(logits, x)
-    _same(one, single, FORWARD)
-    for layer in (one, single):
-        layer.forward_train(logits, x)
-        layer.backward(dy)
-    _same(one, single, FORWARD + BACKWARD + ("dw1_slot", "dw2_slot", "dw1", "dw2"))
-    for layer in (one, single):
-        layer.forward_train(logits, x)
-        layer.backward_accumulate(dy)
-    _same(one, single, BACKWARD + ("dw1_acc", "dw2_acc"))
-
-
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "T%d_d%d_f%d_E%d_k%d_N%d_c%d_%s%s" % (*c[:7], "fb"[c[7]], "gs"[c[8]]))
 def test_passes_have_the_bits_of_the_single_calls(case):
     (one, single), logits, x, dy = _pair(*case)
     for _ in range(2):      # tables and counters of a pass before do not matter
-        _check_passes(one, single, logits, x, dy)
-
-
-@pytest.mark.parametrize("dtype", [lz.LZ_F32, lz.LZ_BF16])
-@pytest.mark.parametrize("names", [("w1",), ("xp",), ("z",), ("h",), ("yp",), ("dyp",), ("dxp",), ("w2", "dw1_slot"), ("dw2_slot", "dx"),
-                                   ("dw1_acc", "y"), ("dw1", "dw2_acc")], ids="+".join)
-def test_unaligned_buffers(dtype, names):
-    """An element past their 16-byte boundary, where the kernels and their tables are others: those the tables were built for."""
-    (one, single), logits, x, dy = _pair(300, 96, 200, 6, 2, 3, 4, dtype, lz.LZ_SWIGLU)
-    for layer in (one, single):
-        for name in names:
-            t = getattr(layer, name)
-            moved = torch.empty(t.numel() + 1, dtype=t.dtype, device=DEV)[1:].view(t.shape)
-            setattr(layer, name, moved.copy_(t))
-            assert moved.data_ptr() % 16 != 0 and moved.is_contiguous()
-    _check_passes(one, single, logits, x, dy)
-
-
-@pytest.mark.parametrize("T", [0, 90, 5000])     # without rows; one workgroup; tables beside the placing workgroups
-@pytest.mark.parametrize("fault", ["uncovered", "split", "no expert"])
-def test_flagged_plans_and_empty_batches(T, fault):
-    """Tables from the slots' sizes are those from the offsets that a flagged plan leaves."""
-    E, N, c = 6, 3, 4
-    plan = np.array([0, 1, 2, 3, 4, 5, 0, 1, 2, 3, 4, 4], dtype=np.int32)
-    off = np.array([0, T // 4, T // 2, T], dtype=np.int32)
-    if fault == "uncovered":
-        plan[plan == 5] = 0
-    if fault == "split":
-        off = np.array([0, T + 9, T // 2, T + 3], dtype=np.int32)
-    if fault == "no expert":
-        plan[7] = E
-        plan[11] = -1
-    for dtype, act in ((lz.LZ_F32, lz.LZ_GELU), (lz.LZ_BF16, lz.LZ_SWIGLU)):
-        (one, single), logits, x, dy = _pair(T, 256, 320, E, 2, N, c, dtype, act, plan=plan, off=off)
-        _check_passes(one, single, logits, x, dy)
-        if T > 0:
-            assert int(one.status.item()) != 0
+        for layer in (one, single):
+            layer.forward(logits, x)
+        _same(one, single, FORWARD)
+        for layer in (one, single):
+            layer.y.zero_()
+            layer.forward_fused(logits, x)
+        _same(one, single, FORWARD)
+        for layer in (one, single):
+            layer.forward_train(logits, x)
+            layer.backward(dy)
+        _same(one, single, FORWARD + BACKWARD + ("dw1_slot", "dw2_slot", "dw1", "dw2"))
+        for layer in (one, single):
+            layer.forward_train(logits, x)
+            layer.backward_accumulate(dy)
+        _same(one, single, BACKWARD + ("dw1_acc", "dw2_acc"))
 
 
 def test_refusals_are_those_of_the_single_calls():
